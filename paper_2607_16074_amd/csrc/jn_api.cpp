@@ -672,14 +672,21 @@ jn_status jn_backbone_forward(jn_ctx* c, const jn_backbone* bb, const jn_packed*
   const int32_t kvh = bb->n_kv_heads ? bb->n_kv_heads : bb->n_heads;
   const int32_t nqkv = (bb->n_heads + 2 * kvh) * hd;  // q | k | v columns of the projection
   hipStream_t s = c->stream;
+  // Residual projections split over K leave their partials to the next norm,
+  // which adds them to the residual stream as it reads it.
+  const int32_t so = gemm_split(EPI_RESID_F32, T, d, d), sd = gemm_split(EPI_RESID_F32, T, d, f);
+  auto norm = [&](int32_t S, const void* g, void* out) {
+    return S > 1 ? launch_rmsnorm_split(s, x, (const float*)sp, S, g, out, T, d, bb->eps)
+                 : launch_rmsnorm_f32in(s, x, g, out, T, d, bb->eps);
+  };
   for (int l = 0; l < bb->n_layers; ++l) {
     const jn_layer& Ly = bb->layers[l];
     if (l == 0)
       JN_TRACED(c, JN_OP_RMSNORM, T, d, 0, launch_rmsnorm_bf16in(s, p->tokens, x, Ly.g1, h, T, d, bb->eps), "rmsnorm");
     else
-      JN_TRACED(c, JN_OP_RMSNORM, T, d, 0, launch_rmsnorm_f32in(s, x, Ly.g1, h, T, d, bb->eps), "rmsnorm");
+      JN_TRACED(c, JN_OP_RMSNORM, T, d, 0, norm(sd, Ly.g1, h), "rmsnorm");
     JN_TRACED(c, JN_OP_GEMM_QKV, T, nqkv, d,
-              launch_gemm(s, EPI_BF16, h, d, Ly.wqkv, nullptr, d, qkv, nqkv, T, nqkv, d, 0, sp, spb), "gemm qkv");
+              launch_gemm(s, EPI_BF16, h, d, Ly.wqkv, nullptr, d, qkv, nqkv, T, nqkv, d, sp, spb), "gemm qkv");
     if (bb->rope_theta > 0.f)
       JN_TRACED(c, JN_OP_ROPE, T, (bb->n_heads + kvh) * hd, 0,
                 launch_rope(s, qkv, nqkv, p->token_pos, T, bb->n_heads + kvh, hd, bb->rope_theta), "rope");
@@ -687,19 +694,19 @@ jn_status jn_backbone_forward(jn_ctx* c, const jn_backbone* bb, const jn_packed*
               launch_attention(s, qkv, att, p->seqlens, p->cu_seqlens, p->N, d, bb->n_heads, kvh, bb->causal != 0,
                                p->max_seqlen, p->align),
               "attention");
-    JN_TRACED(c, JN_OP_GEMM_O, T, d, d, launch_gemm(s, EPI_RESID_F32, att, d, Ly.wo, nullptr, d, x, d, T, d, d, 0, sp, spb),
-              "gemm o");
-    JN_TRACED(c, JN_OP_RMSNORM, T, d, 0, launch_rmsnorm_f32in(s, x, Ly.g2, h, T, d, bb->eps), "rmsnorm");
+    JN_TRACED(c, JN_OP_GEMM_O, T, d, d,
+              launch_gemm(s, EPI_RESID_F32, att, d, Ly.wo, nullptr, d, x, d, T, d, d, sp, spb, true), "gemm o");
+    JN_TRACED(c, JN_OP_RMSNORM, T, d, 0, norm(so, Ly.g2, h), "rmsnorm");
     if (glu)
       JN_TRACED(c, JN_OP_GEMM_UP, T, 2 * f, d,
-                launch_gemm(s, EPI_GEGLU_BF16, h, d, Ly.w_gate, Ly.w_up, d, mid, f, T, f, d, 0), "gemm geglu");
+                launch_gemm(s, EPI_GEGLU_BF16, h, d, Ly.w_gate, Ly.w_up, d, mid, f, T, f, d), "gemm geglu");
     else
-      JN_TRACED(c, JN_OP_GEMM_UP, T, f, d, launch_gemm(s, EPI_GELU_BF16, h, d, Ly.w_up, nullptr, d, mid, f, T, f, d, 0, sp, spb),
+      JN_TRACED(c, JN_OP_GEMM_UP, T, f, d, launch_gemm(s, EPI_GELU_BF16, h, d, Ly.w_up, nullptr, d, mid, f, T, f, d, sp, spb),
                 "gemm up");
     JN_TRACED(c, JN_OP_GEMM_DOWN, T, d, f,
-              launch_gemm(s, EPI_RESID_F32, mid, f, Ly.w_down, nullptr, f, x, d, T, d, f, 0, sp, spb), "gemm down");
+              launch_gemm(s, EPI_RESID_F32, mid, f, Ly.w_down, nullptr, f, x, d, T, d, f, sp, spb, true), "gemm down");
   }
-  JN_TRACED(c, JN_OP_RMSNORM, T, d, 0, launch_rmsnorm_f32in(s, x, bb->gf, hidden, T, d, bb->eps), "final rmsnorm");
+  JN_TRACED(c, JN_OP_RMSNORM, T, d, 0, norm(sd, bb->gf, hidden), "final rmsnorm");
   return JN_OK;
 }
 
@@ -1360,7 +1367,7 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
 
   // ---- recording helpers
   auto gemm = [&](int epi, std::vector<GemmArgs> probs) {
-    const int shape = gemm_grouped_tile_shape(probs.data(), (int32_t)probs.size());
+    const int shape = gemm_grouped_tile_shape(epi, probs.data(), (int32_t)probs.size());
     const int32_t tiles = gemm_grouped_prepare(probs.data(), (int32_t)probs.size(), shape);
     if (tiles < 0) rec.bad_gemm = true;
     const size_t at = rec.add(probs.data(), sizeof(GemmArgs) * probs.size());
@@ -1373,8 +1380,8 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
   // Transposed-operand problems run only on the 256x256 tiles; elsewhere
   // (offsets beyond the loop's 32-bit ones) the caller materialises the
   // transposes instead.  Both give the same MFMA sequence per output element.
-  auto trans_ok = [&](const std::vector<GemmArgs>& probs) {
-    return !c->expert_transposes && gemm_grouped_tile_shape(probs.data(), (int32_t)probs.size()) == 0;
+  auto trans_ok = [&](int epi, const std::vector<GemmArgs>& probs) {
+    return !c->expert_transposes && gemm_grouped_tile_shape(epi, probs.data(), (int32_t)probs.size()) >= 0;
   };
   auto per_tenant_gemm = [&](int epi, std::function<GemmArgs(int32_t)> fn) {
     std::vector<GemmArgs> v;
@@ -1547,7 +1554,7 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
         planes += S;
       }
     }
-    if (trans_ok(vt)) {
+    if (trans_ok(EPI_F32, vt)) {
       gemm(EPI_F32, vt);
     } else {
       trans_rows(dy, out, B(Ly.TA), prefix);
@@ -1579,7 +1586,7 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
       a.trans = GEMM_TRANS_W;
       v.push_back(a);
     }
-    if (trans_ok(v)) {
+    if (trans_ok(epi, v)) {
       gemm(epi, v);
       return;
     }

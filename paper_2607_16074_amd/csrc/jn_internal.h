@@ -41,6 +41,12 @@ hipError_t launch_rmsnorm_bf16in(hipStream_t s, const void* x_bf16, float* x_out
 hipError_t launch_rmsnorm_f32in(hipStream_t s, const float* x, const void* g, void* h, int32_t rows,
                                 int32_t d, float eps);
 
+// x += (part[0] + part[1]) + ... (S fp32 planes of rows x d, added in order),
+// then h = RMS(x) * g (bf16): the reduction of a split residual projection
+// together with the norm that reads its result.
+hipError_t launch_rmsnorm_split(hipStream_t s, float* x, const float* part, int32_t S, const void* g, void* h,
+                                int32_t rows, int32_t d, float eps);
+
 enum GemmEpi : int32_t {
   EPI_BF16 = 0,          // C bf16 = acc
   EPI_GELU_BF16 = 1,     // C bf16 = gelu(acc)
@@ -68,8 +74,7 @@ struct GemmArgs {
   int32_t tiles_m, tiles_n, tile_start;  // filled by the launchers
   int32_t trans;        // GEMM_TRANS_* bits (grouped launches on 256x256 tiles only)
   int64_t split_c;      // split-K: elements between the fp32 partial outputs of
-                        // consecutive K ranges (blockIdx.y); 0 when unsplit
-  int32_t xcd_ranges;   // split-K ring launches: K ranges dealt to XCD groups (set by the launcher)
+                        // consecutive K ranges; 0 when unsplit
 };
 
 // Grouped launch over nprob problems sharing one epilogue: the host fills
@@ -81,7 +86,7 @@ struct GemmArgs {
 // -1 where their offsets do not fit the loop's 32-bit ones); with both
 // operands transposed K need not be a multiple of 64.  Combinations launched:
 // EPI_F32 with GEMM_TRANS_W or both, EPI_GELUGRAD_BF16 with GEMM_TRANS_W.
-int gemm_grouped_tile_shape(const GemmArgs* probs, int32_t nprob);
+int gemm_grouped_tile_shape(int epi, const GemmArgs* probs, int32_t nprob);
 int32_t gemm_grouped_prepare(GemmArgs* probs, int32_t nprob, int shape);
 hipError_t launch_gemm_grouped(hipStream_t s, int epi, const GemmArgs* dprobs, int32_t nprob, int32_t total_tiles,
                                int shape, int trans = 0);
@@ -91,14 +96,16 @@ hipError_t launch_gemm_grouped(hipStream_t s, int epi, const GemmArgs* dprobs, i
 // each [N][K], and C has N columns.
 //
 // Launches with few tiles for the GPU and a long K (epilogues EPI_BF16,
-// EPI_RESID_F32, EPI_GELU_BF16) split K into gemm_split() ranges when
-// `split_ws` holds gemm_split_bytes(): each range writes fp32 partials and a
-// reduction adds them in range order, then applies the epilogue.  The split
-// depends only on (epi, M, N, K).
+// EPI_RESID_F32, EPI_GELU_BF16) split K: each of S ranges writes fp32 partials
+// [S][rows][N] into `split_ws` (gemm_split_bytes(), 0 where nothing is split)
+// and a reduction adds them in range order, then applies the epilogue.  The
+// split depends only on (epi, M, N, K).  gemm_split(): S of a launch that is
+// split over all its rows, else 1; with partials_only such a launch leaves the
+// reduction to the caller (launch_rmsnorm_split).
 hipError_t launch_gemm(hipStream_t s, int epi, const void* A, int64_t lda, const void* B,
                        const void* B2, int64_t ldb, void* C, int64_t ldc, int32_t M, int32_t N,
-                       int32_t K, int tile_hint, void* split_ws = nullptr, size_t split_bytes = 0);
-int gemm_split(int epi, int32_t M, int32_t N, int32_t K);
+                       int32_t K, void* split_ws = nullptr, size_t split_bytes = 0, bool partials_only = false);
+int32_t gemm_split(int epi, int32_t M, int32_t N, int32_t K);
 size_t gemm_split_bytes(int epi, int32_t M, int32_t N, int32_t K);
 
 // Varlen attention over the packed batch (bidirectional or causal inside each

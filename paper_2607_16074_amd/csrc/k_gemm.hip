@@ -24,12 +24,12 @@
 // swizzle.
 //
 // Loops: the 256x256 tile (4 wavefronts, one per SIMD) runs a ring-buffered
-// loop (gemm_ring_kernel, gemm_grouped_ring_kernel); the smaller tiles of
-// short launches and of small grouped problems run an interleaved
-// double-buffered loop (gemm_tile).
+// loop (ring_tile); smaller tiles, of short launches, last partly filled waves
+// and small grouped problems, run flex_tile.  gemm_plan picks shapes and K
+// splits by an estimated time.
 //
-// Launch order: tiles are walked in groups of 32 token-tiles (token tile
-// fastest).  Workgroups are dealt round-robin to the 8 XCDs, so the 32 tiles
+// Launch order of the ring launches: tiles are walked in groups of 32
+// token-tiles (token tile fastest).  Workgroups are dealt round-robin to the 8 XCDs, so the 32 tiles
 // an XCD holds at a time form a block of 4 token tiles x 8 weight tiles, and
 // every weight slab is requested by all XCDs at about the same time.
 // Measured in the step on the 2048-wide workload: groups of 32 give 290.1 ms
@@ -57,7 +57,6 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 #define JN_LPTR(p) ((__attribute__((address_space(3))) void*)(p))
 
 constexpr int kBK = 64;       // K per slab (128-byte rows)
-constexpr int kStages = 3;    // LDS stages of the interleaved loop (prefetch distance 2)
 constexpr int kGroupM = 32;   // token tiles per L2 group
 
 __device__ __forceinline__ int lds_swz(int r) { return (r >> 1) & 7; }
@@ -108,6 +107,13 @@ __device__ __forceinline__ uint32_t pack_bf2_cvt(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(gemm_f32x2{lo, hi}, gemm_bf16x2));
 }
 
+// Largest divisor of `rows` that is at most `most`.
+constexpr int row_batch(int rows, int most) {
+  int b = most < rows ? most : rows;
+  while (rows % b != 0) --b;
+  return b;
+}
+
 // Epilogue shared by the loops: accumulator block (i, j) covers weight rows
 // 16 i .. of the wave's part and tokens 16 j ..; lane l owns output columns
 // n .. n+3, n = 16 i + 4 (l >> 4), of token row 16 j + (l & 15).
@@ -127,8 +133,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, const f32x4 (&a
     // first store of the batch, so a batch costs one memory round trip
     // instead of one per block.  Lanes outside the output read element (0, 0)
     // of the operand and store nothing.
-    constexpr int JB = TM < 32 / TN ? TM : 32 / TN;
-    static_assert(TM % JB == 0, "batch of token-row blocks");
+    constexpr int JB = row_batch(TM, 32 / TN);
     const float* src = EPI == EPI_RESID_F32 ? reinterpret_cast<const float*>(C) : g.aux;
     const int64_t ldr = EPI == EPI_RESID_F32 ? ldc : g.ldaux;
 #pragma unroll
@@ -222,145 +227,6 @@ __device__ __forceinline__ void tile_of(int32_t pid, int32_t tiles_m, int32_t ti
   tn = (pid % per_group) / gsize;
 }
 
-// Interleaved double-buffered loop (tiles of short and grouped launches).
-// Per slab, two K=32 steps: the fragments of step 1 are read under the MFMAs
-// of step 0; the next slab's DMA (into the buffer the previous slab used) is
-// interleaved with the first MFMAs; the one barrier per slab sits before the
-// second step's MFMAs, which then cover the read of the next slab's first
-// fragments.
-template <int BN, int BM, int WGN, int WGM, int EPI>
-__device__ __forceinline__ void gemm_tile(const GemmArgs& g, int32_t pid, uint16_t* __restrict__ lds) {
-  const uint16_t* __restrict__ X = g.X;
-  const int64_t ldx = g.ldx;
-  const int32_t M = g.M, K = g.K;
-  constexpr bool GLU = EPI == EPI_GEGLU_BF16;
-  constexpr int NW = WGN * WGM;                // wavefronts
-  constexpr int WN = BN / WGN, WM = BM / WGM;  // per-wave tile
-  constexpr int TN = WN / 16, TM = WM / 16;
-  constexpr int ROWS = BN + BM;                // weight rows then token rows in a stage
-  constexpr int NI = ROWS / (8 * NW);          // 1 KB DMA instructions per wave per stage
-  constexpr int STAGE = ROWS * kBK;            // elements per stage
-  static_assert(ROWS % (8 * NW) == 0 && TN >= 1 && TM >= 1, "tile shape");
-  static_assert(!GLU || TN % 2 == 0, "GeGLU pairs gate/up blocks inside a wave");
-
-  int32_t tm, tn;
-  tile_of(pid, g.tiles_m, g.tiles_n, tm, tn);
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wn = wave / WGM, wm = wave % WGM;
-
-  // ---- DMA sources: this wave's instruction i fills stage rows 8*(wave*NI+i)
-  // .. +7 (1 KB); lane -> (row lane>>3, position lane&7), and the position
-  // holds logical chunk position ^ swz(row) of that row's 128-byte K segment.
-  const uint16_t* src[NI];
-#pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    const int row = 8 * (wave * NI + i) + (lane >> 3);
-    const int chunk = (lane & 7) ^ lds_swz(row);
-    if (row < BN)
-      src[i] = weight_row<GLU>(g.W, g.W2, g.ldw, tn, BN, row, g.N) + chunk * 8;
-    else
-      src[i] = X + (int64_t)min(tm * BM + row - BN, M - 1) * ldx + chunk * 8;
-  }
-  uint16_t* const dst0 = lds + wave * NI * 512;  // 512 elements = 1 KB per instruction
-
-  f32x4 acc[TN][TM];
-#pragma unroll
-  for (int i = 0; i < TN; ++i)
-#pragma unroll
-    for (int j = 0; j < TM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  const int KT = K / kBK;
-  const int sw = lds_swz(lane & 15), quad = lane >> 4;
-  const int wrow = wn * WN + (lane & 15), xrow = BN + wm * WM + (lane & 15);
-
-  // prologue: slabs 0 .. kStages-2; slab kt+kStages-1 is fetched during slab
-  // kt's first half into the stage slab kt-1 used
-  static_assert(kStages == 3, "prefetch distance 2");
-#pragma unroll
-  for (int i = 0; i < NI; ++i)
-    __builtin_amdgcn_global_load_lds(JN_GPTR(src[i]), JN_LPTR(dst0 + i * 512), 16, 0, 0);
-  {
-    const int s1 = min(1, KT - 1);
-#pragma unroll
-    for (int i = 0; i < NI; ++i)
-      __builtin_amdgcn_global_load_lds(JN_GPTR(src[i] + s1 * kBK), JN_LPTR(dst0 + STAGE + i * 512), 16, 0, 0);
-  }
-  wait_vmcnt<NI>();  // slab 0 landed
-  __builtin_amdgcn_s_barrier();
-
-  // The loop body has no branches (each one in the MFMA stream costs tens of
-  // cycles of issue): past the last slab the fetches repeat slab KT-1 into a
-  // free stage, and the last next-slab fragment reads read a free stage.
-  bf16x8 fw[2][TN], fx[2][TM];
-  gemm_frags<TN>(fw[0], lds, wrow, quad ^ sw);
-  gemm_frags<TM>(fx[0], lds, xrow, quad ^ sw);
-  int st = 0;  // kt % 3
-  for (int kt = 0; kt < KT; ++kt) {
-    const int st1 = st == 2 ? 0 : st + 1, st2 = st == 0 ? 2 : st - 1;  // (kt + 1) % 3, (kt + 2) % 3
-    const uint16_t* cur = lds + st * STAGE;
-    const int sf = min(kt + 2, KT - 1);  // slab fetched into the stage slab kt-1 used
-    uint16_t* const fdst = dst0 + st2 * STAGE;
-#pragma unroll
-    for (int step = 0; step < 2; ++step) {
-      if (step == 0) {
-        const int pos = (4 + quad) ^ sw;
-        gemm_frags<TN>(fw[1], cur, wrow, pos);
-        gemm_frags<TM>(fx[1], cur, xrow, pos);
-      } else {
-        wait_vmcnt<NI>();  // slab kt+1 landed; slab kt+2's fetch may stay in flight
-        wait_lgkmcnt<0>();
-        __builtin_amdgcn_s_barrier();
-        const uint16_t* nxt = lds + st1 * STAGE;
-        gemm_frags<TN>(fw[0], nxt, wrow, quad ^ sw);
-        gemm_frags<TM>(fx[0], nxt, xrow, quad ^ sw);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-      for (int q = 0; q < TN * TM; ++q) {
-        const int i = q / TM, j = q % TM;
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fw[step][i], fx[step][j], acc[i][j], 0, 0, 0);
-        // DMA d of slab kt+1 after MFMA d of the slab (as early as possible)
-        constexpr int PER = (NI + TN * TM - 1) / (TN * TM);  // DMAs per MFMA
-#pragma unroll
-        for (int e = 0; e < PER; ++e) {
-          const int d = (step * TN * TM + q) * PER + e;
-          if (d < NI)
-            __builtin_amdgcn_global_load_lds(JN_GPTR(src[d] + sf * kBK), JN_LPTR(fdst + d * 512), 16, 0, 0);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    }
-    st = st1;
-  }
-  wait_lgkmcnt<0>();
-  wait_vmcnt<0>();  // the repeated slabs' DMAs land before the LDS is released
-  // accumulators pinned to the accumulation registers (as in ring_tile)
-#pragma unroll
-  for (int i = 0; i < TN; ++i)
-#pragma unroll
-    for (int j = 0; j < TM; ++j) asm volatile("" : "+a"(acc[i][j]));
-
-  gemm_epilogue<BN, BM, WGN, WGM, EPI>(g, acc, tm, tn, wn, wm, lane);
-}
-
-// Split-K: K range s of a launch whose g.K is the per-range length.
-__device__ __forceinline__ GemmArgs split_range(const GemmArgs& g, int32_t s) {
-  GemmArgs r = g;
-  if (s) {
-    r.X += (int64_t)s * g.K;
-    r.W += (int64_t)s * g.K;
-    r.C = reinterpret_cast<float*>(g.C) + (int64_t)s * g.split_c;
-  }
-  return r;
-}
-
-template <int BN, int BM, int WGN, int WGM, int EPI>
-__global__ __launch_bounds__(64 * WGN * WGM, 1) void gemm_kernel(GemmArgs g) {
-  __shared__ __attribute__((aligned(1024))) uint16_t lds[kStages * (BN + BM) * kBK];
-  gemm_tile<BN, BM, WGN, WGM, EPI>(split_range(g, blockIdx.y), blockIdx.x, lds);
-}
-
 // Sum of the split-K partials in range order, then the epilogue.  Thread =
 // 4 consecutive output columns of one row.
 template <int EPI>
@@ -397,19 +263,6 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
     *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(C) + (int64_t)m * ldc + n) =
         make_uint2(pack_bf2(acc.x, acc.y), pack_bf2(acc.z, acc.w));
   }
-}
-
-// One launch over several independent problems (one per tenant): block b
-// runs tile b - tile_start[p] of the problem p whose tile range holds b.
-template <int BN, int BM, int WGN, int WGM, int EPI>
-__global__ __launch_bounds__(64 * WGN * WGM, 1) void gemm_grouped_kernel(const GemmArgs* __restrict__ probs,
-                                                                         int32_t nprob) {
-  __shared__ __attribute__((aligned(1024))) uint16_t lds[kStages * (BN + BM) * kBK];
-  const int32_t b = blockIdx.x;
-  int32_t p = 0;
-  while (p + 1 < nprob && probs[p + 1].tile_start <= b) ++p;
-  const GemmArgs g = probs[p];
-  gemm_tile<BN, BM, WGN, WGM, EPI>(g, b - g.tile_start, lds);
 }
 
 // bf16 / GELU-bf16 epilogue of the 256x256 ring loop: the tile is staged
@@ -467,6 +320,286 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t panel_rsrc(const uint16_t* bas
 // half-wave (checked with a bank model on the CPU).
 __device__ __forceinline__ int tswz(int k) { return 2 * ((k & 3) | ((k & 8) >> 1)); }
 
+// Tiles of short, ragged and grouped launches: BN weight rows x BM tokens on
+// 4 wavefronts (2 x 2), LDS stages of one K=64 slab each: NS for the tokens,
+// NSW (NS or NS - 1) for the weights.  Between two barriers every wave issues
+// 2 TN TM MFMAs (the second K=32 half of slab kt, then the first half of slab
+// kt+1), the next half's fragment reads under them, and the DMA of one slab
+// spread evenly over the window, the weights under the first half and the
+// tokens under the second: a DMA instruction occupies the CU's load path for
+// ~16 cycles per KB, so a burst of them after the barrier stalls the wave's
+// MFMA issue.  With all operands in the L2 the
+// 256x160 tile takes 0.67 us per slab (2.0 PFLOP/s over 256 CUs), 128x128
+// 0.32 us, 64x96 0.20 us; the interleaved 128x128 loop it replaced issued a
+// slab's DMA in one burst and took 0.77 us per slab of the one-sample QKV
+// projection.  300 tokens, 2048-wide, before and after: QKV 24.3 -> 17.1 us
+// (128x96), O 15.7 -> 13.3 (64x96), GeGLU 57.5 -> 43.5 (256x160: 256 tiles, 320
+// instead of 512 padded rows), down 51.2 -> 33.8 (128x160, K split 8 ways).
+// More stages measured no faster.  Rows past M and N are fetched as
+// zeros without touching memory (lane offsets past the buffer range).
+//
+// TR as in ring_tile below; a transposed operand's tile side is a multiple of
+// 128 (its 64 k-lines hold BN or BM elements, swizzled by tswz).
+// [kt0, kt1): the K slabs summed.  WIDE: the row offsets inside a panel may
+// exceed 32 bits (leading dimensions beyond 4M elements), so every DMA
+// instruction's 8 rows get a buffer base of their own.
+template <int BN, int BM, int NS, int NSW, int EPI, int TR, bool WIDE = false>
+__device__ __forceinline__ void flex_tile(const GemmArgs& g, int32_t tm, int32_t tn, int32_t kt0, int32_t kt1,
+                                          uint16_t* __restrict__ lds) {
+  constexpr bool TX = (TR & GEMM_TRANS_X) != 0, TW = (TR & GEMM_TRANS_W) != 0;
+  constexpr bool GLU = EPI == EPI_GEGLU_BF16;
+  constexpr int WGN = 2, WGM = 2, NWV = WGN * WGM;
+  constexpr int WN = BN / WGN, WM = BM / WGM;
+  constexpr int TN = WN / 16, TM = WM / 16;
+  constexpr int NW = BN / (8 * NWV), NX = BM / (8 * NWV);  // 1 KB DMA instructions per wave per slab
+  constexpr int SLW = BN * kBK, SLX = BM * kBK;            // elements per stage
+  static_assert(BN % 32 == 0 && BM % 32 == 0 && NS >= 3 && (NSW == NS || NSW == NS - 1), "tile shape");
+  static_assert(!WIDE || (TR == 0 && !GLU), "wide rows");
+  static_assert((!TX || BM % 128 == 0) && (!TW || BN % 128 == 0) && !(GLU && (TR || TN % 2)), "operand layout");
+  const int32_t M = g.M, N = g.N;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wn = wave / WGM, wm = wave % WGM;
+  const int32_t m0 = tm * BM, c0 = GLU ? tn * (BN / 2) : tn * BN;
+  const int KT = kt1 - kt0;
+  // operand panels from slab kt0 on; a row-major panel's lanes past the last
+  // row carry an offset past its range, a transposed one's range ends with K
+  constexpr uint32_t kPast = 0x80000000u;
+  const int64_t k0 = (int64_t)kt0 * kBK;
+  const uint16_t* const xb = TX ? g.X + k0 * g.ldx + m0 : g.X + (int64_t)m0 * g.ldx + k0;
+  const uint16_t* const wb = TW ? g.W + k0 * g.ldw + c0 : g.W + (int64_t)c0 * g.ldw + k0;
+  const uint16_t* const wb2 = GLU ? g.W2 + (int64_t)c0 * g.ldw + k0 : wb;
+  const __amdgpu_buffer_rsrc_t xr = panel_rsrc(xb, TX ? ((g.K - k0) * g.ldx - m0) * 2 : (int64_t)0x7fffffff);
+  const __amdgpu_buffer_rsrc_t wr = panel_rsrc(wb, TW ? ((g.K - k0) * g.ldw - c0) * 2 : (int64_t)0x7fffffff);
+  const __amdgpu_buffer_rsrc_t wr2 = panel_rsrc(wb2, (int64_t)0x7fffffff);
+  uint32_t xo[NX], wo[NW];
+#pragma unroll
+  for (int i = 0; i < NX; ++i) {
+    if constexpr (TX) {
+      constexpr int LPL = BM / 8;  // lanes per k-line
+      const int kl = (wave * NX + i) * (64 / LPL) + lane / LPL;
+      xo[i] = (uint32_t)(((int64_t)kl * g.ldx + ((lane % LPL) ^ tswz(kl)) * 8) * 2);
+    } else {
+      const int r = (BM / NWV) * wave + 8 * i + (lane >> 3);
+      const int64_t row = WIDE ? lane >> 3 : r;
+      xo[i] = m0 + r < M ? (uint32_t)((row * g.ldx + ((lane & 7) ^ lds_swz(r)) * 8) * 2) : kPast;
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    if constexpr (TW) {
+      constexpr int LPL = BN / 8;
+      const int kl = (wave * NW + i) * (64 / LPL) + lane / LPL;
+      wo[i] = (uint32_t)(((int64_t)kl * g.ldw + ((lane % LPL) ^ tswz(kl)) * 8) * 2);
+    } else {
+      const int r = (BN / NWV) * wave + 8 * i + (lane >> 3);
+      const int32_t col = GLU ? c0 + (r >> 5) * 16 + (r & 15) : c0 + r;
+      const int64_t row = WIDE ? lane >> 3 : col - c0;
+      wo[i] = col < N ? (uint32_t)((row * g.ldw + ((lane & 7) ^ lds_swz(r)) * 8) * 2) : kPast;
+    }
+  }
+  const int32_t xso = TX ? (int32_t)(kBK * 2 * g.ldx) : kBK * 2;  // byte step between slabs
+  const int32_t wso = TW ? (int32_t)(kBK * 2 * g.ldw) : kBK * 2;
+  uint16_t* const wl = lds;
+  uint16_t* const xl = lds + NSW * SLW;
+  const int dw = wave * NW * 512, dx = wave * NX * 512;
+  // DMA d of slab `slab` into stage `st` (16-byte DMA to LDS does not exist
+  // for the host pass)
+#ifndef __HIP_DEVICE_COMPILE__
+#define JN_FLEX_DMA_X(d, slab, st) (void)(d)
+#define JN_FLEX_DMA_W(d, slab, st) (void)(d)
+#else
+#define JN_FLEX_DMA_X(d, slab, st)                                                                                    \
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(                                                                           \
+      WIDE ? panel_rsrc(xb + (int64_t)((BM / NWV) * wave + 8 * (d)) * g.ldx, 0x7fffffff) : xr,                        \
+      JN_LPTR(xl + (st) * SLX + dx + (d) * 512), 16, TX ? xo[d] + (uint32_t)((slab) * xso) : xo[d],                   \
+      TX ? 0 : (slab) * xso, 0, 0)
+#define JN_FLEX_DMA_W(d, slab, st)                                                                                    \
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(                                                                           \
+      WIDE ? panel_rsrc(wb + (int64_t)((BN / NWV) * wave + 8 * (d)) * g.ldw, 0x7fffffff)                              \
+           : (GLU && ((((BN / NWV) * wave + 8 * (d)) >> 4) & 1)) ? wr2 : wr,                                          \
+      JN_LPTR(wl + (st) * SLW + dw + (d) * 512), 16, TW ? wo[d] + (uint32_t)((slab) * wso) : wo[d],                   \
+      TW ? 0 : (slab) * wso, 0, 0)
+#endif
+
+  f32x4 acc[TN][TM];
+#pragma unroll
+  for (int i = 0; i < TN; ++i)
+#pragma unroll
+    for (int j = 0; j < TM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int sw = lds_swz(lane & 15), quad = lane >> 4;
+  const int wrow = wn * WN + (lane & 15), xrow = wm * WM + (lane & 15);
+  // transposed reads as in ring_tile, for k-lines of BN / BM elements
+  const int te = (lane & 15) >> 2, tc = lane & 3;
+  const int tsub = 8 * (tc >> 1) + 4 * (tc & 1) + 16 * ((te & 3) | ((quad & 1) << 2));
+  auto frag_w = [&](const uint16_t* slot, int f, int h) -> bf16x8 {
+    if constexpr (TW) {
+      const uint16_t* p = slot + (32 * h + 8 * quad + te) * BN + (tsub ^ (16 * (wn * TN + f)));
+      const bf16x4 lo = __builtin_bit_cast(bf16x4, lds_read_tr_b16<0>(p));
+      const bf16x4 hi = __builtin_bit_cast(bf16x4, lds_read_tr_b16<8 * BN>(p));
+      return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    } else {
+      return *reinterpret_cast<const bf16x8*>(slot + (wrow + 16 * f) * kBK + ((4 * h + quad) ^ sw) * 8);
+    }
+  };
+  auto frag_x = [&](const uint16_t* slot, int f, int h) -> bf16x8 {
+    if constexpr (TX) {
+      const uint16_t* p = slot + (32 * h + 8 * quad + te) * BM + (tsub ^ (16 * (wm * TM + f)));
+      const bf16x4 lo = __builtin_bit_cast(bf16x4, lds_read_tr_b16<0>(p));
+      const bf16x4 hi = __builtin_bit_cast(bf16x4, lds_read_tr_b16<8 * BM>(p));
+      return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    } else {
+      return *reinterpret_cast<const bf16x8*>(slot + (xrow + 16 * f) * kBK + ((4 * h + quad) ^ sw) * 8);
+    }
+  };
+
+  constexpr int Q = TN * TM, F = TN + TM, D = NW + NX;
+  constexpr int FP = (F + Q - 1) / Q, FS = Q / F > 0 ? Q / F : 1;  // fragment reads per MFMA, MFMAs per read
+  // Weight slab kt+NSW is requested in phase 1 of iteration kt and token slab
+  // kt+NS-1 in its phase 0; the first slabs in the same order, so that the
+  // counted waits below hold from the first iteration on.
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    const int sl = min(s, KT - 1);
+    if (NSW < NS && s < NS - 1) {
+#pragma unroll
+      for (int d = 0; d < NX; ++d) JN_FLEX_DMA_X(d, sl, s);
+    }
+    if (s < NSW) {
+#pragma unroll
+      for (int d = 0; d < NW; ++d) JN_FLEX_DMA_W(d, sl, s);
+    }
+    if (NSW == NS && s < NS - 1) {
+#pragma unroll
+      for (int d = 0; d < NX; ++d) JN_FLEX_DMA_X(d, sl, s);
+    }
+  }
+  wait_vmcnt<(NS - 2) * D + (NSW == NS ? NW : 0)>();  // slab 0 landed
+  __builtin_amdgcn_s_barrier();
+  bf16x8 fa[F], fb[F];  // first-half / second-half fragments: weights, then tokens
+#pragma unroll
+  for (int i = 0; i < TN; ++i) fa[i] = frag_w(wl, i, 0);
+#pragma unroll
+  for (int j = 0; j < TM; ++j) fa[TN + j] = frag_x(xl, j, 0);
+  wait_lgkmcnt<0>();
+  int sx = 0, sv = 0;  // kt % NS, kt % NSW
+  for (int kt = 0; kt < KT; ++kt) {
+    const int nxt = sx + 1 == NS ? 0 : sx + 1, prv = sx == 0 ? NS - 1 : sx - 1, nxv = sv + 1 == NSW ? 0 : sv + 1;
+    // past the last slab the DMAs repeat it into a free stage (no branches)
+    const int f0 = min(kt - 1 + NS, KT - 1), f1 = min(kt + NSW, KT - 1);
+    {
+      const uint16_t *cw = wl + sv * SLW, *cx = xl + sx * SLX;
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const int i = q / TM, j = q % TM;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fa[TN + j], acc[i][j], 0, 0, 0);
+        if (q % FS == 0) {
+#pragma unroll
+          for (int e = 0; e < FP; ++e) {
+            const int f = (q / FS) * FP + e;
+            if (f < TN)
+              fb[f] = frag_w(cw, f, 1);
+            else if (f < F)
+              fb[f] = frag_x(cx, f - TN, 1);
+          }
+        }
+#pragma unroll
+        for (int d = 0; d < NX; ++d)
+          if ((2 * d + 1) * Q / (2 * NX) == q) JN_FLEX_DMA_X(d, f0, prv);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    wait_lgkmcnt<0>();
+    wait_vmcnt<(NS - 2) * NX + (NSW - 2) * NW>();  // slab kt+1 landed
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    {
+      const uint16_t *nw = wl + nxv * SLW, *nx = xl + nxt * SLX;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        const int i = q / TM, j = q % TM;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[i], fb[TN + j], acc[i][j], 0, 0, 0);
+        if (q % FS == 0) {
+#pragma unroll
+          for (int e = 0; e < FP; ++e) {
+            const int f = (q / FS) * FP + e;
+            if (f < TN)
+              fa[f] = frag_w(nw, f, 0);
+            else if (f < F)
+              fa[f] = frag_x(nx, f - TN, 0);
+          }
+        }
+#pragma unroll
+        for (int d = 0; d < NW; ++d)
+          if ((2 * d + 1) * Q / (2 * NW) == q) JN_FLEX_DMA_W(d, f1, sv);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    wait_lgkmcnt<0>();
+    sx = nxt;
+    sv = nxv;
+  }
+#undef JN_FLEX_DMA_X
+#undef JN_FLEX_DMA_W
+  wait_vmcnt<0>();  // the repeated slabs' DMAs land before the LDS is released
+  // accumulators pinned to the accumulation registers (as in ring_tile)
+#pragma unroll
+  for (int i = 0; i < TN; ++i)
+#pragma unroll
+    for (int j = 0; j < TM; ++j) asm volatile("" : "+a"(acc[i][j]));
+  gemm_epilogue<BN, BM, WGN, WGM, EPI>(g, acc, tm, tn, wn, wm, lane);
+}
+
+// Tile idx of an XCD-contiguous walk over `total` work items: the hardware
+// deals workgroups round-robin to the 8 XCDs, and every XCD takes one run of
+// consecutive items (the padded grid's workgroups past the end do nothing).
+// A short launch's token tiles are the fast index, so one XCD holds all token
+// tiles of its weight tiles: a weight row is fetched from memory by one L2
+// instead of by all eight.
+__device__ __forceinline__ int32_t xcd_item(int32_t b, int32_t grid) { return (b & 7) * (grid >> 3) + (b >> 3); }
+
+// Tile t of the walk inside a launch or problem: token tiles fastest, all of
+// them for up to 16 (each weight row is then wanted by one XCD at one time),
+// else in groups of 8, so that an XCD's 32 tiles in flight form an 8 x 4 block.
+__device__ __forceinline__ void flex_walk(int32_t t, int32_t tiles_m, int32_t tiles_n, int32_t& tm, int32_t& tn) {
+  const int32_t gm = tiles_m <= 16 ? tiles_m : 8, per = gm * tiles_n;
+  const int32_t grp = t / per, r = t - grp * per, size = min(tiles_m - grp * gm, gm);
+  tm = grp * gm + r % size;
+  tn = r / size;
+}
+
+// One launch over g: K ranges (slabs KT s / S ..), then tiles.
+template <int BN, int BM, int NS, int NSW, int EPI, int OCC, bool WIDE>
+__global__ __launch_bounds__(256, OCC) void gemm_flex_kernel(GemmArgs g, int32_t S) {
+  __shared__ __attribute__((aligned(1024))) uint16_t lds[(NSW * BN + NS * BM) * kBK];
+  const int32_t tiles = g.tiles_m * g.tiles_n, idx = xcd_item(blockIdx.x, gridDim.x);
+  if (idx >= tiles * S) return;
+  const int32_t s = idx / tiles, t = idx - s * tiles;
+  const int64_t KT = g.K / kBK;
+  if (s) g.C = reinterpret_cast<float*>(g.C) + (int64_t)s * g.split_c;
+  int32_t tm, tn;
+  flex_walk(t, g.tiles_m, g.tiles_n, tm, tn);
+  flex_tile<BN, BM, NS, NSW, EPI, 0, WIDE>(g, tm, tn, (int32_t)(KT * s / S), (int32_t)(KT * (s + 1) / S), lds);
+}
+
+// One launch over several independent problems (one per tenant): work item i
+// is tile i - tile_start of the problem whose tile range holds it.
+template <int BN, int BM, int NS, int NSW, int EPI, int TR, int OCC, bool WIDE>
+__global__ __launch_bounds__(256, OCC) void gemm_grouped_flex_kernel(const GemmArgs* __restrict__ probs, int32_t nprob,
+                                                                     int32_t total) {
+  __shared__ __attribute__((aligned(1024))) uint16_t lds[(NSW * BN + NS * BM) * kBK];
+  const int32_t idx = xcd_item(blockIdx.x, gridDim.x);
+  if (idx >= total) return;
+  int32_t p = 0;
+  while (p + 1 < nprob && probs[p + 1].tile_start <= idx) ++p;
+  const GemmArgs g = probs[p];
+  int32_t tm, tn;
+  flex_walk(idx - g.tile_start, g.tiles_m, g.tiles_n, tm, tn);
+  flex_tile<BN, BM, NS, NSW, EPI, TR, WIDE>(g, tm, tn, 0, (g.K + kBK - 1) / kBK, lds);
+}
+
 // Ring-buffered loop of the 256x256 tile on 4 wavefronts, one per SIMD, each
 // 128 weight rows x 128 tokens (64 accumulator blocks, kept in the
 // accumulation registers).  Per K=64 slab kt, phase 0 runs the first k-half's
@@ -486,7 +619,7 @@ __device__ __forceinline__ int tswz(int k) { return 2 * ((k & 3) | ((k & 8) >> 1
 // the 8-wave loop and the first 4-wave versions lost: each conditional branch
 // in the MFMA stream cost 30-50 cycles of issue, and global_load_lds with a
 // 64-bit address computed per instruction cost more than the buffer form.
-// Tile pid of problem g; lds holds 5 x 32 KB.
+// Tile (tm, tn) of problem g; lds holds 5 x 32 KB.
 //
 // TR: operands stored transposed (GEMM_TRANS_X: X is [K][M], element (m, k)
 // at X[k * ldx + m]; GEMM_TRANS_W: W is [K][N]).  A transposed operand's
@@ -497,7 +630,7 @@ __device__ __forceinline__ int tswz(int k) { return 2 * ((k & 3) | ((k & 8) >> 1
 // Loads past line K of a transposed operand return zero (buffer range), so
 // with both operands transposed K need not be a multiple of 64.
 template <int EPI, int TR>
-__device__ __forceinline__ void ring_tile(const GemmArgs& g, int32_t pid, uint16_t* __restrict__ lds) {
+__device__ __forceinline__ void ring_tile(const GemmArgs& g, int32_t tm, int32_t tn, uint16_t* __restrict__ lds) {
   constexpr bool TX = (TR & GEMM_TRANS_X) != 0, TW = (TR & GEMM_TRANS_W) != 0;
   constexpr int BN = 256, BM = 256, WGN = 2, WGM = 2;
   constexpr int WN = BN / WGN, WM = BM / WGM;
@@ -507,8 +640,6 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, int32_t pid, uint16
   constexpr bool GLU = EPI == EPI_GEGLU_BF16;
   const int32_t M = g.M, K = g.K;
 
-  int32_t tm, tn;
-  tile_of(pid, g.tiles_m, g.tiles_n, tm, tn);
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wn = wave / WGM, wm = wave % WGM;
@@ -700,29 +831,29 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, int32_t pid, uint16
   }
 }
 
-// One launch of ring tiles over g (split-K ranges from blockIdx.y as in
-// gemm_kernel).  With g.xcd_ranges (S = gridDim.y ranges, S | 8, at most
-// kGroupM token tiles, 8 / S | tiles_n) workgroup b + gridDim.x y, which the
-// hardware places on XCD x = (b + gridDim.x y) % 8, takes K range
-// x / (8 / S) and, of that range, the tiles of one block of tiles_n / (8 / S)
-// weight tiles over all token tiles.  In the grouped walk every XCD held one
-// token tile over all K ranges and all weight tiles, so each of the 8 L2s
-// fetched the whole weight matrix; now an XCD fetches one range's token rows
-// and a 1/(8/S) share of that range's weight columns.  Which workgroup
-// computes a (range, tile) changes nothing else.
+// One launch of ring tiles over g.
 template <int EPI>
-__global__ __launch_bounds__(256, 1) void gemm_ring_kernel(GemmArgs g0) {
+__global__ __launch_bounds__(256, 1) void gemm_ring_kernel(GemmArgs g) {
   __shared__ __attribute__((aligned(1024))) uint16_t lds[5 * 256 * kBK];
-  int32_t pid = blockIdx.x, s = blockIdx.y;
-  if (g0.xcd_ranges) {
-    const int32_t lin = blockIdx.x + blockIdx.y * gridDim.x;
-    const int32_t x = lin & 7, slot = lin >> 3, nx = 8 / gridDim.y;
-    s = x / nx;
-    const int32_t tm = slot % g0.tiles_m;
-    const int32_t tn = (x % nx) * (g0.tiles_n / nx) + slot / g0.tiles_m;
-    pid = tn * g0.tiles_m + tm;  // tile_of's inverse for tiles_m <= kGroupM
-  }
-  ring_tile<EPI, 0>(split_range(g0, s), pid, lds);
+  int32_t tm, tn;
+  tile_of(blockIdx.x, g.tiles_m, g.tiles_n, tm, tn);
+  ring_tile<EPI, 0>(g, tm, tn, lds);
+}
+
+// The same over S K ranges, fp32 partials, in gemm_flex_kernel's walk.
+__global__ __launch_bounds__(256, 1) void gemm_ring_split_kernel(GemmArgs g, int32_t S) {
+  __shared__ __attribute__((aligned(1024))) uint16_t lds[5 * 256 * kBK];
+  const int32_t tiles = g.tiles_m * g.tiles_n, idx = xcd_item(blockIdx.x, gridDim.x);
+  if (idx >= tiles * S) return;
+  const int32_t s = idx / tiles;
+  const int64_t KT = g.K / kBK, k0 = KT * s / S, k1 = KT * (s + 1) / S;
+  g.X += k0 * kBK;
+  g.W += k0 * kBK;
+  g.K = (int32_t)(k1 - k0) * kBK;
+  g.C = reinterpret_cast<float*>(g.C) + (int64_t)s * g.split_c;
+  int32_t tm, tn;
+  flex_walk(idx - s * tiles, g.tiles_m, g.tiles_n, tm, tn);
+  ring_tile<EPI_F32, 0>(g, tm, tn, lds);
 }
 
 // Grouped ring tiles: problem p owns tiles [tile_start, tile_start + tiles).
@@ -733,57 +864,106 @@ __global__ __launch_bounds__(256, 1) void gemm_grouped_ring_kernel(const GemmArg
   int32_t p = 0;
   while (p + 1 < nprob && probs[p + 1].tile_start <= b) ++p;
   const GemmArgs g = probs[p];
-  ring_tile<EPI, TR>(g, b - g.tile_start, lds);
+  int32_t tm, tn;
+  tile_of(b - g.tile_start, g.tiles_m, g.tiles_n, tm, tn);
+  ring_tile<EPI, TR>(g, tm, tn, lds);
 }
 
-template <int BN, int BM, int WGN, int WGM>
-static hipError_t launch_tile(hipStream_t s, int epi, GemmArgs g, int32_t splits = 1);
+// Tile shapes: the 256x256 ring loop, then shapes of the flexible loop.  occ:
+// workgroups per CU.  slab: microseconds per K=64 slab with all 256 CUs busy,
+// measured on the 2048-wide projections at 2,469 tokens (the chip is then
+// power-limited; a few busy CUs run 1.1 / 0.8 / 0.6 / 0.4 / 0.27); slab1: with
+// one workgroup on the CU.  fix: per tile, fetching the first slabs and the
+// launch's share.
+struct TileShape {
+  int bn, bm, occ;
+  double slab, slab1, fix;
+};
+constexpr TileShape kShapes[] = {
+    {256, 256, 1, 1.45, 1.45, 5.0}, {256, 160, 1, 1.10, 1.10, 4.5}, {256, 128, 1, 0.90, 0.90, 4.5},
+    {128, 160, 1, 0.62, 0.62, 4.0}, {128, 96, 1, 0.46, 0.46, 4.0},  {64, 96, 2, 0.26, 0.28, 4.0},
+    {128, 128, 2, 0.54, 0.62, 2.3},
+};
+constexpr int kNumShapes = 6;   // of every launch
+constexpr int kResidShape = 6;  // and of the unsplit residual adds
 
-// The 256x256 ring loop over all tiles of g (grid.y = split-K ranges).  Its
-// per-lane panel offsets are 32-bit: leading dimensions beyond 4M elements
-// take the 256x128 loop (same MFMA sequence per output element).
-static hipError_t launch_ring(hipStream_t s, int epi, GemmArgs g, int32_t splits = 1) {
-  if ((int64_t)256 * std::max(g.ldx, g.ldw) * 2 > (int64_t)0x7fffffff)
-    return launch_tile<256, 128, 4, 2>(s, epi, g, splits);
+// 32-bit lane offsets span the 256 rows of a panel; beyond (leading dimensions
+// past 4M elements), the small shape runs with one buffer base per DMA
+// instruction (kWideShape of the grouped launches).
+constexpr int kWideShape = 7;
+static bool wide_rows(const GemmArgs& g) { return 512 * std::max(g.ldx, g.ldw) > (int64_t)0x7fffffff; }
+
+// The 256x256 ring loop over all tiles of g (and S K ranges).
+static hipError_t launch_ring(hipStream_t s, int epi, GemmArgs g, int32_t S) {
   const int32_t NL = epi == EPI_GEGLU_BF16 ? 2 * g.N : g.N;
   g.tiles_m = (g.M + 255) / 256;
   g.tiles_n = (NL + 255) / 256;
-  g.tile_start = 0;
-  g.xcd_ranges = splits > 1 && 8 % splits == 0 && g.tiles_m <= kGroupM && g.tiles_n % (8 / splits) == 0;
-  const dim3 grid(g.tiles_m * g.tiles_n, splits), block(256);
+  const dim3 grid(g.tiles_m * g.tiles_n), block(256);
+  if (S > 1) {
+    if (epi != EPI_F32) return hipErrorInvalidValue;
+    gemm_ring_split_kernel<<<dim3((grid.x * S + 7) / 8 * 8), block, 0, s>>>(g, S);
+    return hipGetLastError();
+  }
   switch (epi) {
     case EPI_BF16: gemm_ring_kernel<EPI_BF16><<<grid, block, 0, s>>>(g); break;
     case EPI_GELU_BF16: gemm_ring_kernel<EPI_GELU_BF16><<<grid, block, 0, s>>>(g); break;
     case EPI_RESID_F32: gemm_ring_kernel<EPI_RESID_F32><<<grid, block, 0, s>>>(g); break;
     case EPI_GEGLU_BF16: gemm_ring_kernel<EPI_GEGLU_BF16><<<grid, block, 0, s>>>(g); break;
-    case EPI_F32: gemm_ring_kernel<EPI_F32><<<grid, block, 0, s>>>(g); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-template <int BN, int BM, int WGN, int WGM>
-static hipError_t launch_tile(hipStream_t s, int epi, GemmArgs g, int32_t splits) {
+template <int BN, int BM, int NS, int OCC, bool WIDE = false>
+static hipError_t launch_flex(hipStream_t s, int epi, GemmArgs g, int32_t S) {
   const int32_t NL = epi == EPI_GEGLU_BF16 ? 2 * g.N : g.N;
   g.tiles_m = (g.M + BM - 1) / BM;
   g.tiles_n = (NL + BN - 1) / BN;
-  g.tile_start = 0;
-  dim3 grid(g.tiles_m * g.tiles_n, splits), block(64 * WGN * WGM);
+  const dim3 grid((unsigned)(((int64_t)g.tiles_m * g.tiles_n * S + 7) / 8 * 8)), block(256);
 #define JN_GEMM_CASE(E) \
-  case E: gemm_kernel<BN, BM, WGN, WGM, E><<<grid, block, 0, s>>>(g); break;
-  switch (epi) {
-    JN_GEMM_CASE(EPI_BF16)
-    JN_GEMM_CASE(EPI_GELU_BF16)
-    JN_GEMM_CASE(EPI_RESID_F32)
-    JN_GEMM_CASE(EPI_GEGLU_BF16)
-    JN_GEMM_CASE(EPI_F32)
-    JN_GEMM_CASE(EPI_GELU_SAVE)
-    JN_GEMM_CASE(EPI_GELUGRAD_BF16)
-    default:
-      return hipErrorInvalidValue;
+  case E: gemm_flex_kernel<BN, BM, NS, NS, E, OCC, WIDE><<<grid, block, 0, s>>>(g, S); break;
+  if constexpr (WIDE) {
+    switch (epi) {
+      JN_GEMM_CASE(EPI_RESID_F32)
+      JN_GEMM_CASE(EPI_F32)
+      default: return hipErrorInvalidValue;
+    }
+  } else {
+    switch (epi) {
+      JN_GEMM_CASE(EPI_BF16)
+      JN_GEMM_CASE(EPI_GELU_BF16)
+      JN_GEMM_CASE(EPI_RESID_F32)
+      JN_GEMM_CASE(EPI_GEGLU_BF16)
+      JN_GEMM_CASE(EPI_F32)
+      default: return hipErrorInvalidValue;
+    }
   }
 #undef JN_GEMM_CASE
   return hipGetLastError();
+}
+
+// 128x128 residual tiles, two workgroups per CU (three token and two weight
+// stages each).
+static hipError_t launch_resid128(hipStream_t s, GemmArgs g) {
+  g.tiles_m = (g.M + 127) / 128;
+  g.tiles_n = (g.N + 127) / 128;
+  const dim3 grid((unsigned)(((int64_t)g.tiles_m * g.tiles_n + 7) / 8 * 8));
+  gemm_flex_kernel<128, 128, 3, 2, EPI_RESID_F32, 2, false><<<grid, 256, 0, s>>>(g, 1);
+  return hipGetLastError();
+}
+
+// One launch over all rows of g with tile shape t and S K ranges.
+static hipError_t launch_rows(hipStream_t s, int epi, const GemmArgs& g, int t, int32_t S = 1) {
+  if (wide_rows(g)) return launch_flex<64, 96, 4, 2, true>(s, epi, g, S);
+  switch (t) {
+    case 0: return launch_ring(s, epi, g, S);
+    case 1: return launch_flex<256, 160, 3, 1>(s, epi, g, S);
+    case 2: return launch_flex<256, 128, 3, 1>(s, epi, g, S);
+    case 3: return launch_flex<128, 160, 4, 1>(s, epi, g, S);
+    case 4: return launch_flex<128, 96, 4, 1>(s, epi, g, S);
+    case 5: return launch_flex<64, 96, 4, 2>(s, epi, g, S);
+    default: return epi == EPI_RESID_F32 && S == 1 ? launch_resid128(s, g) : hipErrorInvalidValue;
+  }
 }
 
 static hipError_t launch_grouped_ring(hipStream_t s, int epi, const GemmArgs* dprobs, int32_t nprob,
@@ -807,221 +987,175 @@ static hipError_t launch_grouped_ring(hipStream_t s, int epi, const GemmArgs* dp
   return hipGetLastError();
 }
 
-template <int BN, int BM, int WGN, int WGM>
-static hipError_t launch_grouped_tile(hipStream_t s, int epi, const GemmArgs* dprobs, int32_t nprob,
-                                      int32_t total_tiles) {
-  dim3 grid(total_tiles), block(64 * WGN * WGM);
+template <int BN, int BM, int NS, int OCC, bool WIDE = false>
+static hipError_t launch_grouped_flex(hipStream_t s, int epi, const GemmArgs* dprobs, int32_t nprob, int32_t total) {
+  const dim3 grid((unsigned)((total + 7) / 8 * 8)), block(256);
 #define JN_GEMM_CASE(E) \
-  case E: gemm_grouped_kernel<BN, BM, WGN, WGM, E><<<grid, block, 0, s>>>(dprobs, nprob); break;
-  switch (epi) {
-    JN_GEMM_CASE(EPI_BF16)
-    JN_GEMM_CASE(EPI_RESID_F32)
-    JN_GEMM_CASE(EPI_F32)
-    JN_GEMM_CASE(EPI_GELU_SAVE)
-    JN_GEMM_CASE(EPI_GELUGRAD_BF16)
-    default:
-      return hipErrorInvalidValue;
+  case E: gemm_grouped_flex_kernel<BN, BM, NS, NS, E, 0, OCC, WIDE><<<grid, block, 0, s>>>(dprobs, nprob, total); break;
+  if constexpr (WIDE) {
+    switch (epi) {
+      JN_GEMM_CASE(EPI_RESID_F32)
+      JN_GEMM_CASE(EPI_F32)
+      default: return hipErrorInvalidValue;
+    }
+  } else {
+    switch (epi) {
+      JN_GEMM_CASE(EPI_BF16)
+      JN_GEMM_CASE(EPI_RESID_F32)
+      JN_GEMM_CASE(EPI_F32)
+      JN_GEMM_CASE(EPI_GELU_SAVE)
+      JN_GEMM_CASE(EPI_GELUGRAD_BF16)
+      default: return hipErrorInvalidValue;
+    }
   }
 #undef JN_GEMM_CASE
   return hipGetLastError();
 }
 
-// Tile choice: fewest "tile-waves" over the 256 CUs, weighted by a per-shape
-// efficiency factor (smaller tiles re-read more operand bytes per flop).
-// The same rule serves grouped and per-tenant launches.
-int gemm_pick_tile(int epi, int32_t M, int32_t N) {
-  const int32_t NL = epi == EPI_GEGLU_BF16 ? 2 * N : N;
-  struct Cand { int bn, bm; double eff; } cands[] = {{256, 256, 1.0}, {256, 128, 1.12}, {128, 128, 1.35}};
-  int best = 0;
-  double best_cost = 1e300;
-  for (int c = 0; c < 3; ++c) {
-    const int64_t tiles = (int64_t)((M + cands[c].bm - 1) / cands[c].bm) * ((NL + cands[c].bn - 1) / cands[c].bn);
-    const double waves = (double)((tiles + 255) / 256);
-    const double cost = waves * cands[c].bn * cands[c].bm * cands[c].eff;
-    if (cost < best_cost * 0.999) {
-      best_cost = cost;
-      best = c;
+// Bytes an epilogue reads and writes per tile element (GeGLU: per gate or up
+// element), and the microseconds of its GELU per element and CU.
+static double epi_bytes(int epi) {
+  switch (epi) {
+    case EPI_RESID_F32: return 8.0;
+    case EPI_F32: return 4.0;
+    case EPI_GELU_SAVE: case EPI_GELUGRAD_BF16: return 6.0;
+    case EPI_GEGLU_BF16: return 1.0;
+    default: return 2.0;
+  }
+}
+static double epi_alu(int epi) {
+  switch (epi) {
+    case EPI_GELU_BF16: return 7.5e-5;
+    case EPI_GEGLU_BF16: return 4e-5;
+    case EPI_GELU_SAVE: case EPI_GELUGRAD_BF16: return 1.5e-4;
+    default: return 0.0;
+  }
+}
+
+// Time of `tiles` tiles of shape t with `slabs` slabs each, in microseconds:
+// rounds of 256 tiles, each its slabs, fixed cost and GELU, plus the epilogue's
+// bytes at the copy rate (4.8 TB/s).  One workgroup per CU runs its epilogue
+// while its matrix cores idle, and all tiles of a round reach it together (the
+// 768-wide O projection spends 33 of a round's 55 us there); with two per CU
+// about half of it runs under the other's main loop, and over many rounds the
+// tiles drift apart and the weights stay in the caches (13%).  Against measurements
+// (300 to 28,812 tokens, 768- and 2048-wide projections) within ~15%.
+static double tiles_time(int epi, int64_t tiles, double slabs, int t) {
+  const TileShape& T = kShapes[t];
+  const double elems = (double)T.bn * T.bm, rounds = (double)((tiles + 255) / 256);
+  const double once = rounds * (T.fix + elems * epi_alu(epi)) + tiles * elems * epi_bytes(epi) / 4.8e6;
+  if (T.occ == 2) return rounds * slabs * (rounds > 1 ? T.slab : T.slab1) + 0.5 * (once + T.fix);
+  return (rounds * slabs * T.slab + once) * (1.0 - 0.013 * std::min(rounds - 1.0, 10.0));
+}
+
+// One launch over `rows` rows and S K ranges; a split adds the launch of its
+// reduction and the second half of the fp32 partials' round trip.
+static double tile_time(int epi, int32_t rows, int32_t N, int32_t K, int t, int32_t S) {
+  const TileShape& T = kShapes[t];
+  const int64_t NL = epi == EPI_GEGLU_BF16 ? 2 * (int64_t)N : N;
+  const int64_t tiles = (rows + T.bm - 1) / T.bm * ((NL + T.bn - 1) / T.bn) * S;
+  const double us = tiles_time(S > 1 ? EPI_F32 : epi, tiles, (double)((K / kBK + S - 1) / S), t);
+  return S > 1 ? us + 4.0 + 4e-6 * S * (double)rows * N / 4.8 : us;
+}
+
+// K may be split (fp32 partials of S ranges added in range order by a second
+// launch, which applies the epilogue) where the launch has at most 128 tiles
+// of 256x256 and K >= 2048: with fewer, longer tiles most CUs would idle.  Two
+// launches that split a GEMM differently sum its K ranges differently, so the
+// limits also bound which batches can differ in their last bits.
+static bool may_split(int epi, int32_t rows, int32_t N, int32_t K) {
+  if (epi != EPI_BF16 && epi != EPI_RESID_F32 && epi != EPI_GELU_BF16) return false;
+  return K >= 2048 && N % 4 == 0 && (int64_t)((rows + 255) / 256) * ((N + 255) / 256) <= 128;
+}
+
+// Shape and K split of one launch over `rows` rows; ranges of >= 8 slabs.
+static double plan_launch(int epi, int32_t rows, int32_t N, int32_t K, bool split, int* shape, int32_t* S) {
+  const int32_t smax = split && may_split(epi, rows, N, K) ? std::min(16, K / (8 * kBK)) : 1;
+  double best = 1e300;
+  for (int t = 0; t <= kResidShape; ++t) {
+    if (t == kResidShape && epi != EPI_RESID_F32) break;
+    for (int32_t k = 1; k <= (t == kResidShape ? 1 : smax); ++k) {
+      const double us = tile_time(epi, rows, N, K, t, k);
+      if (us < best * 0.999) {
+        best = us;
+        *shape = t;
+        *S = k;
+      }
     }
   }
   return best;
 }
 
-// Split-K: tile shape and K split S chosen together by an estimated time:
-// waves of tiles * S over kSplitCUs, each a tile of 2 * BN * BM * K / S flops
-// (times the shape factor) at the per-CU rate measured for this GEMM, plus
-// the fp32 partials written and read back (2 * 4 * S * M * N bytes) at a
-// sustained HBM rate.  Splits are considered only for launches of at most
-// kSplitCUs / 2 tiles, with ranges of K / S >= 1024 (16 slabs) and S a power
-// of two; S = 1 reproduces gemm_pick_tile's choice.  Fixed constants keep the
-// size query and the launch in agreement on any device.
-constexpr int32_t kSplitCUs = 256;
-constexpr double kCuFlops = 4.3e12;    // ~1.1 PFLOP/s over 256 CUs
-constexpr double kPartialBw = 5.0e12;  // bytes/s for the partial round trip
+// Launches of one GEMM: rows [0, m1) as whole waves of 256x256 ring tiles and
+// the rest with the shape (and, for K >= kTailSplitK, the K split) that the
+// estimate gives the shortest time, or one launch over all rows.  The cut lies
+// where the leading tiles fill the last or the last but one wave.  The split
+// tail of a long contraction is summed in K ranges, so a row of such a launch
+// can differ in its last bits from the same row in another batch (every shape
+// runs the same MFMA sequence per output element, so nothing else can).
+constexpr int32_t kTailSplitK = 8192;
+constexpr double kLaunchGap = 3.0;  // microseconds between two launches on one stream
 
-static void gemm_plan(int epi, int32_t M, int32_t N, int32_t K, int* tile, int* splits) {
-  *tile = gemm_pick_tile(epi, M, N);
-  *splits = 1;
-  if (epi != EPI_BF16 && epi != EPI_RESID_F32 && epi != EPI_GELU_BF16) return;
-  if (M <= 0 || N <= 0 || K <= 0 || N % 4 != 0) return;
-  static const int bn[3] = {256, 256, 128}, bm[3] = {256, 128, 128};
-  static const double eff[3] = {1.0, 1.12, 1.35};
-  double best = 1e300;
-  for (int t = 0; t < 3; ++t) {
-    const int64_t tiles = (int64_t)((M + bm[t] - 1) / bm[t]) * ((N + bn[t] - 1) / bn[t]);
-    for (int S = 1; S <= 64; S *= 2) {
-      if (S > 1 && (tiles * 2 > kSplitCUs || K % (kBK * S) != 0 || K / S < 1024)) break;
-      const double waves = (double)((tiles * S + kSplitCUs - 1) / kSplitCUs);
-      double cost = waves * 2.0 * bn[t] * bm[t] * eff[t] * ((double)K / S) / kCuFlops;
-      if (S > 1) cost += 8.0 * S * (double)M * N / kPartialBw;
-      if (cost < best * 0.999) {
-        best = cost;
-        *tile = t;
-        *splits = S;
-      }
+struct GemmPlan {
+  int32_t m1 = 0;      // rows of the leading ring launch (0: none)
+  int shape = 0;       // the other rows
+  int32_t S = 1;
+};
+
+static GemmPlan gemm_plan(int epi, int32_t M, int32_t N, int32_t K) {
+  GemmPlan P;
+  if (M <= 0 || N <= 0 || K <= 0) return P;
+  double best = plan_launch(epi, M, N, K, true, &P.shape, &P.S);
+  const int64_t tn = ((epi == EPI_GEGLU_BF16 ? 2 * (int64_t)N : N) + 255) / 256, tm = (M + 255) / 256;
+  const int64_t waves = (tm * tn + 255) / 256;
+  int64_t last = -1;
+  for (int64_t w = waves - 1; w >= 1 && w >= waves - 2; --w) {
+    const int64_t r = std::min(tm - 1, 256 * w / tn);
+    if (r < 1 || r == last) continue;
+    last = r;
+    const int32_t m1 = (int32_t)(r * 256);
+    int t = 0;
+    int32_t S = 1;
+    double us = tile_time(epi, m1, N, K, 0, 1) + kLaunchGap;
+    us += plan_launch(epi, M - m1, N, K, K >= kTailSplitK, &t, &S);
+    if (us < best * 0.99) {
+      best = us;
+      P.m1 = m1;
+      P.shape = t;
+      P.S = S;
     }
   }
+  return P;
 }
 
-int gemm_split(int epi, int32_t M, int32_t N, int32_t K) {
-  int t, S;
-  gemm_plan(epi, M, N, K, &t, &S);
-  return S;
+int32_t gemm_split(int epi, int32_t M, int32_t N, int32_t K) {
+  const GemmPlan P = gemm_plan(epi, M, N, K);
+  return P.m1 == 0 ? P.S : 1;
 }
-
-static int32_t gemm_tail_split(int epi, int32_t M, int32_t N, int32_t K, int32_t* m1, int* t1, int* t2);
 
 size_t gemm_split_bytes(int epi, int32_t M, int32_t N, int32_t K) {
-  const int S = gemm_split(epi, M, N, K);
-  size_t bytes = S > 1 ? (size_t)S * M * N * sizeof(float) : 0;
-  int32_t m1;
-  int t1, t2;
-  const int32_t St = gemm_tail_split(epi, M, N, K, &m1, &t1, &t2);
-  if (St > 1) bytes = std::max(bytes, (size_t)St * (M - m1) * N * sizeof(float));
-  return bytes;
+  const GemmPlan P = gemm_plan(epi, M, N, K);
+  return P.S > 1 ? (size_t)P.S * (M - P.m1) * N * sizeof(float) : 0;
 }
 
-// One launch over all rows of g with tile shape t (0: 256x256 ring loop,
-// 1: 256x128, 2: 128x128).
-static hipError_t launch_rows(hipStream_t s, int epi, GemmArgs g, int t) {
-  switch (t) {
-    case 0: return launch_ring(s, epi, g);
-    case 1: return launch_tile<256, 128, 4, 2>(s, epi, g);
-    default: return launch_tile<128, 128, 2, 2>(s, epi, g);
-  }
-}
-
-// Split-K: S launches' worth of K ranges as one grid (blockIdx.y = range),
-// fp32 partials into split_ws, then their sum in range order with the
-// epilogue (EPI_BF16, EPI_RESID_F32 or EPI_GELU_BF16).
-static hipError_t launch_split(hipStream_t s, int epi, const void* A, int64_t lda, const void* B, int64_t ldb,
-                               void* C, int64_t ldc, int32_t M, int32_t N, int32_t K, int t, int32_t S,
-                               void* split_ws) {
-  GemmArgs g{};
-  g.X = reinterpret_cast<const uint16_t*>(A);
-  g.W = reinterpret_cast<const uint16_t*>(B);
-  g.C = split_ws;
-  g.ldx = lda;
-  g.ldw = ldb;
-  g.ldc = N;
-  g.M = M;
-  g.N = N;
-  g.K = K / S;
-  g.split_c = (int64_t)M * N;
-  hipError_t e;
-  switch (t) {
-    case 0: e = launch_ring(s, EPI_F32, g, S); break;
-    case 1: e = launch_tile<256, 128, 4, 2>(s, EPI_F32, g, S); break;
-    default: e = launch_tile<128, 128, 2, 2>(s, EPI_F32, g, S); break;
-  }
-  if (e != hipSuccess) return e;
-  const int64_t work = (int64_t)M * (N / 4);
+static hipError_t launch_splitk_reduce(hipStream_t s, int epi, const float* part, int32_t S, int32_t M, int32_t N,
+                                       void* C, int64_t ldc) {
+  const int64_t work = (int64_t)M * (N / 4), stride = (int64_t)M * N;
   const dim3 grid((unsigned)((work + 255) / 256));
-  const float* part = reinterpret_cast<const float*>(split_ws);
   switch (epi) {
-    case EPI_BF16: splitk_reduce_kernel<EPI_BF16><<<grid, 256, 0, s>>>(part, S, g.split_c, M, N, C, ldc); break;
-    case EPI_RESID_F32: splitk_reduce_kernel<EPI_RESID_F32><<<grid, 256, 0, s>>>(part, S, g.split_c, M, N, C, ldc); break;
-    case EPI_GELU_BF16: splitk_reduce_kernel<EPI_GELU_BF16><<<grid, 256, 0, s>>>(part, S, g.split_c, M, N, C, ldc); break;
+    case EPI_BF16: splitk_reduce_kernel<EPI_BF16><<<grid, 256, 0, s>>>(part, S, stride, M, N, C, ldc); break;
+    case EPI_RESID_F32: splitk_reduce_kernel<EPI_RESID_F32><<<grid, 256, 0, s>>>(part, S, stride, M, N, C, ldc); break;
+    case EPI_GELU_BF16: splitk_reduce_kernel<EPI_GELU_BF16><<<grid, 256, 0, s>>>(part, S, stride, M, N, C, ldc); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-// Row split against the last, partly filled wave of tiles: rows [0, m1) run
-// as 256x256 ring tiles and rows [m1, M) as a second launch with a smaller
-// shape t2, chosen by the same time estimate as gemm_plan (tile-waves over
-// the 256 CUs, per-shape efficiency) plus the gap between two launches.  For
-// example 2,368 tiles of 256x256 (9.25 waves) become 9 full waves plus one
-// wave of 128x128 tiles.  Measured: the K=16384 down projection 2.3% faster
-// at 75.5K tokens and 7.5% at 9.4K, the O projection 13% at 9.4K, GeGLU 3.6%
-// at 4.7K; the leading part stays on the ring loop because the smaller tiles'
-// loop is much slower per flop than the estimate assumes (a 256x128 +
-// 128x128 plan of the down projection at 4.7K tokens took 0.56 ms against
-// 0.39 ms for one partial wave of 256x256 tiles).  Every tile shape runs the
-// same MFMA sequence per output element, so the split does not change any bit.
-constexpr double kLaunchGap = 6e-6;  // seconds between two launches on one stream
-
-static void gemm_plan_rows(int epi, int32_t M, int32_t N, int32_t K, int* t1, int32_t* m1, int* t2) {
-  const int32_t NL = epi == EPI_GEGLU_BF16 ? 2 * N : N;
-  static const int bn[3] = {256, 256, 128}, bm[3] = {256, 128, 128};
-  static const double eff[3] = {1.0, 1.12, 1.35};
-  auto cost_of = [&](int t, int32_t rows) {
-    const int64_t tiles = (int64_t)((rows + bm[t] - 1) / bm[t]) * ((NL + bn[t] - 1) / bn[t]);
-    const double waves = (double)((tiles + kSplitCUs - 1) / kSplitCUs);
-    return waves * 2.0 * bn[t] * bm[t] * eff[t] * (double)K / kCuFlops;
-  };
-  *t1 = gemm_pick_tile(epi, M, N);
-  *m1 = M;
-  *t2 = *t1;
-  double best = cost_of(*t1, M);
-  const int32_t tma = (M + 255) / 256;
-  for (int32_t r = tma - 1; r >= 1 && r >= tma - 64; --r) {
-    const int32_t ma = r * 256;
-    for (int b = 1; b < 3; ++b) {
-      const double cost = cost_of(0, ma) + cost_of(b, M - ma) + kLaunchGap;
-      if (cost < best * 0.98) {
-        best = cost;
-        *t1 = 0;
-        *m1 = ma;
-        *t2 = b;
-      }
-    }
-  }
-}
-
-// The row-split tail of a long contraction runs split over K on 256x256 ring
-// tiles.  A tail of at most 128 ring tiles on 128x128 tiles keeps the matrix
-// cores ~18% busy (each such tile moves twice the operand bytes per flop of a
-// ring tile; measured on the K=16384 down projection of the 2B-shaped
-// backbone, 1,801 rows: ~0.3 ms per launch), against ~60% on ring tiles; split
-// S ways (the largest power of two with tiles * S <= kSplitCUs, K/S >= 1024
-// and K % (64 S) == 0) the tail fills one wave of ring tiles and a reduction
-// adds the S fp32 partials in range order.  Only for K >= kTailSplitK: there
-// the 128x128 tail costs more than a tenth of the launch.  A tail row summed
-// in K ranges differs in the last bits from the same row computed in one
-// pass (in another batch it may not lie in a tail), so for such launches
-// grouped and isolated runs agree to rounding instead of bitwise.  Returns S
-// (1: no split) with the row plan of gemm_plan_rows.
-constexpr int32_t kTailSplitK = 8192;
-
-static int32_t gemm_tail_split(int epi, int32_t M, int32_t N, int32_t K, int32_t* m1, int* t1, int* t2) {
-  gemm_plan_rows(epi, M, N, K, t1, m1, t2);
-  if (*m1 >= M || *m1 <= 0 || K < kTailSplitK) return 1;
-  if (epi != EPI_BF16 && epi != EPI_RESID_F32 && epi != EPI_GELU_BF16) return 1;
-  if (N % 4 != 0) return 1;
-  const int64_t tiles = (int64_t)((M - *m1 + 255) / 256) * ((N + 255) / 256);
-  int32_t S = 1;
-  while (S < 16 && tiles * (2 * S) <= kSplitCUs && K % (kBK * 2 * S) == 0 && K / (2 * S) >= 1024) S *= 2;
-  return S;
-}
-
 hipError_t launch_gemm(hipStream_t s, int epi, const void* A, int64_t lda, const void* B, const void* B2, int64_t ldb,
-                       void* C, int64_t ldc, int32_t M, int32_t N, int32_t K, int tile_hint, void* split_ws,
-                       size_t split_bytes) {
+                       void* C, int64_t ldc, int32_t M, int32_t N, int32_t K, void* split_ws, size_t split_bytes,
+                       bool partials_only) {
   if (M <= 0 || N <= 0 || K <= 0 || K % kBK != 0 || N % 32 != 0) return hipErrorInvalidValue;
-  int t_split = 0, S = 1;
-  if (tile_hint <= 0) gemm_plan(epi, M, N, K, &t_split, &S);
-  if (S > 1 && split_ws && split_bytes >= (size_t)S * M * N * sizeof(float))
-    return launch_split(s, epi, A, lda, B, ldb, C, ldc, M, N, K, t_split, S, split_ws);
+  const GemmPlan P = gemm_plan(epi, M, N, K);
   GemmArgs g{};
   g.X = reinterpret_cast<const uint16_t*>(A);
   g.W = reinterpret_cast<const uint16_t*>(B);
@@ -1032,56 +1166,65 @@ hipError_t launch_gemm(hipStream_t s, int epi, const void* A, int64_t lda, const
   g.ldc = ldc;
   g.N = N;
   g.K = K;
-  if (tile_hint > 0) {
-    g.M = M;
-    return launch_rows(s, epi, g, tile_hint - 1);
+  if (P.m1 > 0) {
+    g.M = P.m1;
+    const hipError_t e = launch_rows(s, epi, g, 0);
+    if (e != hipSuccess) return e;
+    const size_t esize = epi == EPI_RESID_F32 ? 4 : 2;
+    g.X += (int64_t)P.m1 * lda;
+    g.C = static_cast<char*>(C) + (size_t)P.m1 * ldc * esize;
   }
-  int t1, t2;
-  int32_t m1;
-  const int32_t St = gemm_tail_split(epi, M, N, K, &m1, &t1, &t2);
-  if (m1 > 0) {
-    g.M = m1;
-    const hipError_t e = launch_rows(s, epi, g, t1);
-    if (e != hipSuccess || m1 == M) return e;
-  }
-  const size_t esize = (epi == EPI_RESID_F32 || epi == EPI_F32) ? 4 : 2;
-  void* Ct = static_cast<char*>(C) + (size_t)m1 * ldc * esize;
-  const void* At = reinterpret_cast<const uint16_t*>(A) + (int64_t)m1 * lda;
-  if (St > 1 && split_ws && split_bytes >= (size_t)St * (M - m1) * N * sizeof(float))
-    return launch_split(s, epi, At, lda, B, ldb, Ct, ldc, M - m1, N, K, 0, St, split_ws);
-  g.X += (int64_t)m1 * lda;
-  g.C = Ct;
-  g.M = M - m1;
-  return launch_rows(s, epi, g, t2);
+  g.M = M - P.m1;
+  if (P.S == 1) return launch_rows(s, epi, g, P.shape);
+  if (!split_ws || split_bytes < (size_t)P.S * g.M * N * sizeof(float)) return hipErrorInvalidValue;
+  void* const out = g.C;
+  g.C = split_ws;
+  g.ldc = N;
+  g.split_c = (int64_t)g.M * N;
+  const hipError_t e = launch_rows(s, EPI_F32, g, P.shape, P.S);
+  if (e != hipSuccess || (partials_only && P.m1 == 0)) return e;
+  return launch_splitk_reduce(s, epi, reinterpret_cast<const float*>(split_ws), P.S, g.M, N, out, ldc);
 }
 
-// Ring tiles (shape 0) once the largest problem has kGroupedRingRows rows and
-// every leading dimension fits their 32-bit panel offsets; then 256x128 and
-// 128x128 interleaved tiles.
-constexpr int32_t kGroupedRingRows = 512;
-
-int gemm_grouped_tile_shape(const GemmArgs* probs, int32_t nprob) {
-  int32_t max_m = 0;
-  bool ring_ok = true, trans = false;
+// Shape of a grouped launch: the estimate over all problems' tiles.  256x256
+// ring tiles, and both operands transposed, where every offset fits 32 bits.
+int gemm_grouped_tile_shape(int epi, const GemmArgs* probs, int32_t nprob) {
+  bool narrow = true, trans = false;
   constexpr int64_t kMax = 0x7fffffff;
   for (int32_t p = 0; p < nprob; ++p) {
     const GemmArgs& g = probs[p];
-    max_m = std::max(max_m, g.M);
     // per-lane panel offsets: 256 rows of a row-major operand, or its whole
     // K lines (plus one slab) for a transposed one
     const int64_t kx = (int64_t)g.K + kBK, span_x = (g.trans & GEMM_TRANS_X) ? kx * g.ldx : 256 * g.ldx;
     const int64_t span_w = (g.trans & GEMM_TRANS_W) ? kx * g.ldw : 256 * g.ldw;
-    if (2 * std::max(span_x, span_w) > kMax) ring_ok = false;
+    if (2 * std::max(span_x, span_w) > kMax) narrow = false;
     trans = trans || g.trans != 0;
   }
-  if (trans) return ring_ok ? 0 : -1;
-  if (ring_ok && max_m >= kGroupedRingRows) return 0;
-  return max_m >= 1024 ? 1 : 2;
+  if (!narrow) return trans ? -1 : kWideShape;
+  if (trans) return 0;
+  int best = 0;
+  double best_us = 1e300;
+  for (int t = 0; t < kNumShapes; ++t) {
+    const TileShape& T = kShapes[t];
+    int64_t tiles = 0, work = 0;  // tiles, and slabs of all tiles
+    for (int32_t p = 0; p < nprob; ++p) {
+      const int64_t n = (int64_t)((probs[p].M + T.bm - 1) / T.bm) * ((probs[p].N + T.bn - 1) / T.bn);
+      tiles += n;
+      work += n * (probs[p].K / kBK);
+    }
+    const double us = tiles_time(epi, tiles, (double)work / tiles, t);
+    if (us < best_us * 0.999) {
+      best_us = us;
+      best = t;
+    }
+  }
+  return best;
 }
 
 int32_t gemm_grouped_prepare(GemmArgs* probs, int32_t nprob, int shape) {
-  if (shape < 0 || shape > 2 || nprob <= 0) return -1;
-  const int BN = shape == 2 ? 128 : 256, BM = shape == 0 ? 256 : 128;
+  if (shape < 0 || (shape >= kNumShapes && shape != kWideShape) || nprob <= 0) return -1;
+  const TileShape& T = kShapes[shape == kWideShape ? kNumShapes - 1 : shape];
+  const int BN = T.bn, BM = T.bm;
   int32_t total = 0;
   for (int32_t p = 0; p < nprob; ++p) {
     const GemmArgs& g = probs[p];
@@ -1099,9 +1242,16 @@ int32_t gemm_grouped_prepare(GemmArgs* probs, int32_t nprob, int shape) {
 hipError_t launch_gemm_grouped(hipStream_t s, int epi, const GemmArgs* dprobs, int32_t nprob, int32_t total_tiles,
                                int shape, int trans) {
   if (nprob <= 0 || total_tiles <= 0 || (trans && shape != 0)) return hipErrorInvalidValue;
-  if (shape == 0) return launch_grouped_ring(s, epi, dprobs, nprob, total_tiles, trans);
-  if (shape == 1) return launch_grouped_tile<256, 128, 4, 2>(s, epi, dprobs, nprob, total_tiles);
-  return launch_grouped_tile<128, 128, 2, 2>(s, epi, dprobs, nprob, total_tiles);
+  switch (shape) {
+    case 0: return launch_grouped_ring(s, epi, dprobs, nprob, total_tiles, trans);
+    case 1: return launch_grouped_flex<256, 160, 3, 1>(s, epi, dprobs, nprob, total_tiles);
+    case 2: return launch_grouped_flex<256, 128, 3, 1>(s, epi, dprobs, nprob, total_tiles);
+    case 3: return launch_grouped_flex<128, 160, 4, 1>(s, epi, dprobs, nprob, total_tiles);
+    case 4: return launch_grouped_flex<128, 96, 4, 1>(s, epi, dprobs, nprob, total_tiles);
+    case 5: return launch_grouped_flex<64, 96, 4, 2>(s, epi, dprobs, nprob, total_tiles);
+    case kWideShape: return launch_grouped_flex<64, 96, 4, 2, true>(s, epi, dprobs, nprob, total_tiles);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace jnx
