@@ -1116,7 +1116,7 @@ struct ExpShape {
 struct ExpPlan {
   ExpShape sh{};
   int32_t G = 0, N = 0;
-  std::vector<int32_t> rows, roff, Ka, kaoff, Kz, kzoff;
+  std::vector<int32_t> rows, roff, soff, Ka, kaoff, Kz, kzoff;
   std::vector<int64_t> Pz, zoff;
   int64_t Na = 0, Pzt = 0, KaT = 0, KzT = 0;
 };
@@ -1124,8 +1124,8 @@ struct ExpPlan {
 // Workspace regions (byte offsets); per-layer saves are arrays of offsets.
 struct ExpLayout {
   size_t arena = 0, arena_bytes = 0;
-  size_t x, xf, yb, ub, vel, predp, dpred, dpredb, z, zoff, winp, woutp, woutpT, dx, dxb, tf, dsum, tb, dkvb, gx, part,
-      TA, TB, WT, kpart, dwinp, dwoutp;
+  size_t xf, yb, ub, vel, predp, dpredb, z, zoff, winp, woutp, woutpT, dx, dxb, tf, dsum, tb, dkvb, part, lpart, TA, TB,
+      WT, kpart, dwinp, dwoutp;
   std::vector<size_t> x1, x2, x3, h1, h2, h3, qkv, os, osb, lses, qc, kv, oc, ocb, lsec, pre, mb;
   size_t total = 0;
 };
@@ -1188,6 +1188,7 @@ jn_status exp_plan(jn_ctx* c, const jn_packed* p, const jn_expert* ex, const jn_
   if (n != p->N) return fail(c, JN_ESHAPE, "io holds %lld samples, packed batch %d", (long long)n, p->N);
   P->rows.resize(G);
   P->roff.assign(G + 1, 0);
+  P->soff.assign(G + 1, 0);
   P->Ka.resize(G);
   P->kaoff.assign(G + 1, 0);
   P->Kz.resize(G);
@@ -1197,6 +1198,7 @@ jn_status exp_plan(jn_ctx* c, const jn_packed* p, const jn_expert* ex, const jn_
   for (int32_t g = 0; g < G; ++g) {
     P->rows[g] = io[g].n_samples * sh.chunk;
     P->roff[g + 1] = P->roff[g] + P->rows[g];
+    P->soff[g + 1] = P->soff[g] + (P->rows[g] + kXrmsSeg - 1) / kXrmsSeg;
     P->Ka[g] = (P->rows[g] + kKP - 1) / kKP * kKP;
     P->kaoff[g + 1] = P->kaoff[g] + P->Ka[g];
     P->Pz[g] = io[g].prefix_rows;
@@ -1226,14 +1228,12 @@ ExpLayout exp_layout(const ExpPlan& P) {
   const int64_t wmax = std::max<int64_t>(3 * d, f);
   Ly.arena_bytes = (size_t)(64 * s.L + 64) * G * 224 + (1 << 16);
   Ly.arena = take(Ly.arena_bytes);
-  Ly.x = take(4 * Na * d);
   Ly.xf = take(4 * Na * d);
   Ly.yb = take(2 * Na * d);
   const int64_t KI = s.ki;
   Ly.ub = take(2 * Na * KI);
   Ly.vel = take(s.dt > 0 ? 4 * Na * 32 : 0);
   Ly.predp = take(4 * Na * kAP);
-  Ly.dpred = take(4 * Na * kAP);
   Ly.dpredb = take(2 * Na * kAP);
   Ly.z = take(2 * Pz * s.dp);
   Ly.zoff = take(4 * (P.N + 1));
@@ -1246,8 +1246,8 @@ ExpLayout exp_layout(const ExpPlan& P) {
   Ly.dsum = take(4 * Na * H);
   Ly.tb = take(2 * Na * wmax);
   Ly.dkvb = take(2 * Pz * 2 * d);
-  Ly.gx = take(4 * Na * d);
-  Ly.part = take(4 * G * 16 * d);
+  Ly.part = take(4 * (int64_t)P.soff[P.G] * d);
+  Ly.lpart = take(4 * (int64_t)kXLossParts * G);
   Ly.TA = take(2 * std::max<int64_t>(wmax * P.KaT, 2 * d * P.KzT));
   Ly.TB = take(2 * std::max<int64_t>(std::max<int64_t>(wmax, KI) * P.KaT, (int64_t)s.dp * P.KzT));
   Ly.WT = take(2 * G * std::max<int64_t>(f * d, 3 * d * d) + 2 * G * 2 * d * s.dp);
@@ -1363,6 +1363,7 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
   Recorder rec;
   rec.cap = Ly.arena_bytes;
   const size_t roff_at = rec.add(P.roff.data(), 4 * P.roff.size());
+  const size_t soff_at = rec.add(P.soff.data(), 4 * P.soff.size());
   hipStream_t s = c->stream;
 
   // ---- recording helpers
@@ -1423,12 +1424,12 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
     });
     rec.opcode.push_back(JN_OP_EXPERT_OTHER);
   };
-  auto rms_bwd = [&](size_t x_at, size_t gains_at, size_t dg_at) {
-    const int64_t rows = P.Na;
+  auto rms_bwd = [&](size_t x_at, size_t gains_at, size_t dg_at, bool first) {
+    const int32_t segs = P.soff[G];
     rec.ops.push_back([=](char* a) {
-      return launch_xrms_bwd(s, F(x_at), (const void* const*)(a + gains_at), (const int32_t*)(a + roff_at), G,
-                             (int32_t)rows, (int32_t)d, S.eps, F(Ly.tf), F(Ly.dx), F(Ly.gx), F(Ly.part),
-                             (float* const*)(a + dg_at));
+      return launch_xrms_bwd(s, F(x_at), (const void* const*)(a + gains_at), (const int32_t*)(a + roff_at),
+                             (const int32_t*)(a + soff_at), G, segs, (int32_t)d, S.eps, F(Ly.tf), first, F(Ly.dx),
+                             B(Ly.dxb), F(Ly.part), (float* const*)(a + dg_at));
     });
     rec.opcode.push_back(JN_OP_EXPERT_OTHER);
   };
@@ -1436,21 +1437,6 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
     const int32_t n = P.N;
     rec.ops.push_back([=](char*) { return launch_xattn(s, A, n, bwd); });
     rec.opcode.push_back(JN_OP_EXPERT_ATTENTION);
-  };
-  // whole-buffer copy / conversion of Na rows
-  auto rows_copy = [&](const void* src, bool sb, void* dst, bool db, int64_t rows, int64_t cols) {
-    CopyDesc cd{};
-    cd.src = src;
-    cd.dst = dst;
-    cd.src_ld = cols;
-    cd.dst_ld = cols;
-    cd.rows = (int32_t)rows;
-    cd.cols = (int32_t)cols;
-    cd.src_rows = src ? (int32_t)rows : 0;
-    cd.src_cols = (int32_t)cols;
-    cd.src_bf16 = sb;
-    cd.dst_bf16 = db;
-    copy({cd});
   };
   // transpose a [rows_g][width] per-tenant block of a row buffer (ld = width)
   // into `dst_at` as [width][K_g] blocks (K padded with zeros)
@@ -1641,7 +1627,7 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
                            (int32_t*)(w + Ly.zoff), w + Ly.z);
     });
     rec.opcode.push_back(JN_OP_EXPERT_OTHER);
-    rows_gemm(EPI_F32, B(Ly.ub), KI, [&](int32_t g) { return B(Ly.winp) + (int64_t)g * d * KI; }, d, F(Ly.x), d, true);
+    rows_gemm(EPI_F32, B(Ly.ub), KI, [&](int32_t g) { return B(Ly.winp) + (int64_t)g * d * KI; }, d, F(Ly.x1[0]), d, true);
   }
   const float scale = 1.0f / sqrtf((float)(d / H));
   for (int l = 0; l < S.L; ++l) {
@@ -1649,7 +1635,6 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
     const size_t g2 = ptr_table([&](int32_t g) { return ex[g].layers[l].g2; });
     const size_t g3 = ptr_table([&](int32_t g) { return ex[g].layers[l].g3; });
     // self-attention block
-    rows_copy(F(Ly.x), false, F(Ly.x1[l]), false, P.Na, d);
     rms_fwd(Ly.x1[l], g1, Ly.h1[l]);
     rows_gemm(EPI_BF16, B(Ly.h1[l]), d, Wl(l, &jn_expert_layer::wqkv_s), 3 * d, B(Ly.qkv[l]), 3 * d, false);
     {
@@ -1672,9 +1657,8 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
       A.scale = scale;
       attn(A, false);
     }
-    rows_gemm(EPI_RESID_F32, B(Ly.osb[l]), d, Wl(l, &jn_expert_layer::wo_s), d, F(Ly.x), d, true);
+    rows_gemm(EPI_RESID_F32, B(Ly.osb[l]), d, Wl(l, &jn_expert_layer::wo_s), d, F(Ly.x2[l]), d, true, F(Ly.x1[l]));
     // cross-attention block
-    rows_copy(F(Ly.x), false, F(Ly.x2[l]), false, P.Na, d);
     rms_fwd(Ly.x2[l], g2, Ly.h2[l]);
     rows_gemm(EPI_BF16, B(Ly.h2[l]), d, Wl(l, &jn_expert_layer::wq_c), d, B(Ly.qc[l]), d, false);
     per_tenant_gemm(EPI_BF16, [&](int32_t g) {
@@ -1712,15 +1696,14 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
       A.scale = scale;
       attn(A, false);
     }
-    rows_gemm(EPI_RESID_F32, B(Ly.ocb[l]), d, Wl(l, &jn_expert_layer::wo_c), d, F(Ly.x), d, true);
+    rows_gemm(EPI_RESID_F32, B(Ly.ocb[l]), d, Wl(l, &jn_expert_layer::wo_c), d, F(Ly.x3[l]), d, true, F(Ly.x2[l]));
     // MLP block
-    rows_copy(F(Ly.x), false, F(Ly.x3[l]), false, P.Na, d);
     rms_fwd(Ly.x3[l], g3, Ly.h3[l]);
     rows_gemm(EPI_GELU_SAVE, B(Ly.h3[l]), d, Wl(l, &jn_expert_layer::w_up), f, B(Ly.mb[l]), f, false, F(Ly.pre[l]));
-    rows_gemm(EPI_RESID_F32, B(Ly.mb[l]), f, Wl(l, &jn_expert_layer::w_down), d, F(Ly.x), d, true);
+    rows_gemm(EPI_RESID_F32, B(Ly.mb[l]), f, Wl(l, &jn_expert_layer::w_down), d, F(l + 1 < S.L ? Ly.x1[l + 1] : Ly.xf), d,
+              true, F(Ly.x3[l]));
   }
   const size_t gfa = ptr_table([&](int32_t g) { return ex[g].gf; });
-  rows_copy(F(Ly.x), false, F(Ly.xf), false, P.Na, d);
   rms_fwd(Ly.xf, gfa, Ly.yb);
   rows_gemm(EPI_F32, B(Ly.yb), d, [&](int32_t g) { return B(Ly.woutp) + (int64_t)g * kAP * d; }, kAP, F(Ly.predp),
             kAP, true);
@@ -1732,32 +1715,28 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
     const size_t at = rec.add(v.data(), sizeof(XLossDesc) * G);
     rec.ops.push_back([=](char* a) {
       return launch_xloss(s, (const XLossDesc*)(a + at), (const int32_t*)(a + roff_at), G, F(Ly.predp), kAP,
-                          F(Ly.dpred));
+                          B(Ly.dpredb), F(Ly.lpart));
     });
     rec.opcode.push_back(JN_OP_LOSS);
   }
 
   // --------------------------------------------------------------- backward
-  rows_copy(F(Ly.dpred), false, B(Ly.dpredb), true, P.Na, kAP);
   wgrad_rows(B(Ly.dpredb), kAP, B(Ly.yb), d, [&](int32_t g) { return F(Ly.dwoutp) + (int64_t)g * kAP * d; }, false);
   rows_gemm(EPI_F32, B(Ly.dpredb), kAP, [&](int32_t g) { return B(Ly.woutpT) + (int64_t)g * d * kAP; }, d, F(Ly.tf),
             d, true);
-  rows_copy(nullptr, false, F(Ly.dx), false, P.Na, d);  // dx = 0
-  rms_bwd(Ly.xf, gfa, ptr_table([&](int32_t g) { return (const void*)io[g].dgf; }));
+  rms_bwd(Ly.xf, gfa, ptr_table([&](int32_t g) { return (const void*)io[g].dgf; }), true);
   for (int l = S.L - 1; l >= 0; --l) {
     const size_t g1 = ptr_table([&](int32_t g) { return ex[g].layers[l].g1; });
     const size_t g2 = ptr_table([&](int32_t g) { return ex[g].layers[l].g2; });
     const size_t g3 = ptr_table([&](int32_t g) { return ex[g].layers[l].g3; });
     // MLP block: x += m W_down^T, m = gelu(h3 W_up^T)
-    rows_copy(F(Ly.dx), false, B(Ly.dxb), true, P.Na, d);
     wgrad_rows(B(Ly.dxb), d, B(Ly.mb[l]), f, Gl(l, &jn_expert_layer_grads::w_down), false);
     dgrad_rows(EPI_GELUGRAD_BF16, B(Ly.dxb), d, [&](int32_t g) { return ex[g].layers[l].w_down; }, f, B(Ly.tb), false,
                F(Ly.pre[l]));
     wgrad_rows(B(Ly.tb), f, B(Ly.h3[l]), d, Gl(l, &jn_expert_layer_grads::w_up), false);
     dgrad_rows(EPI_F32, B(Ly.tb), f, [&](int32_t g) { return ex[g].layers[l].w_up; }, d, F(Ly.tf), true);
-    rms_bwd(Ly.x3[l], g3, ptr_table([&](int32_t g) { return (const void*)io[g].layers[l].g3; }));
+    rms_bwd(Ly.x3[l], g3, ptr_table([&](int32_t g) { return (const void*)io[g].layers[l].g3; }), false);
     // cross-attention block
-    rows_copy(F(Ly.dx), false, B(Ly.dxb), true, P.Na, d);
     wgrad_rows(B(Ly.dxb), d, B(Ly.ocb[l]), d, Gl(l, &jn_expert_layer_grads::wo_c), false);
     dgrad_rows(EPI_F32, B(Ly.dxb), d, [&](int32_t g) { return ex[g].layers[l].wo_c; }, d, F(Ly.tf), true);
     {
@@ -1793,9 +1772,8 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
     wgrad_rows(B(Ly.tb), d, B(Ly.h2[l]), d, Gl(l, &jn_expert_layer_grads::wq_c), false);
     dgrad_rows(EPI_F32, B(Ly.tb), d, [&](int32_t g) { return ex[g].layers[l].wq_c; }, d, F(Ly.tf), true);
     wgrad_rows(B(Ly.dkvb), 2 * d, B(Ly.z), dp, Gl(l, &jn_expert_layer_grads::wkv_c), true);
-    rms_bwd(Ly.x2[l], g2, ptr_table([&](int32_t g) { return (const void*)io[g].layers[l].g2; }));
+    rms_bwd(Ly.x2[l], g2, ptr_table([&](int32_t g) { return (const void*)io[g].layers[l].g2; }), false);
     // self-attention block
-    rows_copy(F(Ly.dx), false, B(Ly.dxb), true, P.Na, d);
     wgrad_rows(B(Ly.dxb), d, B(Ly.osb[l]), d, Gl(l, &jn_expert_layer_grads::wo_s), false);
     dgrad_rows(EPI_F32, B(Ly.dxb), d, [&](int32_t g) { return ex[g].layers[l].wo_s; }, d, F(Ly.tf), true);
     {
@@ -1828,10 +1806,9 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
     }
     wgrad_rows(B(Ly.tb), 3 * d, B(Ly.h1[l]), d, Gl(l, &jn_expert_layer_grads::wqkv_s), false);
     dgrad_rows(EPI_F32, B(Ly.tb), 3 * d, [&](int32_t g) { return ex[g].layers[l].wqkv_s; }, d, F(Ly.tf), true);
-    rms_bwd(Ly.x1[l], g1, ptr_table([&](int32_t g) { return (const void*)io[g].layers[l].g1; }));
+    rms_bwd(Ly.x1[l], g1, ptr_table([&](int32_t g) { return (const void*)io[g].layers[l].g1; }), false);
   }
   // input projection and the padded output-projection gradient
-  rows_copy(F(Ly.dx), false, B(Ly.dxb), true, P.Na, d);
   wgrad_rows(B(Ly.dxb), d, B(Ly.ub), KI, [&](int32_t g) { return F(Ly.dwinp) + (int64_t)g * d * KI; }, false);
   {
     std::vector<CopyDesc> v;

@@ -50,7 +50,7 @@ hipError_t launch_rmsnorm_split(hipStream_t s, float* x, const float* part, int3
 enum GemmEpi : int32_t {
   EPI_BF16 = 0,          // C bf16 = acc
   EPI_GELU_BF16 = 1,     // C bf16 = gelu(acc)
-  EPI_RESID_F32 = 2,     // C fp32 += acc
+  EPI_RESID_F32 = 2,     // C fp32 = (aux, or C itself) + acc
   EPI_GEGLU_BF16 = 3,    // weights gate|up interleaved at load; C bf16 = gelu(gate) * up
   EPI_F32 = 4,           // C fp32 = acc
   EPI_GELU_SAVE = 5,     // aux fp32 = acc; C bf16 = gelu(acc)
@@ -68,7 +68,7 @@ struct GemmArgs {
   const uint16_t* W;
   const uint16_t* W2;   // GeGLU up weights
   void* C;
-  float* aux;           // GELU pre-activation (saved or read)
+  float* aux;           // GELU pre-activation (saved or read); residual source (null: C)
   int64_t ldx, ldw, ldc, ldaux;
   int32_t M, N, K;
   int32_t tiles_m, tiles_n, tile_start;  // filled by the launchers
@@ -235,11 +235,14 @@ hipError_t launch_prefix(hipStream_t s, const void* hidden, const int32_t* tenan
 // RMSNorm with per-tenant gains (rows tenant-contiguous, roff [G+1] device).
 hipError_t launch_xrms_fwd(hipStream_t s, const float* x, const void* const* gains, const int32_t* roff, int32_t G,
                            int32_t rows, int32_t d, float eps, void* h);
-// dx += dRMS(x, g) . dh ; dg[t] = column sums over tenant t's rows (gx scratch
-// [rows][d], part scratch [G][16][d]).
-hipError_t launch_xrms_bwd(hipStream_t s, const float* x, const void* const* gains, const int32_t* roff, int32_t G,
-                           int32_t rows, int32_t d, float eps, const float* dh, float* dx, float* gx, float* part,
-                           float* const* dg);
+// dx (+)= dRMS(x, g) . dh (set instead of added to where `first`), dxb = its
+// bf16 copy; dg[t] = column sums over tenant t's rows of dh x r.  Tenant t's
+// rows are cut into segments of kXrmsSeg, numbered from soff[t] (soff [G+1]
+// device, `segs` in all); part: scratch [segs][d].
+constexpr int kXrmsSeg = 8;
+hipError_t launch_xrms_bwd(hipStream_t s, const float* x, const void* const* gains, const int32_t* roff,
+                           const int32_t* soff, int32_t G, int32_t segs, int32_t d, float eps, const float* dh,
+                           bool first, float* dx, uint16_t* dxb, float* part, float* const* dg);
 
 // fp32 attention of each tenant-order sample k over its own keys: queries
 // rows [k*Lq, (k+1)*Lq) of Q; keys / values rows [kv0, kv0 + Lk) with
@@ -286,8 +289,11 @@ struct XLossDesc {
   float* loss;          // [1]
   int32_t a, reserved;
 };
+// dpred_pad: bf16 [rows][ldp], zero past the tenant's a columns; part: scratch
+// of kXLossParts floats per tenant.
+constexpr int kXLossParts = 64;
 hipError_t launch_xloss(hipStream_t s, const XLossDesc* d, const int32_t* roff, int32_t G, const float* pred_pad,
-                        int32_t ldp, float* dpred_pad);
+                        int32_t ldp, uint16_t* dpred_pad, float* part);
 
 // ------------------------------------------------------------ optimizer ---
 

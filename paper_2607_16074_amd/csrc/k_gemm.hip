@@ -134,8 +134,12 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, const f32x4 (&a
     // instead of one per block.  Lanes outside the output read element (0, 0)
     // of the operand and store nothing.
     constexpr int JB = row_batch(TM, 32 / TN);
-    const float* src = EPI == EPI_RESID_F32 ? reinterpret_cast<const float*>(C) : g.aux;
-    const int64_t ldr = EPI == EPI_RESID_F32 ? ldc : g.ldaux;
+    const float* src = g.aux;  // a residual add without aux is in place
+    int64_t ldr = g.ldaux;
+    if (EPI == EPI_RESID_F32 && !src) {
+      src = reinterpret_cast<const float*>(C);
+      ldr = ldc;
+    }
 #pragma unroll
     for (int j0 = 0; j0 < TM; j0 += JB) {
       float4 r[JB][TN];
