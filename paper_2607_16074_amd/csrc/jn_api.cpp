@@ -1378,9 +1378,8 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
         [=](char* a) { return launch_gemm_grouped(s, epi, (const GemmArgs*)(a + at), n, tiles, shape, trans); });
     rec.opcode.push_back(JN_OP_EXPERT_GEMM);
   };
-  // Transposed-operand problems run only on the 256x256 tiles; elsewhere
-  // (offsets beyond the loop's 32-bit ones) the caller materialises the
-  // transposes instead.  Both give the same MFMA sequence per output element.
+  // Where transposed-operand problems' offsets exceed the loops' 32-bit ones
+  // the caller materialises the transposes instead.  Both give the same MFMA sequence per output element.
   auto trans_ok = [&](int epi, const std::vector<GemmArgs>& probs) {
     return !c->expert_transposes && gemm_grouped_tile_shape(epi, probs.data(), (int32_t)probs.size()) >= 0;
   };

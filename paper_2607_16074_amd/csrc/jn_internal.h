@@ -72,7 +72,7 @@ struct GemmArgs {
   int64_t ldx, ldw, ldc, ldaux;
   int32_t M, N, K;
   int32_t tiles_m, tiles_n, tile_start;  // filled by the launchers
-  int32_t trans;        // GEMM_TRANS_* bits (grouped launches on 256x256 tiles only)
+  int32_t trans;        // GEMM_TRANS_* bits (grouped launches only)
   int64_t split_c;      // split-K: elements between the fp32 partial outputs of
                         // consecutive K ranges; 0 when unsplit
 };
@@ -81,11 +81,10 @@ struct GemmArgs {
 // the problems, calls gemm_grouped_prepare (tile ranges, returns the tile
 // total, or -1 if a problem is not M, N, K > 0 with K % 64 == 0 and
 // N % 32 == 0), uploads them and launches.  shape from gemm_grouped_tile_shape.
-// Problems with transposed operands (all of one launch alike) run on the
-// 256x256 tiles (shape 0, which gemm_grouped_tile_shape returns for them, or
-// -1 where their offsets do not fit the loop's 32-bit ones); with both
-// operands transposed K need not be a multiple of 64.  Combinations launched:
-// EPI_F32 with GEMM_TRANS_W or both, EPI_GELUGRAD_BF16 with GEMM_TRANS_W.
+// Problems with transposed operands (all of one launch alike) have no shape
+// (-1) where their offsets do not fit 32 bits; with both operands transposed K
+// need not be a multiple of 64.  Combinations launched: EPI_F32 with
+// GEMM_TRANS_W or both, EPI_GELUGRAD_BF16 with GEMM_TRANS_W.
 int gemm_grouped_tile_shape(int epi, const GemmArgs* probs, int32_t nprob);
 int32_t gemm_grouped_prepare(GemmArgs* probs, int32_t nprob, int shape);
 hipError_t launch_gemm_grouped(hipStream_t s, int epi, const GemmArgs* dprobs, int32_t nprob, int32_t total_tiles,

@@ -889,7 +889,7 @@ constexpr TileShape kShapes[] = {
     {128, 128, 2, 0.54, 0.62, 2.3},
 };
 constexpr int kNumShapes = 6;   // of every launch
-constexpr int kResidShape = 6;  // and of the unsplit residual adds
+constexpr int k128Shape = 6;    // and of unsplit residual adds and grouped weight gradients
 
 // 32-bit lane offsets span the 256 rows of a panel; beyond (leading dimensions
 // past 4M elements), the small shape runs with one buffer base per DMA
@@ -991,29 +991,53 @@ static hipError_t launch_grouped_ring(hipStream_t s, int epi, const GemmArgs* dp
   return hipGetLastError();
 }
 
-template <int BN, int BM, int NS, int OCC, bool WIDE = false>
-static hipError_t launch_grouped_flex(hipStream_t s, int epi, const GemmArgs* dprobs, int32_t nprob, int32_t total) {
+template <int BN, int BM, int NS, int NSW, int OCC, bool WIDE = false>
+static hipError_t launch_grouped_flex(hipStream_t s, int epi, const GemmArgs* dprobs, int32_t nprob, int32_t total,
+                                      int trans) {
   const dim3 grid((unsigned)((total + 7) / 8 * 8)), block(256);
-#define JN_GEMM_CASE(E) \
-  case E: gemm_grouped_flex_kernel<BN, BM, NS, NS, E, 0, OCC, WIDE><<<grid, block, 0, s>>>(dprobs, nprob, total); break;
+#define JN_GEMM_CASE(E, T)                                                                                       \
+  case E * 4 + T:                                                                                                \
+    gemm_grouped_flex_kernel<BN, BM, NS, NSW, E, T, OCC, WIDE><<<grid, block, 0, s>>>(dprobs, nprob, total); break;
   if constexpr (WIDE) {
-    switch (epi) {
-      JN_GEMM_CASE(EPI_RESID_F32)
-      JN_GEMM_CASE(EPI_F32)
+    switch (epi * 4 + trans) {
+      JN_GEMM_CASE(EPI_RESID_F32, 0)
+      JN_GEMM_CASE(EPI_F32, 0)
       default: return hipErrorInvalidValue;
     }
-  } else {
-    switch (epi) {
-      JN_GEMM_CASE(EPI_BF16)
-      JN_GEMM_CASE(EPI_RESID_F32)
-      JN_GEMM_CASE(EPI_F32)
-      JN_GEMM_CASE(EPI_GELU_SAVE)
-      JN_GEMM_CASE(EPI_GELUGRAD_BF16)
-      default: return hipErrorInvalidValue;
+    return hipGetLastError();
+  }
+  if constexpr (BN % 128 == 0 && BM % 128 == 0) {
+    if (trans == (GEMM_TRANS_X | GEMM_TRANS_W)) {
+      switch (epi * 4 + trans) {
+        JN_GEMM_CASE(EPI_F32, GEMM_TRANS_X | GEMM_TRANS_W)
+        default: return hipErrorInvalidValue;
+      }
+      return hipGetLastError();
     }
   }
+  if constexpr (BN % 128 == 0 && NSW == NS) {
+    if (trans == GEMM_TRANS_W) {
+      switch (epi * 4 + trans) {
+        JN_GEMM_CASE(EPI_F32, GEMM_TRANS_W)
+        JN_GEMM_CASE(EPI_GELUGRAD_BF16, GEMM_TRANS_W)
+        default: return hipErrorInvalidValue;
+      }
+      return hipGetLastError();
+    }
+  }
+  if constexpr (NSW == NS) {
+    switch (epi * 4 + trans) {
+      JN_GEMM_CASE(EPI_BF16, 0)
+      JN_GEMM_CASE(EPI_RESID_F32, 0)
+      JN_GEMM_CASE(EPI_F32, 0)
+      JN_GEMM_CASE(EPI_GELU_SAVE, 0)
+      JN_GEMM_CASE(EPI_GELUGRAD_BF16, 0)
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  }
+  return hipErrorInvalidValue;
 #undef JN_GEMM_CASE
-  return hipGetLastError();
 }
 
 // Bytes an epilogue reads and writes per tile element (GeGLU: per gate or up
@@ -1076,9 +1100,9 @@ static bool may_split(int epi, int32_t rows, int32_t N, int32_t K) {
 static double plan_launch(int epi, int32_t rows, int32_t N, int32_t K, bool split, int* shape, int32_t* S) {
   const int32_t smax = split && may_split(epi, rows, N, K) ? std::min(16, K / (8 * kBK)) : 1;
   double best = 1e300;
-  for (int t = 0; t <= kResidShape; ++t) {
-    if (t == kResidShape && epi != EPI_RESID_F32) break;
-    for (int32_t k = 1; k <= (t == kResidShape ? 1 : smax); ++k) {
+  for (int t = 0; t <= k128Shape; ++t) {
+    if (t == k128Shape && epi != EPI_RESID_F32) break;
+    for (int32_t k = 1; k <= (t == k128Shape ? 1 : smax); ++k) {
       const double us = tile_time(epi, rows, N, K, t, k);
       if (us < best * 0.999) {
         best = us;
@@ -1190,8 +1214,16 @@ hipError_t launch_gemm(hipStream_t s, int epi, const void* A, int64_t lda, const
   return launch_splitk_reduce(s, epi, reinterpret_cast<const float*>(split_ws), P.S, g.M, N, out, ldc);
 }
 
-// Shape of a grouped launch: the estimate over all problems' tiles.  256x256
-// ring tiles, and both operands transposed, where every offset fits 32 bits.
+// Shapes a grouped launch may take: a transposed operand's tile side is a
+// multiple of 128 elements.
+static bool grouped_shape_ok(int trans, int t) {
+  if (t == k128Shape) return trans == (GEMM_TRANS_X | GEMM_TRANS_W);
+  const TileShape& T = kShapes[t];
+  return (!(trans & GEMM_TRANS_W) || T.bn % 128 == 0) && (!(trans & GEMM_TRANS_X) || T.bm % 128 == 0);
+}
+
+// Shape of a grouped launch: the estimate over all problems' tiles, where every
+// offset fits 32 bits.
 int gemm_grouped_tile_shape(int epi, const GemmArgs* probs, int32_t nprob) {
   bool narrow = true, trans = false;
   constexpr int64_t kMax = 0x7fffffff;
@@ -1205,16 +1237,16 @@ int gemm_grouped_tile_shape(int epi, const GemmArgs* probs, int32_t nprob) {
     trans = trans || g.trans != 0;
   }
   if (!narrow) return trans ? -1 : kWideShape;
-  if (trans) return 0;
   int best = 0;
   double best_us = 1e300;
-  for (int t = 0; t < kNumShapes; ++t) {
+  for (int t = 0; t <= k128Shape; ++t) {
     const TileShape& T = kShapes[t];
+    if (!grouped_shape_ok(trans ? probs[0].trans : 0, t)) continue;
     int64_t tiles = 0, work = 0;  // tiles, and slabs of all tiles
     for (int32_t p = 0; p < nprob; ++p) {
       const int64_t n = (int64_t)((probs[p].M + T.bm - 1) / T.bm) * ((probs[p].N + T.bn - 1) / T.bn);
       tiles += n;
-      work += n * (probs[p].K / kBK);
+      work += n * ((probs[p].K + kBK - 1) / kBK);
     }
     const double us = tiles_time(epi, tiles, (double)work / tiles, t);
     if (us < best_us * 0.999) {
@@ -1226,14 +1258,15 @@ int gemm_grouped_tile_shape(int epi, const GemmArgs* probs, int32_t nprob) {
 }
 
 int32_t gemm_grouped_prepare(GemmArgs* probs, int32_t nprob, int shape) {
-  if (shape < 0 || (shape >= kNumShapes && shape != kWideShape) || nprob <= 0) return -1;
+  if (shape < 0 || shape > kWideShape || nprob <= 0) return -1;
   const TileShape& T = kShapes[shape == kWideShape ? kNumShapes - 1 : shape];
   const int BN = T.bn, BM = T.bm;
   int32_t total = 0;
   for (int32_t p = 0; p < nprob; ++p) {
     const GemmArgs& g = probs[p];
     const bool ragged_ok = g.trans == (GEMM_TRANS_X | GEMM_TRANS_W);
-    if (g.trans != probs[0].trans || g.trans < 0 || g.trans > 3 || (g.trans && shape != 0)) return -1;
+    if (g.trans != probs[0].trans || g.trans < 0 || g.trans > 3) return -1;
+    if (shape == kWideShape ? g.trans != 0 : !grouped_shape_ok(g.trans, shape)) return -1;
     if (g.M <= 0 || g.N <= 0 || g.K <= 0 || (!ragged_ok && g.K % kBK != 0) || g.N % 32 != 0) return -1;
     probs[p].tiles_m = (probs[p].M + BM - 1) / BM;
     probs[p].tiles_n = (probs[p].N + BN - 1) / BN;
@@ -1245,15 +1278,16 @@ int32_t gemm_grouped_prepare(GemmArgs* probs, int32_t nprob, int shape) {
 
 hipError_t launch_gemm_grouped(hipStream_t s, int epi, const GemmArgs* dprobs, int32_t nprob, int32_t total_tiles,
                                int shape, int trans) {
-  if (nprob <= 0 || total_tiles <= 0 || (trans && shape != 0)) return hipErrorInvalidValue;
+  if (nprob <= 0 || total_tiles <= 0) return hipErrorInvalidValue;
   switch (shape) {
     case 0: return launch_grouped_ring(s, epi, dprobs, nprob, total_tiles, trans);
-    case 1: return launch_grouped_flex<256, 160, 3, 1>(s, epi, dprobs, nprob, total_tiles);
-    case 2: return launch_grouped_flex<256, 128, 3, 1>(s, epi, dprobs, nprob, total_tiles);
-    case 3: return launch_grouped_flex<128, 160, 4, 1>(s, epi, dprobs, nprob, total_tiles);
-    case 4: return launch_grouped_flex<128, 96, 4, 1>(s, epi, dprobs, nprob, total_tiles);
-    case 5: return launch_grouped_flex<64, 96, 4, 2>(s, epi, dprobs, nprob, total_tiles);
-    case kWideShape: return launch_grouped_flex<64, 96, 4, 2, true>(s, epi, dprobs, nprob, total_tiles);
+    case 1: return launch_grouped_flex<256, 160, 3, 3, 1>(s, epi, dprobs, nprob, total_tiles, trans);
+    case 2: return launch_grouped_flex<256, 128, 3, 3, 1>(s, epi, dprobs, nprob, total_tiles, trans);
+    case 3: return launch_grouped_flex<128, 160, 4, 4, 1>(s, epi, dprobs, nprob, total_tiles, trans);
+    case 4: return launch_grouped_flex<128, 96, 4, 4, 1>(s, epi, dprobs, nprob, total_tiles, trans);
+    case 5: return launch_grouped_flex<64, 96, 4, 4, 2>(s, epi, dprobs, nprob, total_tiles, trans);
+    case k128Shape: return launch_grouped_flex<128, 128, 3, 2, 2>(s, epi, dprobs, nprob, total_tiles, trans);
+    case kWideShape: return launch_grouped_flex<64, 96, 4, 4, 2, true>(s, epi, dprobs, nprob, total_tiles, trans);
     default: return hipErrorInvalidValue;
   }
 }
