@@ -1124,7 +1124,7 @@ struct ExpPlan {
 // Workspace regions (byte offsets); per-layer saves are arrays of offsets.
 struct ExpLayout {
   size_t arena = 0, arena_bytes = 0;
-  size_t xf, yb, ub, vel, predp, dpredb, z, zoff, winp, woutp, woutpT, dx, dxb, tf, dsum, tb, dkvb, part, lpart, TA, TB,
+  size_t xf, yb, ub, vel, predp, dpredb, z, zoff, winp, woutp, woutpT, dx, dxb, tf, tb, dkvb, part, lpart, TA, TB,
       WT, kpart, dwinp, dwoutp;
   std::vector<size_t> x1, x2, x3, h1, h2, h3, qkv, os, osb, lses, qc, kv, oc, ocb, lsec, pre, mb;
   size_t total = 0;
@@ -1243,7 +1243,6 @@ ExpLayout exp_layout(const ExpPlan& P) {
   Ly.dx = take(4 * Na * d);
   Ly.dxb = take(2 * Na * d);
   Ly.tf = take(4 * Na * d);
-  Ly.dsum = take(4 * Na * H);
   Ly.tb = take(2 * Na * wmax);
   Ly.dkvb = take(2 * Pz * 2 * d);
   Ly.part = take(4 * (int64_t)P.soff[P.G] * d);
@@ -1745,7 +1744,6 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
       A.V = B(Ly.kv[l]);
       A.O = F(Ly.oc[l]);
       A.lse = F(Ly.lsec[l]);
-      A.dsum = F(Ly.dsum);
       A.dO = F(Ly.tf);
       A.dQ = B(Ly.tb);
       A.dK = B(Ly.dkvb);
@@ -1782,7 +1780,6 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
       A.V = B(Ly.qkv[l]);
       A.O = F(Ly.os[l]);
       A.lse = F(Ly.lses[l]);
-      A.dsum = F(Ly.dsum);
       A.dO = F(Ly.tf);
       A.dQ = B(Ly.tb);
       A.dK = B(Ly.tb);

@@ -254,7 +254,6 @@ struct AttnArgs {
   float* O;        // forward output / backward input (fp32)
   uint16_t* Ob;    // forward output, bf16 copy of O (leading dimension ldo)
   float* lse;      // forward output / backward input, [rows][nheads], log2 domain
-  float* dsum;     // backward scratch, [rows][nheads]: sum(dO * O) per query
   const float* dO;
   uint16_t* dQ;    // bf16 gradients
   uint16_t* dK;

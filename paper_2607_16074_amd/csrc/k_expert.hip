@@ -522,6 +522,15 @@ __device__ __forceinline__ xbf16x8 xa_pack8(const float* v) {
   return r;
 }
 
+// Lanes of quads 2u and 2u + 1 hold 8-byte pieces a (row block t) and b (t + 1)
+// of the same two 32-byte runs; afterwards the even quad has both pieces of
+// block t, the odd one both of block t + 1, in order.
+__device__ __forceinline__ uint4 xa_pair16(uint2 a, uint2 b) {
+  const auto x = __builtin_amdgcn_permlane16_swap(a.x, b.x, false, false);
+  const auto y = __builtin_amdgcn_permlane16_swap(a.y, b.y, false, false);
+  return make_uint4(x[0], y[0], x[1], y[1]);
+}
+
 __device__ __forceinline__ void attn_rows(const AttnArgs& A, int32_t k, int32_t& q0, int32_t& Lq, int64_t& kv0,
                                           int32_t& Lk) {
   q0 = k * A.Lq;
@@ -658,88 +667,145 @@ __global__ __launch_bounds__(256, 2) void xattn_fwd_kernel(AttnArgs A) {
   if (quad == 0) A.lse[row * A.nheads + h] = m + __log2f(l);
 }
 
-// Backward, query side: dQ = scale dS K, dS = P (dP - D), P from the saved
-// lse, dP^T = V dO^T, D = sum(dO * O) per query (also written to dsum for
-// the key side).  Same layout as the forward.
+// Backward: one workgroup per (sample, head) walks the sample's 64-key tiles;
+// its queries (<= 64, zero rows past Lq) and their bf16-rounded output
+// gradients stay in LDS.  Wave w owns keys 16 w .. of a tile: scores
+// untransposed, S = Q K^T (lane = key, registers = 4 queries of each 16-query
+// block), P from the saved lse, dP = dO V^T, dS = P (dP - D) with
+// D = sum(dO * O) per query, so P and dS are already the B operands of
+// dV^T = dO^T P and dK^T = Q^T dS.  dS then goes through LDS ([key][query]),
+// and the wave owning queries 16 w .. adds K^T dS^T to its dQ^T.
+// Memory-bound: K and V are read once and dK and dV written once (16 tenants,
+// 288 samples of ~600 keys: 1.4 GB, 290 us at the copy rate).  As two kernels,
+// a query side and a key side of one workgroup per key tile, K, V, the queries
+// and the output gradients were read again for every tile and S and dP formed
+// twice: 199 + 455 us, now 340 (self attention 55 + 46 -> 72).  One K/V buffer, so that two workgroups
+// share a CU (72 KB of LDS each) and one's products hide the other's loads.
 template <int HD>
-__global__ __launch_bounds__(256, 2) void xattn_bwd_dq_kernel(AttnArgs A) {
+__global__ __launch_bounds__(256, 2) void xattn_bwd_kernel(AttnArgs A) {
   using T = XaTiles<HD>;
-  constexpr int NQC = HD / 32, NOT = HD / 16;
-  __shared__ __attribute__((aligned(1024))) uint16_t lds[2][2 * T::TILE];
+  constexpr int NQC = HD / 32, NOT = HD / 16, CPR = HD / 8;
+  __shared__ __attribute__((aligned(1024))) uint16_t kv[2 * T::TILE];
+  __shared__ __attribute__((aligned(1024))) uint16_t qt[64 * HD];
+  __shared__ __attribute__((aligned(1024))) uint16_t dt[64 * HD];
+  __shared__ __attribute__((aligned(1024))) uint16_t ds[64 * 64];
+  __shared__ float lse_s[64], d_s[64];
   const int k = blockIdx.x, h = blockIdx.y;
   int32_t q0, Lq, Lk;
   int64_t kv0;
   attn_rows(A, k, q0, Lq, kv0, Lk);
   if (Lk <= 0) return;
-  const int lane = threadIdx.x & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int j16 = lane & 15, quad = lane >> 4;
-  const int qi = wave * 16 + j16;
-  const int64_t qrow = q0 + min(qi, Lq - 1);
   const float sl2 = A.scale * 1.4426950408889634f;
-  xbf16x8 qf[NQC], df[NQC];
-  float Dq = 0.f;
-  {
-    const float* drow = A.dO + qrow * A.ldo + h * HD;
-    const float* orow = A.O + qrow * A.ldo + h * HD;
-#pragma unroll
-    for (int c = 0; c < NQC; ++c) {
-      qf[c] = *reinterpret_cast<const xbf16x8*>(A.Q + qrow * A.ldq + h * HD + c * 32 + quad * 8);
-      float v[8];
-      const float4 d0 = *reinterpret_cast<const float4*>(drow + c * 32 + quad * 8);
-      const float4 d1 = *reinterpret_cast<const float4*>(drow + c * 32 + quad * 8 + 4);
-      const float4 o0 = *reinterpret_cast<const float4*>(orow + c * 32 + quad * 8);
-      const float4 o1 = *reinterpret_cast<const float4*>(orow + c * 32 + quad * 8 + 4);
-      v[0] = d0.x; v[1] = d0.y; v[2] = d0.z; v[3] = d0.w; v[4] = d1.x; v[5] = d1.y; v[6] = d1.z; v[7] = d1.w;
-      df[c] = xa_pack8(v);
-      Dq = fmaf(d0.x, o0.x, Dq); Dq = fmaf(d0.y, o0.y, Dq); Dq = fmaf(d0.z, o0.z, Dq); Dq = fmaf(d0.w, o0.w, Dq);
-      Dq = fmaf(d1.x, o1.x, Dq); Dq = fmaf(d1.y, o1.y, Dq); Dq = fmaf(d1.z, o1.z, Dq); Dq = fmaf(d1.w, o1.w, Dq);
-    }
-    Dq = sum_xor32(sum_xor16(Dq));
-  }
-  const float lse = A.lse[qrow * A.nheads + h];
-  if (qi < Lq && quad == 0) A.dsum[(q0 + qi) * A.nheads + h] = Dq;
   const uint16_t* Kb = A.K + A.kcol + h * HD;
   const uint16_t* Vb = A.V + A.vcol + h * HD;
-  const int tswz = xa_swz<HD>(4 * quad + (j16 >> 2));
+  const uint16_t *Ks = kv, *Vs = kv + T::TILE;
+  // Q and bf16(dO): 64 rows x CPR chunks of 8 elements; D by CPR lanes per row
+  for (int e = tid; e < 64 * CPR; e += 256) {
+    const int r = e / CPR, c = e % CPR;
+    const int pos = r * HD + ((c ^ xa_swz<HD>(r)) * 8);
+    uint4 qv = make_uint4(0, 0, 0, 0), dv = make_uint4(0, 0, 0, 0);
+    float D = 0.f;
+    if (r < Lq) {
+      const int64_t row = q0 + r;
+      const float* dp = A.dO + row * A.ldo + h * HD + c * 8;
+      const float* op = A.O + row * A.ldo + h * HD + c * 8;
+      qv = *reinterpret_cast<const uint4*>(A.Q + row * A.ldq + h * HD + c * 8);
+      const float4 a = *reinterpret_cast<const float4*>(dp), b = *reinterpret_cast<const float4*>(dp + 4);
+      const float4 u = *reinterpret_cast<const float4*>(op), v = *reinterpret_cast<const float4*>(op + 4);
+      dv = make_uint4(pack_bf2(a.x, a.y), pack_bf2(a.z, a.w), pack_bf2(b.x, b.y), pack_bf2(b.z, b.w));
+      D = fmaf(a.x, u.x, fmaf(a.y, u.y, fmaf(a.z, u.z, a.w * u.w))) +
+          fmaf(b.x, v.x, fmaf(b.y, v.y, fmaf(b.z, v.z, b.w * v.w)));
+    }
+#pragma unroll
+    for (int o = CPR / 2; o > 0; o >>= 1) D += __shfl_xor(D, o, kWave);
+    if (c == 0) d_s[r] = D;
+    *reinterpret_cast<uint4*>(qt + pos) = qv;
+    *reinterpret_cast<uint4*>(dt + pos) = dv;
+  }
+  if (tid < 64) lse_s[tid] = tid < Lq ? A.lse[(q0 + tid) * A.nheads + h] : INFINITY;  // P = 0 past Lq
+  T::issue(kv, Kb, Vb, A.ldkv, kv0, Lk, 0, wave, lane);
 
+  const int tswz = xa_swz<HD>(4 * quad + (j16 >> 2)), sswz = xa_swz<64>(4 * quad + (j16 >> 2));
+  const int krow = wave * 16 + j16;  // this lane's key in the tile
   xf32x4 dq[NOT];
 #pragma unroll
   for (int t = 0; t < NOT; ++t) dq[t] = xf32x4{0.f, 0.f, 0.f, 0.f};
   const int32_t ntiles = (Lk + 63) / 64;
-  T::issue(&lds[0][0], Kb, Vb, A.ldkv, kv0, Lk, 0, wave, lane);
   for (int32_t jt = 0; jt < ntiles; ++jt) {
-    const int32_t j0 = jt * 64;
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_s_barrier();
-    T::issue(&lds[(jt + 1) & 1][0], Kb, Vb, A.ldkv, kv0, Lk, min(j0 + 64, (ntiles - 1) * 64), wave, lane);
-    const uint16_t* Ks = &lds[jt & 1][0];
-    const uint16_t* Vs = Ks + T::TILE;
+    const int32_t key = jt * 64 + krow;
+    __syncthreads();  // tile jt (first: the staged rows) landed
     xf32x4 s[4], dp[4];
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) s[kb] = dp[kb] = xf32x4{0.f, 0.f, 0.f, 0.f};
+    for (int qb = 0; qb < 4; ++qb) s[qb] = dp[qb] = xf32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int c = 0; c < NQC; ++c)
+    for (int c = 0; c < NQC; ++c) {
+      const xbf16x8 kf = xa_frag<HD>(Ks, krow, 4 * c + quad), vf = xa_frag<HD>(Vs, krow, 4 * c + quad);
 #pragma unroll
-      for (int kb = 0; kb < 4; ++kb) {
-        s[kb] = xa_mfma(xa_frag<HD>(Ks, kb * 16 + j16, 4 * c + quad), qf[c], s[kb]);
-        dp[kb] = xa_mfma(xa_frag<HD>(Vs, kb * 16 + j16, 4 * c + quad), df[c], dp[kb]);
+      for (int qb = 0; qb < 4; ++qb) {
+        s[qb] = xa_mfma(xa_frag<HD>(qt, qb * 16 + j16, 4 * c + quad), kf, s[qb]);
+        dp[qb] = xa_mfma(xa_frag<HD>(dt, qb * 16 + j16, 4 * c + quad), vf, dp[qb]);
       }
-    xbf16x8 dsf[2];
+    }
+    // P and dS as B operands: k-slot s of chunk c is query 32 c + 4 quad + (s & 3) + 16 (s >> 2)
+    xbf16x8 pb[2], db[2];
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb)
+    for (int qb = 0; qb < 4; ++qb) {
+      xbf16x4 w;
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        const bool live = j0 + kb * 16 + quad * 4 + e < Lk;
-        const float pv = live ? exp2f(fmaf(s[kb][e], sl2, -lse)) : 0.f;
-        dsf[kb >> 1][(kb & 1) * 4 + e] = (__bf16)(pv * (dp[kb][e] - Dq));
+        const int q = qb * 16 + quad * 4 + e;
+        const float pv = key < Lk ? exp2f(fmaf(s[qb][e], sl2, -lse_s[q])) : 0.f;
+        pb[qb >> 1][(qb & 1) * 4 + e] = (__bf16)pv;
+        w[e] = (__bf16)(pv * (dp[qb][e] - d_s[q]));
+        db[qb >> 1][(qb & 1) * 4 + e] = w[e];
       }
+      *reinterpret_cast<xbf16x4*>(ds + krow * 64 + (((2 * qb + (quad >> 1)) ^ xa_swz<64>(krow)) * 8) + 4 * (quad & 1)) = w;
+    }
+    uint16_t* const vrow = A.dV + (kv0 + key) * A.lddkv + A.dvcol + h * HD;
+    uint16_t* const krw = A.dK + (kv0 + key) * A.lddkv + A.dkcol + h * HD;
+    // lane holds dV^T / dK^T rows (head dims) 16 t + 4 quad .. +3 of its key;
+    // quads 2u and 2u + 1 swap halves of a pair of t, so a lane stores 16 bytes
+#pragma unroll
+    for (int t = 0; t < NOT; t += 2) {
+      xf32x4 dv[2], dk[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        dv[i] = dk[i] = xf32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+          dv[i] = xa_mfma(xa_tr<HD>(dt, c, t + i, quad, j16, tswz), pb[c], dv[i]);
+          dk[i] = xa_mfma(xa_tr<HD>(qt, c, t + i, quad, j16, tswz), db[c], dk[i]);
+        }
+      }
+      const uint4 vo = xa_pair16(make_uint2(pack_bf2(dv[0][0], dv[0][1]), pack_bf2(dv[0][2], dv[0][3])),
+                                 make_uint2(pack_bf2(dv[1][0], dv[1][1]), pack_bf2(dv[1][2], dv[1][3])));
+      const uint4 ko = xa_pair16(make_uint2(pack_bf2(dk[0][0] * A.scale, dk[0][1] * A.scale),
+                                            pack_bf2(dk[0][2] * A.scale, dk[0][3] * A.scale)),
+                                 make_uint2(pack_bf2(dk[1][0] * A.scale, dk[1][1] * A.scale),
+                                            pack_bf2(dk[1][2] * A.scale, dk[1][3] * A.scale)));
+      const int col = (t + (quad & 1)) * 16 + 8 * (quad >> 1);
+      if (key < Lk) {
+        *reinterpret_cast<uint4*>(vrow + col) = vo;
+        *reinterpret_cast<uint4*>(krw + col) = ko;
+      }
+    }
+    __syncthreads();  // dS of every key
+    xbf16x8 sb[2];
+#pragma unroll
+    for (int c = 0; c < 2; ++c) sb[c] = xa_tr<64>(ds, c, wave, quad, j16, sswz);
 #pragma unroll
     for (int t = 0; t < NOT; ++t)
 #pragma unroll
-      for (int c = 0; c < 2; ++c) dq[t] = xa_mfma(xa_tr<HD>(Ks, c, t, quad, j16, tswz), dsf[c], dq[t]);
+      for (int c = 0; c < 2; ++c) dq[t] = xa_mfma(xa_tr<HD>(Ks, c, t, quad, j16, tswz), sb[c], dq[t]);
+    if (jt + 1 < ntiles) {
+      __syncthreads();  // K and V free
+      T::issue(kv, Kb, Vb, A.ldkv, kv0, Lk, (jt + 1) * 64, wave, lane);
+    }
   }
-  __builtin_amdgcn_s_waitcnt(0);
+  const int qi = wave * 16 + j16;
   if (qi >= Lq) return;
   uint16_t* out = A.dQ + (q0 + qi) * A.lddq + h * HD + quad * 4;
 #pragma unroll
@@ -748,118 +814,20 @@ __global__ __launch_bounds__(256, 2) void xattn_bwd_dq_kernel(AttnArgs A) {
                                                          pack_bf2(dq[t][2] * A.scale, dq[t][3] * A.scale));
 }
 
-// Backward, key side: one workgroup per (sample, head, 64-key tile), wave w =
-// keys 16 w ..; the sample's queries (<= 64, zero rows past Lq) and its
-// bf16-rounded output gradients sit in LDS.  Scores untransposed, S = Q K^T
-// (lane = key, registers = 4 queries of each 16-query block), so P and dS
-// are already the B operands of dV^T = dO^T P and dK^T = Q^T dS.
-template <int HD>
-__global__ __launch_bounds__(256, 2) void xattn_bwd_dkv_kernel(AttnArgs A) {
-  constexpr int NQC = HD / 32, NOT = HD / 16, CPR = HD / 8;
-  __shared__ __attribute__((aligned(1024))) uint16_t qt[64 * HD];
-  __shared__ __attribute__((aligned(1024))) uint16_t dt[64 * HD];
-  __shared__ float lse_s[64], d_s[64];
-  const int k = blockIdx.x, h = blockIdx.y;
-  int32_t q0, Lq, Lk;
-  int64_t kv0;
-  attn_rows(A, k, q0, Lq, kv0, Lk);
-  const int32_t j0 = blockIdx.z * 64;
-  if (j0 >= Lk) return;
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int j16 = lane & 15, quad = lane >> 4;
-  const float sl2 = A.scale * 1.4426950408889634f;
-  // stage Q and bf16(dO): 64 rows x CPR chunks of 8 elements
-  for (int e = tid; e < 64 * CPR; e += 256) {
-    const int r = e / CPR, c = e % CPR;
-    const int pos = r * HD + ((c ^ xa_swz<HD>(r)) * 8);
-    uint4 qv = make_uint4(0, 0, 0, 0), dv = make_uint4(0, 0, 0, 0);
-    if (r < Lq) {
-      const int64_t row = q0 + r;
-      qv = *reinterpret_cast<const uint4*>(A.Q + row * A.ldq + h * HD + c * 8);
-      const float4 a = *reinterpret_cast<const float4*>(A.dO + row * A.ldo + h * HD + c * 8);
-      const float4 b = *reinterpret_cast<const float4*>(A.dO + row * A.ldo + h * HD + c * 8 + 4);
-      dv = make_uint4(pack_bf2(a.x, a.y), pack_bf2(a.z, a.w), pack_bf2(b.x, b.y), pack_bf2(b.z, b.w));
-    }
-    *reinterpret_cast<uint4*>(qt + pos) = qv;
-    *reinterpret_cast<uint4*>(dt + pos) = dv;
-  }
-  if (tid < 64) {
-    const bool live = tid < Lq;
-    lse_s[tid] = live ? A.lse[(q0 + tid) * A.nheads + h] : INFINITY;  // P = 0 past Lq
-    d_s[tid] = live ? A.dsum[(q0 + tid) * A.nheads + h] : 0.f;
-  }
-  __syncthreads();
-
-  const int32_t key = j0 + wave * 16 + j16;  // this lane's key
-  const int64_t krow = kv0 + min(key, Lk - 1);
-  xbf16x8 kf[NQC], vf[NQC];
-#pragma unroll
-  for (int c = 0; c < NQC; ++c) {
-    kf[c] = *reinterpret_cast<const xbf16x8*>(A.K + krow * A.ldkv + A.kcol + h * HD + c * 32 + quad * 8);
-    vf[c] = *reinterpret_cast<const xbf16x8*>(A.V + krow * A.ldkv + A.vcol + h * HD + c * 32 + quad * 8);
-  }
-  // S[q][key] and dP[q][key] for the four 16-query blocks
-  xf32x4 s[4], dp[4];
-#pragma unroll
-  for (int qb = 0; qb < 4; ++qb) s[qb] = dp[qb] = xf32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int c = 0; c < NQC; ++c)
-#pragma unroll
-    for (int qb = 0; qb < 4; ++qb) {
-      s[qb] = xa_mfma(xa_frag<HD>(qt, qb * 16 + j16, 4 * c + quad), kf[c], s[qb]);
-      dp[qb] = xa_mfma(xa_frag<HD>(dt, qb * 16 + j16, 4 * c + quad), vf[c], dp[qb]);
-    }
-  // P and dS as B operands: k-slot s of chunk c is query 32 c + 4 quad + (s & 3) + 16 (s >> 2)
-  xbf16x8 pb[2], db[2];
-#pragma unroll
-  for (int qb = 0; qb < 4; ++qb)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int q = qb * 16 + quad * 4 + e;
-      const float pv = exp2f(fmaf(s[qb][e], sl2, -lse_s[q]));
-      pb[qb >> 1][(qb & 1) * 4 + e] = (__bf16)pv;
-      db[qb >> 1][(qb & 1) * 4 + e] = (__bf16)(pv * (dp[qb][e] - d_s[q]));
-    }
-  const int tswz = xa_swz<HD>(4 * quad + (j16 >> 2));
-  xf32x4 dv[NOT], dk[NOT];
-#pragma unroll
-  for (int t = 0; t < NOT; ++t) {
-    dv[t] = dk[t] = xf32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      dv[t] = xa_mfma(xa_tr<HD>(dt, c, t, quad, j16, tswz), pb[c], dv[t]);
-      dk[t] = xa_mfma(xa_tr<HD>(qt, c, t, quad, j16, tswz), db[c], dk[t]);
-    }
-  }
-  if (key >= Lk) return;
-  // lane holds dV^T / dK^T rows (head dims) 16 t + 4 quad .. +3 of its key
-  uint16_t* vrow = A.dV + (kv0 + key) * A.lddkv + A.dvcol + h * HD + quad * 4;
-  uint16_t* krw = A.dK + (kv0 + key) * A.lddkv + A.dkcol + h * HD + quad * 4;
-#pragma unroll
-  for (int t = 0; t < NOT; ++t) {
-    *reinterpret_cast<uint2*>(vrow + t * 16) = make_uint2(pack_bf2(dv[t][0], dv[t][1]), pack_bf2(dv[t][2], dv[t][3]));
-    *reinterpret_cast<uint2*>(krw + t * 16) =
-        make_uint2(pack_bf2(dk[t][0] * A.scale, dk[t][1] * A.scale), pack_bf2(dk[t][2] * A.scale, dk[t][3] * A.scale));
-  }
-}
-
 hipError_t launch_xattn(hipStream_t s, const AttnArgs& A, int32_t nsamples, bool backward) {
   if (A.Lq > 64 || A.Lq < 1 || A.max_lk < 1) return hipErrorInvalidValue;
-  const dim3 grid(nsamples, A.nheads), gk(nsamples, A.nheads, (A.max_lk + 63) / 64);
+  const dim3 grid(nsamples, A.nheads);
   switch (A.hd) {
     case 64:
       if (backward) {
-        xattn_bwd_dq_kernel<64><<<grid, 256, 0, s>>>(A);
-        xattn_bwd_dkv_kernel<64><<<gk, 256, 0, s>>>(A);
+        xattn_bwd_kernel<64><<<grid, 256, 0, s>>>(A);
       } else {
         xattn_fwd_kernel<64><<<grid, 256, 0, s>>>(A);
       }
       break;
     case 128:
       if (backward) {
-        xattn_bwd_dq_kernel<128><<<grid, 256, 0, s>>>(A);
-        xattn_bwd_dkv_kernel<128><<<gk, 256, 0, s>>>(A);
+        xattn_bwd_kernel<128><<<grid, 256, 0, s>>>(A);
       } else {
         xattn_fwd_kernel<128><<<grid, 256, 0, s>>>(A);
       }
