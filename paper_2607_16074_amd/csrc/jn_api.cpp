@@ -719,17 +719,13 @@ struct HeadPlan {
   std::vector<int64_t> width;      // per layer index k: max output width
   size_t P = 0, Z0 = 0, total = 0; // offsets
   std::vector<size_t> Z, H, dZ;    // per k
-  size_t descs = 0, tiles = 0, part = 0, lpart = 0;
-  std::vector<HeadGemm> dv;
-  std::vector<HeadTile> tv;
-  std::vector<LossDesc> lv;
-  size_t losses = 0;
-  // launch ranges into tv
-  std::vector<std::pair<int32_t, int32_t>> fwd, bwd;
+  size_t descs = 0, tiles = 0, lpart = 0;
 };
 
-constexpr int kHTM = 32;  // fp32 head GEMM tile: rows
-constexpr int kHTN = 64;  // and columns
+int64_t head_tiles(int64_t n) { return (n + kHeadTile - 1) / kHeadTile; }
+int64_t wgrad_tiles(int64_t out, int64_t in) {
+  return (out + kHeadWgradM - 1) / kHeadWgradM * ((in + kHeadWgradN - 1) / kHeadWgradN);
+}
 
 jn_status check_heads(jn_ctx* c, const jn_packed* p, const jn_head* heads, int32_t G) {
   if (!heads) return fail(c, JN_EINVAL, "null heads");
@@ -748,12 +744,11 @@ jn_status check_heads(jn_ctx* c, const jn_packed* p, const jn_head* heads, int32
   return JN_OK;
 }
 
-// Workspace layout: pooled P [N][d] | per layer k: Z_k, H_k, dZ_k [N][width_k] |
-// split-K partial sums (the largest ksplit x N x width of any split launch) |
-// per-tenant loss partial sums (16 G floats) |
-// loss descriptors | gemm descriptors | tiles.  Tenant g's rows of every
-// [N][*] buffer are its tenant-order rows [off_g, off_g + n_g).
-void head_layout(const jn_packed* p, const jn_head* heads, int32_t G, HeadPlan* hp, bool with_descs) {
+// Workspace layout: pooled P [N][d] | per layer k: Z_k, H_k (hidden layers),
+// dZ_k [N][width_k] | per-tenant, per-tile loss sums | gemm descriptors |
+// tiles.  Tenant g's rows of every [N][*] buffer are its tenant-order rows
+// [off_g, off_g + n_g).
+void head_layout(const jn_packed* p, const jn_head* heads, int32_t G, HeadPlan* hp) {
   size_t o = 0;
   auto take = [&](size_t bytes) {
     size_t at = o;
@@ -767,38 +762,33 @@ void head_layout(const jn_packed* p, const jn_head* heads, int32_t G, HeadPlan* 
   for (int32_t g = 0; g < G; ++g)
     for (int k = 0; k < heads[g].n_layers; ++k) hp->width[k] = std::max<int64_t>(hp->width[k], heads[g].dims[k + 1]);
   hp->P = take(4 * N * p->d);
-  hp->Z.resize(hp->maxL);
-  hp->H.resize(hp->maxL);
+  hp->Z.assign(hp->maxL, 0);
+  hp->H.assign(hp->maxL, 0);
   hp->dZ.resize(hp->maxL);
   for (int k = 0; k < hp->maxL; ++k) {
-    hp->Z[k] = take(4 * N * hp->width[k]);
-    hp->H[k] = take(4 * N * hp->width[k]);
+    if (k + 1 < hp->maxL) {
+      hp->Z[k] = take(4 * N * hp->width[k]);
+      hp->H[k] = take(4 * N * hp->width[k]);
+    }
     hp->dZ[k] = take(4 * N * hp->width[k]);
   }
-  if (!with_descs) {
-    // descriptor counts are bounded by G * 2 * maxL; tiles computed exactly below
-  }
-  // tile counts: fwd M-dynamic (rows bounded by the largest tenant), bwd
-  // wgrad + dgrad; a split descriptor has ksplit tiles per output tile plus
-  // one reduce tile
-  const int64_t tm_dyn = (tenant_rows_bound(p) + kHTM - 1) / kHTM;
-  int64_t ntiles = 0, ndesc = 0, part_elems = 0;
+  // tiles: forward and data gradient over the rows of the largest tenant,
+  // weight gradient, loss
+  const int64_t tm_dyn = head_tiles(tenant_rows_bound(p));
+  int64_t ntiles = 0, ndesc = 0;
   for (int32_t g = 0; g < G; ++g) {
     const jn_head& Hh = heads[g];
     for (int k = 0; k < Hh.n_layers; ++k) {
-      int64_t in = Hh.dims[k], out = Hh.dims[k + 1];
-      const int64_t sf = head_ksplit(in), sd = head_ksplit(out);
-      ntiles += tm_dyn * ((out + kHTN - 1) / kHTN) * (sf + (sf > 1));           // fwd
-      ntiles += ((out + kHTM - 1) / kHTM) * ((in + kHTN - 1) / kHTN);           // wgrad
-      if (k > 0) ntiles += tm_dyn * ((in + kHTN - 1) / kHTN) * (sd + (sd > 1)); // dgrad
+      const int64_t in = Hh.dims[k], out = Hh.dims[k + 1];
+      ntiles += tm_dyn * head_tiles(out) + wgrad_tiles(out, in) + (k > 0 ? tm_dyn * head_tiles(in) : 0);
       ndesc += (k > 0) ? 3 : 2;
-      if (sf > 1) part_elems = std::max(part_elems, sf * N * hp->width[k]);
-      if (k > 0 && sd > 1) part_elems = std::max(part_elems, sd * N * hp->width[k - 1]);
     }
+    ntiles += 1;
+    ndesc += 1;
   }
-  hp->part = take(4 * part_elems);
-  hp->lpart = take(4 * 16 * G);
-  hp->losses = take(sizeof(LossDesc) * G);
+  int64_t lparts = 0;
+  for (int32_t g = 0; g < G; ++g) lparts += tm_dyn * head_tiles(heads[g].dims[heads[g].n_layers]);
+  hp->lpart = take(4 * lparts);
   hp->descs = take(sizeof(HeadGemm) * ndesc);
   hp->tiles = take(sizeof(HeadTile) * ntiles);
   hp->total = o;
@@ -811,7 +801,7 @@ jn_status jn_heads_workspace_size(const jn_packed* p, const jn_head* heads, int3
   jn_status st = check_heads(nullptr, p, heads, G);
   if (st != JN_OK) return st;
   HeadPlan hp;
-  head_layout(p, heads, G, &hp, false);
+  head_layout(p, heads, G, &hp);
   *bytes = hp.total;
   return JN_OK;
 }
@@ -838,188 +828,134 @@ jn_status heads_run(jn_ctx* c, const jn_packed* p, const void* hidden, const jn_
       if (!I.dW[k] || !I.db[k]) return fail(c, JN_EINVAL, "io %d layer %d null gradient", g, k);
   }
   HeadPlan hp;
-  head_layout(p, heads, G, &hp, true);
+  head_layout(p, heads, G, &hp);
   if (ws_bytes < hp.total) return fail(c, JN_ENOSPACE, "workspace %zu B < %zu B", ws_bytes, hp.total);
   if (((uintptr_t)ws) % 256 != 0) return fail(c, JN_EUNSUPPORTED, "workspace must be 256-byte aligned");
 
   char* w = (char*)ws;
   float* P = pooled ? pooled : (float*)(w + hp.P);
-  const int64_t N = p->N, d = p->d;
-  const int32_t tm_dyn = (int32_t)((tenant_rows_bound(p) + kHTM - 1) / kHTM);
+  const int64_t d = p->d;
+  const int32_t tm_dyn = (int32_t)head_tiles(tenant_rows_bound(p));
   auto Zk = [&](int k) { return (float*)(w + hp.Z[k]); };
   auto Hk = [&](int k) { return (float*)(w + hp.H[k]); };
   auto dZk = [&](int k) { return (float*)(w + hp.dZ[k]); };
 
-  std::vector<HeadGemm> descs;
-  std::vector<HeadTile> tiles;
-  std::vector<std::pair<int32_t, int32_t>> fwd_rng, bwd_rng, fwd_red, bwd_red;
-  // a descriptor whose K is long enough is split into K ranges whose sums go
-  // to the partial area (plane = the [N][width] extent of its C buffer)
-  float* const part = (float*)(w + hp.part);
-  auto split_desc = [&](HeadGemm& D, int64_t plane) {
-    D.ksplit = head_ksplit(D.K);
-    if (D.ksplit > 1) {
-      D.part = part;
-      D.part_plane = plane;
-    }
+  // tables built in place in their upload image: descs | tiles
+  std::vector<char> img(hp.total - hp.descs);
+  HeadGemm* const dd0 = (HeadGemm*)img.data();
+  HeadTile* const dt0 = (HeadTile*)(img.data() + (hp.tiles - hp.descs));
+  int32_t nd = 0, nt = 0;
+  std::vector<std::pair<int32_t, int32_t>> fwd_rng, bwd_rng;
+  auto add_tiles = [&](const HeadGemm& D, int32_t g, int32_t tms, int32_t tns) {
+    dd0[nd] = D;
+    for (int32_t tm = 0; tm < tms; ++tm)
+      for (int32_t tn = 0; tn < tns; ++tn) dt0[nt++] = HeadTile{nd, g, tm, tn};
+    ++nd;
   };
-  // reduce tiles of the split descriptors among tiles [t0, end): appended
-  // after them, returned as a range
-  auto reduce_tiles = [&](int32_t t0) {
-    const int32_t t1 = (int32_t)tiles.size();
-    for (int32_t t = t0; t < t1; ++t)
-      if (descs[tiles[t].desc].ksplit > 1 && tiles[t].tk == 0) tiles.push_back(HeadTile{tiles[t].desc, tiles[t].tm, tiles[t].tn, 0});
-    return std::make_pair(t1, (int32_t)tiles.size() - t1);
-  };
-  // forward, one launch per layer index
+  // forward, one launch per layer index; a tenant's last layer forms its loss
+  // gradient in dZ
+  float* lpart = (float*)(w + hp.lpart);
+  std::vector<float*> lparts(G);
+  for (int32_t g = 0; g < G; ++g) {
+    lparts[g] = lpart;
+    lpart += (int64_t)tm_dyn * head_tiles(heads[g].dims[heads[g].n_layers]);
+  }
   for (int k = 0; k < hp.maxL; ++k) {
-    int32_t t0 = (int32_t)tiles.size();
+    const int32_t t0 = nt;
     for (int32_t g = 0; g < G; ++g) {
       const jn_head& Hh = heads[g];
       if (k >= Hh.n_layers) continue;
-      const int64_t in = Hh.dims[k], out = Hh.dims[k + 1];
-      const float* X = (k == 0) ? P : Hk(k - 1);
-      const int64_t ldx = (k == 0) ? d : hp.width[k - 1];
+      const bool last = k + 1 == Hh.n_layers;
       HeadGemm D{};
-      D.A = X;
-      D.sam = ldx;
-      D.sak = 1;
+      D.mode = HEAD_FWD;
+      D.A = (k == 0) ? P : Hk(k - 1);
+      D.lda = (k == 0) ? d : hp.width[k - 1];
       D.B = Hh.W[k];
-      D.sbk = 1;
-      D.sbn = in;
-      D.C = Zk(k);
+      D.ldb = Hh.dims[k];
+      D.C = last ? dZk(k) : Zk(k);
       D.ldc = hp.width[k];
       D.bias = Hh.b[k];
-      D.Cact = (k + 1 < Hh.n_layers) ? Hk(k) : nullptr;
-      D.bumpA = ldx;
-      D.bumpB = 0;
-      D.bumpC = hp.width[k];
-      D.M = -1;
-      D.N = (int32_t)out;
-      D.K = (int32_t)in;
-      D.tenant = g;
-      D.tiles_n = (int32_t)((out + kHTN - 1) / kHTN);
-      split_desc(D, N * hp.width[k]);
-      int32_t di = (int32_t)descs.size();
-      descs.push_back(D);
-      for (int32_t tk = 0; tk < D.ksplit; ++tk)
-        for (int32_t tm = 0; tm < tm_dyn; ++tm)
-          for (int32_t tn = 0; tn < D.tiles_n; ++tn) tiles.push_back(HeadTile{di, tm, tn, tk});
+      D.Cact = last ? nullptr : Hk(k);
+      if (last) {
+        D.target = io[g].targets;
+        D.actions = io[g].actions;
+        D.lpart = lparts[g];
+      }
+      D.N = Hh.dims[k + 1];
+      D.K = Hh.dims[k];
+      add_tiles(D, g, tm_dyn, (int32_t)head_tiles(D.N));
     }
-    fwd_rng.emplace_back(t0, (int32_t)tiles.size() - t0);
-    fwd_red.push_back(reduce_tiles(t0));
+    fwd_rng.emplace_back(t0, nt - t0);
   }
-  // loss: y = Z_{L-1} rows, dY -> dZ_{L-1}
-  std::vector<LossDesc> losses(G);
-  for (int32_t g = 0; g < G; ++g) {
-    const int L = heads[g].n_layers;
-    losses[g] = LossDesc{Zk(L - 1), io[g].targets, dZk(L - 1), io[g].loss, io[g].actions,
-                         heads[g].dims[L], hp.width[L - 1], g, 0};
-  }
-  // backward, one launch per step s (tenant g at layer k = L_g - 1 - s)
+  // backward, one launch per step s (tenant g at layer k = L_g - 1 - s), the
+  // first with the tenants' losses
   for (int sidx = 0; sidx < hp.maxL; ++sidx) {
-    int32_t t0 = (int32_t)tiles.size();
+    const int32_t t0 = nt;
     for (int32_t g = 0; g < G; ++g) {
       const jn_head& Hh = heads[g];
       const int k = Hh.n_layers - 1 - sidx;
       if (k < 0) continue;
-      const int64_t in = Hh.dims[k], out = Hh.dims[k + 1];
-      const float* X = (k == 0) ? P : Hk(k - 1);
-      const int64_t ldx = (k == 0) ? d : hp.width[k - 1];
+      const int32_t in = Hh.dims[k], out = Hh.dims[k + 1];
       // wgrad: dW[out][in] = sum_rows dZ[row][o] X[row][i]; db[o] = sum_rows dZ[row][o]
       HeadGemm Wg{};
+      Wg.mode = HEAD_WGRAD;
       Wg.A = dZk(k);
-      Wg.sam = 1;
-      Wg.sak = hp.width[k];
-      Wg.B = X;
-      Wg.sbk = ldx;
-      Wg.sbn = 1;
+      Wg.lda = hp.width[k];
+      Wg.B = (k == 0) ? P : Hk(k - 1);
+      Wg.ldb = (k == 0) ? d : hp.width[k - 1];
       Wg.C = io[g].dW[k];
       Wg.ldc = in;
       Wg.db = io[g].db[k];
-      Wg.bumpA = hp.width[k];
-      Wg.bumpB = ldx;
-      Wg.bumpC = 0;
-      Wg.M = (int32_t)out;
-      Wg.N = (int32_t)in;
-      Wg.K = -1;
-      Wg.tenant = g;
-      Wg.tiles_n = (int32_t)((in + kHTN - 1) / kHTN);
-      int32_t di = (int32_t)descs.size();
-      descs.push_back(Wg);
-      const int32_t tmw = (int32_t)((out + kHTM - 1) / kHTM);
-      for (int32_t tm = 0; tm < tmw; ++tm)
-        for (int32_t tn = 0; tn < Wg.tiles_n; ++tn) tiles.push_back(HeadTile{di, tm, tn, 0});
+      Wg.M = out;
+      Wg.N = in;
+      // dgrad: dZ_{k-1}[row][i] = (sum_o dZ_k[row][o] W[o][i]) * gelu'(Z_{k-1}[row][i]);
+      // its tiles come first, they are the longer ones
       if (k > 0) {
-        // dgrad: dZ_{k-1}[row][i] = (sum_o dZ_k[row][o] W[o][i]) * gelu'(Z_{k-1}[row][i])
         HeadGemm Dg{};
+        Dg.mode = HEAD_DGRAD;
         Dg.A = dZk(k);
-        Dg.sam = hp.width[k];
-        Dg.sak = 1;
+        Dg.lda = hp.width[k];
         Dg.B = Hh.W[k];
-        Dg.sbk = in;
-        Dg.sbn = 1;
+        Dg.ldb = in;
         Dg.C = dZk(k - 1);
         Dg.ldc = hp.width[k - 1];
         Dg.Zg = Zk(k - 1);
-        Dg.bumpA = hp.width[k];
-        Dg.bumpB = 0;
-        Dg.bumpC = hp.width[k - 1];
-        Dg.M = -1;
-        Dg.N = (int32_t)in;
-        Dg.K = (int32_t)out;
-        Dg.tenant = g;
-        Dg.tiles_n = (int32_t)((in + kHTN - 1) / kHTN);
-        split_desc(Dg, N * hp.width[k - 1]);
-        int32_t dj = (int32_t)descs.size();
-        descs.push_back(Dg);
-        for (int32_t tk = 0; tk < Dg.ksplit; ++tk)
-          for (int32_t tm = 0; tm < tm_dyn; ++tm)
-            for (int32_t tn = 0; tn < Dg.tiles_n; ++tn) tiles.push_back(HeadTile{dj, tm, tn, tk});
+        Dg.N = in;
+        Dg.K = out;
+        add_tiles(Dg, g, tm_dyn, (int32_t)head_tiles(in));
+      }
+      add_tiles(Wg, g, (out + kHeadWgradM - 1) / kHeadWgradM, (in + kHeadWgradN - 1) / kHeadWgradN);
+      if (sidx == 0) {
+        HeadGemm Ls{};
+        Ls.mode = HEAD_LOSS;
+        Ls.lpart = lparts[g];
+        Ls.C = io[g].loss;
+        Ls.N = out;
+        add_tiles(Ls, g, 1, 1);
       }
     }
-    bwd_rng.emplace_back(t0, (int32_t)tiles.size() - t0);
-    bwd_red.push_back(reduce_tiles(t0));
+    bwd_rng.emplace_back(t0, nt - t0);
   }
 
-  // one upload of every table: losses | descs | tiles (contiguous in ws)
-  const size_t lbytes = sizeof(LossDesc) * G, dbytes = sizeof(HeadGemm) * descs.size(),
-               tbytes = sizeof(HeadTile) * tiles.size();
-  if (hp.descs + dbytes > hp.tiles || hp.tiles + tbytes > hp.total)
+  // one upload of both tables
+  const size_t tbytes = sizeof(HeadTile) * (size_t)nt;
+  if (hp.descs + sizeof(HeadGemm) * (size_t)nd > hp.tiles || hp.tiles + tbytes > hp.total)
     return fail(c, JN_ENOSPACE, "internal: head table sizing");
-  std::vector<char> img(hp.total - hp.losses, 0);
-  std::memcpy(img.data(), losses.data(), lbytes);
-  std::memcpy(img.data() + (hp.descs - hp.losses), descs.data(), dbytes);
-  std::memcpy(img.data() + (hp.tiles - hp.losses), tiles.data(), tbytes);
-  st = fixed ? stage_copy_fixed(c, w + hp.losses, img.data(), hp.tiles - hp.losses + tbytes)
-             : stage_copy(c, w + hp.losses, img.data(), hp.tiles - hp.losses + tbytes);
+  st = fixed ? stage_copy_fixed(c, w + hp.descs, img.data(), hp.tiles - hp.descs + tbytes)
+             : stage_copy(c, w + hp.descs, img.data(), hp.tiles - hp.descs + tbytes);
   if (st != JN_OK) return st;
-  const LossDesc* dl = (const LossDesc*)(w + hp.losses);
   const HeadGemm* dd = (const HeadGemm*)(w + hp.descs);
   const HeadTile* dt = (const HeadTile*)(w + hp.tiles);
   hipStream_t s = c->stream;
 
   JN_TRACED(c, JN_OP_POOL, p->T, p->d, p->N,
             launch_pool(s, hidden, p->seqlens, p->cu_seqlens, p->sample_tenant_rank, p->N, p->d, P), "pool");
-  for (size_t i = 0; i < fwd_rng.size(); ++i) {
-    const auto r = fwd_rng[i], q = fwd_red[i];
-    if (r.second)
-      JN_TRACED(c, JN_OP_HEAD_FWD, r.second, 0, 0, launch_head_gemm(s, dd, dt + r.first, r.second, p->tenant_sample_off),
-                "head fwd");
-    if (q.second)
-      JN_TRACED(c, JN_OP_HEAD_FWD, q.second, 0, 0, launch_head_reduce(s, dd, dt + q.first, q.second, p->tenant_sample_off),
-                "head fwd reduce");
-  }
-  JN_TRACED(c, JN_OP_LOSS, G, 0, 0, launch_mse(s, dl, G, p->tenant_sample_off, (float*)(w + hp.lpart)), "loss");
-  for (size_t i = 0; i < bwd_rng.size(); ++i) {
-    const auto r = bwd_rng[i], q = bwd_red[i];
-    if (r.second)
-      JN_TRACED(c, JN_OP_HEAD_BWD, r.second, 0, 0, launch_head_gemm(s, dd, dt + r.first, r.second, p->tenant_sample_off),
-                "head bwd");
-    if (q.second)
-      JN_TRACED(c, JN_OP_HEAD_BWD, q.second, 0, 0, launch_head_reduce(s, dd, dt + q.first, q.second, p->tenant_sample_off),
-                "head bwd reduce");
-  }
+  for (const auto& r : fwd_rng)
+    JN_TRACED(c, JN_OP_HEAD_FWD, r.second, 0, 0, launch_head_gemm(s, dd, dt + r.first, r.second, p->tenant_sample_off, true),
+              "head fwd");
+  for (const auto& r : bwd_rng)
+    JN_TRACED(c, JN_OP_HEAD_BWD, r.second, 0, 0, launch_head_gemm(s, dd, dt + r.first, r.second, p->tenant_sample_off, false),
+              "head bwd");
   return JN_OK;
 }
 
@@ -1039,7 +975,7 @@ jn_status jn_tenant_heads_fwd_bwd_noalloc(jn_ctx* c, const jn_packed* p, const v
   if (!c->scratch) return fail(c, JN_EHIP, "the library scratch array has no device address on device %d", c->device);
   if (valid_packed(p) && heads && G == p->G && check_heads(nullptr, p, heads, G) == JN_OK) {
     HeadPlan hp;
-    head_layout(p, heads, G, &hp, false);
+    head_layout(p, heads, G, &hp);
     if (hp.total > kHeadsScratchBytes)
       return fail(c, JN_ENOSPACE, "heads need %zu B of workspace; the allocation-free call has %zu B", hp.total,
                   kHeadsScratchBytes);
@@ -1954,7 +1890,7 @@ struct jn_infer_plan {
   float* P = nullptr;
   const HeadGemm* dd = nullptr;
   const HeadTile* dt = nullptr;
-  std::vector<std::pair<int32_t, int32_t>> fwd_rng, fwd_red;
+  std::vector<std::pair<int32_t, int32_t>> fwd_rng;
   int32_t max_rows = 0;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
@@ -1999,7 +1935,7 @@ void collector_prefix(const jn_collector* c, int32_t* count, int64_t* samples, b
 struct HeadFwdLayout {
   int maxL = 0;
   std::vector<int64_t> width;
-  size_t P = 0, part = 0, descs = 0, tiles = 0, total = 0;
+  size_t P = 0, descs = 0, tiles = 0, total = 0;
   std::vector<size_t> Z, H;
 };
 
@@ -2022,16 +1958,13 @@ HeadFwdLayout head_fwd_layout(int64_t N, int64_t rows_bound, int64_t d, const jn
     L.Z[k] = take(4 * N * L.width[k]);
     L.H[k] = take(4 * N * L.width[k]);
   }
-  const int64_t tm_dyn = (rows_bound + kHTM - 1) / kHTM;
-  int64_t ntiles = 0, ndesc = 0, part_elems = 0;
+  const int64_t tm_dyn = head_tiles(rows_bound);
+  int64_t ntiles = 0, ndesc = 0;
   for (int32_t g = 0; g < G; ++g)
     for (int k = 0; k < heads[g].n_layers; ++k) {
-      const int64_t sk = k + 1 < heads[g].n_layers ? head_ksplit(heads[g].dims[k]) : 1;
-      ntiles += tm_dyn * ((heads[g].dims[k + 1] + kHTN - 1) / kHTN) * (sk + (sk > 1));
-      if (sk > 1) part_elems = std::max(part_elems, sk * N * L.width[k]);
+      ntiles += tm_dyn * head_tiles(heads[g].dims[k + 1]);
       ++ndesc;
     }
-  L.part = take(4 * part_elems);
   L.descs = take(sizeof(HeadGemm) * ndesc);
   L.tiles = take(sizeof(HeadTile) * ntiles);
   L.total = o;
@@ -2105,15 +2038,9 @@ jn_status infer_enqueue(jn_ctx* c, const jn_infer_plan* pl) {
   if (st != JN_OK) return st;
   JN_TRACED(c, JN_OP_POOL, pk.T, pk.d, pk.N,
             launch_pool(s, pl->hidden, pk.seqlens, pk.cu_seqlens, pk.sample_tenant_rank, pk.N, pk.d, pl->P), "pool");
-  for (size_t i = 0; i < pl->fwd_rng.size(); ++i) {
-    const auto r = pl->fwd_rng[i], q = pl->fwd_red[i];
-    if (r.second)
-      JN_TRACED(c, JN_OP_HEAD_FWD, r.second, 0, 0,
-                launch_head_gemm(s, pl->dd, pl->dt + r.first, r.second, pk.tenant_sample_off), "head fwd");
-    if (q.second)
-      JN_TRACED(c, JN_OP_HEAD_FWD, q.second, 0, 0,
-                launch_head_reduce(s, pl->dd, pl->dt + q.first, q.second, pk.tenant_sample_off), "head fwd reduce");
-  }
+  for (const auto& r : pl->fwd_rng)
+    JN_TRACED(c, JN_OP_HEAD_FWD, r.second, 0, 0,
+              launch_head_gemm(s, pl->dd, pl->dt + r.first, r.second, pk.tenant_sample_off, true), "head fwd");
   return JN_OK;
 }
 
@@ -2227,8 +2154,8 @@ jn_status jn_infer_plan_create(jn_ctx* c, const jn_request* req, int32_t R, cons
   const HeadFwdLayout& hl = L.hl;
   char* hw = w + L.heads;
   pl->P = (float*)(hw + hl.P);
-  const int64_t N = p.N, d = o->d_model;
-  const int32_t tm_dyn = (int32_t)((tenant_rows_bound(&pl->packed) + kHTM - 1) / kHTM);
+  const int64_t d = o->d_model;
+  const int32_t tm_dyn = (int32_t)head_tiles(tenant_rows_bound(&pl->packed));
   std::vector<HeadGemm> descs;
   std::vector<HeadTile> tiles;
   for (int k = 0; k < hl.maxL; ++k) {
@@ -2239,40 +2166,24 @@ jn_status jn_infer_plan_create(jn_ctx* c, const jn_request* req, int32_t R, cons
       const int64_t in = Hh.dims[k], outw = Hh.dims[k + 1];
       const bool last = k + 1 == Hh.n_layers;
       HeadGemm D{};
+      D.mode = HEAD_FWD;
       D.A = (k == 0) ? pl->P : (const float*)(hw + hl.H[k - 1]);
-      D.sam = (k == 0) ? d : hl.width[k - 1];
-      D.sak = 1;
+      D.lda = (k == 0) ? d : hl.width[k - 1];
       D.B = Hh.W[k];
-      D.sbk = 1;
-      D.sbn = in;
+      D.ldb = in;
       D.C = last ? actions[g] : (float*)(hw + hl.Z[k]);
       D.ldc = last ? outw : hl.width[k];
+      D.own_rows = last;
       D.bias = Hh.b[k];
       D.Cact = last ? nullptr : (float*)(hw + hl.H[k]);
-      D.bumpA = D.sam;
-      D.bumpB = 0;
-      D.bumpC = last ? 0 : hl.width[k];
-      D.M = -1;
       D.N = (int32_t)outw;
       D.K = (int32_t)in;
-      D.tenant = g;
-      D.tiles_n = (int32_t)((outw + kHTN - 1) / kHTN);
-      D.ksplit = last ? 1 : head_ksplit(in);
-      if (D.ksplit > 1) {
-        D.part = (float*)(hw + hl.part);
-        D.part_plane = N * hl.width[k];
-      }
       const int32_t di = (int32_t)descs.size();
       descs.push_back(D);
-      for (int32_t tk = 0; tk < D.ksplit; ++tk)
-        for (int32_t tm = 0; tm < tm_dyn; ++tm)
-          for (int32_t tn = 0; tn < D.tiles_n; ++tn) tiles.push_back(HeadTile{di, tm, tn, tk});
+      for (int32_t tm = 0; tm < tm_dyn; ++tm)
+        for (int32_t tn = 0; tn < (int32_t)head_tiles(outw); ++tn) tiles.push_back(HeadTile{di, g, tm, tn});
     }
     pl->fwd_rng.emplace_back(t0, (int32_t)tiles.size() - t0);
-    const int32_t t1 = (int32_t)tiles.size();
-    for (int32_t t = t0; t < t1; ++t)
-      if (descs[tiles[t].desc].ksplit > 1 && tiles[t].tk == 0) tiles.push_back(tiles[t]);
-    pl->fwd_red.emplace_back(t1, (int32_t)tiles.size() - t1);
   }
   const size_t dbytes = sizeof(HeadGemm) * descs.size(), tbytes = sizeof(HeadTile) * tiles.size();
   if (hl.descs + dbytes > hl.tiles || hl.tiles + tbytes > hl.total) {

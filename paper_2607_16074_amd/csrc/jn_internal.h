@@ -126,68 +126,47 @@ hipError_t launch_pool(hipStream_t s, const void* hidden, const int32_t* seqlens
                        const int32_t* cu_seqlens, const int32_t* rank, int32_t N, int32_t d,
                        float* pooled);
 
-// Grouped fp32 GEMM descriptor for the tenant heads:
-//   C(m,n) = sum_k A(m,k) B(k,n),  A(m,k) = A[m*sam + k*sak],  B(k,n) = B[k*sbk + n*sbn].
-// Tenant-ordered operands are addressed from the tenant's first row: the
-// kernel adds off_g * bump{A,B,C} to the base pointers, with
-// off_g = tenant_sample_off[tenant] read on the device.  The one dimension
-// equal to the tenant's row count n_g (M for forward / data-gradient, K for
-// weight-gradient) is given as -1 and read on the device as well.
+// One fp32 GEMM of a tenant head, C(m, n) = sum_k A B, by mode:
+//   HEAD_FWD    A = X [row][k], B = W [n][k], C [row][n]
+//   HEAD_DGRAD  A = dZ [row][k], B = W [k][n], C [row][n]
+//   HEAD_WGRAD  A = dZ [row][m], B = X [row][n], C = dW [m][n], contracted over
+//               the tenant's rows
+//   HEAD_LOSS   C[0] = the tenant's loss from its lpart sums
+// Row operands are tenant-ordered buffers: the kernel starts at the tenant's
+// first row (tenant_sample_off, read on the device), and its row count stands
+// for M (FWD, DGRAD) or K (WGRAD).
+enum HeadMode : int32_t { HEAD_FWD = 0, HEAD_DGRAD = 1, HEAD_WGRAD = 2, HEAD_LOSS = 3 };
 struct HeadGemm {
   const float* A;
   const float* B;
   float* C;
-  const float* bias;  // forward: C(m,n) += bias[n]          (may be null)
-  float* Cact;        // forward: also store gelu(C) (same ldc / bump as C)
-  const float* Zg;    // data-gradient: C *= gelu'(Zg)  (same ldc / bump as C)
-  float* db;          // weight-gradient: db[m] = sum_k A(m,k), by tn == 0 tiles
-  float* part;        // ksplit > 1: K range t of tile (m, n) writes its raw sum to
-                      // part[t * part_plane + off * bumpC + m * ldc + n]; the
-                      // reduce launch adds the ranges in order and applies the epilogue
-  int64_t part_plane;
-  int64_t sam, sak, sbk, sbn, ldc;
-  int64_t bumpA, bumpB, bumpC;
-  int32_t M, N, K;
-  int32_t tenant;
-  int32_t tiles_n;
-  int32_t ksplit;     // K ranges (1: the tile writes C with its epilogue)
+  const float* bias;    // FWD: C += bias[n]
+  float* Cact;          // FWD: also store gelu(C) (same layout as C; may be null)
+  const float* Zg;      // DGRAD: C *= gelu'(Zg) (same layout as C)
+  float* db;            // WGRAD: db[m] = sum of A over the rows
+  // FWD of a training head's last layer (target set): actions = y, C = dL/dy of
+  // L = mean((y - target)^2), lpart[tile] = sum of squared errors; target and
+  // actions are the tenant's own [n_g][N] buffers
+  const float* target;
+  float* actions;
+  float* lpart;
+  int64_t lda, ldb, ldc;
+  int32_t M, N, K;      // M: WGRAD only; K: FWD and DGRAD only
+  int32_t mode;
+  int32_t own_rows;     // FWD: C is the tenant's own buffer (rows from 0)
+  int32_t reserved;
 };
 struct HeadTile {
   int32_t desc;
+  int32_t tenant;
   int32_t tm;
   int32_t tn;
-  int32_t tk;  // K range (ksplit > 1)
 };
+constexpr int kHeadTile = 32;                        // FWD and DGRAD tiles are 32 x 32
+constexpr int kHeadWgradM = 64, kHeadWgradN = 256;   // WGRAD tiles
+// forward: every tile is HEAD_FWD; otherwise none is.
 hipError_t launch_head_gemm(hipStream_t s, const HeadGemm* descs, const HeadTile* tiles, int32_t n_tiles,
-                            const int32_t* tenant_sample_off);
-// Sum of the K ranges of split descriptors, then bias / GELU' / GELU as in
-// the unsplit epilogue; tiles (desc, tm, tn, 0) of the split descriptors.
-hipError_t launch_head_reduce(hipStream_t s, const HeadGemm* descs, const HeadTile* tiles, int32_t n_tiles,
-                              const int32_t* tenant_sample_off);
-// K ranges of a head GEMM of contraction length K (a function of K only, so
-// a tenant's result does not depend on the rest of the batch).
-inline int32_t head_ksplit(int64_t K) {
-  const int64_t s = K / 256;
-  return K < 512 ? 1 : (int32_t)(s > 8 ? 8 : s);
-}
-
-// Per-tenant mean squared error over n_g * out elements:
-//   loss = mean((y - t)^2), dy = 2 (y - t) / (n_g * out), actions = y.
-// y and dy are tenant-ordered ([N][ld], rows from off_g); target and actions
-// are the tenant's own [n_g][out] buffers.
-struct LossDesc {
-  const float* y;
-  const float* target;
-  float* dy;
-  float* loss;
-  float* actions;
-  int32_t out;
-  int64_t ld;
-  int32_t tenant;
-  int32_t reserved;
-};
-// part: 16 G floats of scratch (per-tenant partial sums, two launches).
-hipError_t launch_mse(hipStream_t s, const LossDesc* descs, int32_t G, const int32_t* tenant_sample_off, float* part);
+                            const int32_t* tenant_sample_off, bool forward);
 
 // ---- action expert (k_expert.hip) ----
 // dst[r][c] = cvt(src[r][c]) for r < src_rows, c < src_cols, else 0; r < rows, c < cols.

@@ -1,12 +1,11 @@
 // Tenant split and tenant-private action heads (fp32):
 //   pool       mean of each sample's valid rows of the shared feature, written
 //              in tenant order (the split of the shared features by slices)
-//   head_gemm  one launch per head layer for all tenants, fp32 matrix-core
-//              tiles: forward (bias + GELU fused), weight gradient (bias
-//              gradient fused) and data gradient (GELU derivative fused);
-//              tenant row ranges are read from the device maps, so the host
-//              needs no per-tenant counts
-//   mse        per-tenant mean squared error and its gradient
+//   head_gemm  one launch per head layer and direction for all tenants, fp32
+//              matrix-core tiles: forward (bias, GELU or the squared-error loss
+//              and its gradient fused), weight gradient (bias gradient fused)
+//              and data gradient (GELU derivative fused); tenant row ranges are
+//              read from the device maps, so the host needs no per-tenant counts
 // Every reduction runs in a fixed order: results are bitwise reproducible.
 #include "jn_device.h"
 #include "jn_internal.h"
@@ -17,7 +16,7 @@ namespace jnx {
 
 // Block = (sample, 512-column chunk); 256 threads = 4 wavefronts, lane l
 // owning columns 8 l .. 8 l + 7 (one 16-byte load covers 1 KB of a row per
-// wave).  Wave w sums rows w, w+4, w+8, ... of the sample in that order, four
+// wave).  Wave w sums rows w, w+4, w+8, ... of the sample in that order, eight
 // loads in flight per lane; the four wave sums are combined as
 // (s0 + s1) + (s2 + s3).  The order depends only on the sample's own length,
 // so a sample pools to the same bits in any batch.
@@ -50,6 +49,13 @@ __global__ __launch_bounds__(256) void pool_kernel(const uint16_t* __restrict__ 
       }
     };
     int32_t j = w;
+    for (; j + 7 * kPoolWaves < L; j += 8 * kPoolWaves) {
+      uint4 q[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) q[k] = *reinterpret_cast<const uint4*>(base + (int64_t)(j + k * kPoolWaves) * d);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) add(q[k]);
+    }
     for (; j + 3 * kPoolWaves < L; j += 4 * kPoolWaves) {
       uint4 q[4];
 #pragma unroll
@@ -80,258 +86,368 @@ hipError_t launch_pool(hipStream_t s, const void* hidden, const int32_t* seqlens
 
 // ------------------------------------------------------------- head gemm ---
 
-// fp32 matrix-core tiles (v_mfma_f32_16x16x4_f32, the heads' precision): a
-// workgroup computes a 32 x 64 tile of C with 4 wavefronts, wave w owning
-// rows 16 (w >> 1) .. +15 and columns 32 (w & 1) .. +31 (two 16 x 16 MFMA
-// blocks).  32 rows fit the local batch of a tenant in one row tile.  Operands
-// go through LDS in K chunks of 32, stored K-major (As[k][m], Bs[k][n], row
-// stride padded by one float); the next chunk is loaded into registers while
-// the current one is multiplied; steps past the end of a short K (a weight
-// gradient's K is the tenant's row count) are skipped.  Measured on the
-// 2B-shaped workload's heads: chunks of 128 (4x the loads in flight) left the
-// forward launches unchanged and made the weight-gradient launches, whose
-// K is 32, 3x slower (more LDS per workgroup, zero-filled chunk work).  MFMA operand layout (16x16x4): lane l holds
-// A(m = l & 15, k = l >> 4) and B(k = l >> 4, n = l & 15); the result block
-// gives lane l rows 4 (l >> 4) .. +3 of column l & 15.  The K order of every
-// output element is fixed (chunks in order, four k per MFMA), and the bias
-// gradient of a weight-gradient tile is the row sum of its A operand taken
-// from LDS chunk by chunk in k order, so results are bitwise reproducible and
-// independent of the other tenants of the launch.
-constexpr int HM = 32;   // tile rows
-constexpr int HN = 64;   // tile columns
-constexpr int HKC = 32;   // K chunk
-
+// fp32 matrix cores (v_mfma_f32_16x16x4_f32, the heads' precision), operands
+// loaded from global memory straight into the MFMA layout: lane l supplies
+// A(m = l & 15, k = l >> 4), and which k a step and lane quad stand for, or
+// which column a block and lane stand for, is free as long as both operands
+// agree, so every operand loads whole vectors along its contiguous dimension.
+//   HEAD_FWD    C[m][n] = X[m][k] W[n][k]: 16-byte loads along k (step s of a
+//               16-wide k block is k = 4 quad + s)
+//   HEAD_DGRAD  C[m][n] = dZ[m][k] W[k][n]: 16-byte loads of dZ along k, 8-byte
+//               loads of W along n (block b holds columns 2 j + b)
+//   HEAD_WGRAD  C[m][n] = sum_k dZ[k][m] X[k][n]: 4-byte loads along m, 16-byte
+//               along n (step = 4 rows, one per quad)
+// A workgroup has 8 wavefronts.  FWD and DGRAD: a 32 x 32 tile, the waves each
+// take a K range (ceil(K / 8) rounded up to 32) and the eight partial tiles
+// are added through LDS in wave order, so a long contraction needs neither
+// partial sums in memory nor a second launch.  WGRAD (K is a tenant's row
+// count): 64 x 256 tile, 32 x 64 per wave.  The order of every sum depends on
+// K alone, so a tenant's bits do not depend on the batch.
+// Bound by the weights' and gradients' HBM traffic (one read, one write) and by
+// launches: with LDS staging, K ranges as workgroups and a reduction launch
+// after each, the heads of 8 tenants x 32 rows on 2,048-wide features took
+// thirteen launches and 276 us after the pool; now six launches and 141 us
+// (forward 26 + 15 + 15, backward 24 + 33 + 28 us).  Per launch about 4.7 us go
+// to the launch and the first descriptor, 2.5 us to the last tile's store.
 typedef float f32x4h __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));  // rows need not be 16-byte aligned
+typedef float f32x2u __attribute__((ext_vector_type(2), aligned(4)));
 
-__global__ __launch_bounds__(256) void head_gemm_kernel(const HeadGemm* __restrict__ descs,
-                                                        const HeadTile* __restrict__ tiles,
-                                                        const int32_t* __restrict__ tso) {
-  __shared__ float As[HKC][HM + 1];
-  __shared__ float Bs[HKC][HN + 1];
-  const HeadTile tile = tiles[blockIdx.x];
-  const HeadGemm D = descs[tile.desc];
-  const int32_t off = tso[D.tenant];
-  const int32_t ng = tso[D.tenant + 1] - off;
-  const int32_t M = D.M < 0 ? ng : D.M;
-  const int32_t N = D.N;
-  const int32_t K = D.K < 0 ? ng : D.K;
-  const int32_t m0 = tile.tm * HM, n0 = tile.tn * HN;
-  if (m0 >= M) return;  // tiles past a tenant's row count (upper-bound grid)
-  // K range of this tile: all of K, or range tk of ksplit (chunk-aligned)
-  int32_t kb = 0, ke = K;
-  if (D.ksplit > 1) {
-    const int32_t kc = ((K + D.ksplit - 1) / D.ksplit + HKC - 1) / HKC * HKC;
-    kb = min(K, tile.tk * kc);
-    ke = min(K, kb + kc);
-  }
-  const float* A = D.A + (int64_t)off * D.bumpA;
-  const float* B = D.B + (int64_t)off * D.bumpB;
+__device__ __forceinline__ f32x4h head_mfma(float a, float b, f32x4h c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+constexpr int kHeadWaves = 8;
+constexpr int kHeadDepth = 4;  // slabs in flight per wave
+constexpr int kHeadRed = kHeadTile + 4;  // LDS row stride of a partial tile
+
+// Epilogue of the 32 x 32 tile: sum of the waves' partials, then per element
+// bias, GELU' (DGRAD), GELU copy, or -- a training forward's last layer -- the
+// loss: actions, dL/dy and the tile's sum of squared errors.
+__device__ __forceinline__ void head_finish(const HeadGemm& D, const float* red, float* scratch, int32_t off, int32_t ng,
+                                            int32_t m0, int32_t n0, int32_t M, int32_t tile_slot) {
   const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const bool a_k_fast = D.sak == 1;
-  const bool b_k_fast = D.sbk == 1;
-  const bool want_db = D.db != nullptr && tile.tn == 0;
-
-  constexpr int QA = HM * HKC / 256;  // A elements per thread per chunk (4)
-  constexpr int QB = HN * HKC / 256;  // B elements per thread per chunk (8)
-  float ra[QA], rb[QB];
-  auto load = [&](int32_t k0) {
+  const int32_t r = tid >> 4, c = (tid & 15) * 2;
+  const int32_t m = m0 + r;
+  float ss = 0.f;
+  if (m < M) {
+    float v[2];
 #pragma unroll
-    for (int q = 0; q < QA; ++q) {
-      const int e = tid + 256 * q;
-      int mm, kk;
-      if (a_k_fast) { kk = e % HKC; mm = e / HKC; } else { mm = e % HM; kk = e / HM; }
-      const int32_t m = m0 + mm, k = k0 + kk;
-      ra[q] = (m < M && k < ke) ? A[(int64_t)m * D.sam + (int64_t)k * D.sak] : 0.f;
-    }
+    for (int e = 0; e < 2; ++e) {
+      v[e] = red[r * kHeadRed + c + e];
 #pragma unroll
-    for (int q = 0; q < QB; ++q) {
-      const int e = tid + 256 * q;
-      int nn, kk;
-      if (b_k_fast) { kk = e % HKC; nn = e / HKC; } else { nn = e % HN; kk = e / HN; }
-      const int32_t n = n0 + nn, k = k0 + kk;
-      rb[q] = (n < N && k < ke) ? B[(int64_t)k * D.sbk + (int64_t)n * D.sbn] : 0.f;
+      for (int w = 1; w < kHeadWaves; ++w) v[e] += red[(w * kHeadTile + r) * kHeadRed + c + e];
     }
-  };
-  auto store = [&]() {
+    const int64_t row = (int64_t)(off + m) * D.ldc;
+    const float scale = 2.0f / ((float)ng * (float)D.N);
 #pragma unroll
-    for (int q = 0; q < QA; ++q) {
-      const int e = tid + 256 * q;
-      if (a_k_fast) As[e % HKC][e / HKC] = ra[q]; else As[e / HM][e % HM] = ra[q];
-    }
-#pragma unroll
-    for (int q = 0; q < QB; ++q) {
-      const int e = tid + 256 * q;
-      if (b_k_fast) Bs[e % HKC][e / HKC] = rb[q]; else Bs[e / HN][e % HN] = rb[q];
-    }
-  };
-
-  f32x4h acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-  float dbs = 0.f;  // bias gradient of row m0 + tid (tid < HM), k in order
-  const int am = wm * 16 + (lane & 15), kq = lane >> 4;
-  const int bn0 = wn * 32 + (lane & 15);
-  load(kb);
-  for (int32_t k0 = kb; k0 < ke; k0 += HKC) {
-    store();
-    __syncthreads();
-    if (k0 + HKC < ke) load(k0 + HKC);
-    const int kend = min(HKC, ke - k0);  // zero-filled beyond the range
-#pragma unroll 8
-    for (int kk = 0; kk < kend; kk += 4) {
-      const float a = As[kk + kq][am];
-      acc0 = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Bs[kk + kq][bn0], acc0, 0, 0, 0);
-      acc1 = __builtin_amdgcn_mfma_f32_16x16x4f32(a, Bs[kk + kq][bn0 + 16], acc1, 0, 0, 0);
-    }
-    if (want_db && tid < HM) {
-#pragma unroll 8
-      for (int kk = 0; kk < kend; ++kk) dbs += As[kk][tid];
-    }
-    __syncthreads();
-  }
-
-  if (D.ksplit > 1) {  // raw sum of this K range; the reduce launch finishes the tile
-    float* Pt = D.part + tile.tk * D.part_plane + (int64_t)off * D.bumpC;
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int32_t n = n0 + wn * 32 + j * 16 + (lane & 15);
-      if (n >= N) continue;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int32_t m = m0 + wm * 16 + 4 * (lane >> 4) + e;
-        if (m < M) Pt[(int64_t)m * D.ldc + n] = j == 0 ? acc0[e] : acc1[e];
+    for (int e = 0; e < 2; ++e) {
+      const int32_t n = n0 + c + e;
+      if (n >= D.N) break;
+      float y = v[e];
+      if (D.bias) y += D.bias[n];
+      if (D.Zg) y *= gelu_grad_f(D.Zg[row + n]);
+      if (D.target) {
+        const int64_t i = (int64_t)m * D.N + n;
+        const float diff = y - D.target[i];
+        D.actions[i] = y;
+        D.C[row + n] = scale * diff;
+        ss = fmaf(diff, diff, ss);
+      } else {
+        D.C[row + n] = y;
+        if (D.Cact) D.Cact[row + n] = gelu_f(y);
       }
+    }
+  }
+  if (D.target) {
+    ss = wave_sum(ss);
+    if ((tid & 63) == 0) scratch[tid >> 6] = ss;
+    __syncthreads();
+    if (tid == 0) {
+      float s = 0.f;
+      for (int w = 0; w < kHeadWaves; ++w) s += scratch[w];
+      D.lpart[tile_slot] = s;
+    }
+  }
+}
+
+// The K range of a wave; its whole slabs of S end at `kw` (kb where the tile
+// cannot take vector loads), the rest goes four k at a time with element loads.
+struct HeadRange {
+  int32_t kb, kw, ke;
+};
+template <int S>
+__device__ __forceinline__ HeadRange head_range(int32_t K, int wave, bool vectors) {
+  const int32_t kc = ((K + kHeadWaves - 1) / kHeadWaves + 31) / 32 * 32;
+  HeadRange r;
+  r.kb = min(K, wave * kc);
+  r.ke = min(K, r.kb + kc);
+  r.kw = vectors ? r.kb + (r.ke - r.kb) / S * S : r.kb;
+  return r;
+}
+
+__device__ __forceinline__ void head_fwd_tile(const HeadGemm& D, float* red, int32_t off, int32_t m0, int32_t n0, int32_t M) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int j = lane & 15, quad = lane >> 4;
+  const HeadRange R = head_range<32>(D.K, wave, true);
+  const float *A[2], *B[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    A[i] = D.A + (int64_t)(off + min(m0 + 16 * i + j, M - 1)) * D.lda;
+    B[i] = D.B + (int64_t)min(n0 + 16 * i + j, D.N - 1) * D.ldb;
+  }
+  f32x4h acc[2][2] = {};
+  f32x4h a[kHeadDepth][2][2], b[kHeadDepth][2][2];  // [slab in flight][16-wide k block][operand block]
+  auto load = [&](int u, int32_t k0) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        a[u][h][i] = *reinterpret_cast<const f32x4u*>(A[i] + k0 + 16 * h + 4 * quad);
+        b[u][h][i] = *reinterpret_cast<const f32x4u*>(B[i] + k0 + 16 * h + 4 * quad);
+      }
+  };
+#pragma unroll
+  for (int u = 0; u < kHeadDepth; ++u)
+    if (R.kb + 32 * u < R.kw) load(u, R.kb + 32 * u);
+  for (int32_t k0 = R.kb; k0 < R.kw; k0 += 32 * kHeadDepth) {
+#pragma unroll
+    for (int u = 0; u < kHeadDepth; ++u) {
+      if (k0 + 32 * u >= R.kw) break;
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int y = 0; y < 2; ++y)
+#pragma unroll
+            for (int x = 0; x < 2; ++x) acc[y][x] = head_mfma(b[u][h][y][s], a[u][h][x][s], acc[y][x]);
+      if (k0 + 32 * (u + kHeadDepth) < R.kw) load(u, k0 + 32 * (u + kHeadDepth));
+    }
+  }
+  for (int32_t k0 = R.kw; k0 < R.ke; k0 += 4) {
+    const int32_t k = min(k0 + quad, R.ke - 1);
+    const bool live = k0 + quad < R.ke;
+    float av[2], bv[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float x = A[i][k], w = B[i][k];
+      av[i] = live ? x : 0.f;
+      bv[i] = live ? w : 0.f;
+    }
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int x = 0; x < 2; ++x) acc[y][x] = head_mfma(bv[y], av[x], acc[y][x]);
+  }
+  // lane: columns n = 16 y + 4 quad .. +3 of row m = 16 x + j
+#pragma unroll
+  for (int y = 0; y < 2; ++y)
+#pragma unroll
+    for (int x = 0; x < 2; ++x)
+      *reinterpret_cast<f32x4h*>(red + (wave * kHeadTile + 16 * x + j) * kHeadRed + 16 * y + 4 * quad) = acc[y][x];
+}
+
+__device__ __forceinline__ void head_dgrad_tile(const HeadGemm& D, float* red, int32_t off, int32_t m0, int32_t n0,
+                                                int32_t M) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int j = lane & 15, quad = lane >> 4;
+  const HeadRange R = head_range<16>(D.K, wave, n0 + kHeadTile <= D.N);
+  const float* A[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) A[i] = D.A + (int64_t)(off + min(m0 + 16 * i + j, M - 1)) * D.lda;
+  const int64_t ldb = D.ldb;
+  const uint32_t bo = 4 * quad * (uint32_t)ldb + n0 + 2 * j;
+  f32x4h acc[2][2] = {};
+  f32x4h a[kHeadDepth][2];
+  f32x2u b[kHeadDepth][4];
+  auto load = [&](int u, int32_t k0) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) a[u][i] = *reinterpret_cast<const f32x4u*>(A[i] + k0 + 4 * quad);
+    const float* p = D.B + (int64_t)k0 * ldb;  // uniform; 32-bit lane offsets
+#pragma unroll
+    for (int s = 0; s < 4; ++s) b[u][s] = *reinterpret_cast<const f32x2u*>(p + s * ldb + bo);
+  };
+#pragma unroll
+  for (int u = 0; u < kHeadDepth; ++u)
+    if (R.kb + 16 * u < R.kw) load(u, R.kb + 16 * u);
+  for (int32_t k0 = R.kb; k0 < R.kw; k0 += 16 * kHeadDepth) {
+#pragma unroll
+    for (int u = 0; u < kHeadDepth; ++u) {
+      if (k0 + 16 * u >= R.kw) break;
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int y = 0; y < 2; ++y)
+#pragma unroll
+          for (int x = 0; x < 2; ++x) acc[y][x] = head_mfma(b[u][s][y], a[u][x][s], acc[y][x]);
+      if (k0 + 16 * (u + kHeadDepth) < R.kw) load(u, k0 + 16 * (u + kHeadDepth));
+    }
+  }
+#pragma unroll 4
+  for (int32_t k0 = R.kw; k0 < R.ke; k0 += 4) {
+    const int32_t k = min(k0 + quad, R.ke - 1);
+    const bool live = k0 + quad < R.ke;
+    float av[2], bv[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const float x = A[i][k], w = D.B[(int64_t)k * ldb + min(n0 + 2 * j + i, D.N - 1)];
+      av[i] = live ? x : 0.f;
+      bv[i] = live ? w : 0.f;
+    }
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int x = 0; x < 2; ++x) acc[y][x] = head_mfma(bv[y], av[x], acc[y][x]);
+  }
+  // lane: columns n = 8 quad + 2 e + y of row m = 16 x + j
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    float* p = red + (wave * kHeadTile + 16 * x + j) * kHeadRed + 8 * quad;
+    *reinterpret_cast<f32x4h*>(p) = f32x4h{acc[0][x][0], acc[1][x][0], acc[0][x][1], acc[1][x][1]};
+    *reinterpret_cast<f32x4h*>(p + 4) = f32x4h{acc[0][x][2], acc[1][x][2], acc[0][x][3], acc[1][x][3]};
+  }
+}
+
+__device__ __forceinline__ void head_wgrad_tile(const HeadGemm& D, int32_t off, int32_t tm, int32_t tn, int32_t K) {
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int j = lane & 15, quad = lane >> 4;
+  const int32_t M = D.M, N = D.N;
+  const int32_t m0 = tm * kHeadWgradM + 32 * (wave >> 2), n0 = tn * kHeadWgradN + 64 * (wave & 3);
+  if (m0 >= M || n0 >= N) return;
+  const int64_t lda = D.lda, ldb = D.ldb;
+  const float *const A = D.A + (int64_t)off * lda, *const B = D.B + (int64_t)off * ldb;
+  const uint32_t a0 = quad * (uint32_t)lda + min(m0 + j, M - 1), a1 = quad * (uint32_t)lda + min(m0 + 16 + j, M - 1);
+  const int cj = n0 + 4 * ((j >> 2) + 4 * (j & 3));  // this lane's four columns
+  const uint32_t bo = quad * (uint32_t)ldb + cj;
+  const bool whole = n0 + 64 <= N;  // uniform: vector loads along n
+  f32x4h acc[4][2] = {};            // [column block b][row block a]
+  float cs[2] = {0.f, 0.f};         // bias gradient: this quad's rows of columns m0 + j, m0 + 16 + j
+  float a[2][4][2];                 // [16 rows in flight][step][row block]
+  f32x4h b[2][4];
+  auto load = [&](int u, int32_t k0) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const float *pa = A + (int64_t)(k0 + 4 * s) * lda, *pb = B + (int64_t)(k0 + 4 * s) * ldb;  // uniform
+      a[u][s][0] = pa[a0];
+      a[u][s][1] = pa[a1];
+      b[u][s] = *reinterpret_cast<const f32x4u*>(pb + bo);
+    }
+  };
+  const int32_t kw = whole ? K / 16 * 16 : 0;
+#pragma unroll
+  for (int u = 0; u < 2; ++u)
+    if (16 * u < kw) load(u, 16 * u);
+  for (int32_t k0 = 0; k0 < kw; k0 += 32) {
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      if (k0 + 16 * u >= kw) break;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+#pragma unroll
+        for (int x = 0; x < 2; ++x) cs[x] += a[u][s][x];
+#pragma unroll
+        for (int y = 0; y < 4; ++y)
+#pragma unroll
+          for (int x = 0; x < 2; ++x) acc[y][x] = head_mfma(b[u][s][y], a[u][s][x], acc[y][x]);
+      }
+      if (k0 + 16 * (u + 2) < kw) load(u, k0 + 16 * (u + 2));
+    }
+  }
+#pragma unroll 2
+  for (int32_t k0 = kw; k0 < K; k0 += 4) {
+    const int64_t k = min(k0 + quad, K - 1);
+    const bool live = k0 + quad < K;
+    float av[2] = {A[k * lda + min(m0 + j, M - 1)], A[k * lda + min(m0 + 16 + j, M - 1)]};
+    float bv[4];
+#pragma unroll
+    for (int y = 0; y < 4; ++y) bv[y] = B[k * ldb + min(cj + y, N - 1)];
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      av[x] = live ? av[x] : 0.f;
+      cs[x] += av[x];
+    }
+#pragma unroll
+    for (int y = 0; y < 4; ++y) {
+      bv[y] = live ? bv[y] : 0.f;
+#pragma unroll
+      for (int x = 0; x < 2; ++x) acc[y][x] = head_mfma(bv[y], av[x], acc[y][x]);
+    }
+  }
+  // lane: columns n0 + 16 e + 4 quad + y of rows m0 + 16 x + j (the loads' column
+  // order makes a store instruction cover 64 contiguous bytes of 16 rows)
+#pragma unroll
+  for (int x = 0; x < 2; ++x) {
+    const int32_t m = m0 + 16 * x + j;
+    if (m >= M) break;
+    float* p = D.C + (int64_t)m * D.ldc + n0 + 4 * quad;
+    if (whole) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        *reinterpret_cast<f32x4u*>(p + 16 * e) = f32x4h{acc[0][x][e], acc[1][x][e], acc[2][x][e], acc[3][x][e]};
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int y = 0; y < 4; ++y)
+          if (n0 + 16 * e + 4 * quad + y < N) p[16 * e + y] = acc[y][x][e];
+    }
+  }
+  if (n0 == 0) {
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      const float v = sum_xor32(sum_xor16(cs[x]));
+      if (quad == 0 && m0 + 16 * x + j < M) D.db[m0 + 16 * x + j] = v;
+    }
+  }
+}
+
+// FORWARD: HEAD_FWD tiles only (one workgroup per CU on the 2048-wide heads,
+// its slabs in flight are what hides the weights' latency); otherwise the
+// backward modes, in at most 128 registers so that two workgroups share a CU.
+template <bool FORWARD>
+__global__ __launch_bounds__(64 * kHeadWaves, FORWARD ? 2 : 4) void head_gemm_kernel(const HeadGemm* __restrict__ descs,
+                                                                                     const HeadTile* __restrict__ tiles,
+                                                                                     const int32_t* __restrict__ tso) {
+  __shared__ __attribute__((aligned(16))) float red[kHeadWaves * kHeadTile * kHeadRed];
+  __shared__ float scratch[kHeadWaves];
+  const HeadTile tile = tiles[blockIdx.x];
+  const int32_t off = tso[tile.tenant], ng = tso[tile.tenant + 1] - off;
+  const HeadGemm D = descs[tile.desc];
+  if (!FORWARD && D.mode == HEAD_WGRAD) {
+    head_wgrad_tile(D, off, tile.tm, tile.tn, ng);
+    return;
+  }
+  if (!FORWARD && D.mode == HEAD_LOSS) {  // the tenant's loss from its tiles' sums, in tile order per thread, then a fixed tree
+    const int32_t n = (ng + kHeadTile - 1) / kHeadTile * ((D.N + kHeadTile - 1) / kHeadTile);
+    float s = 0.f;
+    for (int32_t i = threadIdx.x; i < n; i += 64 * kHeadWaves) s += D.lpart[i];
+    s = wave_sum(s);
+    if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = s;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      float t = 0.f;
+      for (int w = 0; w < kHeadWaves; ++w) t += scratch[w];
+      D.C[0] = t / ((float)ng * (float)D.N);
     }
     return;
   }
-  float* C = D.C + (int64_t)off * D.bumpC;
-  const float* Zg = D.Zg ? D.Zg + (int64_t)off * D.bumpC : nullptr;
-  float* Cact = D.Cact ? D.Cact + (int64_t)off * D.bumpC : nullptr;
-#pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int32_t n = n0 + wn * 32 + j * 16 + (lane & 15);
-    if (n >= N) continue;
-    const float bias = D.bias ? D.bias[n] : 0.f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const int32_t m = m0 + wm * 16 + 4 * (lane >> 4) + e;
-      if (m >= M) continue;
-      float v = (j == 0 ? acc0[e] : acc1[e]) + bias;
-      const int64_t ci = (int64_t)m * D.ldc + n;
-      if (Zg) v *= gelu_grad_f(Zg[ci]);
-      C[ci] = v;
-      if (Cact) Cact[ci] = gelu_f(v);
-    }
-  }
-  if (want_db && tid < HM && m0 + tid < M) D.db[m0 + tid] = dbs;
+  const int32_t m0 = tile.tm * kHeadTile, n0 = tile.tn * kHeadTile;
+  if (m0 >= ng) return;  // tiles past a tenant's row count (upper-bound grid)
+  if (FORWARD)
+    head_fwd_tile(D, red, off, m0, n0, ng);
+  else
+    head_dgrad_tile(D, red, off, m0, n0, ng);
+  __syncthreads();
+  head_finish(D, red, scratch, D.own_rows ? 0 : off, ng, m0, n0, ng, tile.tm * ((D.N + kHeadTile - 1) / kHeadTile) + tile.tn);
 }
 
 hipError_t launch_head_gemm(hipStream_t s, const HeadGemm* descs, const HeadTile* tiles, int32_t n_tiles,
-                            const int32_t* tso) {
-  head_gemm_kernel<<<n_tiles, 256, 0, s>>>(descs, tiles, tso);
-  return hipGetLastError();
-}
-
-// A long contraction (K >= 512) split into ksplit ranges keeps ~8x more
-// workgroups busy: the 2048-wide first layer of the 2B-shaped workload's
-// heads is 64 sequential K chunks per tile otherwise, each waiting for its
-// loads.  This launch finishes such tiles: thread t owns column n0 + t % 64
-// of rows m0 + t / 64 + 4 i; ranges are added in order, then the epilogue.
-__global__ __launch_bounds__(256) void head_reduce_kernel(const HeadGemm* __restrict__ descs,
-                                                          const HeadTile* __restrict__ tiles,
-                                                          const int32_t* __restrict__ tso) {
-  const HeadTile tile = tiles[blockIdx.x];
-  const HeadGemm D = descs[tile.desc];
-  const int32_t off = tso[D.tenant];
-  const int32_t ng = tso[D.tenant + 1] - off;
-  const int32_t M = D.M < 0 ? ng : D.M;
-  const int32_t m0 = tile.tm * HM;
-  const int32_t n = tile.tn * HN + (threadIdx.x & 63);
-  if (m0 >= M || n >= D.N) return;
-  const float* Pt = D.part + (int64_t)off * D.bumpC;
-  float* C = D.C + (int64_t)off * D.bumpC;
-  const float* Zg = D.Zg ? D.Zg + (int64_t)off * D.bumpC : nullptr;
-  float* Cact = D.Cact ? D.Cact + (int64_t)off * D.bumpC : nullptr;
-  const float bias = D.bias ? D.bias[n] : 0.f;
-#pragma unroll
-  for (int i = 0; i < HM / 4; ++i) {
-    const int32_t m = m0 + (threadIdx.x >> 6) + 4 * i;
-    if (m >= M) break;
-    const int64_t ci = (int64_t)m * D.ldc + n;
-    float v = Pt[ci];
-    for (int32_t t = 1; t < D.ksplit; ++t) v += Pt[t * D.part_plane + ci];
-    v += bias;
-    if (Zg) v *= gelu_grad_f(Zg[ci]);
-    C[ci] = v;
-    if (Cact) Cact[ci] = gelu_f(v);
-  }
-}
-
-hipError_t launch_head_reduce(hipStream_t s, const HeadGemm* descs, const HeadTile* tiles, int32_t n_tiles,
-                              const int32_t* tso) {
-  head_reduce_kernel<<<n_tiles, 256, 0, s>>>(descs, tiles, tso);
-  return hipGetLastError();
-}
-
-// ------------------------------------------------------------------- mse ---
-
-// Block (tenant g, part b) of kMseParts takes elements [b c, (b + 1) c) of
-// the tenant's row-major [n_g][out] block (c = ceil(count / kMseParts)),
-// thread t every 256th of them in order; the block's partial sum of squared
-// errors goes to part[g kMseParts + b] (fixed-order tree), and a second
-// launch adds a tenant's parts in order.  One block per tenant measured
-// ~0.1 ms on the 2B-shaped workload (eight CUs waiting on their loads).
-constexpr int kMseParts = 16;
-
-__global__ __launch_bounds__(256) void mse_kernel(const LossDesc* __restrict__ descs,
-                                                  const int32_t* __restrict__ tso, float* __restrict__ part) {
-  __shared__ float red[256];
-  const int32_t g = blockIdx.x / kMseParts, b = blockIdx.x % kMseParts;
-  const LossDesc D = descs[g];
-  const int32_t off = tso[D.tenant];
-  const int32_t ng = tso[D.tenant + 1] - off;
-  const int32_t cnt = ng * D.out;
-  const float scale = 2.0f / (float)cnt;
-  const float* y = D.y + (int64_t)off * D.ld;
-  float* dy = D.dy + (int64_t)off * D.ld;
-  const int32_t c = (cnt + kMseParts - 1) / kMseParts;
-  const int32_t e1 = min(cnt, (b + 1) * c);
-  float ss = 0.f;
-#pragma unroll 4
-  for (int32_t e = b * c + (int32_t)threadIdx.x; e < e1; e += 256) {
-    const int32_t m = e / D.out, n = e - m * D.out;
-    const float yv = y[(int64_t)m * D.ld + n];
-    const float diff = yv - D.target[e];
-    D.actions[e] = yv;
-    dy[(int64_t)m * D.ld + n] = scale * diff;
-    ss = fmaf(diff, diff, ss);
-  }
-  red[threadIdx.x] = ss;
-  __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) part[blockIdx.x] = red[0];
-}
-
-__global__ __launch_bounds__(64) void mse_final_kernel(const LossDesc* __restrict__ descs,
-                                                       const int32_t* __restrict__ tso, const float* __restrict__ part,
-                                                       int32_t G) {
-  const int32_t g = blockIdx.x * 64 + threadIdx.x;
-  if (g >= G) return;
-  const LossDesc D = descs[g];
-  const int32_t cnt = (tso[D.tenant + 1] - tso[D.tenant]) * D.out;
-  float ss = 0.f;
-  for (int b = 0; b < kMseParts; ++b) ss += part[g * kMseParts + b];
-  D.loss[0] = ss / (float)cnt;
-}
-
-hipError_t launch_mse(hipStream_t s, const LossDesc* descs, int32_t G, const int32_t* tso, float* part) {
-  mse_kernel<<<G * kMseParts, 256, 0, s>>>(descs, tso, part);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  mse_final_kernel<<<(G + 63) / 64, 64, 0, s>>>(descs, tso, part, G);
+                            const int32_t* tso, bool forward) {
+  if (forward)
+    head_gemm_kernel<true><<<n_tiles, 64 * kHeadWaves, 0, s>>>(descs, tiles, tso);
+  else
+    head_gemm_kernel<false><<<n_tiles, 64 * kHeadWaves, 0, s>>>(descs, tiles, tso);
   return hipGetLastError();
 }
 

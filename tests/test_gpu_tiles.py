@@ -49,3 +49,31 @@ def test_sample_alone_equals_sample_in_a_batch_bitwise():
     for g, n in enumerate(lens):
         assert torch.equal(hidden(wl, [g]).hidden, full[at: at + n]), g
         at += n
+
+
+@pytest.mark.parametrize("hidden_dims,rows", [
+    ((33, 1), (1,)), ((31, 65), (2, 33)), ((300, 257), (32, 1, 31)), ((64, 1030), (65, 7)), ((515,), (40, 24))])
+def test_head_tiles_at_edges(hidden_dims, rows):
+    """Head widths that end inside a 32-wide tile, a 64 x 256 weight-gradient
+    tile, a wave's K range or a 16-byte vector, and row counts around one tile.
+    fp32 throughout: a sum of K <= 1,030 products grows by about sqrt(K) 2^-24
+    = 2e-6, over at most five chained products (three forward, two backward)."""
+    import oracle
+    print(f"widths {hidden_dims} rows {rows}", flush=True)
+    d, act, chunk = 640, 3, 5
+    ten = tuple(W.TenantSpec(n, 0, 1, 9, 9, (d,) + hidden_dims + (act * chunk,), act, chunk) for n in rows)
+    wl = W.make_workload(W.WorkloadSpec(98, W.BackboneSpec(1, d, 5, 256, False), ten, 0, "head edges"))
+    st = hidden(wl, range(len(rows)))
+    pooled, off = st.pooled.cpu().numpy().astype(np.float64), 0
+
+    def rel(t, ref):
+        return np.linalg.norm(t.cpu().numpy().astype(np.float64) - ref) / max(np.linalg.norm(ref), 1e-30)
+
+    for g, n in enumerate(rows):
+        ref = oracle.step.tenant_from_pooled(wl, g, pooled[off: off + n])
+        off += n
+        io = st.ios[g]
+        assert rel(io.actions, ref["actions"]) < 1e-5
+        assert abs(float(io.loss) - ref["loss"]) <= 1e-5 * abs(ref["loss"])
+        for layer, (dw, db) in enumerate(ref["grads"]):
+            assert rel(io.dW[layer], dw) < 1e-5 and rel(io.db[layer], db) < 1e-5, (g, layer)
