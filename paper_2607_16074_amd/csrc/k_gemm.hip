@@ -24,7 +24,7 @@
 // swizzle.
 //
 // Loops: the 256x256 tile (4 wavefronts, one per SIMD) runs a ring-buffered
-// loop (ring_tile); smaller tiles, of short launches, last partly filled waves
+// loop (ring_run); smaller tiles, of short launches, last partly filled waves
 // and small grouped problems, run flex_tile.  gemm_plan picks shapes and K
 // splits by an estimated time.
 //
@@ -43,6 +43,7 @@
 // loaded, so the gate and up accumulators of an output column land in the
 // same lane.
 #include <algorithm>
+#include <type_traits>
 
 #include "jn_device.h"
 #include "jn_internal.h"
@@ -114,114 +115,6 @@ constexpr int row_batch(int rows, int most) {
   return b;
 }
 
-// Epilogue shared by the loops: accumulator block (i, j) covers weight rows
-// 16 i .. of the wave's part and tokens 16 j ..; lane l owns output columns
-// n .. n+3, n = 16 i + 4 (l >> 4), of token row 16 j + (l & 15).
-template <int BN, int BM, int WGN, int WGM, int EPI>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, const f32x4 (&acc)[BN / WGN / 16][BM / WGM / 16],
-                                              int32_t tm, int32_t tn, int wn, int wm, int lane) {
-  constexpr bool GLU = EPI == EPI_GEGLU_BF16;
-  constexpr int WN = BN / WGN, WM = BM / WGM;
-  constexpr int TN = WN / 16, TM = WM / 16;
-  void* __restrict__ C = g.C;
-  const int64_t ldc = g.ldc;
-  const int32_t M = g.M, N = g.N;
-  const int q4 = (lane >> 4) * 4;
-  if constexpr (EPI == EPI_RESID_F32 || EPI == EPI_GELUGRAD_BF16) {
-    // Read-modify epilogues: the fp32 operands (residual rows, or saved
-    // pre-activations) of JB token-row blocks are all requested before the
-    // first store of the batch, so a batch costs one memory round trip
-    // instead of one per block.  Lanes outside the output read element (0, 0)
-    // of the operand and store nothing.
-    constexpr int JB = row_batch(TM, 32 / TN);
-    const float* src = g.aux;  // a residual add without aux is in place
-    int64_t ldr = g.ldaux;
-    if (EPI == EPI_RESID_F32 && !src) {
-      src = reinterpret_cast<const float*>(C);
-      ldr = ldc;
-    }
-#pragma unroll
-    for (int j0 = 0; j0 < TM; j0 += JB) {
-      float4 r[JB][TN];
-#pragma unroll
-      for (int jj = 0; jj < JB; ++jj) {
-        const int32_t m = tm * BM + wm * WM + (j0 + jj) * 16 + (lane & 15);
-        const int32_t mr = m < M ? m : 0;
-#pragma unroll
-        for (int i = 0; i < TN; ++i) {
-          const int32_t n = tn * BN + wn * WN + i * 16 + q4;
-          const int32_t nr = n < N ? n : 0;
-          r[jj][i] = *reinterpret_cast<const float4*>(src + (int64_t)mr * ldr + nr);
-        }
-      }
-#pragma unroll
-      for (int jj = 0; jj < JB; ++jj) {
-        const int32_t m = tm * BM + wm * WM + (j0 + jj) * 16 + (lane & 15);
-        if (m >= M) continue;
-#pragma unroll
-        for (int i = 0; i < TN; ++i) {
-          const int32_t n = tn * BN + wn * WN + i * 16 + q4;
-          if (n >= N) continue;
-          const f32x4 a = acc[i][j0 + jj];
-          const float4 z = r[jj][i];
-          if constexpr (EPI == EPI_RESID_F32) {
-            *reinterpret_cast<float4*>(reinterpret_cast<float*>(C) + (int64_t)m * ldc + n) =
-                make_float4(z.x + a[0], z.y + a[1], z.z + a[2], z.w + a[3]);
-          } else {
-            *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(C) + (int64_t)m * ldc + n) =
-                make_uint2(pack_bf2(a[0] * gelu_grad_fast_f(z.x), a[1] * gelu_grad_fast_f(z.y)),
-                           pack_bf2(a[2] * gelu_grad_fast_f(z.z), a[3] * gelu_grad_fast_f(z.w)));
-          }
-        }
-      }
-    }
-    return;
-  }
-#pragma unroll
-  for (int j = 0; j < TM; ++j) {
-    const int32_t m = tm * BM + wm * WM + j * 16 + (lane & 15);
-    if (m >= M) continue;
-    if constexpr (GLU) {
-#pragma unroll
-      for (int i = 0; i < TN; i += 2) {
-        const int32_t n = tn * (BN / 2) + wn * (WN / 2) + (i >> 1) * 16 + q4;
-        if (n >= N) continue;
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = gelu_fast_f(acc[i][j][e]) * acc[i + 1][j][e];
-        *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(C) + (int64_t)m * ldc + n) =
-            make_uint2(pack_bf2_cvt(v[0], v[1]), pack_bf2_cvt(v[2], v[3]));
-      }
-    } else {
-#pragma unroll
-      for (int i = 0; i < TN; ++i) {
-        const int32_t n = tn * BN + wn * WN + i * 16 + q4;
-        if (n >= N) continue;
-        float v[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = acc[i][j][e];
-        if constexpr (EPI == EPI_F32) {
-          *reinterpret_cast<float4*>(reinterpret_cast<float*>(C) + (int64_t)m * ldc + n) =
-              make_float4(v[0], v[1], v[2], v[3]);
-        } else if constexpr (EPI == EPI_GELU_SAVE) {
-          *reinterpret_cast<float4*>(g.aux + (int64_t)m * g.ldaux + n) = make_float4(v[0], v[1], v[2], v[3]);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = gelu_fast_f(v[e]);
-          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(C) + (int64_t)m * ldc + n) =
-              make_uint2(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]));
-        } else {
-          if constexpr (EPI == EPI_GELU_BF16) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = gelu_fast_f(v[e]);
-          }
-          *reinterpret_cast<uint2*>(reinterpret_cast<uint16_t*>(C) + (int64_t)m * ldc + n) =
-              make_uint2(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]));
-        }
-      }
-    }
-  }
-}
-
 // Position of tile pid in the grouped walk (kGroupM token tiles per group).
 __device__ __forceinline__ void tile_of(int32_t pid, int32_t tiles_m, int32_t tiles_n, int32_t& tm, int32_t& tn) {
   const int32_t per_group = kGroupM * tiles_n;
@@ -269,46 +162,166 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
   }
 }
 
-// bf16 / GELU-bf16 epilogue of the 256x256 ring loop: the tile is staged
-// through the (then free) LDS, row stride padded by 16 bytes (132 KB), so that
-// global memory sees whole rows (16-byte lanes, 256 / NW rows per wave, 2 rows
-// per instruction); written directly from the MFMA layout, each lane would
-// touch 8 bytes of 16 different rows per instruction.  The caller has passed a
-// barrier after the loop's last LDS access.  Wave w holds accumulator rows
-// wm * 16 TM ...  The GeGLU tile (GELU-bound) and the fp32 residual add keep
-// the direct path: with four waves the staged residual add (two 128-row halves,
-// each read-add-write of C behind a barrier) measured 0.83 ms on the 2048x2048
-// O projection against 0.75 direct, and 4.21 against 3.78 ms on the down
-// projection.
-template <int EPI, int TM, int NW>
-__device__ __forceinline__ void ring_epilogue_bf16(const GemmArgs& g, const f32x4 (&acc)[8][TM], uint16_t* lds,
-                                                   int32_t tm, int32_t tn, int wn, int wm, int wave, int lane) {
-  constexpr int OS = 256 + 8;  // LDS row stride (elements)
-  const int q4 = (lane >> 4) * 4;
+// Epilogues of both loops.  acc[i][j] covers weight rows 16 i .. and tokens
+// 16 j .. of the wave's part (first token m0, first output column n0); lane l
+// owns columns 16 i + 4 (l >> 4) .. +3 of token 16 j + (l & 15).  Each wave
+// turns its part around in LDS of its own (`stage`, no barriers), 16-byte
+// chunks at position chunk ^ f(row) so that writes and reads cover all banks,
+// and then touches global memory in whole row segments (128 to 512 contiguous
+// bytes per row and instruction; straight from the MFMA layout an instruction
+// touches 64 bytes, or in bf16 32, of 16 rows).  A wave whose part lies inside
+// the output takes a path without lane masks: a mask per store is a branch, and
+// each then waits for its own LDS read.
+//
+// Results of 16 bits (bf16, GELU, GeGLU): converted by v_cvt_pk_bf16_f32 on the
+// way into LDS; batches of 16-token blocks that fit 8 KB.  The others pass
+// through as fp32, one 16-token block at a time, and the fp32 rows they read
+// (residual, saved pre-activation) are requested AHEAD blocks in advance.
+// 256x256 tiles of 65,536 tokens x 3,072 columns, K = 768, before (direct
+// stores, masks; bf16 staged behind barriers) and now: bf16 311 -> 264 us, GELU
+// 356 -> 320, GeGLU 281 -> 262, residual add 523 -> 461; 72 tiles (the chip
+// mostly idle): 21.1 -> 19.8, 25.3 -> 23.9, 21.4 -> 20.4 and 33.7 -> 24.0 us.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+constexpr bool epi_bf16(int epi) { return epi == EPI_BF16 || epi == EPI_GELU_BF16 || epi == EPI_GEGLU_BF16; }
+constexpr bool epi_reads(int epi) { return epi == EPI_RESID_F32 || epi == EPI_GELUGRAD_BF16; }
+
+template <int EPI, int TN, int TM, bool WHOLE>
+__device__ __forceinline__ void epilogue_bf16(const GemmArgs& g, const f32x4 (&acc)[TN][TM], uint16_t* stage,
+                                              int32_t m0, int32_t n0, int lane) {
+  constexpr bool GLU = EPI == EPI_GEGLU_BF16;
+  constexpr int WC = GLU ? 8 * TN : 16 * TN;          // output columns per wave
+  constexpr int CH = WC / 8, RI = 64 / CH;            // 16-byte chunks per row, rows per instruction
+  constexpr int NB = row_batch(TM, 4096 / (16 * WC)); // 16-token blocks per batch
+  constexpr int NI = (NB * 16 + RI - 1) / RI;         // instructions per batch (the last of 16-column parts half used)
+  static_assert((CH & (CH - 1)) == 0 && CH <= 16, "row segments");
+  const int quad = lane >> 4, row = lane & 15, c = lane & (CH - 1), rr = lane / CH;
+  const int32_t m = m0 + rr, n = n0 + c * 8;
+  uint16_t* C = reinterpret_cast<uint16_t*>(g.C) + (int64_t)m * g.ldc + n;
+  const int64_t step = RI * g.ldc;
+  auto swz = [](int r) { return CH == 16 ? r & 15 : (r / (16 / CH)) & (CH - 1); };
+  auto put = [&](int j) __attribute__((always_inline)) {  // blocks j .. j + NB - 1
+#pragma unroll
+    for (int jj = 0; jj < NB; ++jj) {
+#pragma unroll
+      for (int i = 0; i < TN; i += GLU ? 2 : 1) {
+        float v[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const float a = acc[i][j + jj][e];
+          v[e] = GLU ? gelu_fast_f(a) * acc[i + (GLU ? 1 : 0)][j + jj][e] : EPI == EPI_GELU_BF16 ? gelu_fast_f(a) : a;
+        }
+        const int chunk = 2 * (GLU ? i / 2 : i) + (quad >> 1);
+        *reinterpret_cast<u32x2*>(stage + (16 * jj + row) * WC + (chunk ^ swz(row)) * 8 + (quad & 1) * 4) =
+            u32x2{pack_bf2_cvt(v[0], v[1]), pack_bf2_cvt(v[2], v[3])};
+      }
+    }
+  };
+  u32x4 v[NI];
+  put(0);
+#pragma unroll
+  for (int j = 0; j < TM; j += NB) {
+#pragma unroll
+    for (int it = 0; it < NI; ++it)
+      v[it] = *reinterpret_cast<const u32x4*>(stage + (RI * it + rr) * WC + (c ^ swz((RI * it + rr) & 15)) * 8);
+    if (j + NB < TM) put(j + NB);  // (a wave's LDS operations stay in order)
+#pragma unroll
+    for (int it = 0; it < NI; ++it)
+      if ((NB * 16 % RI == 0 || RI * it + rr < NB * 16) && (WHOLE || (m + 16 * j + RI * it < g.M && n < g.N)))
+        *reinterpret_cast<u32x4*>(C + it * step) = v[it];
+    C += NB * 16 * g.ldc;
+  }
+}
+
+template <int EPI, int TN, int TM, bool WHOLE>
+__device__ __forceinline__ void epilogue_f32(const GemmArgs& g, const f32x4 (&acc)[TN][TM], float* stage, int32_t m0,
+                                             int32_t n0, int lane) {
+  constexpr int WC = 16 * TN, CH = 4 * TN, RI = 64 / CH, NI = TN;  // as above; NI per block
+  constexpr bool READS = epi_reads(EPI);
+  constexpr int AHEAD = TM < 3 ? TM : 3;
+  static_assert((CH & (CH - 1)) == 0 && RI >= 2, "row segments");
+  const int quad = lane >> 4, row = lane & 15, c = lane & (CH - 1), rr = lane / CH;
+  const int32_t m = m0 + rr, n = n0 + c * 4;
+  const float* src = g.aux;  // a residual add without aux is in place
+  int64_t ldr = g.ldaux;
+  if (EPI == EPI_RESID_F32 && !src) {
+    src = reinterpret_cast<const float*>(g.C);
+    ldr = g.ldc;
+  }
+  const float* R = READS ? src + (int64_t)m * ldr + n : nullptr;
+  f32x4 r[READS ? AHEAD : 1][NI];
+  auto fetch = [&](int j) __attribute__((always_inline)) {
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+      if constexpr (WHOLE)
+        r[j % AHEAD][it] = *reinterpret_cast<const f32x4*>(R + it * RI * ldr);
+      else  // lanes outside the output read its last row or column block
+        r[j % AHEAD][it] = *reinterpret_cast<const f32x4*>(src + (int64_t)min(m + 16 * j + RI * it, g.M - 1) * ldr +
+                                                           min(n, g.N - 4));
+    }
+    R += 16 * ldr;
+  };
+  if constexpr (READS) {
+#pragma unroll
+    for (int j = 0; j < AHEAD; ++j) fetch(j);
+  }
+  const int64_t base = (int64_t)m * g.ldc + n, step = RI * g.ldc;
 #pragma unroll
   for (int j = 0; j < TM; ++j) {
-    const int row = wm * 16 * TM + j * 16 + (lane & 15);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      float v[4];
+    for (int i = 0; i < TN; ++i)
+      *reinterpret_cast<f32x4*>(stage + row * WC + ((4 * i + quad) ^ (row & (CH - 1))) * 4) = acc[i][j];
+    f32x4 v[NI];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) v[e] = EPI == EPI_GELU_BF16 ? gelu_fast_f(acc[i][j][e]) : acc[i][j][e];
-      *reinterpret_cast<uint2*>(lds + row * OS + wn * 128 + i * 16 + q4) =
-          make_uint2(pack_bf2(v[0], v[1]), pack_bf2(v[2], v[3]));
+    for (int it = 0; it < NI; ++it)
+      v[it] = *reinterpret_cast<const f32x4*>(stage + (RI * it + rr) * WC + (c ^ ((RI * it + rr) & (CH - 1))) * 4);
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+      if (!WHOLE && !(m + 16 * j + RI * it < g.M && n < g.N)) continue;
+      const int64_t at = base + 16 * j * g.ldc + it * step;
+      const f32x4 a = v[it];
+      if constexpr (EPI == EPI_F32 || EPI == EPI_RESID_F32) {
+        *reinterpret_cast<f32x4*>(reinterpret_cast<float*>(g.C) + at) = READS ? r[j % AHEAD][it] + a : a;
+      } else {
+        float y[4];
+        if constexpr (EPI == EPI_GELU_SAVE) {
+          *reinterpret_cast<f32x4*>(g.aux + (int64_t)(m + 16 * j + RI * it) * g.ldaux + n) = a;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) y[e] = gelu_fast_f(a[e]);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 4; ++e) y[e] = a[e] * gelu_grad_fast_f(r[j % AHEAD][it][e]);
+        }
+        *reinterpret_cast<u32x2*>(reinterpret_cast<uint16_t*>(g.C) + at) =
+            u32x2{pack_bf2_cvt(y[0], y[1]), pack_bf2_cvt(y[2], y[3])};
+      }
     }
+    if constexpr (READS)
+      if (j + AHEAD < TM) fetch(j + AHEAD);
   }
-  wait_lgkmcnt<0>();
-  __builtin_amdgcn_s_barrier();
-  const int c = lane & 31, rr = lane >> 5;  // 32 chunks of 16 bytes per row
-  const int32_t n = tn * 256 + c * 8;
-  constexpr int RW = 256 / NW;  // rows per wave
-#pragma unroll
-  for (int it = 0; it < RW / 2; ++it) {
-    const int row = wave * RW + it * 2 + rr;
-    const int32_t m = tm * 256 + row;
-    const uint4 v = *reinterpret_cast<const uint4*>(lds + row * OS + c * 8);
-    if (m < g.M && n < g.N) *reinterpret_cast<uint4*>(reinterpret_cast<uint16_t*>(g.C) + (int64_t)m * g.ldc + n) = v;
+}
+
+// stage: 8 KB of the wave's own.  Returns whether the part lay inside the
+// output.
+template <int EPI, int TN, int TM>
+__device__ __forceinline__ bool gemm_epilogue(const GemmArgs& g, const f32x4 (&acc)[TN][TM], uint16_t* stage,
+                                              int32_t m0, int32_t n0, int lane) {
+  const bool whole = m0 + 16 * TM <= g.M && n0 + (EPI == EPI_GEGLU_BF16 ? 8 : 16) * TN <= g.N;
+  asm volatile("" : "+v"(lane));  // lane offsets are formed here, not held in registers through a loop over tiles
+  if constexpr (epi_bf16(EPI)) {
+    if (whole)
+      epilogue_bf16<EPI, TN, TM, true>(g, acc, stage, m0, n0, lane);
+    else
+      epilogue_bf16<EPI, TN, TM, false>(g, acc, stage, m0, n0, lane);
+  } else {
+    if (whole)
+      epilogue_f32<EPI, TN, TM, true>(g, acc, reinterpret_cast<float*>(stage), m0, n0, lane);
+    else
+      epilogue_f32<EPI, TN, TM, false>(g, acc, reinterpret_cast<float*>(stage), m0, n0, lane);
   }
+  wait_lgkmcnt<0>();  // the stage is read before anything else is written there
+  __builtin_amdgcn_sched_barrier(0);
+  return whole;
 }
 
 // Buffer resource of a row-major bf16 panel starting at `base`, `bytes` long
@@ -342,7 +355,7 @@ __device__ __forceinline__ int tswz(int k) { return 2 * ((k & 3) | ((k & 8) >> 1
 // More stages measured no faster.  Rows past M and N are fetched as
 // zeros without touching memory (lane offsets past the buffer range).
 //
-// TR as in ring_tile below; a transposed operand's tile side is a multiple of
+// TR as in ring_run below; a transposed operand's tile side is a multiple of
 // 128 (its 64 k-lines hold BN or BM elements, swizzled by tswz).
 // [kt0, kt1): the K slabs summed.  WIDE: the row offsets inside a panel may
 // exceed 32 bits (leading dimensions beyond 4M elements), so every DMA
@@ -433,7 +446,7 @@ __device__ __forceinline__ void flex_tile(const GemmArgs& g, int32_t tm, int32_t
     for (int j = 0; j < TM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int sw = lds_swz(lane & 15), quad = lane >> 4;
   const int wrow = wn * WN + (lane & 15), xrow = wm * WM + (lane & 15);
-  // transposed reads as in ring_tile, for k-lines of BN / BM elements
+  // transposed reads as in ring_run, for k-lines of BN / BM elements
   const int te = (lane & 15) >> 2, tc = lane & 3;
   const int tsub = 8 * (tc >> 1) + 4 * (tc & 1) + 16 * ((te & 3) | ((quad & 1) << 2));
   auto frag_w = [&](const uint16_t* slot, int f, int h) -> bf16x8 {
@@ -547,13 +560,15 @@ __device__ __forceinline__ void flex_tile(const GemmArgs& g, int32_t tm, int32_t
   }
 #undef JN_FLEX_DMA_X
 #undef JN_FLEX_DMA_W
-  wait_vmcnt<0>();  // the repeated slabs' DMAs land before the LDS is released
-  // accumulators pinned to the accumulation registers (as in ring_tile)
+  wait_vmcnt<0>();  // the repeated slabs' DMAs land before the LDS is used again
+  __builtin_amdgcn_s_barrier();
+  // accumulators pinned to the accumulation registers (as in ring_run)
 #pragma unroll
   for (int i = 0; i < TN; ++i)
 #pragma unroll
     for (int j = 0; j < TM; ++j) asm volatile("" : "+a"(acc[i][j]));
-  gemm_epilogue<BN, BM, WGN, WGM, EPI>(g, acc, tm, tn, wn, wm, lane);
+  static_assert(4 * 4096 <= NSW * SLW + NS * SLX, "epilogue stages");
+  gemm_epilogue<EPI, TN, TM>(g, acc, lds + wave * 4096, m0 + wm * WM, (tn * BN + wn * WN) / (GLU ? 2 : 1), lane);
 }
 
 // Tile idx of an XCD-contiguous walk over `total` work items: the hardware
@@ -613,17 +628,27 @@ __global__ __launch_bounds__(256, OCC) void gemm_grouped_flex_kernel(const GemmA
 // kt+1's first-half fragments and fetching the weight half of slab kt+2.  The
 // LDS holds two weight slots and three token slots (5 x 32 KB = 160 KB): a
 // slot is refilled only after the barrier that follows its last fragment
-// read.  The stream has no branches: past the last slab the DMAs repeat slab
-// KT-1 into free slots and the fragment reads read a free slot, so every
-// phase issues the same instructions; each DMA is one buffer load to LDS with
-// a per-lane 32-bit offset and the slab offset in a scalar register.
+// read.  The stream has no branches: past a tile's last slab the DMAs fetch the
+// next tile's first two slabs (behind the workgroup's last tile, or where either
+// tile has fewer than three slabs, they repeat slab KT-1 into free slots), so
+// every phase issues the same instructions; each DMA is one buffer load to LDS
+// with a per-lane 32-bit offset and the slab offset in a scalar register.  The
+// epilogue runs between the last slab and the next tile's first, whose MFMAs
+// take zero accumulators and whose wait counts the epilogue's stores (memory
+// operations finish in order) instead of waiting for them.
 // Measured on the 2048-wide shapes against the 8-wave ping-pong loop it
 // replaces (two waves per SIMD alternating memory and compute phases): GeGLU
 // 8.27 -> 7.36 ms, QKV 1.63 -> 1.50 ms.  Per-phase cycle stamps showed what
 // the 8-wave loop and the first 4-wave versions lost: each conditional branch
 // in the MFMA stream cost 30-50 cycles of issue, and global_load_lds with a
 // 64-bit address computed per instruction cost more than the buffer form.
-// Tile (tm, tn) of problem g; lds holds 5 x 32 KB.
+// Cycle stamps of the one-tile form on 65,536 x 3,072, K = 768: 2.5 to 3.5 us
+// until the first fragments, 1.25 to 1.6 us per slab (2,330 cycles, 2,048 of
+// MFMA; the clock falls to 1.5 to 1.9 GHz with the whole chip busy, so this is
+// power), then the epilogue; with kRingChain tiles in a row the first part goes
+// (bf16 291 -> 262 us).
+// next(r, q, tm, tn): problem and tile of the workgroup's r-th turn, or false;
+// lds holds 5 x 32 KB.
 //
 // TR: operands stored transposed (GEMM_TRANS_X: X is [K][M], element (m, k)
 // at X[k * ldx + m]; GEMM_TRANS_W: W is [K][N]).  A transposed operand's
@@ -633,8 +658,8 @@ __global__ __launch_bounds__(256, OCC) void gemm_grouped_flex_kernel(const GemmA
 // the MFMA sequence per output element is the one of the row-major layout.
 // Loads past line K of a transposed operand return zero (buffer range), so
 // with both operands transposed K need not be a multiple of 64.
-template <int EPI, int TR>
-__device__ __forceinline__ void ring_tile(const GemmArgs& g, int32_t tm, int32_t tn, uint16_t* __restrict__ lds) {
+template <int EPI, int TR, class Next>
+__device__ __forceinline__ void ring_run(const Next& next, uint16_t* __restrict__ lds) {
   constexpr bool TX = (TR & GEMM_TRANS_X) != 0, TW = (TR & GEMM_TRANS_W) != 0;
   constexpr int BN = 256, BM = 256, WGN = 2, WGM = 2;
   constexpr int WN = BN / WGN, WM = BM / WGM;
@@ -642,55 +667,65 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, int32_t tm, int32_t
   constexpr int NI = 8;            // 1 KB DMA instructions per wave per half-slab
   constexpr int SLOT = 256 * kBK;  // elements per half-slab slot
   constexpr bool GLU = EPI == EPI_GEGLU_BF16;
-  const int32_t M = g.M, K = g.K;
+  constexpr int STORES = GLU ? 16 : 32;  // of a whole tile's 16-bit epilogue, per wave
+  static_assert(!(GLU && TW), "GeGLU weights are row-major");
 
+  GemmArgs g;
+  int32_t tm, tn;
+  if (!next(0, g, tm, tn)) return;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wn = wave / WGM, wm = wave % WGM;
 
-  // panels of this tile: token rows tm*256.., weight rows (GeGLU: gate and up
-  // columns tn*128..) -- rows past the end are clamped to the last one
-  const int32_t m0 = tm * BM;
-  const int32_t c0 = GLU ? tn * (BN / 2) : tn * BN;
-  static_assert(!(GLU && TW), "GeGLU weights are row-major");
-  const uint16_t* const xb = TX ? g.X + m0 : g.X + (int64_t)m0 * g.ldx;
-  const uint16_t* const wb = TW ? g.W + c0 : g.W + (int64_t)c0 * g.ldw;
-  const uint16_t* const wb2 = GLU ? g.W2 + (int64_t)c0 * g.ldw : wb;
-  const __amdgpu_buffer_rsrc_t xr =
-      panel_rsrc(xb, TX ? ((int64_t)K * g.ldx - m0) * 2 : (int64_t)(M - m0) * g.ldx * 2);
-  const __amdgpu_buffer_rsrc_t wr =
-      panel_rsrc(wb, TW ? ((int64_t)K * g.ldw - c0) * 2 : (int64_t)(g.N - c0) * g.ldw * 2);
-  const __amdgpu_buffer_rsrc_t wr2 = panel_rsrc(wb2, (int64_t)(g.N - c0) * g.ldw * 2);
-  // row-major operand: wave w fetches rows 64w .. 64w+63 of the half-slab, 8
-  // rows per instruction; transposed: k-lines 16w .. 16w+15, 2 per instruction
+  // DMA sources of the tile being fetched: token rows tm*256.., weight rows
+  // (GeGLU: gate and up columns tn*128..) -- rows past the end are clamped to
+  // the last one.  row-major operand: wave w fetches rows 64w .. 64w+63 of the
+  // half-slab, 8 rows per instruction; transposed: k-lines 16w .. 16w+15, 2 per
+  // instruction.  Byte step between slabs: one 128-byte row segment (in the
+  // scalar offset), or 64 k-lines of a transposed operand (in the lane offset,
+  // which the buffer range check covers, so lines past K read zero).
+  __amdgpu_buffer_rsrc_t xr, wr, wr2;
   uint32_t xo[NI], wo[NI];
+  int32_t xso, wso;
+  auto source = [&](const GemmArgs& q, int32_t qm, int32_t qn) {
+    const int32_t m0 = qm * BM;
+    const int32_t c0 = GLU ? qn * (BN / 2) : qn * BN;
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));  // (as in gemm_epilogue)
+    xr = panel_rsrc(TX ? q.X + m0 : q.X + (int64_t)m0 * q.ldx,
+                    TX ? ((int64_t)q.K * q.ldx - m0) * 2 : (int64_t)(q.M - m0) * q.ldx * 2);
+    wr = panel_rsrc(TW ? q.W + c0 : q.W + (int64_t)c0 * q.ldw,
+                    TW ? ((int64_t)q.K * q.ldw - c0) * 2 : (int64_t)(q.N - c0) * q.ldw * 2);
+    if constexpr (GLU) wr2 = panel_rsrc(q.W2 + (int64_t)c0 * q.ldw, (int64_t)(q.N - c0) * q.ldw * 2);
 #pragma unroll
-  for (int i = 0; i < NI; ++i) {
-    const int r = 64 * wave + 8 * i + (lane >> 3);
-    const int chunk = (lane & 7) ^ lds_swz(r);
-    const int kl = 16 * wave + 2 * i + (lane >> 5);
-    const int tchunk = (lane & 31) ^ tswz(kl);
-    if constexpr (TX)
-      xo[i] = (uint32_t)(((int64_t)kl * g.ldx + tchunk * 8) * 2);
-    else
-      xo[i] = (uint32_t)(((int64_t)(min(m0 + r, M - 1) - m0) * g.ldx + chunk * 8) * 2);
-    if constexpr (TW) {
-      wo[i] = (uint32_t)(((int64_t)kl * g.ldw + tchunk * 8) * 2);
-    } else {
-      const int32_t col = GLU ? min(c0 + (r >> 5) * 16 + (r & 15), g.N - 1) : min(c0 + r, g.N - 1);
-      wo[i] = (uint32_t)(((int64_t)(col - c0) * g.ldw + chunk * 8) * 2);
+    for (int i = 0; i < NI; ++i) {
+      const int r = 64 * wave + 8 * i + (lane >> 3);
+      const int chunk = (lane & 7) ^ lds_swz(r);
+      const int kl = 16 * wave + 2 * i + (lane >> 5);
+      const int tchunk = (lane & 31) ^ tswz(kl);
+      if constexpr (TX)
+        xo[i] = (uint32_t)(((int64_t)kl * q.ldx + tchunk * 8) * 2);
+      else
+        xo[i] = (uint32_t)min(r, q.M - 1 - m0) * (uint32_t)(q.ldx * 2) + chunk * 16;
+      if constexpr (TW) {
+        wo[i] = (uint32_t)(((int64_t)kl * q.ldw + tchunk * 8) * 2);
+      } else {
+        const int32_t col = GLU ? (r >> 5) * 16 + (r & 15) : r;
+        wo[i] = (uint32_t)min(col, q.N - 1 - c0) * (uint32_t)(q.ldw * 2) + chunk * 16;
+      }
     }
-  }
-  // byte step between slabs: one 128-byte row segment (in the scalar offset),
-  // or 64 k-lines of a transposed operand (in the lane offset, which the
-  // buffer range check covers, so lines past K read zero)
-  const int32_t xso = TX ? (int32_t)(kBK * 2 * g.ldx) : kBK * 2;
-  const int32_t wso = TW ? (int32_t)(kBK * 2 * g.ldw) : kBK * 2;
+    xso = TX ? (int32_t)(kBK * 2 * q.ldx) : kBK * 2;
+    wso = TW ? (int32_t)(kBK * 2 * q.ldw) : kBK * 2;
+  };
   const int dro = wave * NI * 512;         // this wave's 1 KB blocks inside a slot
-  uint16_t* const ring2 = lds;             // weight slabs, slot kt % 2
-  uint16_t* const ring3 = lds + 2 * SLOT;  // token slabs, slot kt % 3
+  uint16_t* const ring2 = lds;             // weight slabs, two slots
+  uint16_t* const ring3 = lds + 2 * SLOT;  // token slabs, three slots
   // DMA i of slab `slab` into a slot; in GeGLU tiles, instruction i covers
   // weight rows of one 16-row block, all gate (W) or all up (W2)
+#ifndef __HIP_DEVICE_COMPILE__
+#define JN_DMA_W(i, slab, slot) (void)(slab)
+#define JN_DMA_X(i, slab, slot) (void)(slab)
+#else
 #define JN_DMA_W(i, slab, slot)                                                                                  \
   __builtin_amdgcn_raw_ptr_buffer_load_lds((GLU && (((i) >> 1) & 1)) ? wr2 : wr,                                \
                                            JN_LPTR(ring2 + (slot) * SLOT + dro + (i) * 512), 16,                \
@@ -699,14 +734,9 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, int32_t tm, int32_t
   __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, JN_LPTR(ring3 + (slot) * SLOT + dro + (i) * 512), 16,            \
                                            TX ? xo[i] + (uint32_t)((slab) * xso) : xo[i], TX ? 0 : (slab) * xso, 0, \
                                            0)
+#endif
 
   f32x4 acc[TN][TM];
-#pragma unroll
-  for (int i = 0; i < TN; ++i)
-#pragma unroll
-    for (int j = 0; j < TM; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  const int KT = (K + kBK - 1) / kBK;
   const int sw = lds_swz(lane & 15), quad = lane >> 4;
   const int wrow = wn * WN + (lane & 15), xrow = wm * WM + (lane & 15);
   // transposed reads (inline assembly, covered by the loop's LDS waits at
@@ -737,9 +767,11 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, int32_t tm, int32_t
       return *reinterpret_cast<const bf16x8*>(slot + (xrow + 16 * f) * kBK + ((4 * h + quad) ^ sw) * 8);
     }
   };
+  bf16x8 fa[TN + TM], fb[TN + TM];  // first-half / second-half fragments: weights, then tokens
+  int slot2 = 0, slot3 = 0;         // slots of the current slab
 
-  // prologue: slabs 0 and 1 (both halves), then slab 0's first-half fragments
-  {
+  // slabs 0 and 1 of a tile (both halves)
+  auto prologue = [&](int KT) {
     const int s1 = min(1, KT - 1);
 #pragma unroll
     for (int i = 0; i < NI; ++i) JN_DMA_W(i, 0, 0);
@@ -750,22 +782,23 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, int32_t tm, int32_t
 #pragma unroll
     for (int i = 0; i < NI; ++i) JN_DMA_W(i, s1, 1);
     wait_vmcnt<2 * NI>();
-  }
-  __builtin_amdgcn_s_barrier();
-  bf16x8 fa[TN + TM], fb[TN + TM];  // first-half / second-half fragments: weights, then tokens
+    __builtin_amdgcn_s_barrier();
+    slot2 = slot3 = 0;
+  };
+  auto first_frags = [&]() {
 #pragma unroll
-  for (int i = 0; i < TN; ++i) fa[i] = frag_w(ring2, i, 0);
+    for (int i = 0; i < TN; ++i) fa[i] = frag_w(ring2 + slot2 * SLOT, i, 0);
 #pragma unroll
-  for (int j = 0; j < TM; ++j) fa[TN + j] = frag_x(ring3, j, 0);
-  wait_lgkmcnt<0>();
-
-  int slot3 = 0;  // kt % 3
-  for (int kt = 0; kt < KT; ++kt) {
-    const int slot2 = kt & 1;
-    const int next3 = slot3 == 2 ? 0 : slot3 + 1;   // (kt + 1) % 3
-    const int prev3 = slot3 == 0 ? 2 : slot3 - 1;   // (kt + 2) % 3
-    const int sf = min(kt + 2, KT - 1);             // slab fetched this iteration
-    // ---- phase 0: first k-half MFMAs; second-half fragments; token DMA of slab kt+2
+    for (int j = 0; j < TM; ++j) fa[TN + j] = frag_x(ring3 + slot3 * SLOT, j, 0);
+    wait_lgkmcnt<0>();
+  };
+  // One slab; sf: slab fetched; stored: the last STORES memory operations
+  // before this slab's were stores.
+  auto slab = [&](auto first, int sf, bool stored) __attribute__((always_inline)) {
+    constexpr bool FIRST = decltype(first)::value;
+    const int next3 = slot3 == 2 ? 0 : slot3 + 1;
+    const int prev3 = slot3 == 0 ? 2 : slot3 - 1;
+    // ---- phase 0: first k-half MFMAs; second-half fragments; token DMA of the slab after next
     {
       const uint16_t* cw = ring2 + slot2 * SLOT;
       const uint16_t* cx = ring3 + slot3 * SLOT;
@@ -773,7 +806,8 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, int32_t tm, int32_t
 #pragma unroll
       for (int q = 0; q < TN * TM; ++q) {
         const int i = q / TM, j = q % TM;
-        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fa[TN + j], acc[i][j], 0, 0, 0);
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[i], fa[TN + j],
+                                                            FIRST ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[i][j], 0, 0, 0);
         if ((q & 3) == 0) {
           const int f = q >> 2;
           if (f < TN)
@@ -785,13 +819,16 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, int32_t tm, int32_t
         __builtin_amdgcn_sched_barrier(0);
       }
     }
-    // slab kt+1 landed (the token DMA of slab kt+2, issued last, may stay in flight)
+    // the next slab landed (the token DMA just issued may stay in flight)
     wait_lgkmcnt<0>();
-    wait_vmcnt<NI>();
+    if (FIRST && epi_bf16(EPI) && stored)
+      wait_vmcnt<NI + STORES>();
+    else
+      wait_vmcnt<NI>();
     __builtin_amdgcn_sched_barrier(0);
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
-    // ---- phase 1: second k-half MFMAs; slab kt+1's first-half fragments; weight DMA of slab kt+2
+    // ---- phase 1: second k-half MFMAs; the next slab's first-half fragments; weight DMA of the slab after next
     {
       const uint16_t* nw = ring2 + (slot2 ^ 1) * SLOT;
       const uint16_t* nx = ring3 + next3 * SLOT;
@@ -811,66 +848,111 @@ __device__ __forceinline__ void ring_tile(const GemmArgs& g, int32_t tm, int32_t
       }
     }
     wait_lgkmcnt<0>();
+    slot2 ^= 1;
     slot3 = next3;
+  };
+
+  source(g, tm, tn);
+  int KT = (g.K + kBK - 1) / kBK;
+  prologue(KT);
+  bool stored = false;
+  for (int r = 1;; ++r) {
+    // the last two slabs fetch the next tile's first two, where both tiles
+    // have three slabs; else (and behind the last tile) they repeat a slab
+    GemmArgs gn;
+    int32_t tmn, tnn;
+    const bool more = next(r, gn, tmn, tnn);
+    const int KTn = (gn.K + kBK - 1) / kBK;
+    const bool joined = more && KT >= 3 && KTn >= 3;
+    first_frags();  // (read again behind an epilogue, which needs the registers)
+    slab(std::true_type{}, min(2, KT - 1), stored);
+    for (int kt = 1; kt < KT - 2; ++kt) slab(std::false_type{}, kt + 2, false);
+    if (joined) source(gn, tmn, tnn);
+    for (int kt = max(1, KT - 2); kt < KT; ++kt) slab(std::false_type{}, joined ? kt + 2 - KT : KT - 1, false);
+    // Pin the accumulators to the accumulation registers where the loop ends.
+    // Left to itself, the register allocator placed some accumulators of the
+    // epilogues that can store straight from either register file (fp32 store,
+    // fp32 pre-activation save) in vector registers and copied them into
+    // accumulation registers before every MFMA of the loop (with spills to
+    // scratch in the grouped variants).
+#pragma unroll
+    for (int i = 0; i < TN; ++i)
+#pragma unroll
+      for (int j = 0; j < TM; ++j) asm volatile("" : "+a"(acc[i][j]));
+    // the free token slot; a wave uses the part that only its own DMAs fill
+    const bool whole =
+        gemm_epilogue<EPI, TN, TM>(g, acc, ring3 + (slot3 == 0 ? 2 : slot3 - 1) * SLOT + dro, tm * BM + wm * WM,
+                                   (tn * BN + wn * WN) / (GLU ? 2 : 1), lane);
+    if (!more) break;
+    stored = joined && whole;
+    g = gn;
+    tm = tmn;
+    tn = tnn;
+    KT = KTn;
+    if (!joined) {
+      wait_vmcnt<0>();  // the repeated slabs' DMAs land before their slots are filled
+      __builtin_amdgcn_s_barrier();
+      source(g, tm, tn);
+      prologue(KT);
+    }
   }
 #undef JN_DMA_W
 #undef JN_DMA_X
-  wait_vmcnt<0>();  // the repeated slabs' DMAs land before the LDS is reused or released
-  // Pin the accumulators to the accumulation registers where the loop ends.
-  // Left to itself, the register allocator placed some accumulators of the
-  // epilogues that can store straight from either register file (fp32 store,
-  // fp32 pre-activation save) in vector registers and copied them into
-  // accumulation registers before every MFMA of the loop (with spills to
-  // scratch in the grouped variants).
-#pragma unroll
-  for (int i = 0; i < TN; ++i)
-#pragma unroll
-    for (int j = 0; j < TM; ++j) asm volatile("" : "+a"(acc[i][j]));
+  wait_vmcnt<0>();  // ... or before the LDS is released
+}
 
-  if constexpr (EPI == EPI_BF16 || EPI == EPI_GELU_BF16) {
-    __builtin_amdgcn_s_barrier();
-    ring_epilogue_bf16<EPI, TM, 4>(g, acc, lds, tm, tn, wn, wm, wave, lane);
-  } else {
-    gemm_epilogue<BN, BM, WGN, WGM, EPI>(g, acc, tm, tn, wn, wm, lane);
-  }
+// Position of a workgroup's r-th tile: groups of 256 workgroups, `chain` tiles
+// each, walk chain x 256 consecutive tiles in rounds of 256.
+__device__ __forceinline__ int64_t chain_tile(int32_t b, int32_t chain, int32_t r) {
+  return (int64_t)(b >> 8) * 256 * chain + 256 * r + (b & 255);
 }
 
 // One launch of ring tiles over g.
 template <int EPI>
-__global__ __launch_bounds__(256, 1) void gemm_ring_kernel(GemmArgs g) {
+__global__ __launch_bounds__(256, 1) void gemm_ring_kernel(GemmArgs g, int32_t chain) {
   __shared__ __attribute__((aligned(1024))) uint16_t lds[5 * 256 * kBK];
-  int32_t tm, tn;
-  tile_of(blockIdx.x, g.tiles_m, g.tiles_n, tm, tn);
-  ring_tile<EPI, 0>(g, tm, tn, lds);
+  auto next = [&](int32_t r, GemmArgs& q, int32_t& tm, int32_t& tn) __attribute__((always_inline)) {
+    const int64_t t = chain_tile(blockIdx.x, chain, r);
+    q = g;
+    tile_of((int32_t)t, g.tiles_m, g.tiles_n, tm, tn);
+    return r < chain && t < (int64_t)g.tiles_m * g.tiles_n;
+  };
+  ring_run<EPI, 0>(next, lds);
 }
 
 // The same over S K ranges, fp32 partials, in gemm_flex_kernel's walk.
 __global__ __launch_bounds__(256, 1) void gemm_ring_split_kernel(GemmArgs g, int32_t S) {
   __shared__ __attribute__((aligned(1024))) uint16_t lds[5 * 256 * kBK];
-  const int32_t tiles = g.tiles_m * g.tiles_n, idx = xcd_item(blockIdx.x, gridDim.x);
-  if (idx >= tiles * S) return;
-  const int32_t s = idx / tiles;
-  const int64_t KT = g.K / kBK, k0 = KT * s / S, k1 = KT * (s + 1) / S;
-  g.X += k0 * kBK;
-  g.W += k0 * kBK;
-  g.K = (int32_t)(k1 - k0) * kBK;
-  g.C = reinterpret_cast<float*>(g.C) + (int64_t)s * g.split_c;
-  int32_t tm, tn;
-  flex_walk(idx - s * tiles, g.tiles_m, g.tiles_n, tm, tn);
-  ring_tile<EPI_F32, 0>(g, tm, tn, lds);
+  auto next = [&](int32_t r, GemmArgs& q, int32_t& tm, int32_t& tn) __attribute__((always_inline)) {
+    const int32_t tiles = g.tiles_m * g.tiles_n, idx = xcd_item(blockIdx.x, gridDim.x);
+    const int32_t s = idx / tiles;
+    const int64_t KT = g.K / kBK, k0 = KT * s / S, k1 = KT * (s + 1) / S;
+    q = g;
+    q.X += k0 * kBK;
+    q.W += k0 * kBK;
+    q.K = (int32_t)(k1 - k0) * kBK;
+    q.C = reinterpret_cast<float*>(g.C) + (int64_t)s * g.split_c;
+    flex_walk(idx - s * tiles, g.tiles_m, g.tiles_n, tm, tn);
+    return r == 0 && idx < tiles * S;
+  };
+  ring_run<EPI_F32, 0>(next, lds);
 }
 
 // Grouped ring tiles: problem p owns tiles [tile_start, tile_start + tiles).
 template <int EPI, int TR>
-__global__ __launch_bounds__(256, 1) void gemm_grouped_ring_kernel(const GemmArgs* __restrict__ probs, int32_t nprob) {
+__global__ __launch_bounds__(256, 1) void gemm_grouped_ring_kernel(const GemmArgs* __restrict__ probs, int32_t nprob,
+                                                                   int32_t total, int32_t chain) {
   __shared__ __attribute__((aligned(1024))) uint16_t lds[5 * 256 * kBK];
-  const int32_t b = blockIdx.x;
   int32_t p = 0;
-  while (p + 1 < nprob && probs[p + 1].tile_start <= b) ++p;
-  const GemmArgs g = probs[p];
-  int32_t tm, tn;
-  tile_of(b - g.tile_start, g.tiles_m, g.tiles_n, tm, tn);
-  ring_tile<EPI, TR>(g, tm, tn, lds);
+  auto next = [&](int32_t r, GemmArgs& q, int32_t& tm, int32_t& tn) __attribute__((always_inline)) {
+    const int64_t t = chain_tile(blockIdx.x, chain, r);
+    if (r >= chain || t >= total) return false;
+    while (p + 1 < nprob && probs[p + 1].tile_start <= t) ++p;
+    q = probs[p];
+    tile_of((int32_t)t - q.tile_start, q.tiles_m, q.tiles_n, tm, tn);
+    return true;
+  };
+  ring_run<EPI, TR>(next, lds);
 }
 
 // Tile shapes: the 256x256 ring loop, then shapes of the flexible loop.  occ:
@@ -897,22 +979,34 @@ constexpr int k128Shape = 6;    // and of unsplit residual adds and grouped weig
 constexpr int kWideShape = 7;
 static bool wide_rows(const GemmArgs& g) { return 512 * std::max(g.ldx, g.ldw) > (int64_t)0x7fffffff; }
 
+// Tiles per workgroup of a ring launch, and its workgroups.  Eight: 1, 4, 8 and
+// 64 tiles in a row take 289, 277, 275 and 273 us on 65,536 x 3,072, K = 768,
+// and workgroups that are replaced every few tiles keep sharing the chip with
+// other streams' launches.
+constexpr int32_t kRingChain = 8;
+static int32_t ring_chain(int32_t tiles) { return std::min(kRingChain, (tiles + 255) / 256); }
+static unsigned ring_groups(int32_t tiles, int32_t chain) {
+  const int64_t whole = tiles / (256 * (int64_t)chain), rest = tiles - whole * 256 * chain;
+  return (unsigned)(whole * 256 + std::min<int64_t>(rest, 256));
+}
+
 // The 256x256 ring loop over all tiles of g (and S K ranges).
 static hipError_t launch_ring(hipStream_t s, int epi, GemmArgs g, int32_t S) {
   const int32_t NL = epi == EPI_GEGLU_BF16 ? 2 * g.N : g.N;
   g.tiles_m = (g.M + 255) / 256;
   g.tiles_n = (NL + 255) / 256;
-  const dim3 grid(g.tiles_m * g.tiles_n), block(256);
+  const int32_t tiles = g.tiles_m * g.tiles_n, chain = ring_chain(tiles);
+  const dim3 grid(ring_groups(tiles, chain)), block(256);
   if (S > 1) {
     if (epi != EPI_F32) return hipErrorInvalidValue;
-    gemm_ring_split_kernel<<<dim3((grid.x * S + 7) / 8 * 8), block, 0, s>>>(g, S);
+    gemm_ring_split_kernel<<<dim3((tiles * S + 7) / 8 * 8), block, 0, s>>>(g, S);
     return hipGetLastError();
   }
   switch (epi) {
-    case EPI_BF16: gemm_ring_kernel<EPI_BF16><<<grid, block, 0, s>>>(g); break;
-    case EPI_GELU_BF16: gemm_ring_kernel<EPI_GELU_BF16><<<grid, block, 0, s>>>(g); break;
-    case EPI_RESID_F32: gemm_ring_kernel<EPI_RESID_F32><<<grid, block, 0, s>>>(g); break;
-    case EPI_GEGLU_BF16: gemm_ring_kernel<EPI_GEGLU_BF16><<<grid, block, 0, s>>>(g); break;
+    case EPI_BF16: gemm_ring_kernel<EPI_BF16><<<grid, block, 0, s>>>(g, chain); break;
+    case EPI_GELU_BF16: gemm_ring_kernel<EPI_GELU_BF16><<<grid, block, 0, s>>>(g, chain); break;
+    case EPI_RESID_F32: gemm_ring_kernel<EPI_RESID_F32><<<grid, block, 0, s>>>(g, chain); break;
+    case EPI_GEGLU_BF16: gemm_ring_kernel<EPI_GEGLU_BF16><<<grid, block, 0, s>>>(g, chain); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -972,9 +1066,10 @@ static hipError_t launch_rows(hipStream_t s, int epi, const GemmArgs& g, int t, 
 
 static hipError_t launch_grouped_ring(hipStream_t s, int epi, const GemmArgs* dprobs, int32_t nprob,
                                       int32_t total_tiles, int trans) {
-  dim3 grid(total_tiles), block(256);
+  const int32_t chain = ring_chain(total_tiles);
+  dim3 grid(ring_groups(total_tiles, chain)), block(256);
 #define JN_GEMM_CASE(E, T) \
-  case E * 4 + T: gemm_grouped_ring_kernel<E, T><<<grid, block, 0, s>>>(dprobs, nprob); break;
+  case E * 4 + T: gemm_grouped_ring_kernel<E, T><<<grid, block, 0, s>>>(dprobs, nprob, total_tiles, chain); break;
   switch (epi * 4 + trans) {
     JN_GEMM_CASE(EPI_BF16, 0)
     JN_GEMM_CASE(EPI_RESID_F32, 0)

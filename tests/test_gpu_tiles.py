@@ -51,6 +51,25 @@ def test_sample_alone_equals_sample_in_a_batch_bitwise():
         at += n
 
 
+@pytest.mark.parametrize("d", [128, 384])
+def test_workgroups_with_several_tiles_bitwise(d):
+    """Launches whose workgroups take several 256x256 tiles in turn (19,903
+    rows, 1,920 columns: 632 tiles), joined (384 columns are six K slabs) and
+    not (128 are two): samples at both ends and the middle equal themselves
+    alone, where no tile follows another."""
+    lens = (313,) * 31 + (300,) * 34
+    wl = W.make_workload(W.WorkloadSpec(
+        96, W.BackboneSpec(1, d, d // 128, 1920, False),
+        tuple(W.TenantSpec(1, n, 0, 0, n, (d, 64, 6), 3, 2) for n in lens), 0, "many tiles"))
+    full, at = hidden(wl, range(len(lens))).hidden, 0
+    assert full.shape[0] == sum(lens)
+    for g, n in enumerate(lens):
+        if g in (0, 1, 30, 31, 47, 63, 64):
+            print(f"sample {g}", flush=True)
+            assert torch.equal(hidden(wl, [g]).hidden, full[at: at + n]), g
+        at += n
+
+
 @pytest.mark.parametrize("hidden_dims,rows", [
     ((33, 1), (1,)), ((31, 65), (2, 33)), ((300, 257), (32, 1, 31)), ((64, 1030), (65, 7)), ((515,), (40, 24))])
 def test_head_tiles_at_edges(hidden_dims, rows):
