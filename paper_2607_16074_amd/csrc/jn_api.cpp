@@ -175,11 +175,11 @@ jn_status stage_copy(jn_ctx* c, void* dst, const void* src, size_t bytes) {
     s.host = nullptr;
     s.cap = 0;
     size_t cap = align_up(std::max<size_t>(bytes, 1 << 16), 1 << 16);
-    JN_HIP(c, hipHostMalloc(&s.host, cap, hipHostMallocDefault), "hipHostMalloc(staging)");
+    JN_HIP(c, hipHostMalloc(&s.host, cap, hipHostMallocCoherent), "hipHostMalloc(staging)");
     s.cap = cap;
   }
   std::memcpy(s.host, src, bytes);
-  JN_HIP(c, hipMemcpyAsync(dst, s.host, bytes, hipMemcpyHostToDevice, c->stream), "hipMemcpyAsync(H2D)");
+  JN_HIP(c, launch_upload(c->stream, dst, s.host, bytes), "table upload");
   JN_HIP(c, hipEventRecord(s.ev, c->stream), "hipEventRecord(staging)");
   s.pending = true;
   return JN_OK;
@@ -197,7 +197,7 @@ jn_status stage_copy_fixed(jn_ctx* c, void* dst, const void* src, size_t bytes) 
     c->fixed_pending = false;
   }
   std::memcpy(c->fixed_host, src, bytes);
-  JN_HIP(c, hipMemcpyAsync(dst, c->fixed_host, bytes, hipMemcpyHostToDevice, c->stream), "hipMemcpyAsync(H2D)");
+  JN_HIP(c, launch_upload(c->stream, dst, c->fixed_host, bytes), "table upload");
   JN_HIP(c, hipEventRecord(c->fixed_ev, c->stream), "hipEventRecord(fixed staging)");
   c->fixed_pending = true;
   return JN_OK;
@@ -225,9 +225,9 @@ MapLayout map_layout(int64_t N, int64_t T, int64_t G, int64_t R) {
   m.toff = take(4 * (G + 1));
   m.tperm = take(4 * N);
   m.trank = take(4 * N);
+  m.reqtab = take(sizeof(ReqEntry) * R);  // the host's tables are one piece: one upload
   m.tsamp = take(4 * T);
   m.tpos = take(4 * T);
-  m.reqtab = take(sizeof(ReqEntry) * R);
   m.total = o;
   return m;
 }
@@ -339,7 +339,7 @@ void fill_packed(jn_packed* out, char* base, const MapLayout& m, const Plan& p, 
 }
 
 // Host image of the maps region [0, m.tsamp) (the N/G-sized arrays).
-std::vector<char> host_head_image(const MapLayout& m, const Plan& p) {
+std::vector<char> host_head_image(const MapLayout& m, const Plan& p, const jn_request* req) {
   std::vector<char> img(m.tsamp, 0);
   auto put = [&](size_t off, const std::vector<int32_t>& v) {
     if (!v.empty()) std::memcpy(img.data() + off, v.data(), 4 * v.size());
@@ -352,6 +352,9 @@ std::vector<char> host_head_image(const MapLayout& m, const Plan& p) {
   put(m.toff, p.toff);
   put(m.tperm, p.tperm);
   put(m.trank, p.trank);
+  ReqEntry* rt = reinterpret_cast<ReqEntry*>(img.data() + m.reqtab);
+  for (size_t r = 0; r < p.req_first.size(); ++r)
+    rt[r] = ReqEntry{req[r].embeds, nullptr, req[r].max_len, req[r].n_samples, p.req_first[r], 0};
   return img;
 }
 
@@ -408,7 +411,7 @@ jn_status jn_ctx_create(jn_ctx** out, void* hip_stream) {
     }
   }
   if (hipEventCreateWithFlags(&c->fixed_ev, hipEventDisableTiming) != hipSuccess ||
-      hipHostMalloc(&c->fixed_host, kFixedStageBytes, hipHostMallocDefault) != hipSuccess) {
+      hipHostMalloc(&c->fixed_host, kFixedStageBytes, hipHostMallocCoherent) != hipSuccess) {
     c->fixed_host = nullptr;
     jn_ctx_destroy(c);
     return JN_EHIP;
@@ -500,7 +503,7 @@ jn_status jn_pack_maps_host(const jn_request* req, int32_t R, const jn_tenant* t
   if (st != JN_OK) return st;
   MapLayout m = map_layout(p.N, p.T, G, R);
   if (map_bytes < m.total) return JN_ENOSPACE;
-  std::vector<char> img = host_head_image(m, p);
+  const std::vector<char> img = host_head_image(m, p, req);
   char* base = (char*)host_maps;
   std::memset(base, 0, m.total);
   std::memcpy(base, img.data(), img.size());
@@ -513,8 +516,6 @@ jn_status jn_pack_maps_host(const jn_request* req, int32_t R, const jn_tenant* t
       tp[t] = j < p.seqlens[i] ? j : -1;
     }
   }
-  ReqEntry* rt = (ReqEntry*)(base + m.reqtab);
-  for (int32_t r = 0; r < R; ++r) rt[r] = ReqEntry{req[r].embeds, nullptr, req[r].max_len, req[r].n_samples, p.req_first[r], 0};
   fill_packed(out, base, m, p, R, G, o);
   out->req_sig = request_signature(req, R);
   return JN_OK;
@@ -537,13 +538,9 @@ jn_status jn_pack_group(jn_ctx* c, const jn_request* req, int32_t R, const jn_te
     if (((uintptr_t)req[r].embeds) % 16 != 0) return fail(c, JN_EUNSUPPORTED, "request %d embeds not 16-byte aligned", r);
   if (((uintptr_t)tokens) % 16 != 0) return fail(c, JN_EUNSUPPORTED, "token buffer not 16-byte aligned");
 
-  std::vector<char> img = host_head_image(m, p);
-  std::vector<ReqEntry> rt(R);
-  for (int32_t r = 0; r < R; ++r) rt[r] = ReqEntry{req[r].embeds, nullptr, req[r].max_len, req[r].n_samples, p.req_first[r], 0};
+  const std::vector<char> img = host_head_image(m, p, req);
   char* base = (char*)maps;
   st = stage_copy(c, base, img.data(), img.size());
-  if (st != JN_OK) return st;
-  st = stage_copy(c, base + m.reqtab, rt.data(), sizeof(ReqEntry) * R);
   if (st != JN_OK) return st;
   jn_packed tmp;
   fill_packed(&tmp, base, m, p, R, G, o);
@@ -2194,14 +2191,11 @@ jn_status jn_infer_plan_create(jn_ctx* c, const jn_request* req, int32_t R, cons
   pl->dt = (const HeadTile*)(hw + hl.tiles);
 
   // one-time uploads: maps, request table, head tables
-  std::vector<char> img = host_head_image(L.m, p);
-  std::vector<ReqEntry> rt(R);
-  for (int32_t r = 0; r < R; ++r) rt[r] = ReqEntry{req[r].embeds, nullptr, req[r].max_len, req[r].n_samples, p.req_first[r], 0};
+  const std::vector<char> img = host_head_image(L.m, p, req);
   std::vector<char> himg(hl.total - hl.descs, 0);
   std::memcpy(himg.data(), descs.data(), dbytes);
   std::memcpy(himg.data() + (hl.tiles - hl.descs), tiles.data(), tbytes);
   st = stage_copy(c, maps, img.data(), img.size());
-  if (st == JN_OK) st = stage_copy(c, maps + L.m.reqtab, rt.data(), sizeof(ReqEntry) * R);
   if (st == JN_OK) st = stage_copy(c, hw + hl.descs, himg.data(), hl.tiles - hl.descs + tbytes);
   if (st != JN_OK) {
     delete pl;

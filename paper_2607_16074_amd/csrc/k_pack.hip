@@ -8,6 +8,27 @@ namespace jnx {
 
 constexpr int kRowsPerBlock = 16;
 
+// A small host table to device memory by a kernel that reads the (coherent)
+// pinned staging buffer: a launch costs the host about 3 us less than an
+// asynchronous copy and the copy's own kernel, and the stream waits for no copy
+// in between (two tenants' smallest step 115.6 -> 106.9 us, 8 x 32 heads 231 ->
+// 217, one tenant's expert step 816 -> 792).  Above 64 KB the copy's bandwidth
+// counts.
+// System-scope loads: a staging buffer is rewritten by the host between calls.
+__global__ __launch_bounds__(256) void upload_kernel(uint32_t* __restrict__ dst, const uint32_t* src, int32_t words) {
+  const int32_t i = blockIdx.x * 256 + threadIdx.x;
+  if (i < words) dst[i] = __hip_atomic_load(src + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+hipError_t launch_upload(hipStream_t s, void* dst, const void* src, size_t bytes) {
+  if (bytes > kUploadBytes || bytes % 4 != 0 || (uintptr_t)dst % 4 != 0)
+    return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
+  const int32_t words = (int32_t)(bytes / 4);
+  upload_kernel<<<(words + 255) / 256, 256, 0, s>>>(static_cast<uint32_t*>(dst), static_cast<const uint32_t*>(src),
+                                                    words);
+  return hipGetLastError();
+}
+
 __global__ __launch_bounds__(256) void pack_kernel(const ReqEntry* __restrict__ req_table,
                                                    const int32_t* __restrict__ sample_request,
                                                    const int32_t* __restrict__ sample_local,
