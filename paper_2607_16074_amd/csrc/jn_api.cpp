@@ -1430,10 +1430,16 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
   // row buffers (dY [rows][out], X [rows][in]; prefix: the tenant's prefix
   // rows), read transposed by the GEMM -- or from zero-padded transposes
   // (TA_g [out][K_g], TB_g [in][K_g]) -- in the K ranges of wgrad_splits
-  auto wgrad_rows = [&](const uint16_t* dy, int64_t out, const uint16_t* xin, int64_t in,
-                        std::function<float*(int32_t)> Csel, bool prefix) {
+  struct WGrad {
+    const uint16_t *dy, *xin;
+    int64_t out, in;
+    bool prefix;
     std::vector<GemmArgs> vt, vm;  // transposed loads / materialised transposes
     std::vector<KSumDesc> sums;
+  };
+  auto wgrad_of = [&](const uint16_t* dy, int64_t out, const uint16_t* xin, int64_t in,
+                      std::function<float*(int32_t)> Csel, bool prefix) {
+    WGrad W{dy, xin, out, in, prefix, {}, {}, {}};
     int64_t planes = 0;  // partial planes handed out
     for (int32_t g = 0; g < G; ++g) {
       const int64_t K = prefix ? P.Pz[g] : P.rows[g];
@@ -1456,7 +1462,7 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
         a.ldw = in;
         a.K = (int32_t)(k1 - k0);
         a.trans = GEMM_TRANS_X | GEMM_TRANS_W;
-        vt.push_back(a);
+        W.vt.push_back(a);
         GemmArgs m = a;  // columns k0.. of the tenant's [out][Kp] / [in][Kp] transposed blocks
         m.trans = 0;
         m.X = B(Ly.TA) + out * kz0 + k0;
@@ -1464,26 +1470,33 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
         m.W = B(Ly.TB) + in * kz0 + k0;
         m.ldw = Kp;
         m.K = (int32_t)((r == S - 1 ? Kp : k1) - k0);
-        vm.push_back(m);
+        W.vm.push_back(m);
       }
       if (S > 1) {
-        sums.push_back(KSumDesc{part, Csel(g), out * in, S, 0});
+        W.sums.push_back(KSumDesc{part, Csel(g), out * in, S, 0});
         planes += S;
       }
     }
-    if (trans_ok(EPI_F32, vt)) {
-      gemm(EPI_F32, vt);
+    return W;
+  };
+  auto wgrad_run = [&](const WGrad& W) {
+    if (trans_ok(EPI_F32, W.vt)) {
+      gemm(EPI_F32, W.vt);
     } else {
-      trans_rows(dy, out, B(Ly.TA), prefix);
-      trans_rows(xin, in, B(Ly.TB), prefix);
-      gemm(EPI_F32, vm);
+      trans_rows(W.dy, W.out, B(Ly.TA), W.prefix);
+      trans_rows(W.xin, W.in, B(Ly.TB), W.prefix);
+      gemm(EPI_F32, W.vm);
     }
-    if (!sums.empty()) ksum(sums);
+    if (!W.sums.empty()) ksum(W.sums);
+  };
+  auto wgrad_rows = [&](const uint16_t* dy, int64_t out, const uint16_t* xin, int64_t in,
+                        std::function<float*(int32_t)> Csel, bool prefix) {
+    wgrad_run(wgrad_of(dy, out, xin, in, Csel, prefix));
   };
   // data gradient C[rows][in] = epi(dY[rows][out] W_g[out][in]) per tenant,
   // the weight read transposed by the GEMM -- or from a transposed copy
-  auto dgrad_rows = [&](int epi, const uint16_t* dy, int64_t out, std::function<const void*(int32_t)> wsel, int64_t in,
-                        void* C, bool cfp32, float* aux = nullptr) {
+  auto dgrad_of = [&](const uint16_t* dy, int64_t out, std::function<const void*(int32_t)> wsel, int64_t in, void* C,
+                      bool cfp32, float* aux) {
     std::vector<GemmArgs> v;
     for (int32_t g = 0; g < G; ++g) {
       GemmArgs a{};
@@ -1503,12 +1516,46 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
       a.trans = GEMM_TRANS_W;
       v.push_back(a);
     }
+    return v;
+  };
+  auto dgrad_rows = [&](int epi, const uint16_t* dy, int64_t out, std::function<const void*(int32_t)> wsel, int64_t in,
+                        void* C, bool cfp32, float* aux) {
+    const std::vector<GemmArgs> v = dgrad_of(dy, out, wsel, in, C, cfp32, aux);
     if (trans_ok(epi, v)) {
       gemm(epi, v);
       return;
     }
     trans_w(wsel, out, in);
     rows_gemm(epi, dy, out, [&](int32_t g) { return (const uint16_t*)WTg(g, out, in); }, in, C, in, cfp32, aux);
+  };
+  // Both gradients of the layer y = x W^T from dY [rows][out]: weight gradient
+  // over x = xin [rows][in] into Csel, data gradient into C; one launch where
+  // the tile shapes of both form a pair.  more: a weight gradient beside them.
+  auto layer_grads = [&](const uint16_t* dy, int64_t out, const uint16_t* xin, int64_t in,
+                         std::function<float*(int32_t)> Csel, int epi, std::function<const void*(int32_t)> wsel, void* C,
+                         bool cfp32, float* aux = nullptr, const WGrad* more = nullptr) {
+    WGrad W = wgrad_of(dy, out, xin, in, Csel, false);
+    std::vector<GemmArgs> dv = dgrad_of(dy, out, wsel, in, C, cfp32, aux), wv = W.vt;
+    // contractions over prefix rows are the longest: first
+    if (more) wv.insert(wv.begin(), more->vt.begin(), more->vt.end());
+    if (trans_ok(epi, dv) && trans_ok(EPI_F32, wv) && (!more || W.sums.empty() || more->sums.empty())) {
+      const int32_t nd = (int32_t)dv.size(), nw = (int32_t)wv.size();
+      const int ds = gemm_grouped_tile_shape(epi, dv.data(), nd), wsh = gemm_grouped_tile_shape(EPI_F32, wv.data(), nw);
+      const int32_t td = gemm_grouped_prepare(dv.data(), nd, ds), tw = gemm_grouped_prepare(wv.data(), nw, wsh);
+      if (td > 0 && tw > 0 && gemm_grad_pair_ok(epi, ds, wsh, tw)) {
+        const size_t dat = rec.add(dv.data(), sizeof(GemmArgs) * nd), wat = rec.add(wv.data(), sizeof(GemmArgs) * nw);
+        rec.ops.push_back([=](char* a) {
+          return launch_gemm_grad_pair(s, epi, (const GemmArgs*)(a + dat), nd, td, (const GemmArgs*)(a + wat), nw, tw);
+        });
+        rec.opcode.push_back(JN_OP_EXPERT_GEMM);
+        if (!W.sums.empty()) ksum(W.sums);
+        if (more && !more->sums.empty()) ksum(more->sums);
+        return;
+      }
+    }
+    wgrad_run(W);
+    dgrad_rows(epi, dy, out, wsel, in, C, cfp32, aux);
+    if (more) wgrad_run(*more);
   };
   auto Wl = [&](int l, const void* jn_expert_layer::*m) {
     return [=](int32_t g) { return (const uint16_t*)(ex[g].layers[l].*m); };
@@ -1661,15 +1708,14 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
     const size_t g2 = ptr_table([&](int32_t g) { return ex[g].layers[l].g2; });
     const size_t g3 = ptr_table([&](int32_t g) { return ex[g].layers[l].g3; });
     // MLP block: x += m W_down^T, m = gelu(h3 W_up^T)
-    wgrad_rows(B(Ly.dxb), d, B(Ly.mb[l]), f, Gl(l, &jn_expert_layer_grads::w_down), false);
-    dgrad_rows(EPI_GELUGRAD_BF16, B(Ly.dxb), d, [&](int32_t g) { return ex[g].layers[l].w_down; }, f, B(Ly.tb), false,
-               F(Ly.pre[l]));
-    wgrad_rows(B(Ly.tb), f, B(Ly.h3[l]), d, Gl(l, &jn_expert_layer_grads::w_up), false);
-    dgrad_rows(EPI_F32, B(Ly.tb), f, [&](int32_t g) { return ex[g].layers[l].w_up; }, d, F(Ly.tf), true);
+    layer_grads(B(Ly.dxb), d, B(Ly.mb[l]), f, Gl(l, &jn_expert_layer_grads::w_down), EPI_GELUGRAD_BF16,
+                [&](int32_t g) { return ex[g].layers[l].w_down; }, B(Ly.tb), false, F(Ly.pre[l]));
+    layer_grads(B(Ly.tb), f, B(Ly.h3[l]), d, Gl(l, &jn_expert_layer_grads::w_up), EPI_F32,
+                [&](int32_t g) { return ex[g].layers[l].w_up; }, F(Ly.tf), true);
     rms_bwd(Ly.x3[l], g3, ptr_table([&](int32_t g) { return (const void*)io[g].layers[l].g3; }), false);
     // cross-attention block
-    wgrad_rows(B(Ly.dxb), d, B(Ly.ocb[l]), d, Gl(l, &jn_expert_layer_grads::wo_c), false);
-    dgrad_rows(EPI_F32, B(Ly.dxb), d, [&](int32_t g) { return ex[g].layers[l].wo_c; }, d, F(Ly.tf), true);
+    layer_grads(B(Ly.dxb), d, B(Ly.ocb[l]), d, Gl(l, &jn_expert_layer_grads::wo_c), EPI_F32,
+                [&](int32_t g) { return ex[g].layers[l].wo_c; }, F(Ly.tf), true);
     {
       AttnArgs A{};
       A.Q = B(Ly.qc[l]);
@@ -1699,13 +1745,13 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
       A.scale = scale;
       attn(A, true);
     }
-    wgrad_rows(B(Ly.tb), d, B(Ly.h2[l]), d, Gl(l, &jn_expert_layer_grads::wq_c), false);
-    dgrad_rows(EPI_F32, B(Ly.tb), d, [&](int32_t g) { return ex[g].layers[l].wq_c; }, d, F(Ly.tf), true);
-    wgrad_rows(B(Ly.dkvb), 2 * d, B(Ly.z), dp, Gl(l, &jn_expert_layer_grads::wkv_c), true);
+    const WGrad kvw = wgrad_of(B(Ly.dkvb), 2 * d, B(Ly.z), dp, Gl(l, &jn_expert_layer_grads::wkv_c), true);
+    layer_grads(B(Ly.tb), d, B(Ly.h2[l]), d, Gl(l, &jn_expert_layer_grads::wq_c), EPI_F32,
+                [&](int32_t g) { return ex[g].layers[l].wq_c; }, F(Ly.tf), true, nullptr, &kvw);
     rms_bwd(Ly.x2[l], g2, ptr_table([&](int32_t g) { return (const void*)io[g].layers[l].g2; }), false);
     // self-attention block
-    wgrad_rows(B(Ly.dxb), d, B(Ly.osb[l]), d, Gl(l, &jn_expert_layer_grads::wo_s), false);
-    dgrad_rows(EPI_F32, B(Ly.dxb), d, [&](int32_t g) { return ex[g].layers[l].wo_s; }, d, F(Ly.tf), true);
+    layer_grads(B(Ly.dxb), d, B(Ly.osb[l]), d, Gl(l, &jn_expert_layer_grads::wo_s), EPI_F32,
+                [&](int32_t g) { return ex[g].layers[l].wo_s; }, F(Ly.tf), true);
     {
       AttnArgs A{};
       A.Q = B(Ly.qkv[l]);
@@ -1733,8 +1779,8 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
       A.scale = scale;
       attn(A, true);
     }
-    wgrad_rows(B(Ly.tb), 3 * d, B(Ly.h1[l]), d, Gl(l, &jn_expert_layer_grads::wqkv_s), false);
-    dgrad_rows(EPI_F32, B(Ly.tb), 3 * d, [&](int32_t g) { return ex[g].layers[l].wqkv_s; }, d, F(Ly.tf), true);
+    layer_grads(B(Ly.tb), 3 * d, B(Ly.h1[l]), d, Gl(l, &jn_expert_layer_grads::wqkv_s), EPI_F32,
+                [&](int32_t g) { return ex[g].layers[l].wqkv_s; }, F(Ly.tf), true);
     rms_bwd(Ly.x1[l], g1, ptr_table([&](int32_t g) { return (const void*)io[g].layers[l].g1; }), false);
   }
   // input projection and the padded output-projection gradient

@@ -94,6 +94,13 @@ int32_t gemm_grouped_prepare(GemmArgs* probs, int32_t nprob, int shape);
 hipError_t launch_gemm_grouped(hipStream_t s, int epi, const GemmArgs* dprobs, int32_t nprob, int32_t total_tiles,
                                int shape, int trans = 0);
 
+// A data gradient (GEMM_TRANS_W) and a weight gradient (EPI_F32, both operands
+// transposed), prepared as above with the shapes that gemm_grad_pair_ok takes,
+// in one launch; neither reads what the other writes.
+bool gemm_grad_pair_ok(int epi, int dshape, int wshape, int32_t wtiles);
+hipError_t launch_gemm_grad_pair(hipStream_t s, int epi, const GemmArgs* dprobs, int32_t nd, int32_t td,
+                                 const GemmArgs* wprobs, int32_t nw, int32_t tw);
+
 // C[M][N] (+)= epi(A[M][K] * B[N][K]^T); A, B bf16 row-major with leading
 // dims lda, ldb (elements); for EPI_GEGLU_BF16, B is w_gate and B2 is w_up,
 // each [N][K], and C has N columns.

@@ -955,6 +955,40 @@ __global__ __launch_bounds__(256, 1) void gemm_grouped_ring_kernel(const GemmArg
   ring_run<EPI, TR>(next, lds);
 }
 
+// Data and weight gradients of one layer in one launch: both read dY, neither
+// the other's output.  Workgroups [0, gd) run the data gradient's 128x96 tiles
+// (contractions over the layer's width, the longer ones, so they start first),
+// the rest the weight gradient's 128x128 tiles (contractions over the tenant's
+// rows).  gd and the rest are multiples of 8, so both keep their XCD walk.
+// Alone, a single tenant's launches fill few CUs (400 rows, 1,024 wide: 40
+// data-gradient tiles of 10 to 26 us, 64 to 256 weight-gradient tiles of 9 to
+// 12 us); a pair takes about the longer of the two (24.7 -> 12, 37 -> 26 us,
+// with the key/value weight gradient 45 -> 26), one tenant's step 792 -> 696 us.
+template <int EPI>
+__global__ __launch_bounds__(256, 1) void gemm_grad_pair_kernel(const GemmArgs* __restrict__ dprobs, int32_t nd,
+                                                                int32_t td, int32_t gd,
+                                                                const GemmArgs* __restrict__ wprobs, int32_t nw,
+                                                                int32_t tw) {
+  constexpr int BN = 128, BM = 96, NS = 4, LDS = NS * (BN + BM) * kBK;
+  static_assert(LDS >= 5 * 128 * kBK, "stages of both loops");
+  __shared__ __attribute__((aligned(1024))) uint16_t lds[LDS];
+  const bool data = (int32_t)blockIdx.x < gd;
+  const GemmArgs* const probs = data ? dprobs : wprobs;
+  const int32_t n = data ? nd : nw;
+  const int32_t idx = data ? xcd_item(blockIdx.x, gd) : xcd_item(blockIdx.x - gd, gridDim.x - gd);
+  if (idx >= (data ? td : tw)) return;
+  int32_t p = 0;
+  while (p + 1 < n && probs[p + 1].tile_start <= idx) ++p;
+  const GemmArgs g = probs[p];
+  int32_t tm, tn;
+  flex_walk(idx - g.tile_start, g.tiles_m, g.tiles_n, tm, tn);
+  const int32_t KT = (g.K + kBK - 1) / kBK;
+  if (data)
+    flex_tile<BN, BM, NS, NS, EPI, GEMM_TRANS_W>(g, tm, tn, 0, KT, lds);
+  else
+    flex_tile<128, 128, 3, 2, EPI_F32, GEMM_TRANS_X | GEMM_TRANS_W>(g, tm, tn, 0, KT, lds);
+}
+
 // Tile shapes: the 256x256 ring loop, then shapes of the flexible loop.  occ:
 // workgroups per CU.  slab: microseconds per K=64 slab with all 256 CUs busy,
 // measured on the 2048-wide projections at 2,469 tokens (the chip is then
@@ -1385,6 +1419,30 @@ hipError_t launch_gemm_grouped(hipStream_t s, int epi, const GemmArgs* dprobs, i
     case kWideShape: return launch_grouped_flex<64, 96, 4, 4, 2, true>(s, epi, dprobs, nprob, total_tiles, trans);
     default: return hipErrorInvalidValue;
   }
+}
+
+// Which data and weight gradients run as a pair: those whose estimates pick the
+// tile shapes of few rows.  Two 128x128 tiles share a CU in their own launch
+// but not in a pair, so up to two rounds of them.  Many tenants' gradients fill
+// the chip by themselves: 256x128 and ring tiles as a pair were slower (16
+// tenants' MLP layer 362 -> 436 us, query and key/value 612 -> 701).
+bool gemm_grad_pair_ok(int epi, int dshape, int wshape, int32_t wtiles) {
+  return (epi == EPI_F32 || epi == EPI_GELUGRAD_BF16) && dshape == 4 && wshape == k128Shape && wtiles <= 512;
+}
+
+hipError_t launch_gemm_grad_pair(hipStream_t s, int epi, const GemmArgs* dprobs, int32_t nd, int32_t td,
+                                 const GemmArgs* wprobs, int32_t nw, int32_t tw) {
+  if (nd <= 0 || nw <= 0 || td <= 0 || tw <= 0) return hipErrorInvalidValue;
+  const int32_t gd = (td + 7) / 8 * 8, gw = (tw + 7) / 8 * 8;
+  const dim3 grid(gd + gw), block(256);
+  switch (epi) {
+    case EPI_F32: gemm_grad_pair_kernel<EPI_F32><<<grid, block, 0, s>>>(dprobs, nd, td, gd, wprobs, nw, tw); break;
+    case EPI_GELUGRAD_BF16:
+      gemm_grad_pair_kernel<EPI_GELUGRAD_BF16><<<grid, block, 0, s>>>(dprobs, nd, td, gd, wprobs, nw, tw);
+      break;
+    default: return hipErrorInvalidValue;
+  }
+  return hipGetLastError();
 }
 
 }  // namespace jnx
