@@ -1178,7 +1178,7 @@ ExpLayout exp_layout(const ExpPlan& P) {
   Ly.tf = take(4 * Na * d);
   Ly.tb = take(2 * Na * wmax);
   Ly.dkvb = take(2 * Pz * 2 * d);
-  Ly.part = take(4 * (int64_t)P.soff[P.G] * d);
+  Ly.part = take(4 * (3 * (int64_t)s.L + 1) * P.soff[P.G] * d);  // of every norm
   Ly.lpart = take(4 * (int64_t)kXLossParts * G);
   Ly.TA = take(2 * std::max<int64_t>(wmax * P.KaT, 2 * d * P.KzT));
   Ly.TB = take(2 * std::max<int64_t>(std::max<int64_t>(wmax, KI) * P.KaT, (int64_t)s.dp * P.KzT));
@@ -1355,12 +1355,15 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
     });
     rec.opcode.push_back(JN_OP_EXPERT_OTHER);
   };
-  auto rms_bwd = [&](size_t x_at, size_t gains_at, size_t dg_at, bool first) {
-    const int32_t segs = P.soff[G];
+  const int32_t segs = P.soff[G];
+  std::vector<const void*> gain_out;  // [norm][tenant], in the order of the backward pass
+  auto rms_bwd = [&](size_t x_at, size_t gains_at, std::function<const void*(int32_t)> dg, bool first) {
+    float* const part = F(Ly.part) + (int64_t)(gain_out.size() / G) * segs * d;
+    for (int32_t g = 0; g < G; ++g) gain_out.push_back(dg(g));
     rec.ops.push_back([=](char* a) {
       return launch_xrms_bwd(s, F(x_at), (const void* const*)(a + gains_at), (const int32_t*)(a + roff_at),
                              (const int32_t*)(a + soff_at), G, segs, (int32_t)d, S.eps, F(Ly.tf), first, F(Ly.dx),
-                             B(Ly.dxb), F(Ly.part), (float* const*)(a + dg_at));
+                             B(Ly.dxb), part);
     });
     rec.opcode.push_back(JN_OP_EXPERT_OTHER);
   };
@@ -1702,7 +1705,7 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
   wgrad_rows(B(Ly.dpredb), kAP, B(Ly.yb), d, [&](int32_t g) { return F(Ly.dwoutp) + (int64_t)g * kAP * d; }, false);
   rows_gemm(EPI_F32, B(Ly.dpredb), kAP, [&](int32_t g) { return B(Ly.woutpT) + (int64_t)g * d * kAP; }, d, F(Ly.tf),
             d, true);
-  rms_bwd(Ly.xf, gfa, ptr_table([&](int32_t g) { return (const void*)io[g].dgf; }), true);
+  rms_bwd(Ly.xf, gfa, [&](int32_t g) { return (const void*)io[g].dgf; }, true);
   for (int l = S.L - 1; l >= 0; --l) {
     const size_t g1 = ptr_table([&](int32_t g) { return ex[g].layers[l].g1; });
     const size_t g2 = ptr_table([&](int32_t g) { return ex[g].layers[l].g2; });
@@ -1712,7 +1715,7 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
                 [&](int32_t g) { return ex[g].layers[l].w_down; }, B(Ly.tb), false, F(Ly.pre[l]));
     layer_grads(B(Ly.tb), f, B(Ly.h3[l]), d, Gl(l, &jn_expert_layer_grads::w_up), EPI_F32,
                 [&](int32_t g) { return ex[g].layers[l].w_up; }, F(Ly.tf), true);
-    rms_bwd(Ly.x3[l], g3, ptr_table([&](int32_t g) { return (const void*)io[g].layers[l].g3; }), false);
+    rms_bwd(Ly.x3[l], g3, [&](int32_t g) { return (const void*)io[g].layers[l].g3; }, false);
     // cross-attention block
     layer_grads(B(Ly.dxb), d, B(Ly.ocb[l]), d, Gl(l, &jn_expert_layer_grads::wo_c), EPI_F32,
                 [&](int32_t g) { return ex[g].layers[l].wo_c; }, F(Ly.tf), true);
@@ -1748,7 +1751,7 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
     const WGrad kvw = wgrad_of(B(Ly.dkvb), 2 * d, B(Ly.z), dp, Gl(l, &jn_expert_layer_grads::wkv_c), true);
     layer_grads(B(Ly.tb), d, B(Ly.h2[l]), d, Gl(l, &jn_expert_layer_grads::wq_c), EPI_F32,
                 [&](int32_t g) { return ex[g].layers[l].wq_c; }, F(Ly.tf), true, nullptr, &kvw);
-    rms_bwd(Ly.x2[l], g2, ptr_table([&](int32_t g) { return (const void*)io[g].layers[l].g2; }), false);
+    rms_bwd(Ly.x2[l], g2, [&](int32_t g) { return (const void*)io[g].layers[l].g2; }, false);
     // self-attention block
     layer_grads(B(Ly.dxb), d, B(Ly.osb[l]), d, Gl(l, &jn_expert_layer_grads::wo_s), EPI_F32,
                 [&](int32_t g) { return ex[g].layers[l].wo_s; }, F(Ly.tf), true);
@@ -1781,7 +1784,16 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
     }
     layer_grads(B(Ly.tb), 3 * d, B(Ly.h1[l]), d, Gl(l, &jn_expert_layer_grads::wqkv_s), EPI_F32,
                 [&](int32_t g) { return ex[g].layers[l].wqkv_s; }, F(Ly.tf), true);
-    rms_bwd(Ly.x1[l], g1, ptr_table([&](int32_t g) { return (const void*)io[g].layers[l].g1; }), false);
+    rms_bwd(Ly.x1[l], g1, [&](int32_t g) { return (const void*)io[g].layers[l].g1; }, false);
+  }
+  {
+    const size_t at = rec.add(gain_out.data(), sizeof(void*) * gain_out.size());
+    const int32_t norms = (int32_t)(gain_out.size() / G);
+    rec.ops.push_back([=](char* a) {
+      return launch_gain_sums(s, F(Ly.part), (const int32_t*)(a + soff_at), G, segs, (int32_t)d, norms,
+                              (float* const*)(a + at));
+    });
+    rec.opcode.push_back(JN_OP_EXPERT_OTHER);
   }
   // input projection and the padded output-projection gradient
   wgrad_rows(B(Ly.dxb), d, B(Ly.ub), KI, [&](int32_t g) { return F(Ly.dwinp) + (int64_t)g * d * KI; }, false);

@@ -225,13 +225,16 @@ hipError_t launch_prefix(hipStream_t s, const void* hidden, const int32_t* tenan
 hipError_t launch_xrms_fwd(hipStream_t s, const float* x, const void* const* gains, const int32_t* roff, int32_t G,
                            int32_t rows, int32_t d, float eps, void* h);
 // dx (+)= dRMS(x, g) . dh (set instead of added to where `first`), dxb = its
-// bf16 copy; dg[t] = column sums over tenant t's rows of dh x r.  Tenant t's
-// rows are cut into segments of kXrmsSeg, numbered from soff[t] (soff [G+1]
-// device, `segs` in all); part: scratch [segs][d].
+// bf16 copy; part [segs][d]: column sums of dh x r over each segment.  Tenant
+// t's rows are cut into segments of kXrmsSeg, numbered from soff[t] (soff [G+1]
+// device, `segs` in all).
 constexpr int kXrmsSeg = 8;
 hipError_t launch_xrms_bwd(hipStream_t s, const float* x, const void* const* gains, const int32_t* roff,
                            const int32_t* soff, int32_t G, int32_t segs, int32_t d, float eps, const float* dh,
-                           bool first, float* dx, uint16_t* dxb, float* part, float* const* dg);
+                           bool first, float* dx, uint16_t* dxb, float* part);
+// dg[n G + t] = sum over tenant t's segments of part [norms][segs][d].
+hipError_t launch_gain_sums(hipStream_t s, const float* part, const int32_t* soff, int32_t G, int32_t segs, int32_t d,
+                            int32_t norms, float* const* dg);
 
 // fp32 attention of each tenant-order sample k over its own keys: queries
 // rows [k*Lq, (k+1)*Lq) of Q; keys / values rows [kv0, kv0 + Lk) with

@@ -390,13 +390,17 @@ __global__ __launch_bounds__(256) void xrms_bwd_kernel(const float* __restrict__
     part[(int64_t)b * d + j] = (red[0][j] + red[1][j]) + (red[2][j] + red[3][j]);
 }
 
-// dg_t[j] = sum of tenant t's segment partials: block = (tenant, 64 columns),
-// wave w adds segments w, w + 4, .. in order, then the four sums in order.
+// dg_t[j] = sum of tenant t's segment partials, of every norm of the step in
+// one launch (z: norm n's partials at n * stride, its pointers at out + n G;
+// one launch per norm cost 4.5 us each): block = (tenant, 64 columns), wave w
+// adds segments w, w + 4, .. in order, then the four sums in order.
 __global__ __launch_bounds__(256) void colsum_final_kernel(const float* __restrict__ part, const int32_t* __restrict__ soff,
                                                            float* const* __restrict__ out, int32_t d) {
   __shared__ float red[4][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int32_t t = blockIdx.x, j = blockIdx.y * 64 + lane;
+  const int32_t t = blockIdx.x, j = blockIdx.y * 64 + lane, G = gridDim.x;
+  part += (int64_t)blockIdx.z * soff[G] * d;
+  out += (int64_t)blockIdx.z * G;
   float s = 0.f;
 #pragma unroll 8
   for (int32_t b = soff[t] + w; b < soff[t + 1]; b += 4) s += part[(int64_t)b * d + j];
@@ -422,7 +426,7 @@ hipError_t launch_xrms_fwd(hipStream_t s, const float* x, const void* const* gai
 
 hipError_t launch_xrms_bwd(hipStream_t s, const float* x, const void* const* gains, const int32_t* roff,
                            const int32_t* soff, int32_t G, int32_t segs, int32_t d, float eps, const float* dh,
-                           bool first, float* dx, uint16_t* dxb, float* part, float* const* dg) {
+                           bool first, float* dx, uint16_t* dxb, float* part) {
   auto gp = reinterpret_cast<const uint16_t* const*>(gains);
 #define JN_XRMS(NC) \
   case 256 * NC:    \
@@ -435,8 +439,18 @@ hipError_t launch_xrms_bwd(hipStream_t s, const float* x, const void* const* gai
     default: return hipErrorInvalidValue;
   }
 #undef JN_XRMS
-  colsum_final_kernel<<<dim3(G, d / 64), 256, 0, s>>>(part, soff, dg, d);
   return hipGetLastError();
+}
+
+hipError_t launch_gain_sums(hipStream_t s, const float* part, const int32_t* soff, int32_t G, int32_t segs, int32_t d,
+                            int32_t norms, float* const* dg) {
+  for (int32_t n = 0; n < norms; n += 65535) {  // (the grid's z limit)
+    colsum_final_kernel<<<dim3(G, d / 64, std::min(norms - n, 65535)), 256, 0, s>>>(part + (int64_t)n * segs * d, soff,
+                                                                                   dg + (int64_t)n * G, d);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 // -------------------------------------------------------------- attention ---
