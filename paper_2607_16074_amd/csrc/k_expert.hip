@@ -524,6 +524,18 @@ __device__ __forceinline__ xbf16x8 xa_tr(const uint16_t* t, int c, int ct, int q
   return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
 }
 
+// The same without the compiler's vmcnt(0) in front of it, which would wait for
+// the K/V tile being fetched; the caller waits (lgkmcnt).
+template <int HD>
+__device__ __forceinline__ xbf16x8 xa_tr_async(const uint16_t* t, int c, int ct, int quad, int j16, int swz) {
+  const int col = ct * 16 + 4 * (j16 & 3);
+  const int pos = (((col >> 3) ^ swz) * 8) + (col & 7);
+  const uint16_t* p = t + (c * 32 + 4 * quad + (j16 >> 2)) * HD + pos;
+  const xbf16x4 lo = __builtin_bit_cast(xbf16x4, lds_read_tr_b16<0>(p));
+  const xbf16x4 hi = __builtin_bit_cast(xbf16x4, lds_read_tr_b16<16 * HD * 2>(p));
+  return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
 __device__ __forceinline__ xf32x4 xa_mfma(xbf16x8 a, xbf16x8 b, xf32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
 }
@@ -583,12 +595,16 @@ struct XaTiles {
 
 // Forward: one workgroup per (sample, head), wave w = queries 16 w ..;
 // O = softmax(Q K^T scale) V in fp32 (and a bf16 copy), lse per query.
+// K and V are read once (16 tenants, 288 samples of ~600 keys: 0.68 GB, 141 us
+// at the copy rate, 194 measured).  A sample's heads are consecutive
+// workgroups, so that the 256-byte head slices of a K / V row are read at about
+// the same time (backward 343 -> 325 us, forward unchanged).
 template <int HD>
 __global__ __launch_bounds__(256, 2) void xattn_fwd_kernel(AttnArgs A) {
   using T = XaTiles<HD>;
   constexpr int NQC = HD / 32, NOT = HD / 16;
   __shared__ __attribute__((aligned(1024))) uint16_t lds[2][2 * T::TILE];
-  const int k = blockIdx.x, h = blockIdx.y;
+  const int k = blockIdx.x / A.nheads, h = blockIdx.x % A.nheads;
   int32_t q0, Lq, Lk;
   int64_t kv0;
   attn_rows(A, k, q0, Lq, kv0, Lk);
@@ -639,17 +655,19 @@ __global__ __launch_bounds__(256, 2) void xattn_fwd_kernel(AttnArgs A) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) mx = fmaxf(mx, s[kb][e]);
     const float m_new = fmaxf(m, max_xor32(max_xor16(mx)) * sl2);
-    const float alpha = exp2f(m - m_new);
-    l *= alpha;
+    if (__any(m_new > m)) {  // (else alpha is 1 for every lane)
+      const float alpha = __builtin_amdgcn_exp2f(m - m_new);
+      l *= alpha;
 #pragma unroll
-    for (int t = 0; t < NOT; ++t) o[t] *= alpha;
-    m = m_new;
+      for (int t = 0; t < NOT; ++t) o[t] *= alpha;
+      m = m_new;
+    }
     float lsum = 0.f;
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb)
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        s[kb][e] = exp2f(fmaf(s[kb][e], sl2, -m));
+        s[kb][e] = __builtin_amdgcn_exp2f(fmaf(s[kb][e], sl2, -m));  // (below 2^-126: zero)
         lsum += s[kb][e];
       }
     l += sum_xor32(sum_xor16(lsum));
@@ -661,10 +679,24 @@ __global__ __launch_bounds__(256, 2) void xattn_fwd_kernel(AttnArgs A) {
         pf[c][e] = (__bf16)s[2 * c][e];
         pf[c][4 + e] = (__bf16)s[2 * c + 1][e];
       }
+    // V^T of head-dim block t + 1 is read under the products of block t
+    xbf16x8 vb[2][2];
 #pragma unroll
-    for (int t = 0; t < NOT; ++t)
+    for (int c = 0; c < 2; ++c) vb[0][c] = xa_tr_async<HD>(Vs, c, 0, quad, j16, vswz);
 #pragma unroll
-      for (int c = 0; c < 2; ++c) o[t] = xa_mfma(xa_tr<HD>(Vs, c, t, quad, j16, vswz), pf[c], o[t]);
+    for (int t = 0; t < NOT; ++t) {
+      if (t + 1 < NOT) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) vb[(t + 1) & 1][c] = xa_tr_async<HD>(Vs, c, t + 1, quad, j16, vswz);
+        __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4) | (4 << 8));  // lgkmcnt(4): block t's reads
+      } else {
+        __builtin_amdgcn_s_waitcnt(15 | (3 << 14) | (7 << 4));  // lgkmcnt(0)
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) o[t] = xa_mfma(vb[t & 1][c], pf[c], o[t]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
   __builtin_amdgcn_s_waitcnt(0);  // the repeated last tile's DMA lands before the LDS is released
   if (qi >= Lq) return;
@@ -693,7 +725,7 @@ __global__ __launch_bounds__(256, 2) void xattn_fwd_kernel(AttnArgs A) {
 // 288 samples of ~600 keys: 1.4 GB, 290 us at the copy rate).  As two kernels,
 // a query side and a key side of one workgroup per key tile, K, V, the queries
 // and the output gradients were read again for every tile and S and dP formed
-// twice: 199 + 455 us, now 340 (self attention 55 + 46 -> 72).  One K/V buffer, so that two workgroups
+// twice: 199 + 455 us, now 325 (self attention 55 + 46 -> 72).  One K/V buffer, so that two workgroups
 // share a CU (72 KB of LDS each) and one's products hide the other's loads.
 template <int HD>
 __global__ __launch_bounds__(256, 2) void xattn_bwd_kernel(AttnArgs A) {
@@ -704,7 +736,7 @@ __global__ __launch_bounds__(256, 2) void xattn_bwd_kernel(AttnArgs A) {
   __shared__ __attribute__((aligned(1024))) uint16_t dt[64 * HD];
   __shared__ __attribute__((aligned(1024))) uint16_t ds[64 * 64];
   __shared__ float lse_s[64], d_s[64];
-  const int k = blockIdx.x, h = blockIdx.y;
+  const int k = blockIdx.x / A.nheads, h = blockIdx.x % A.nheads;
   int32_t q0, Lq, Lk;
   int64_t kv0;
   attn_rows(A, k, q0, Lq, kv0, Lk);
@@ -830,7 +862,9 @@ __global__ __launch_bounds__(256, 2) void xattn_bwd_kernel(AttnArgs A) {
 
 hipError_t launch_xattn(hipStream_t s, const AttnArgs& A, int32_t nsamples, bool backward) {
   if (A.Lq > 64 || A.Lq < 1 || A.max_lk < 1) return hipErrorInvalidValue;
-  const dim3 grid(nsamples, A.nheads);
+  const int64_t wgs = (int64_t)nsamples * A.nheads;  // heads fastest: they share the rows of K and V
+  if (wgs > 0x7fffffff) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)wgs);
   switch (A.hd) {
     case 64:
       if (backward) {
