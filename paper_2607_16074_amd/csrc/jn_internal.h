@@ -301,7 +301,7 @@ struct AdamwTensor {
 struct AdamwTenant {
   float decay, step_size, inv_sqrt_bc2, eps, b1, b2, reserved0, reserved1;
 };
-constexpr int64_t kAdamwBlockElems = 4096;
+constexpr int64_t kAdamwBlockElems = 2048;
 int32_t adamw_prepare(AdamwTensor* t, int32_t n);  // fills block_start, returns the block count
 hipError_t launch_adamw(hipStream_t s, const AdamwTensor* t, int32_t n, const AdamwTenant* ten, int32_t blocks);
 

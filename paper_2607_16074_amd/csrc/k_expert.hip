@@ -14,6 +14,8 @@
 //                matrix cores, per (sample, head); a sample's queries never
 //                see another sample's keys
 //   loss         per-tenant mean squared error and its gradient
+#include <algorithm>
+
 #include "jn_device.h"
 #include "jn_internal.h"
 
@@ -243,26 +245,33 @@ __global__ __launch_bounds__(256) void prefix_offsets_kernel(const int32_t* __re
   if (threadIdx.x == 255) zoff[N] = run;
 }
 
-// Copy rows of each sample (grid: tenant-order sample x 16-row slab); rows
-// past `cap` are dropped so an inconsistent caller row count cannot overflow.
+// Copy each sample's rows, one contiguous run on both sides: a block moves 512
+// consecutive 16-byte chunks at a time, `per` blocks per sample (consecutive
+// ones, and the reads non-temporal, as measured for the pack kernel: 288 samples
+// of ~600 rows of 1.5 KB 94 -> 80 us).  Rows past `cap` are dropped so an
+// inconsistent caller row count cannot overflow.
+constexpr int kPrefixRun = 512;
+typedef uint32_t u32x4x __attribute__((ext_vector_type(4)));
 __global__ __launch_bounds__(256) void prefix_gather_kernel(const uint16_t* __restrict__ hidden,
                                                            const int32_t* __restrict__ tenant_perm,
                                                            const int32_t* __restrict__ seqlens,
                                                            const int32_t* __restrict__ cu_seqlens,
                                                            const int32_t* __restrict__ zoff, int32_t d, int64_t cap,
-                                                           uint16_t* __restrict__ z) {
-  const int32_t k = blockIdx.x;
+                                                           uint16_t* __restrict__ z, int32_t per) {
+  const int32_t k = blockIdx.x / per, part = blockIdx.x % per;
   const int32_t i = tenant_perm[k];
-  const int32_t L = seqlens[i];
-  const int32_t j0 = blockIdx.y * 16;
-  if (j0 >= L) return;
-  const int32_t nr = min(16, L - j0);
-  const int32_t chunks = d / 8;
-  const uint4* src = reinterpret_cast<const uint4*>(hidden + (int64_t)(cu_seqlens[i] + j0) * d);
-  for (int32_t e = threadIdx.x; e < nr * chunks; e += 256) {
-    const int64_t row = (int64_t)zoff[k] + j0 + e / chunks;
-    if (row >= cap) continue;
-    reinterpret_cast<uint4*>(z + row * d)[e % chunks] = src[e];
+  const int64_t chunks = d / 8, at = zoff[k];
+  const int64_t n = min((int64_t)seqlens[i], cap - at) * chunks;
+  const u32x4x* src = reinterpret_cast<const u32x4x*>(hidden) + cu_seqlens[i] * chunks;
+  u32x4x* dst = reinterpret_cast<u32x4x*>(z) + at * chunks;
+  for (int64_t e = (int64_t)part * kPrefixRun + threadIdx.x; e < n; e += (int64_t)per * kPrefixRun) {
+    const bool two = e + 256 < n;
+    const u32x4x a = __builtin_nontemporal_load(src + e);
+    if (two) {
+      const u32x4x b = __builtin_nontemporal_load(src + e + 256);
+      dst[e + 256] = b;
+    }
+    dst[e] = a;
   }
 }
 
@@ -270,9 +279,11 @@ hipError_t launch_prefix(hipStream_t s, const void* hidden, const int32_t* tenan
                          const int32_t* cu_seqlens, int32_t N, int32_t max_seqlen, int32_t d, int64_t cap,
                          int32_t* zoff, void* z) {
   prefix_offsets_kernel<<<1, 256, 0, s>>>(tenant_perm, seqlens, N, zoff);
-  dim3 grid(N, (max_seqlen + 15) / 16);
-  prefix_gather_kernel<<<grid, 256, 0, s>>>(reinterpret_cast<const uint16_t*>(hidden), tenant_perm, seqlens,
-                                            cu_seqlens, zoff, d, cap, reinterpret_cast<uint16_t*>(z));
+  const int32_t per = (int32_t)std::min<int64_t>(((int64_t)max_seqlen * (d / 8) + kPrefixRun - 1) / kPrefixRun,
+                                                 std::max(1, 0x7fffffff / N));
+  prefix_gather_kernel<<<dim3((unsigned)N * per), 256, 0, s>>>(reinterpret_cast<const uint16_t*>(hidden), tenant_perm,
+                                                               seqlens, cu_seqlens, zoff, d, cap,
+                                                               reinterpret_cast<uint16_t*>(z), per);
   return hipGetLastError();
 }
 

@@ -19,7 +19,10 @@ namespace jnx {
 // wave).  Wave w sums rows w, w+4, w+8, ... of the sample in that order, eight
 // loads in flight per lane; the four wave sums are combined as
 // (s0 + s1) + (s2 + s3).  The order depends only on the sample's own length,
-// so a sample pools to the same bits in any batch.
+// so a sample pools to the same bits in any batch.  Bound by HBM, one read of
+// every valid row, non-temporal: 256 samples of ~296 rows of 4 KB 69 -> 50 us
+// (6.2 TB/s).
+typedef uint32_t u32x4h __attribute__((ext_vector_type(4)));
 constexpr int kPoolCols = 512;
 constexpr int kPoolWaves = 4;
 
@@ -40,30 +43,30 @@ __global__ __launch_bounds__(256) void pool_kernel(const uint16_t* __restrict__ 
   for (int e = 0; e < 8; ++e) acc[e] = 0.f;
   if (col < d) {
     const uint16_t* base = hidden + (int64_t)cu_seqlens[i] * d + col;
-    auto add = [&](const uint4& q) {
-      const uint32_t v[4] = {q.x, q.y, q.z, q.w};
+    auto add = [&](const u32x4h& q) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        acc[2 * e] += __uint_as_float(v[e] << 16);
-        acc[2 * e + 1] += __uint_as_float(v[e] & 0xffff0000u);
+        acc[2 * e] += __uint_as_float(q[e] << 16);
+        acc[2 * e + 1] += __uint_as_float(q[e] & 0xffff0000u);
       }
     };
+    auto load = [&](int32_t j) { return __builtin_nontemporal_load(reinterpret_cast<const u32x4h*>(base + (int64_t)j * d)); };
     int32_t j = w;
     for (; j + 7 * kPoolWaves < L; j += 8 * kPoolWaves) {
-      uint4 q[8];
+      u32x4h q[8];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) q[k] = *reinterpret_cast<const uint4*>(base + (int64_t)(j + k * kPoolWaves) * d);
+      for (int k = 0; k < 8; ++k) q[k] = load(j + k * kPoolWaves);
 #pragma unroll
       for (int k = 0; k < 8; ++k) add(q[k]);
     }
     for (; j + 3 * kPoolWaves < L; j += 4 * kPoolWaves) {
-      uint4 q[4];
+      u32x4h q[4];
 #pragma unroll
-      for (int k = 0; k < 4; ++k) q[k] = *reinterpret_cast<const uint4*>(base + (int64_t)(j + k * kPoolWaves) * d);
+      for (int k = 0; k < 4; ++k) q[k] = load(j + k * kPoolWaves);
 #pragma unroll
       for (int k = 0; k < 4; ++k) add(q[k]);
     }
-    for (; j < L; j += kPoolWaves) add(*reinterpret_cast<const uint4*>(base + (int64_t)j * d));
+    for (; j < L; j += kPoolWaves) add(load(j));
   }
 #pragma unroll
   for (int e = 0; e < 8; ++e) red[w][lane * 8 + e] = acc[e];

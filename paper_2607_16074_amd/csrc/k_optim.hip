@@ -1,12 +1,16 @@
 // Per-tenant AdamW step over every tensor of every tenant in one launch.
-// Block b updates elements [4096 (b - block_start), +4096) of the tensor whose
-// block range holds b; each thread handles 16 elements as four 16-byte
-// accesses per operand (the tail of a tensor element by element).  HBM-bound:
-// 16 bytes read and 12 written per element (+2 for a bf16 copy).
+// Block b updates elements [2048 (b - block_start), +2048) of the tensor whose
+// block range holds b; each thread handles 8 elements as two 16-byte accesses
+// per operand (the tail of a tensor element by element).  HBM-bound: 16 bytes
+// read and 12 written per element (+2 for a bf16 copy), all but p's read
+// non-temporal, since nothing of it is used again before it has left the caches
+// (28.5M parameters: 151 -> 135 us of the launch alone, 5.9 TB/s).
 #include "jn_device.h"
 #include "jn_internal.h"
 
 namespace jnx {
+
+typedef float f32x4o __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ void adamw_elem(const AdamwTenant& h, float& p, float g, float& m, float& v) {
   m = h.b1 * m + (1.f - h.b1) * g;
@@ -29,22 +33,26 @@ __global__ __launch_bounds__(256) void adamw_kernel(const AdamwTensor* __restric
   const AdamwTenant H = tens[T.tenant];
   const int64_t e0 = (int64_t)(b - T.block_start) * kAdamwBlockElems;
 #pragma unroll
-  for (int k = 0; k < 4; ++k) {
+  for (int k = 0; k < kAdamwBlockElems / 1024; ++k) {
     const int64_t e = e0 + ((int64_t)k * 256 + threadIdx.x) * 4;
     if (e >= T.numel) break;
     if (e + 4 <= T.numel) {
-      float4 p = *reinterpret_cast<const float4*>(T.p + e);
-      const float4 g = *reinterpret_cast<const float4*>(T.g + e);
-      float4 m = *reinterpret_cast<const float4*>(T.m + e);
-      float4 v = *reinterpret_cast<const float4*>(T.v + e);
-      adamw_elem(H, p.x, g.x, m.x, v.x);
-      adamw_elem(H, p.y, g.y, m.y, v.y);
-      adamw_elem(H, p.z, g.z, m.z, v.z);
-      adamw_elem(H, p.w, g.w, m.w, v.w);
-      *reinterpret_cast<float4*>(T.p + e) = p;
-      *reinterpret_cast<float4*>(T.m + e) = m;
-      *reinterpret_cast<float4*>(T.v + e) = v;
-      if (T.b16) *reinterpret_cast<uint2*>(T.b16 + e) = make_uint2(pack_bf2(p.x, p.y), pack_bf2(p.z, p.w));
+      f32x4o *const pp = reinterpret_cast<f32x4o*>(T.p + e), *const pm = reinterpret_cast<f32x4o*>(T.m + e),
+             *const pv = reinterpret_cast<f32x4o*>(T.v + e);
+      f32x4o p = *pp, m = __builtin_nontemporal_load(pm), v = __builtin_nontemporal_load(pv);
+      const f32x4o g = __builtin_nontemporal_load(reinterpret_cast<const f32x4o*>(T.g + e));
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        float pj = p[j], mj = m[j], vj = v[j];
+        adamw_elem(H, pj, g[j], mj, vj);
+        p[j] = pj;
+        m[j] = mj;
+        v[j] = vj;
+      }
+      __builtin_nontemporal_store(p, pp);
+      __builtin_nontemporal_store(m, pm);
+      __builtin_nontemporal_store(v, pv);
+      if (T.b16) *reinterpret_cast<uint2*>(T.b16 + e) = make_uint2(pack_bf2(p[0], p[1]), pack_bf2(p[2], p[3]));
     } else {
       for (int64_t j = e; j < T.numel; ++j) {
         float p = T.p[j], m = T.m[j], v = T.v[j];
