@@ -1306,8 +1306,10 @@ jn_status jn_tenant_experts_fwd_bwd(jn_ctx* c, const jn_packed* p, const void* h
     const size_t at = rec.add(probs.data(), sizeof(GemmArgs) * probs.size());
     const int32_t n = (int32_t)probs.size();
     const int trans = probs.empty() ? 0 : probs[0].trans;
-    rec.ops.push_back(
-        [=](char* a) { return launch_gemm_grouped(s, epi, (const GemmArgs*)(a + at), n, tiles, shape, trans); });
+    const bool uneven = gemm_grouped_uneven(probs.data(), n);
+    rec.ops.push_back([=](char* a) {
+      return launch_gemm_grouped(s, epi, (const GemmArgs*)(a + at), n, tiles, shape, trans, uneven);
+    });
     rec.opcode.push_back(JN_OP_EXPERT_GEMM);
   };
   // Where transposed-operand problems' offsets exceed the loops' 32-bit ones

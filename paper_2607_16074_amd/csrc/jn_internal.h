@@ -90,9 +90,10 @@ struct GemmArgs {
 // need not be a multiple of 64.  Combinations launched: EPI_F32 with
 // GEMM_TRANS_W or both, EPI_GELUGRAD_BF16 with GEMM_TRANS_W.
 int gemm_grouped_tile_shape(int epi, const GemmArgs* probs, int32_t nprob);
+bool gemm_grouped_uneven(const GemmArgs* probs, int32_t nprob);
 int32_t gemm_grouped_prepare(GemmArgs* probs, int32_t nprob, int shape);
 hipError_t launch_gemm_grouped(hipStream_t s, int epi, const GemmArgs* dprobs, int32_t nprob, int32_t total_tiles,
-                               int shape, int trans = 0);
+                               int shape, int trans, bool uneven);
 
 // A data gradient (GEMM_TRANS_W) and a weight gradient (EPI_F32, both operands
 // transposed), prepared as above with the shapes that gemm_grad_pair_ok takes,
