@@ -89,6 +89,8 @@ struct GemmArgs {
 // (-1) where their offsets do not fit 32 bits; with both operands transposed K
 // need not be a multiple of 64.  Combinations launched: EPI_F32 with
 // GEMM_TRANS_W or both, EPI_GELUGRAD_BF16 with GEMM_TRANS_W.
+// uneven: gemm_grouped_uneven of the problems; gemm_grouped_prepare then sorts
+// them, longest contraction first.
 int gemm_grouped_tile_shape(int epi, const GemmArgs* probs, int32_t nprob);
 bool gemm_grouped_uneven(const GemmArgs* probs, int32_t nprob);
 int32_t gemm_grouped_prepare(GemmArgs* probs, int32_t nprob, int shape);
