@@ -280,7 +280,7 @@ hipError_t launch_prefix(hipStream_t s, const void* hidden, const int32_t* tenan
                          int32_t* zoff, void* z) {
   prefix_offsets_kernel<<<1, 256, 0, s>>>(tenant_perm, seqlens, N, zoff);
   const int32_t per = (int32_t)std::min<int64_t>(((int64_t)max_seqlen * (d / 8) + kPrefixRun - 1) / kPrefixRun,
-                                                 std::max(1, 0x7fffffff / N));
+                                                 std::max(1, 0xffffff / N));
   prefix_gather_kernel<<<dim3((unsigned)N * per), 256, 0, s>>>(reinterpret_cast<const uint16_t*>(hidden), tenant_perm,
                                                                seqlens, cu_seqlens, zoff, d, cap,
                                                                reinterpret_cast<uint16_t*>(z), per);

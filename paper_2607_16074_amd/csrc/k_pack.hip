@@ -104,9 +104,10 @@ __global__ __launch_bounds__(256) void unpack_kernel(const ReqEntry* __restrict_
     move_run(src, reinterpret_cast<V*>(e.out) + s * n, at, live, n);
 }
 
-// Blocks per sample of a run of `n` elements, of N samples.
+// Blocks per sample of a run of `n` elements, of N samples; a dispatch holds at
+// most 2^32 - 1 threads, beyond which blocks move more than one piece.
 static int32_t flat_blocks(int64_t n, int32_t N) {
-  return (int32_t)std::min<int64_t>((n + kFlat - 1) / kFlat, std::max(1, 0x7fffffff / N));
+  return (int32_t)std::min<int64_t>((n + kFlat - 1) / kFlat, std::max(1, 0xffffff / N));
 }
 
 hipError_t launch_pack(hipStream_t s, const ReqEntry* req_table, const int32_t* sample_request,
