@@ -653,8 +653,8 @@ __global__ __launch_bounds__(256, OCC) void gemm_grouped_flex_kernel(const GemmA
 // MFMA; the clock falls to 1.5 to 1.9 GHz with the whole chip busy, so this is
 // power), then the epilogue; with kRingChain tiles in a row the first part goes
 // (bf16 291 -> 262 us).
-// next(r, q, tm, tn): problem and tile of the workgroup's r-th turn, or false;
-// lds holds 5 x 32 KB.
+// next(r, q, tm, tn): problem and tile of the workgroup's r-th turn, or false,
+// and then nothing of them is set or read; lds holds 5 x 32 KB.
 //
 // TR: operands stored transposed (GEMM_TRANS_X: X is [K][M], element (m, k)
 // at X[k * ldx + m]; GEMM_TRANS_W: W is [K][N]).  A transposed operand's
@@ -868,8 +868,8 @@ __device__ __forceinline__ void ring_run(const Next& next, uint16_t* __restrict_
     GemmArgs gn;
     int32_t tmn, tnn;
     const bool more = next(r, gn, tmn, tnn);
-    const int KTn = (gn.K + kBK - 1) / kBK;
-    const bool joined = more && KT >= 3 && KTn >= 3;
+    const int KTn = more ? (gn.K + kBK - 1) / kBK : 0;
+    const bool joined = KT >= 3 && KTn >= 3;
     first_frags();  // (read again behind an epilogue, which needs the registers)
     slab(std::true_type{}, min(2, KT - 1), stored);
     for (int kt = 1; kt < KT - 2; ++kt) slab(std::false_type{}, kt + 2, false);
@@ -919,9 +919,10 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_kernel(GemmArgs g, int32_t c
   __shared__ __attribute__((aligned(1024))) uint16_t lds[5 * 256 * kBK];
   auto next = [&](int32_t r, GemmArgs& q, int32_t& tm, int32_t& tn) __attribute__((always_inline)) {
     const int64_t t = chain_tile(blockIdx.x, chain, r);
+    if (r >= chain || t >= (int64_t)g.tiles_m * g.tiles_n) return false;
     q = g;
     tile_of((int32_t)t, g.tiles_m, g.tiles_n, tm, tn);
-    return r < chain && t < (int64_t)g.tiles_m * g.tiles_n;
+    return true;
   };
   ring_run<EPI, 0>(next, lds);
 }
@@ -931,6 +932,7 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_split_kernel(GemmArgs g, int
   __shared__ __attribute__((aligned(1024))) uint16_t lds[5 * 256 * kBK];
   auto next = [&](int32_t r, GemmArgs& q, int32_t& tm, int32_t& tn) __attribute__((always_inline)) {
     const int32_t tiles = g.tiles_m * g.tiles_n, idx = xcd_item(blockIdx.x, gridDim.x);
+    if (r > 0 || idx >= tiles * S) return false;
     const int32_t s = idx / tiles;
     const int64_t KT = g.K / kBK, k0 = KT * s / S, k1 = KT * (s + 1) / S;
     q = g;
@@ -939,7 +941,7 @@ __global__ __launch_bounds__(256, 1) void gemm_ring_split_kernel(GemmArgs g, int
     q.K = (int32_t)(k1 - k0) * kBK;
     q.C = reinterpret_cast<float*>(g.C) + (int64_t)s * g.split_c;
     flex_walk(idx - s * tiles, g.tiles_m, g.tiles_n, tm, tn);
-    return r == 0 && idx < tiles * S;
+    return true;
   };
   ring_run<EPI_F32, 0>(next, lds);
 }

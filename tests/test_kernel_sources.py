@@ -1,0 +1,41 @@
+"""Order of statements in the kernels that no run shows: the compiler may hide a
+missing one today.  Read from the sources, on the CPU."""
+import os
+import re
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2607_16074_amd", "csrc")
+
+
+def source(name):
+    return re.sub(r"//[^\n]*", "", open(os.path.join(CSRC, name)).read())
+
+
+def bodies(text, head):
+    """Text of every brace block that starts at a match of `head`."""
+    out = []
+    for m in re.finditer(head, text):
+        at = text.index("{", m.end() - 1)
+        end, depth = at, 0
+        while True:
+            depth += {"{": 1, "}": -1}.get(text[end], 0)
+            if depth == 0:
+                break
+            end += 1
+        out.append(text[at:end])
+    return out
+
+
+@pytest.mark.parametrize("walk", ["tile_of", "flex_walk"])
+def test_ring_walks_check_the_range_first(walk):
+    """The walks divide by a group size that is zero or negative past the last tile."""
+    found = [b for b in bodies(source("k_gemm.hip"), r"auto next = \[&\]") if walk + "(" in b]
+    assert found
+    for b in found:
+        assert "return false" in b[: b.index(walk + "(")], b
+
+
+def test_ring_reads_the_next_tile_only_where_there_is_one():
+    ring = bodies(source("k_gemm.hip"), r"void ring_run\(")[0]
+    assert ring.count("gn.K") == 1 and "more ? (gn.K" in ring
