@@ -186,15 +186,24 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr bool epi_bf16(int epi) { return epi == EPI_BF16 || epi == EPI_GELU_BF16 || epi == EPI_GEGLU_BF16; }
 constexpr bool epi_reads(int epi) { return epi == EPI_RESID_F32 || epi == EPI_GELUGRAD_BF16; }
 
+// Sizes of the 16-bit epilogue of a wave's part.
+template <int EPI, int TN, int TM>
+struct Epi16 {
+  static constexpr bool GLU = EPI == EPI_GEGLU_BF16;
+  static constexpr int WC = GLU ? 8 * TN : 16 * TN;           // output columns per wave
+  static constexpr int CH = WC / 8, RI = 64 / CH;             // 16-byte chunks per row, rows per instruction
+  static constexpr int NB = row_batch(TM, 4096 / (16 * WC));  // 16-token blocks per batch
+  static constexpr int NI = (NB * 16 + RI - 1) / RI;          // instructions per batch (the last of 16-column parts half used)
+  static constexpr int STORES = TM / NB * NI;                 // of a whole part, one per instruction
+  static_assert((CH & (CH - 1)) == 0 && CH <= 16 && TM % NB == 0, "row segments");
+};
+
 template <int EPI, int TN, int TM, bool WHOLE>
 __device__ __forceinline__ void epilogue_bf16(const GemmArgs& g, const f32x4 (&acc)[TN][TM], uint16_t* stage,
                                               int32_t m0, int32_t n0, int lane) {
-  constexpr bool GLU = EPI == EPI_GEGLU_BF16;
-  constexpr int WC = GLU ? 8 * TN : 16 * TN;          // output columns per wave
-  constexpr int CH = WC / 8, RI = 64 / CH;            // 16-byte chunks per row, rows per instruction
-  constexpr int NB = row_batch(TM, 4096 / (16 * WC)); // 16-token blocks per batch
-  constexpr int NI = (NB * 16 + RI - 1) / RI;         // instructions per batch (the last of 16-column parts half used)
-  static_assert((CH & (CH - 1)) == 0 && CH <= 16, "row segments");
+  using E = Epi16<EPI, TN, TM>;
+  constexpr bool GLU = E::GLU;
+  constexpr int WC = E::WC, CH = E::CH, RI = E::RI, NB = E::NB, NI = E::NI;
   const int quad = lane >> 4, row = lane & 15, c = lane & (CH - 1), rr = lane / CH;
   const int32_t m = m0 + rr, n = n0 + c * 8;
   uint16_t* C = reinterpret_cast<uint16_t*>(g.C) + (int64_t)m * g.ldc + n;
@@ -673,7 +682,10 @@ __device__ __forceinline__ void ring_run(const Next& next, uint16_t* __restrict_
   constexpr int NI = 8;            // 1 KB DMA instructions per wave per half-slab
   constexpr int SLOT = 256 * kBK;  // elements per half-slab slot
   constexpr bool GLU = EPI == EPI_GEGLU_BF16;
-  constexpr int STORES = GLU ? 16 : 32;  // of a whole tile's 16-bit epilogue, per wave
+  // Stores of a whole tile's 16-bit epilogue per wave, counted by the first
+  // slab's wait: one fewer and the wait would pass before slab 1 has landed.
+  using E16 = Epi16<EPI, TN, TM>;
+  static_assert(E16::NB * 16 % E16::RI == 0, "every instruction of a whole part stores");
   static_assert(!(GLU && TW), "GeGLU weights are row-major");
 
   GemmArgs g;
@@ -828,7 +840,7 @@ __device__ __forceinline__ void ring_run(const Next& next, uint16_t* __restrict_
     // the next slab landed (the token DMA just issued may stay in flight)
     wait_lgkmcnt<0>();
     if (FIRST && epi_bf16(EPI) && stored)
-      wait_vmcnt<NI + STORES>();
+      wait_vmcnt<NI + E16::STORES>();
     else
       wait_vmcnt<NI>();
     __builtin_amdgcn_sched_barrier(0);

@@ -39,3 +39,13 @@ def test_ring_walks_check_the_range_first(walk):
 def test_ring_reads_the_next_tile_only_where_there_is_one():
     ring = bodies(source("k_gemm.hip"), r"void ring_run\(")[0]
     assert ring.count("gn.K") == 1 and "more ? (gn.K" in ring
+
+
+def test_ring_counts_the_stores_of_its_own_epilogue():
+    """The counted wait behind a 16-bit epilogue takes the store count from the
+    sizes the epilogue itself is written with."""
+    text = source("k_gemm.hip")
+    ring, epi = (bodies(text, r"void %s\(" % f)[0] for f in ("ring_run", "epilogue_bf16"))
+    assert "using E16 = Epi16<EPI, TN, TM>" in ring and "wait_vmcnt<NI + E16::STORES>" in ring
+    assert not re.search(r"STORES\s*=", ring)
+    assert "using E = Epi16<EPI, TN, TM>" in epi and "NB = E::NB, NI = E::NI" in epi
