@@ -793,7 +793,8 @@ __global__ __launch_bounds__(256, 2) void xattn_bwd_kernel(AttnArgs A) {
   const int32_t ntiles = (Lk + 63) / 64;
   for (int32_t jt = 0; jt < ntiles; ++jt) {
     const int32_t key = jt * 64 + krow;
-    __syncthreads();  // tile jt (first: the staged rows) landed
+    __builtin_amdgcn_s_waitcnt(0);  // this wave's part of tile jt landed: a barrier alone waits for no DMA
+    __syncthreads();                // every wave's did (first: the staged rows too)
     xf32x4 s[4], dp[4];
 #pragma unroll
     for (int qb = 0; qb < 4; ++qb) s[qb] = dp[qb] = xf32x4{0.f, 0.f, 0.f, 0.f};

@@ -49,3 +49,20 @@ def test_ring_counts_the_stores_of_its_own_epilogue():
     assert "using E16 = Epi16<EPI, TN, TM>" in ring and "wait_vmcnt<NI + E16::STORES>" in ring
     assert not re.search(r"STORES\s*=", ring)
     assert "using E = Epi16<EPI, TN, TM>" in epi and "NB = E::NB, NI = E::NI" in epi
+
+
+@pytest.mark.parametrize("name", ["k_expert.hip", "k_attn.hip"])
+def test_barriers_that_publish_fetched_tiles_follow_a_wait(name):
+    """A barrier does not wait for LDS DMA: in a kernel that fetches tiles by it,
+    the barrier at the top of the tile loop stands behind an explicit wait."""
+    found = 0
+    for body in bodies(source(name), r"__global__ [^;{]*"):
+        if not re.search(r"\bissue(_kv)?\(|global_load_lds", body):
+            continue
+        loop = re.search(r"for \((?:int32_t|int) j\w* = ", body)
+        assert loop, body[:200]
+        top = re.search(r"__syncthreads\(\)|s_barrier\(\)", body[loop.start():])
+        before = body[loop.start(): loop.start() + top.start()]
+        assert re.search(r"s_waitcnt\(0\)|attn_wait_vmcnt<0>\(\)", before), body[:300]
+        found += 1
+    assert found >= 2
