@@ -717,6 +717,7 @@ struct HeadPlan {
   size_t P = 0, Z0 = 0, total = 0; // offsets
   std::vector<size_t> Z, H, dZ;    // per k
   size_t descs = 0, tiles = 0, lpart = 0;
+  int32_t ldp = 0;
 };
 
 int64_t head_tiles(int64_t n) { return (n + kHeadTile - 1) / kHeadTile; }
@@ -742,9 +743,10 @@ jn_status check_heads(jn_ctx* c, const jn_packed* p, const jn_head* heads, int32
 }
 
 // Workspace layout: pooled P [N][d] | per layer k: Z_k, H_k (hidden layers),
-// dZ_k [N][width_k] | per-tenant, per-tile loss sums | gemm descriptors |
-// tiles.  Tenant g's rows of every [N][*] buffer are its tenant-order rows
-// [off_g, off_g + n_g).
+// dZ_k [N][width_k] | per-tile loss sums | gemm descriptors | tiles.  Tenant
+// g's rows of every [N][*] buffer are its tenant-order rows [off_g, off_g + n_g);
+// its row tiles of the loss sums start at off_g / 32 + g (that many always lie
+// in front of the next tenant's).
 void head_layout(const jn_packed* p, const jn_head* heads, int32_t G, HeadPlan* hp) {
   size_t o = 0;
   auto take = [&](size_t bytes) {
@@ -769,23 +771,20 @@ void head_layout(const jn_packed* p, const jn_head* heads, int32_t G, HeadPlan* 
     }
     hp->dZ[k] = take(4 * N * hp->width[k]);
   }
-  // tiles: forward and data gradient over the rows of the largest tenant,
-  // weight gradient, loss
-  const int64_t tm_dyn = head_tiles(tenant_rows_bound(p));
-  int64_t ntiles = 0, ndesc = 0;
+  // forward and data gradient: a tile column each; weight gradient; loss
+  int64_t ntiles = 0, ndesc = 0, last = 0;
   for (int32_t g = 0; g < G; ++g) {
     const jn_head& Hh = heads[g];
     for (int k = 0; k < Hh.n_layers; ++k) {
       const int64_t in = Hh.dims[k], out = Hh.dims[k + 1];
-      ntiles += tm_dyn * head_tiles(out) + wgrad_tiles(out, in) + (k > 0 ? tm_dyn * head_tiles(in) : 0);
+      ntiles += head_tiles(out) + wgrad_tiles(out, in) + (k > 0 ? head_tiles(in) : 0);
       ndesc += (k > 0) ? 3 : 2;
     }
     ntiles += 1;
-    ndesc += 1;
+    last = std::max<int64_t>(last, Hh.dims[Hh.n_layers]);
   }
-  int64_t lparts = 0;
-  for (int32_t g = 0; g < G; ++g) lparts += tm_dyn * head_tiles(heads[g].dims[heads[g].n_layers]);
-  hp->lpart = take(4 * lparts);
+  hp->ldp = (int32_t)head_tiles(last);
+  hp->lpart = take(4 * (N / kHeadTile + G) * hp->ldp);
   hp->descs = take(sizeof(HeadGemm) * ndesc);
   hp->tiles = take(sizeof(HeadTile) * ntiles);
   hp->total = o;
@@ -842,7 +841,7 @@ jn_status heads_run(jn_ctx* c, const jn_packed* p, const void* hidden, const jn_
   HeadGemm* const dd0 = (HeadGemm*)img.data();
   HeadTile* const dt0 = (HeadTile*)(img.data() + (hp.tiles - hp.descs));
   int32_t nd = 0, nt = 0;
-  std::vector<std::pair<int32_t, int32_t>> fwd_rng, bwd_rng;
+  std::vector<HeadLaunch> fwd, bwd;
   auto add_tiles = [&](const HeadGemm& D, int32_t g, int32_t tms, int32_t tns) {
     dd0[nd] = D;
     for (int32_t tm = 0; tm < tms; ++tm)
@@ -851,20 +850,14 @@ jn_status heads_run(jn_ctx* c, const jn_packed* p, const void* hidden, const jn_
   };
   // forward, one launch per layer index; a tenant's last layer forms its loss
   // gradient in dZ
-  float* lpart = (float*)(w + hp.lpart);
-  std::vector<float*> lparts(G);
-  for (int32_t g = 0; g < G; ++g) {
-    lparts[g] = lpart;
-    lpart += (int64_t)tm_dyn * head_tiles(heads[g].dims[heads[g].n_layers]);
-  }
+  float* const lpart = (float*)(w + hp.lpart);
   for (int k = 0; k < hp.maxL; ++k) {
-    const int32_t t0 = nt;
+    HeadLaunch n{nt};
     for (int32_t g = 0; g < G; ++g) {
       const jn_head& Hh = heads[g];
       if (k >= Hh.n_layers) continue;
       const bool last = k + 1 == Hh.n_layers;
       HeadGemm D{};
-      D.mode = HEAD_FWD;
       D.A = (k == 0) ? P : Hk(k - 1);
       D.lda = (k == 0) ? d : hp.width[k - 1];
       D.B = Hh.W[k];
@@ -876,18 +869,39 @@ jn_status heads_run(jn_ctx* c, const jn_packed* p, const void* hidden, const jn_
       if (last) {
         D.target = io[g].targets;
         D.actions = io[g].actions;
-        D.lpart = lparts[g];
+        D.lpart = lpart;
+        D.ldp = hp.ldp;
       }
       D.N = Hh.dims[k + 1];
       D.K = Hh.dims[k];
-      add_tiles(D, g, tm_dyn, (int32_t)head_tiles(D.N));
+      add_tiles(D, g, 1, (int32_t)head_tiles(D.N));
     }
-    fwd_rng.emplace_back(t0, nt - t0);
+    n.nrow = nt - n.first;
+    fwd.push_back(n);
   }
-  // backward, one launch per step s (tenant g at layer k = L_g - 1 - s), the
-  // first with the tenants' losses
+  // backward, one launch per step s (tenant g at layer k = L_g - 1 - s): data
+  // gradients, the longer ones, then weight gradients, in the first step with
+  // the tenants' losses
   for (int sidx = 0; sidx < hp.maxL; ++sidx) {
-    const int32_t t0 = nt;
+    HeadLaunch n{nt};
+    for (int32_t g = 0; g < G; ++g) {
+      const jn_head& Hh = heads[g];
+      const int k = Hh.n_layers - 1 - sidx;
+      if (k < 1) continue;
+      // dgrad: dZ_{k-1}[row][i] = (sum_o dZ_k[row][o] W[o][i]) * gelu'(Z_{k-1}[row][i])
+      HeadGemm Dg{};
+      Dg.A = dZk(k);
+      Dg.lda = hp.width[k];
+      Dg.B = Hh.W[k];
+      Dg.ldb = Hh.dims[k];
+      Dg.C = dZk(k - 1);
+      Dg.ldc = hp.width[k - 1];
+      Dg.Zg = Zk(k - 1);
+      Dg.N = Hh.dims[k];
+      Dg.K = Hh.dims[k + 1];
+      add_tiles(Dg, g, 1, (int32_t)head_tiles(Dg.N));
+    }
+    n.nrow = nt - n.first;
     for (int32_t g = 0; g < G; ++g) {
       const jn_head& Hh = heads[g];
       const int k = Hh.n_layers - 1 - sidx;
@@ -895,7 +909,6 @@ jn_status heads_run(jn_ctx* c, const jn_packed* p, const void* hidden, const jn_
       const int32_t in = Hh.dims[k], out = Hh.dims[k + 1];
       // wgrad: dW[out][in] = sum_rows dZ[row][o] X[row][i]; db[o] = sum_rows dZ[row][o]
       HeadGemm Wg{};
-      Wg.mode = HEAD_WGRAD;
       Wg.A = dZk(k);
       Wg.lda = hp.width[k];
       Wg.B = (k == 0) ? P : Hk(k - 1);
@@ -905,33 +918,16 @@ jn_status heads_run(jn_ctx* c, const jn_packed* p, const void* hidden, const jn_
       Wg.db = io[g].db[k];
       Wg.M = out;
       Wg.N = in;
-      // dgrad: dZ_{k-1}[row][i] = (sum_o dZ_k[row][o] W[o][i]) * gelu'(Z_{k-1}[row][i]);
-      // its tiles come first, they are the longer ones
-      if (k > 0) {
-        HeadGemm Dg{};
-        Dg.mode = HEAD_DGRAD;
-        Dg.A = dZk(k);
-        Dg.lda = hp.width[k];
-        Dg.B = Hh.W[k];
-        Dg.ldb = in;
-        Dg.C = dZk(k - 1);
-        Dg.ldc = hp.width[k - 1];
-        Dg.Zg = Zk(k - 1);
-        Dg.N = in;
-        Dg.K = out;
-        add_tiles(Dg, g, tm_dyn, (int32_t)head_tiles(in));
+      if (sidx == 0) {
+        Wg.lpart = lpart;
+        Wg.ldp = hp.ldp;
+        Wg.loss = io[g].loss;
+        dt0[nt++] = HeadTile{nd, g, kHeadLossTile, 0};
       }
       add_tiles(Wg, g, (out + kHeadWgradM - 1) / kHeadWgradM, (in + kHeadWgradN - 1) / kHeadWgradN);
-      if (sidx == 0) {
-        HeadGemm Ls{};
-        Ls.mode = HEAD_LOSS;
-        Ls.lpart = lparts[g];
-        Ls.C = io[g].loss;
-        Ls.N = out;
-        add_tiles(Ls, g, 1, 1);
-      }
     }
-    bwd_rng.emplace_back(t0, nt - t0);
+    n.nown = nt - n.first - n.nrow;
+    bwd.push_back(n);
   }
 
   // one upload of both tables
@@ -947,12 +943,12 @@ jn_status heads_run(jn_ctx* c, const jn_packed* p, const void* hidden, const jn_
 
   JN_TRACED(c, JN_OP_POOL, p->T, p->d, p->N,
             launch_pool(s, hidden, p->seqlens, p->cu_seqlens, p->sample_tenant_rank, p->N, p->d, P), "pool");
-  for (const auto& r : fwd_rng)
-    JN_TRACED(c, JN_OP_HEAD_FWD, r.second, 0, 0, launch_head_gemm(s, dd, dt + r.first, r.second, p->tenant_sample_off, true),
-              "head fwd");
-  for (const auto& r : bwd_rng)
-    JN_TRACED(c, JN_OP_HEAD_BWD, r.second, 0, 0, launch_head_gemm(s, dd, dt + r.first, r.second, p->tenant_sample_off, false),
-              "head bwd");
+  for (const HeadLaunch& n : fwd)
+    JN_TRACED(c, JN_OP_HEAD_FWD, n.nrow * (int64_t)tm_dyn, 0, 0,
+              launch_head_gemm(s, dd, dt, n, tm_dyn, p->tenant_sample_off, true), "head fwd");
+  for (const HeadLaunch& n : bwd)
+    JN_TRACED(c, JN_OP_HEAD_BWD, n.nrow * (int64_t)tm_dyn + n.nown, 0, 0,
+              launch_head_gemm(s, dd, dt, n, tm_dyn, p->tenant_sample_off, false), "head bwd");
   return JN_OK;
 }
 
@@ -1955,8 +1951,8 @@ struct jn_infer_plan {
   float* P = nullptr;
   const HeadGemm* dd = nullptr;
   const HeadTile* dt = nullptr;
-  std::vector<std::pair<int32_t, int32_t>> fwd_rng;
-  int32_t max_rows = 0;
+  std::vector<HeadLaunch> fwd;
+  int32_t max_rows = 0, row_tiles = 0;
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
 };
@@ -1994,9 +1990,8 @@ void collector_prefix(const jn_collector* c, int32_t* count, int64_t* samples, b
   *samples = total;
 }
 
-// Forward-only head plan inside `w` (fwd tables only): P | Z_k | H_k | split-K
-// partials | descs | tiles.  A tenant's last layer writes the caller's action
-// buffer (rows from 0) and is never split.
+// Forward-only head plan inside `w` (fwd tables only): P | Z_k | H_k | descs |
+// tiles.  A tenant's last layer writes the caller's action buffer (rows from 0).
 struct HeadFwdLayout {
   int maxL = 0;
   std::vector<int64_t> width;
@@ -2004,7 +1999,7 @@ struct HeadFwdLayout {
   std::vector<size_t> Z, H;
 };
 
-HeadFwdLayout head_fwd_layout(int64_t N, int64_t rows_bound, int64_t d, const jn_head* heads, int32_t G) {
+HeadFwdLayout head_fwd_layout(int64_t N, int64_t d, const jn_head* heads, int32_t G) {
   HeadFwdLayout L;
   size_t o = 0;
   auto take = [&](size_t bytes) {
@@ -2023,11 +2018,10 @@ HeadFwdLayout head_fwd_layout(int64_t N, int64_t rows_bound, int64_t d, const jn
     L.Z[k] = take(4 * N * L.width[k]);
     L.H[k] = take(4 * N * L.width[k]);
   }
-  const int64_t tm_dyn = head_tiles(rows_bound);
   int64_t ntiles = 0, ndesc = 0;
   for (int32_t g = 0; g < G; ++g)
     for (int k = 0; k < heads[g].n_layers; ++k) {
-      ntiles += tm_dyn * head_tiles(heads[g].dims[k + 1]);
+      ntiles += head_tiles(heads[g].dims[k + 1]);
       ++ndesc;
     }
   L.descs = take(sizeof(HeadGemm) * ndesc);
@@ -2073,9 +2067,7 @@ jn_status infer_layout(jn_ctx* c, const jn_request* req, int32_t R, const jn_ten
   }
   L->m = map_layout(p->N, p->T, G, R);
   L->bl = bb_layout(bb, p->T);
-  int32_t max_n = 0;
-  for (int32_t g = 0; g < G; ++g) max_n = std::max(max_n, p->toff[g + 1] - p->toff[g]);
-  L->hl = head_fwd_layout(p->N, max_n, o->d_model, heads, G);
+  L->hl = head_fwd_layout(p->N, o->d_model, heads, G);
   size_t off = 0;
   auto take = [&](size_t bytes) {
     size_t at = off;
@@ -2103,9 +2095,9 @@ jn_status infer_enqueue(jn_ctx* c, const jn_infer_plan* pl) {
   if (st != JN_OK) return st;
   JN_TRACED(c, JN_OP_POOL, pk.T, pk.d, pk.N,
             launch_pool(s, pl->hidden, pk.seqlens, pk.cu_seqlens, pk.sample_tenant_rank, pk.N, pk.d, pl->P), "pool");
-  for (const auto& r : pl->fwd_rng)
-    JN_TRACED(c, JN_OP_HEAD_FWD, r.second, 0, 0,
-              launch_head_gemm(s, pl->dd, pl->dt + r.first, r.second, pk.tenant_sample_off, true), "head fwd");
+  for (const HeadLaunch& n : pl->fwd)
+    JN_TRACED(c, JN_OP_HEAD_FWD, n.nrow * (int64_t)pl->row_tiles, 0, 0,
+              launch_head_gemm(s, pl->dd, pl->dt, n, pl->row_tiles, pk.tenant_sample_off, true), "head fwd");
   return JN_OK;
 }
 
@@ -2220,7 +2212,7 @@ jn_status jn_infer_plan_create(jn_ctx* c, const jn_request* req, int32_t R, cons
   char* hw = w + L.heads;
   pl->P = (float*)(hw + hl.P);
   const int64_t d = o->d_model;
-  const int32_t tm_dyn = (int32_t)head_tiles(tenant_rows_bound(&pl->packed));
+  pl->row_tiles = (int32_t)head_tiles(tenant_rows_bound(&pl->packed));
   std::vector<HeadGemm> descs;
   std::vector<HeadTile> tiles;
   for (int k = 0; k < hl.maxL; ++k) {
@@ -2231,7 +2223,6 @@ jn_status jn_infer_plan_create(jn_ctx* c, const jn_request* req, int32_t R, cons
       const int64_t in = Hh.dims[k], outw = Hh.dims[k + 1];
       const bool last = k + 1 == Hh.n_layers;
       HeadGemm D{};
-      D.mode = HEAD_FWD;
       D.A = (k == 0) ? pl->P : (const float*)(hw + hl.H[k - 1]);
       D.lda = (k == 0) ? d : hl.width[k - 1];
       D.B = Hh.W[k];
@@ -2245,10 +2236,9 @@ jn_status jn_infer_plan_create(jn_ctx* c, const jn_request* req, int32_t R, cons
       D.K = (int32_t)in;
       const int32_t di = (int32_t)descs.size();
       descs.push_back(D);
-      for (int32_t tm = 0; tm < tm_dyn; ++tm)
-        for (int32_t tn = 0; tn < (int32_t)head_tiles(outw); ++tn) tiles.push_back(HeadTile{di, g, tm, tn});
+      for (int32_t tn = 0; tn < (int32_t)head_tiles(outw); ++tn) tiles.push_back(HeadTile{di, g, 0, tn});
     }
-    pl->fwd_rng.emplace_back(t0, (int32_t)tiles.size() - t0);
+    pl->fwd.push_back(HeadLaunch{t0, (int32_t)tiles.size() - t0, 0});
   }
   const size_t dbytes = sizeof(HeadGemm) * descs.size(), tbytes = sizeof(HeadTile) * tiles.size();
   if (hl.descs + dbytes > hl.tiles || hl.tiles + tbytes > hl.total) {

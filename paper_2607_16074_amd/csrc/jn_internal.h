@@ -140,16 +140,14 @@ hipError_t launch_pool(hipStream_t s, const void* hidden, const int32_t* seqlens
                        const int32_t* cu_seqlens, const int32_t* rank, int32_t N, int32_t d,
                        float* pooled);
 
-// One fp32 GEMM of a tenant head, C(m, n) = sum_k A B, by mode:
-//   HEAD_FWD    A = X [row][k], B = W [n][k], C [row][n]
-//   HEAD_DGRAD  A = dZ [row][k], B = W [k][n], C [row][n]
-//   HEAD_WGRAD  A = dZ [row][m], B = X [row][n], C = dW [m][n], contracted over
-//               the tenant's rows
-//   HEAD_LOSS   C[0] = the tenant's loss from its lpart sums
+// One fp32 GEMM of a tenant head, C(m, n) = sum_k A B, of one of three kinds:
+//   FWD    A = X [row][k], B = W [n][k], C [row][n]
+//   DGRAD  A = dZ [row][k], B = W [k][n], C [row][n]
+//   WGRAD  A = dZ [row][m], B = X [row][n], C = dW [m][n], contracted over
+//          the tenant's rows
 // Row operands are tenant-ordered buffers: the kernel starts at the tenant's
 // first row (tenant_sample_off, read on the device), and its row count stands
 // for M (FWD, DGRAD) or K (WGRAD).
-enum HeadMode : int32_t { HEAD_FWD = 0, HEAD_DGRAD = 1, HEAD_WGRAD = 2, HEAD_LOSS = 3 };
 struct HeadGemm {
   const float* A;
   const float* B;
@@ -159,28 +157,38 @@ struct HeadGemm {
   const float* Zg;      // DGRAD: C *= gelu'(Zg) (same layout as C)
   float* db;            // WGRAD: db[m] = sum of A over the rows
   // FWD of a training head's last layer (target set): actions = y, C = dL/dy of
-  // L = mean((y - target)^2), lpart[tile] = sum of squared errors; target and
-  // actions are the tenant's own [n_g][N] buffers
+  // L = mean((y - target)^2), and the tile's sum of squared errors in lpart;
+  // target and actions are the tenant's own [n_g][N] buffers.  The last layer's
+  // WGRAD: lpart, and loss for the tenant's loss tile
   const float* target;
-  float* actions;
-  float* lpart;
+  union {
+    float* actions;
+    float* loss;
+  };
+  float* lpart;         // [row tile of all tenants][ldp]: tenant t starts at off_t / 32 + t
   int64_t lda, ldb, ldc;
   int32_t M, N, K;      // M: WGRAD only; K: FWD and DGRAD only
-  int32_t mode;
   int32_t own_rows;     // FWD: C is the tenant's own buffer (rows from 0)
+  int32_t ldp;
   int32_t reserved;
 };
 struct HeadTile {
   int32_t desc;
   int32_t tenant;
-  int32_t tm;
+  int32_t tm;  // WGRAD (FWD and DGRAD: 0); kHeadLossTile: sum the tenant's lpart
   int32_t tn;
 };
 constexpr int kHeadTile = 32;                        // FWD and DGRAD tiles are 32 x 32
 constexpr int kHeadWgradM = 64, kHeadWgradN = 256;   // WGRAD tiles
-// forward: every tile is HEAD_FWD; otherwise none is.
-hipError_t launch_head_gemm(hipStream_t s, const HeadGemm* descs, const HeadTile* tiles, int32_t n_tiles,
-                            const int32_t* tenant_sample_off, bool forward);
+constexpr int32_t kHeadLossTile = -1;
+// The first nrow of the list are column tiles of FWD or DGRAD, each run for row
+// tiles 0 .. tms - 1; the nown behind them (WGRAD and loss tiles) run once.
+// forward: every tile is FWD; otherwise none is.
+struct HeadLaunch {
+  int32_t first = 0, nrow = 0, nown = 0;
+};
+hipError_t launch_head_gemm(hipStream_t s, const HeadGemm* descs, const HeadTile* tiles, const HeadLaunch& n,
+                            int32_t tms, const int32_t* tenant_sample_off, bool forward);
 
 // ---- action expert (k_expert.hip) ----
 // dst[r][c] = cvt(src[r][c]) for r < src_rows, c < src_cols, else 0; r < rows, c < cols.

@@ -7,6 +7,8 @@
 //              and data gradient (GELU derivative fused); tenant row ranges are
 //              read from the device maps, so the host needs no per-tenant counts
 // Every reduction runs in a fixed order: results are bitwise reproducible.
+#include <algorithm>
+
 #include "jn_device.h"
 #include "jn_internal.h"
 
@@ -94,12 +96,12 @@ hipError_t launch_pool(hipStream_t s, const void* hidden, const int32_t* seqlens
 // A(m = l & 15, k = l >> 4), and which k a step and lane quad stand for, or
 // which column a block and lane stand for, is free as long as both operands
 // agree, so every operand loads whole vectors along its contiguous dimension.
-//   HEAD_FWD    C[m][n] = X[m][k] W[n][k]: 16-byte loads along k (step s of a
-//               16-wide k block is k = 4 quad + s)
-//   HEAD_DGRAD  C[m][n] = dZ[m][k] W[k][n]: 16-byte loads of dZ along k, 8-byte
-//               loads of W along n (block b holds columns 2 j + b)
-//   HEAD_WGRAD  C[m][n] = sum_k dZ[k][m] X[k][n]: 4-byte loads along m, 16-byte
-//               along n (step = 4 rows, one per quad)
+//   FWD    C[m][n] = X[m][k] W[n][k]: 16-byte loads along k (step s of a
+//          16-wide k block is k = 4 quad + s)
+//   DGRAD  C[m][n] = dZ[m][k] W[k][n]: 16-byte loads of dZ along k, 8-byte
+//          loads of W along n (block b holds columns 2 j + b)
+//   WGRAD  C[m][n] = sum_k dZ[k][m] X[k][n]: 4-byte loads along m, 16-byte
+//          along n (step = 4 rows, one per quad)
 // A workgroup has 8 wavefronts.  FWD and DGRAD: a 32 x 32 tile, the waves each
 // take a K range (ceil(K / 8) rounded up to 32) and the eight partial tiles
 // are added through LDS in wave order, so a long contraction needs neither
@@ -124,11 +126,16 @@ constexpr int kHeadWaves = 8;
 constexpr int kHeadDepth = 4;  // slabs in flight per wave
 constexpr int kHeadRed = kHeadTile + 4;  // LDS row stride of a partial tile
 
+// A tenant's first row of the loss sums.
+__device__ __forceinline__ float* head_lpart(const HeadGemm& D, int32_t off, int32_t tenant) {
+  return D.lpart + (int64_t)(off / kHeadTile + tenant) * D.ldp;
+}
+
 // Epilogue of the 32 x 32 tile: sum of the waves' partials, then per element
 // bias, GELU' (DGRAD), GELU copy, or -- a training forward's last layer -- the
 // loss: actions, dL/dy and the tile's sum of squared errors.
 __device__ __forceinline__ void head_finish(const HeadGemm& D, const float* red, float* scratch, int32_t off, int32_t ng,
-                                            int32_t m0, int32_t n0, int32_t M, int32_t tile_slot) {
+                                            int32_t m0, int32_t n0, int32_t M, float* lpart) {
   const int tid = threadIdx.x;
   const int32_t r = tid >> 4, c = (tid & 15) * 2;
   const int32_t m = m0 + r;
@@ -169,7 +176,7 @@ __device__ __forceinline__ void head_finish(const HeadGemm& D, const float* red,
     if (tid == 0) {
       float s = 0.f;
       for (int w = 0; w < kHeadWaves; ++w) s += scratch[w];
-      D.lpart[tile_slot] = s;
+      *lpart = s;
     }
   }
 }
@@ -405,53 +412,75 @@ __device__ __forceinline__ void head_wgrad_tile(const HeadGemm& D, int32_t off, 
   }
 }
 
-// FORWARD: HEAD_FWD tiles only (one workgroup per CU on the 2048-wide heads,
+// FORWARD: FWD tiles only (one workgroup per CU on the 2048-wide heads,
 // its slabs in flight are what hides the weights' latency); otherwise the
 // backward modes, in at most 128 registers so that two workgroups share a CU.
+// Workgroup b < nrow * tms: row tile tm0 + b / nrow of entry b % nrow.  The list
+// holds a column of tiles once, not once per row tile of the largest tenant: 32
+// tenants of up to 4,096 samples would list 110,000 tiles.
 template <bool FORWARD>
 __global__ __launch_bounds__(64 * kHeadWaves, FORWARD ? 2 : 4) void head_gemm_kernel(const HeadGemm* __restrict__ descs,
                                                                                      const HeadTile* __restrict__ tiles,
-                                                                                     const int32_t* __restrict__ tso) {
+                                                                                     const int32_t* __restrict__ tso,
+                                                                                     int32_t nrow, int32_t tms,
+                                                                                     int32_t tm0) {
   __shared__ __attribute__((aligned(16))) float red[kHeadWaves * kHeadTile * kHeadRed];
   __shared__ float scratch[kHeadWaves];
-  const HeadTile tile = tiles[blockIdx.x];
+  const int32_t b = blockIdx.x;
+  const bool own = !FORWARD && b >= nrow * tms;
+  const int32_t row = own ? 0 : b / nrow;
+  const HeadTile tile = tiles[own ? nrow + (b - nrow * tms) : b - row * nrow];
   const int32_t off = tso[tile.tenant], ng = tso[tile.tenant + 1] - off;
   const HeadGemm D = descs[tile.desc];
-  if (!FORWARD && D.mode == HEAD_WGRAD) {
-    head_wgrad_tile(D, off, tile.tm, tile.tn, ng);
-    return;
-  }
-  if (!FORWARD && D.mode == HEAD_LOSS) {  // the tenant's loss from its tiles' sums, in tile order per thread, then a fixed tree
-    const int32_t n = (ng + kHeadTile - 1) / kHeadTile * ((D.N + kHeadTile - 1) / kHeadTile);
+  if (!FORWARD && own) {
+    if (tile.tm != kHeadLossTile) {
+      head_wgrad_tile(D, off, tile.tm, tile.tn, ng);
+      return;
+    }
+    // the tenant's loss from its tiles' sums, in tile order per thread, then a fixed tree
+    const int32_t tn = (D.M + kHeadTile - 1) / kHeadTile, n = (ng + kHeadTile - 1) / kHeadTile * tn;
+    const float* const part = head_lpart(D, off, tile.tenant);
     float s = 0.f;
-    for (int32_t i = threadIdx.x; i < n; i += 64 * kHeadWaves) s += D.lpart[i];
+    for (int32_t i = threadIdx.x; i < n; i += 64 * kHeadWaves) s += part[(int64_t)(i / tn) * D.ldp + i % tn];
     s = wave_sum(s);
     if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = s;
     __syncthreads();
     if (threadIdx.x == 0) {
       float t = 0.f;
       for (int w = 0; w < kHeadWaves; ++w) t += scratch[w];
-      D.C[0] = t / ((float)ng * (float)D.N);
+      D.loss[0] = t / ((float)ng * (float)D.M);
     }
     return;
   }
-  const int32_t m0 = tile.tm * kHeadTile, n0 = tile.tn * kHeadTile;
+  const int32_t tm = tm0 + row, m0 = tm * kHeadTile, n0 = tile.tn * kHeadTile;
   if (m0 >= ng) return;  // tiles past a tenant's row count (upper-bound grid)
   if (FORWARD)
     head_fwd_tile(D, red, off, m0, n0, ng);
   else
     head_dgrad_tile(D, red, off, m0, n0, ng);
   __syncthreads();
-  head_finish(D, red, scratch, D.own_rows ? 0 : off, ng, m0, n0, ng, tile.tm * ((D.N + kHeadTile - 1) / kHeadTile) + tile.tn);
+  head_finish(D, red, scratch, D.own_rows ? 0 : off, ng, m0, n0, ng,
+              head_lpart(D, off, tile.tenant) + (int64_t)tm * D.ldp + tile.tn);
 }
 
-hipError_t launch_head_gemm(hipStream_t s, const HeadGemm* descs, const HeadTile* tiles, int32_t n_tiles,
-                            const int32_t* tso, bool forward) {
-  if (forward)
-    head_gemm_kernel<true><<<n_tiles, 64 * kHeadWaves, 0, s>>>(descs, tiles, tso);
-  else
-    head_gemm_kernel<false><<<n_tiles, 64 * kHeadWaves, 0, s>>>(descs, tiles, tso);
-  return hipGetLastError();
+hipError_t launch_head_gemm(hipStream_t s, const HeadGemm* descs, const HeadTile* tiles, const HeadLaunch& n,
+                            int32_t tms, const int32_t* tso, bool forward) {
+  tiles += n.first;
+  // a dispatch holds at most 2^32 - 1 threads: row tiles beyond it in further launches
+  constexpr int64_t kMost = 0xffffffffll / (64 * kHeadWaves);
+  if (n.nrow + (int64_t)n.nown > kMost) return hipErrorInvalidValue;
+  const int32_t step = n.nrow ? (int32_t)std::min<int64_t>(tms, (kMost - n.nown) / n.nrow) : 0;
+  for (int32_t tm0 = 0, own = n.nown;; own = 0) {
+    const int32_t rows = std::min(step, tms - tm0);
+    const dim3 grid((unsigned)(n.nrow * (int64_t)rows + own));
+    if (forward)
+      head_gemm_kernel<true><<<grid, 64 * kHeadWaves, 0, s>>>(descs, tiles, tso, n.nrow, rows, tm0);
+    else
+      head_gemm_kernel<false><<<grid, 64 * kHeadWaves, 0, s>>>(descs, tiles, tso, n.nrow, rows, tm0);
+    const hipError_t e = hipGetLastError();
+    tm0 += rows;
+    if (e != hipSuccess || n.nrow == 0 || tm0 >= tms) return e;
+  }
 }
 
 }  // namespace jnx

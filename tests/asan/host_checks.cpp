@@ -404,6 +404,114 @@ void check_heads(jn_ctx* c) {
   }
 }
 
+// The allocation-free call's limits, 64 MiB of workspace and 1 MiB of tables:
+// whatever fitted when the tables listed every 32 x 64 tile of every row tile
+// (nine times where its contraction of 512 and more was split in eight) fits.
+struct HeadNeed {
+  size_t tables = 0, total = 0;
+};
+HeadNeed listed_need(const std::vector<std::vector<int32_t>>& dims, int64_t N, int64_t most_rows, int64_t d) {
+  auto up = [](int64_t x, int64_t a) { return (x + a - 1) / a; };
+  auto at = [&](size_t x) { return (x + 255) / 256 * 256; };
+  auto split = [](int64_t K) { return K < 512 ? (int64_t)1 : std::min<int64_t>(8, K / 256); };
+  size_t maxL = 0;
+  for (const auto& x : dims) maxL = std::max(maxL, x.size() - 1);
+  std::vector<int64_t> width(maxL, 0);
+  for (const auto& x : dims)
+    for (size_t k = 0; k + 1 < x.size(); ++k) width[k] = std::max<int64_t>(width[k], x[k + 1]);
+  HeadNeed n;
+  n.total = at(4 * N * d);
+  for (size_t k = 0; k < maxL; ++k) n.total += 3 * at(4 * N * width[k]);
+  const int64_t tm = up(most_rows, 32);
+  int64_t tiles = 0, descs = 0, part = 0;
+  for (const auto& x : dims)
+    for (size_t k = 0; k + 1 < x.size(); ++k) {
+      const int64_t in = x[k], out = x[k + 1], sf = split(in), sd = split(out);
+      tiles += tm * up(out, 64) * (sf + (sf > 1)) + up(out, 32) * up(in, 64) +
+               (k > 0 ? tm * up(in, 64) * (sd + (sd > 1)) : 0);
+      descs += k > 0 ? 3 : 2;
+      if (sf > 1) part = std::max(part, sf * N * width[k]);
+      if (k > 0 && sd > 1) part = std::max(part, sd * N * width[k - 1]);
+    }
+  n.total += at(4 * part) + at(64 * dims.size());
+  n.tables = at(64 * dims.size()) + at(160 * descs) + 16 * tiles;
+  n.total += at(n.tables);
+  return n;
+}
+
+void check_head_limits(jn_ctx* c) {
+  void* some = dev(64);
+  int accepted = 0;
+  auto run = [&](const std::vector<int>& samples, const std::vector<std::vector<int32_t>>& dims) {
+    const int G = (int)samples.size(), d = dims[0][0];
+    Group g;
+    g.opts.d_model = d;
+    g.opts.align = 1;
+    g.ten.assign(G, jn_tenant{0x1234, d, 0});
+    g.lens.resize(G);
+    int64_t N = 0, most = 0;
+    for (int t = 0; t < G; ++t) {
+      g.lens[t].assign(samples[t], 1);
+      jn_request q{};
+      q.tenant = t;
+      q.n_samples = samples[t];
+      q.max_len = 1;
+      q.embeds = some;  // (kernels run nothing here)
+      q.lengths = g.lens[t].data();
+      g.req.push_back(q);
+      N += samples[t];
+      most = std::max<int64_t>(most, samples[t]);
+    }
+    jn_pack_sizes sz{};
+    CHECK(jn_pack_plan(g.req.data(), G, g.ten.data(), G, &g.opts, &sz) == JN_OK);
+    std::vector<char> maps(sz.map_bytes);
+    jn_packed p{};
+    CHECK(jn_pack_maps_host(g.req.data(), G, g.ten.data(), G, &g.opts, maps.data(), maps.size(), &p) == JN_OK);
+    std::vector<const float*> in(8, (const float*)some);
+    std::vector<float*> out(8, (float*)some);
+    std::vector<jn_head> h(G);
+    std::vector<jn_head_io> io(G);
+    for (int t = 0; t < G; ++t) {
+      h[t].n_layers = (int32_t)dims[t].size() - 1;
+      h[t].dims = dims[t].data();
+      h[t].action_dim = dims[t].back();
+      h[t].chunk = 1;
+      h[t].W = in.data();
+      h[t].b = in.data();
+      io[t].targets = (const float*)some;
+      io[t].actions = io[t].loss = (float*)some;
+      io[t].dW = io[t].db = out.data();
+    }
+    size_t ws = 0;
+    CHECK(jn_heads_workspace_size(&p, h.data(), G, &ws) == JN_OK);
+    const HeadNeed need = listed_need(dims, N, most, d);
+    const jn_status st = jn_tenant_heads_fwd_bwd_noalloc(c, &p, some, h.data(), io.data(), G, nullptr);
+    CHECK(st == JN_OK || st == JN_ENOSPACE);
+    if (need.tables <= (1u << 20) && need.total <= JN_HEADS_SCRATCH_BYTES) CHECK(st == JN_OK);
+    accepted += st == JN_OK;
+  };
+  // 32 tenants, the largest of 4,096 samples, widths below 512
+  std::vector<int> samples(32, 1);
+  samples[5] = 4096;
+  run(samples, std::vector<std::vector<int32_t>>(32, {384, 256, 350}));
+  // narrow heads of one and two layers, as many tenants as the tables held
+  run(std::vector<int>(2424, 1), std::vector<std::vector<int32_t>>(2424, {64, 64}));
+  run(std::vector<int>(1100, 1), std::vector<std::vector<int32_t>>(1100, {64, 64, 1}));
+  Rng r(9);
+  for (int it = 0; it < 400; ++it) {
+    const int G = 1 << r.range(0, 10), layers = r.range(1, 3), d = 8 * r.range(1, r.range(0, 1) ? 512 : 40);
+    std::vector<int> s(G);
+    for (int& x : s) x = r.range(1, r.range(0, 2) ? 3 : 33);
+    s[r.next() % G] = 1 << r.range(0, 13);
+    std::vector<std::vector<int32_t>> dims(G, {d});
+    const int wide = 1 << r.range(0, 11);
+    for (auto& x : dims)
+      for (int k = r.range(0, 3) ? 0 : layers - 1; k < layers; ++k) x.push_back(r.range(1, wide));
+    run(s, dims);
+  }
+  CHECK(accepted > 200);
+}
+
 // ------------------------------------------------------------ experts ---
 
 void check_experts(jn_ctx* c, bool flow, bool long_prefix = false) {
@@ -582,6 +690,7 @@ int main() {
   CHECK(jn_ctx_create(&c, nullptr) == JN_OK);
   check_backbones(c);
   check_heads(c);
+  check_head_limits(c);
   check_experts(c, false);
   check_experts(c, true);
   check_experts(c, false, true);
