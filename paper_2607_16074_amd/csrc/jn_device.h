@@ -94,14 +94,19 @@ __device__ __forceinline__ float gelu_fast_f(float u) {
   return u * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(y));
 }
 
-// Its derivative from the same two hardware functions: with e = 2^y and
-// s = 1 / (1 + e), s + s (e s) u (2c + 6c 0.044715 u^2).  Against float64 over
-// [-8, 8] and normal values 4.9e-8 relative (rms), where the tanhf form below
-// has 1.3e-7; the exponent is capped so that e s stays finite.
+// Its derivative from the same two hardware functions: with e = 2^-|y|,
+// p = 1 / (1 + e) and q = e p = 1 - p, the derivative is q (1 - p w) for u < 0 and
+// one minus that for u > 0, w = |u| (2c + 6c 0.044715 u^2).  Written from the
+// small side, so that the last step is its only rounding near 1; |u| is capped in
+// w, where q is zero, so that nothing overflows, and a NaN still comes through q.
+// Against float64, rms over normal values of deviation 0.64 (the pre-activations
+// of a 1024-wide layer with 0.02 weights), 1 and 3: 3.6e-8, 3.6e-8, 3.5e-8
+// relative; the tanhf form below 4.0e-8, 4.5e-8, 13.8e-8.
 __device__ __forceinline__ float gelu_grad_fast_f(float u) {
-  const float y = u * (-2.302208198144325f - 0.1029432395800235f * u * u);
-  const float e = __builtin_amdgcn_exp2f(fminf(y, 126.0f)), s = __builtin_amdgcn_rcpf(1.0f + e);
-  return fmaf(s * (e * s), u * (1.5957691216057308f + 0.21406444881780076f * u * u), s);
+  const float e = __builtin_amdgcn_exp2f(fabsf(u) * (-2.302208198144325f - 0.1029432395800235f * u * u));
+  const float p = __builtin_amdgcn_rcpf(1.0f + e), a = fminf(fabsf(u), 16.0f);
+  const float k = e * p * fmaf(-p, a * (1.5957691216057308f + 0.21406444881780076f * a * a), 1.0f);
+  return u > 0.0f ? 1.0f - k : k;
 }
 
 __device__ __forceinline__ float gelu_grad_f(float u) {
