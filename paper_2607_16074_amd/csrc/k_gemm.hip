@@ -300,7 +300,7 @@ __device__ __forceinline__ void epilogue_f32(const GemmArgs& g, const f32x4 (&ac
         if constexpr (EPI == EPI_GELU_SAVE) {
           *reinterpret_cast<f32x4*>(g.aux + (int64_t)(m + 16 * j + RI * it) * g.ldaux + n) = a;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) y[e] = gelu_fast_f(a[e]);
+          for (int e = 0; e < 4; ++e) y[e] = gelu_exact_f(a[e]);
         } else {
 #pragma unroll
           for (int e = 0; e < 4; ++e) y[e] = a[e] * gelu_grad_fast_f(r[j % AHEAD][it][e]);

@@ -17,7 +17,7 @@ HEADER = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))
 def forms(tmp_path_factory):
     text = open(HEADER).read()
     text = text[text.index("// tanh-form GELU and its derivative"): text.index("}  // namespace jnx")]
-    names = ("gelu_f", "gelu_fast_f", "gelu_grad_f", "gelu_grad_fast_f")
+    names = [n for n in ("gelu_f", "gelu_exact_f", "gelu_grad_f", "gelu_grad_fast_f") if f" {n}(float u)" in text]
     src = ("#include <cmath>\n#define __device__\n#define __forceinline__ inline\n"
            "static float __builtin_amdgcn_exp2f(float x) { return x < -126.f ? 0.f : exp2f(x); }\n"
            "static float __builtin_amdgcn_rcpf(float x) { return 1.f / x; }\n" + text)
@@ -61,3 +61,25 @@ def test_derivative_is_no_less_exact_than_the_tanhf_form(forms, sigma):
     ref = exact(u.astype(np.float64))[1]
     fast, form = (np.linalg.norm(forms(n, u) - ref) for n in ("gelu_grad_fast_f", "gelu_grad_f"))
     assert fast <= form, (fast / np.linalg.norm(ref), form / np.linalg.norm(ref))
+
+
+def test_value_of_large_values(forms):
+    big = np.array([12, 20, 1e3, 1e6, 1e13, 1e30, 3e38, np.inf], dtype=np.float32)
+    assert np.array_equal(forms("gelu_exact_f", big), big)
+    assert np.array_equal(np.isnan(forms("gelu_exact_f", -big)), np.isinf(big))  # as the tanhf form
+    assert np.max(np.abs(forms("gelu_exact_f", -big[:-1]))) < 1e-34
+    assert np.isnan(forms("gelu_exact_f", [np.nan]))
+
+
+@pytest.mark.parametrize("sigma", [0.3, 0.5, 0.64, 1.0, 3.0])
+def test_value_is_no_less_exact_than_the_tanhf_form(forms, sigma):
+    u = np.random.default_rng(1).normal(0, sigma, 1 << 20).astype(np.float32)
+    ref = exact(u.astype(np.float64))[0]
+    fast, form = (np.linalg.norm(forms(n, u) - ref) for n in ("gelu_exact_f", "gelu_f"))
+    assert fast <= form, (fast / np.linalg.norm(ref), form / np.linalg.norm(ref))
+
+
+def test_the_saved_gelu_takes_that_form():
+    gemm = open(os.path.join(os.path.dirname(HEADER), "k_gemm.hip")).read()
+    at = gemm.index("EPI == EPI_GELU_SAVE) {")
+    assert "gelu_exact_f(" in gemm[at: at + 400]
