@@ -150,13 +150,13 @@ hipError_t traced(jn_ctx* c, int32_t op, int64_t M, int64_t N, int64_t K, F&& la
 #define JN_TRACED(ctx, op, M, N, K, call, what) \
   JN_HIP(ctx, traced(ctx, op, M, N, K, [&]() { return (call); }), what)
 
-// Stage `bytes` of host data in pinned memory and copy it to `dst` on the
-// context stream.  Slots are reused round-robin; a slot is rewritten only
+// Stage `bytes` of host data in pinned memory and copy it to `dst` (its last
+// `tail` bytes to `tail_dst`) on the context stream.  Slots are reused round-robin; a slot is rewritten only
 // after the copy that last read it has completed.  When the next slot's copy
 // is still in flight the ring grows by a slot instead (up to kMaxSlots), so
 // the host does not wait on the device while the device runs behind by fewer
 // than kMaxSlots uploads.
-jn_status stage_copy(jn_ctx* c, void* dst, const void* src, size_t bytes) {
+jn_status stage_copy(jn_ctx* c, void* dst, const void* src, size_t bytes, void* tail_dst = nullptr, size_t tail = 0) {
   if (bytes == 0) return JN_OK;
   if (c->slots[c->next].pending && hipEventQuery(c->slots[c->next].ev) == hipErrorNotReady &&
       c->slots.size() < (size_t)kMaxSlots) {
@@ -179,7 +179,7 @@ jn_status stage_copy(jn_ctx* c, void* dst, const void* src, size_t bytes) {
     s.cap = cap;
   }
   std::memcpy(s.host, src, bytes);
-  JN_HIP(c, launch_upload(c->stream, dst, s.host, bytes), "table upload");
+  JN_HIP(c, launch_upload(c->stream, dst, s.host, bytes - tail, tail_dst, tail), "table upload");
   JN_HIP(c, hipEventRecord(s.ev, c->stream), "hipEventRecord(staging)");
   s.pending = true;
   return JN_OK;
@@ -197,7 +197,7 @@ jn_status stage_copy_fixed(jn_ctx* c, void* dst, const void* src, size_t bytes) 
     c->fixed_pending = false;
   }
   std::memcpy(c->fixed_host, src, bytes);
-  JN_HIP(c, launch_upload(c->stream, dst, c->fixed_host, bytes), "table upload");
+  JN_HIP(c, launch_upload(c->stream, dst, c->fixed_host, bytes, nullptr, 0), "table upload");
   JN_HIP(c, hipEventRecord(c->fixed_ev, c->stream), "hipEventRecord(fixed staging)");
   c->fixed_pending = true;
   return JN_OK;
@@ -225,9 +225,9 @@ MapLayout map_layout(int64_t N, int64_t T, int64_t G, int64_t R) {
   m.toff = take(4 * (G + 1));
   m.tperm = take(4 * N);
   m.trank = take(4 * N);
-  m.reqtab = take(sizeof(ReqEntry) * R);  // the host's tables are one piece: one upload
   m.tsamp = take(4 * T);
   m.tpos = take(4 * T);
+  m.reqtab = take(sizeof(ReqEntry) * R);
   m.total = o;
   return m;
 }
@@ -338,9 +338,10 @@ void fill_packed(jn_packed* out, char* base, const MapLayout& m, const Plan& p, 
   out->req_table = base + m.reqtab;
 }
 
-// Host image of the maps region [0, m.tsamp) (the N/G-sized arrays).
-std::vector<char> host_head_image(const MapLayout& m, const Plan& p, const jn_request* req) {
-  std::vector<char> img(m.tsamp, 0);
+// Host image of the tables the host plans: the maps region [0, m.tsamp) (the
+// N/G-sized arrays), then the request table, which belongs behind the token maps.
+std::vector<char> host_image(const MapLayout& m, const Plan& p, const jn_request* req) {
+  std::vector<char> img(m.tsamp + sizeof(ReqEntry) * p.req_first.size(), 0);
   auto put = [&](size_t off, const std::vector<int32_t>& v) {
     if (!v.empty()) std::memcpy(img.data() + off, v.data(), 4 * v.size());
   };
@@ -352,7 +353,7 @@ std::vector<char> host_head_image(const MapLayout& m, const Plan& p, const jn_re
   put(m.toff, p.toff);
   put(m.tperm, p.tperm);
   put(m.trank, p.trank);
-  ReqEntry* rt = reinterpret_cast<ReqEntry*>(img.data() + m.reqtab);
+  ReqEntry* rt = reinterpret_cast<ReqEntry*>(img.data() + m.tsamp);
   for (size_t r = 0; r < p.req_first.size(); ++r)
     rt[r] = ReqEntry{req[r].embeds, nullptr, req[r].max_len, req[r].n_samples, p.req_first[r], 0};
   return img;
@@ -503,10 +504,11 @@ jn_status jn_pack_maps_host(const jn_request* req, int32_t R, const jn_tenant* t
   if (st != JN_OK) return st;
   MapLayout m = map_layout(p.N, p.T, G, R);
   if (map_bytes < m.total) return JN_ENOSPACE;
-  const std::vector<char> img = host_head_image(m, p, req);
+  const std::vector<char> img = host_image(m, p, req);
   char* base = (char*)host_maps;
   std::memset(base, 0, m.total);
-  std::memcpy(base, img.data(), img.size());
+  std::memcpy(base, img.data(), m.tsamp);
+  std::memcpy(base + m.reqtab, img.data() + m.tsamp, img.size() - m.tsamp);
   int32_t* ts = (int32_t*)(base + m.tsamp);
   int32_t* tp = (int32_t*)(base + m.tpos);
   for (int32_t i = 0; i < p.N; ++i) {
@@ -538,9 +540,9 @@ jn_status jn_pack_group(jn_ctx* c, const jn_request* req, int32_t R, const jn_te
     if (((uintptr_t)req[r].embeds) % 16 != 0) return fail(c, JN_EUNSUPPORTED, "request %d embeds not 16-byte aligned", r);
   if (((uintptr_t)tokens) % 16 != 0) return fail(c, JN_EUNSUPPORTED, "token buffer not 16-byte aligned");
 
-  const std::vector<char> img = host_head_image(m, p, req);
+  const std::vector<char> img = host_image(m, p, req);
   char* base = (char*)maps;
-  st = stage_copy(c, base, img.data(), img.size());
+  st = stage_copy(c, base, img.data(), img.size(), base + m.reqtab, img.size() - m.tsamp);
   if (st != JN_OK) return st;
   jn_packed tmp;
   fill_packed(&tmp, base, m, p, R, G, o);
@@ -2249,11 +2251,11 @@ jn_status jn_infer_plan_create(jn_ctx* c, const jn_request* req, int32_t R, cons
   pl->dt = (const HeadTile*)(hw + hl.tiles);
 
   // one-time uploads: maps, request table, head tables
-  const std::vector<char> img = host_head_image(L.m, p, req);
+  const std::vector<char> img = host_image(L.m, p, req);
   std::vector<char> himg(hl.total - hl.descs, 0);
   std::memcpy(himg.data(), descs.data(), dbytes);
   std::memcpy(himg.data() + (hl.tiles - hl.descs), tiles.data(), tbytes);
-  st = stage_copy(c, maps, img.data(), img.size());
+  st = stage_copy(c, maps, img.data(), img.size(), maps + L.m.reqtab, img.size() - L.m.tsamp);
   if (st == JN_OK) st = stage_copy(c, hw + hl.descs, himg.data(), hl.tiles - hl.descs + tbytes);
   if (st != JN_OK) {
     delete pl;

@@ -25,9 +25,10 @@ static_assert(sizeof(ReqEntry) == 32, "ReqEntry layout");
 // ------------------------------------------------------------ launchers ---
 // All launchers enqueue on `s`; shapes were validated by the caller.
 
-// Table of `bytes` at `src` (pinned, coherent) to device memory.
+// Table of `bytes` at `src` (pinned, coherent) to device memory, and the `tail`
+// bytes behind it to `tail_dst`.
 constexpr size_t kUploadBytes = 64 << 10;
-hipError_t launch_upload(hipStream_t s, void* dst, const void* src, size_t bytes);
+hipError_t launch_upload(hipStream_t s, void* dst, const void* src, size_t bytes, void* tail_dst, size_t tail);
 
 hipError_t launch_pack(hipStream_t s, const ReqEntry* req_table, const int32_t* sample_request,
                        const int32_t* sample_local, const int32_t* seqlens, const int32_t* cu_seqlens,

@@ -17,17 +17,26 @@ constexpr int kFlat = 512;  // elements (16 or 4 bytes) a block moves at a time
 // 217, one tenant's expert step 816 -> 792).  Above 64 KB the copy's bandwidth
 // counts.
 // System-scope loads: a staging buffer is rewritten by the host between calls.
-__global__ __launch_bounds__(256) void upload_kernel(uint32_t* __restrict__ dst, const uint32_t* src, int32_t words) {
+__global__ __launch_bounds__(256) void upload_kernel(uint32_t* __restrict__ dst, const uint32_t* src, int32_t words,
+                                                     uint32_t* __restrict__ tail_dst, int32_t all) {
   const int32_t i = blockIdx.x * 256 + threadIdx.x;
-  if (i < words) dst[i] = __hip_atomic_load(src + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (i >= all) return;
+  const uint32_t v = __hip_atomic_load(src + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  if (i < words)
+    dst[i] = v;
+  else
+    tail_dst[i - words] = v;
 }
 
-hipError_t launch_upload(hipStream_t s, void* dst, const void* src, size_t bytes) {
-  if (bytes > kUploadBytes || bytes % 4 != 0 || (uintptr_t)dst % 4 != 0)
-    return hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
-  const int32_t words = (int32_t)(bytes / 4);
-  upload_kernel<<<(words + 255) / 256, 256, 0, s>>>(static_cast<uint32_t*>(dst), static_cast<const uint32_t*>(src),
-                                                    words);
+hipError_t launch_upload(hipStream_t s, void* dst, const void* src, size_t bytes, void* tail_dst, size_t tail) {
+  if (bytes + tail > kUploadBytes || (bytes | tail) % 4 != 0 || ((uintptr_t)dst | (uintptr_t)tail_dst) % 4 != 0) {
+    const hipError_t e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
+    if (e != hipSuccess || tail == 0) return e;
+    return hipMemcpyAsync(tail_dst, static_cast<const char*>(src) + bytes, tail, hipMemcpyHostToDevice, s);
+  }
+  const int32_t words = (int32_t)(bytes / 4), all = (int32_t)((bytes + tail) / 4);
+  upload_kernel<<<(all + 255) / 256, 256, 0, s>>>(static_cast<uint32_t*>(dst), static_cast<const uint32_t*>(src), words,
+                                                  static_cast<uint32_t*>(tail_dst), all);
   return hipGetLastError();
 }
 

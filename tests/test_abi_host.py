@@ -94,6 +94,28 @@ def test_host_plan_bit_exact(lib, case):
     assert sz.token_bytes == ref["T"] * d * 2 and sz.max_seqlen == max(max(l) for l in lens)
 
 
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_maps_lie_in_the_documented_order(lib, case):
+    """The header promises a caller the arrays' order in its buffer: each starts
+    on the next 256-byte boundary, the request table last."""
+    tn, lens, mls, G, align = CASES[case]
+    text = open(HEADER).read()
+    order = re.search(r"in the layout jn_pack_group uses on the device:\n(.*?),\s+each", text, re.S).group(1)
+    names = [x.strip() for x in re.sub(r"\n \*", " ", order).lstrip(" *").split("|")]
+    assert names[-1].startswith("request table")
+    abi, d = lib._abi, 128
+    ra, keep = lib._requests(_reqs(lib, tn, lens, mls))
+    ta, o, out = lib._tenants([lib.Tenant(7, d)] * G), lib._opts(d, align), abi.jn_packed()
+    buf = np.zeros(int(lib.jn_pack_plan(_reqs(lib, tn, lens, mls), [lib.Tenant(7, d)] * G, d, align).map_bytes), np.uint8)
+    assert lib._lib.jn_pack_maps_host(ra, len(tn), ta, G, C.byref(o), buf.ctypes.data_as(C.c_void_p), buf.nbytes,
+                                      C.byref(out)) == abi.JN_OK
+    at = 0
+    for name in [n.split()[0] for n in names[:-1]]:
+        assert C.cast(getattr(out, name), C.c_void_p).value - buf.ctypes.data == at, name
+        at += -(-4 * out.map_len(name) // 256) * 256
+    assert out.req_table - buf.ctypes.data == at and at + -(-32 * len(tn) // 256) * 256 == buf.nbytes
+
+
 def test_host_plan_random_bit_exact(lib):
     rng = np.random.default_rng(7)
     for trial in range(20):
