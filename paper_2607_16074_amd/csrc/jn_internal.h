@@ -182,6 +182,7 @@ struct HeadTile {
 constexpr int kHeadTile = 32;                        // FWD and DGRAD tiles are 32 x 32
 constexpr int kHeadWgradM = 64, kHeadWgradN = 256;   // WGRAD tiles
 constexpr int32_t kHeadLossTile = -1;
+constexpr int32_t kHeadLongRows = 256;               // up to here no WGRAD is cut into K ranges
 // The first nrow of the list are column tiles of FWD or DGRAD, each run for row
 // tiles 0 .. tms - 1; the nown behind them (WGRAD and loss tiles) run once.
 // forward: every tile is FWD; otherwise none is.

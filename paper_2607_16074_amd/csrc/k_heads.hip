@@ -106,8 +106,11 @@ hipError_t launch_pool(hipStream_t s, const void* hidden, const int32_t* seqlens
 // take a K range (ceil(K / 8) rounded up to 32) and the eight partial tiles
 // are added through LDS in wave order, so a long contraction needs neither
 // partial sums in memory nor a second launch.  WGRAD (K is a tenant's row
-// count): 64 x 256 tile, 32 x 64 per wave.  The order of every sum depends on
-// K alone, so a tenant's bits do not depend on the batch.
+// count): 64 x 256 tile, 32 x 64 per wave over all rows; long contractions
+// (head_long_rows) by eight workgroups, 32 x 64 each, the waves again sharing K: in
+// one wave they are a serial chain that a few workgroups walk on an empty chip.
+// The order of every sum depends on the layer's sizes and the tenant's rows alone,
+// so a tenant's bits do not depend on the batch.
 // Bound by the weights' and gradients' HBM traffic (one read, one write) and by
 // launches: with LDS staging, K ranges as workgroups and a reduction launch
 // after each, the heads of 8 tenants x 32 rows on 2,048-wide features took
@@ -179,6 +182,18 @@ __device__ __forceinline__ void head_finish(const HeadGemm& D, const float* red,
       *lpart = s;
     }
   }
+}
+
+// Weight gradients over more rows than this are shared by a workgroup's waves.  One
+// tenant's short contractions want the wide tiles' less traffic and its long ones
+// more workgroups, small gradients sooner: 768 x 256 over 256, 512 and 4,096 rows
+// in the whole call 80, 125 and 794 us unshared, 41, 48 and 179 shared; 2048 x 1024 x
+// 1024 over 512 and 4,096 264 and 1,796, 174 and 1,068 -- but eight tenants of it over
+// 64, 275 and 1,000 rows (16 tenants) 205, 711 and 4,644 unshared, 252, 736 and 4,617
+// shared.  The line is the layer's own, so a tenant's bits do not depend on its batch.
+__device__ __forceinline__ int32_t head_long_rows(int32_t M, int32_t N) {
+  const int32_t tiles = (M + kHeadWgradM - 1) / kHeadWgradM * ((N + kHeadWgradN - 1) / kHeadWgradN);
+  return tiles > 32 ? 2 * kHeadLongRows : kHeadLongRows;
 }
 
 // The K range of a wave; its whole slabs of S end at `kw` (kb where the tile
@@ -319,14 +334,23 @@ __device__ __forceinline__ void head_dgrad_tile(const HeadGemm& D, float* red, i
   }
 }
 
-__device__ __forceinline__ void head_wgrad_tile(const HeadGemm& D, int32_t off, int32_t tm, int32_t tn, int32_t K) {
+// piece: which 32 x 64 of the tile; where `shared`, the whole workgroup's, each wave
+// a K range, else the wave's own over all rows.
+__device__ __forceinline__ void head_wgrad_tile(const HeadGemm& D, float* red, int32_t off, int32_t tm, int32_t tn,
+                                                int32_t rows, int piece, bool shared) {
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int j = lane & 15, quad = lane >> 4;
   const int32_t M = D.M, N = D.N;
-  const int32_t m0 = tm * kHeadWgradM + 32 * (wave >> 2), n0 = tn * kHeadWgradN + 64 * (wave & 3);
+  const int32_t m0 = tm * kHeadWgradM + 32 * (piece >> 2), n0 = tn * kHeadWgradN + 64 * (piece & 3);
   if (m0 >= M || n0 >= N) return;
+  int32_t K = rows, kb = 0;  // the wave's rows, from off + kb
+  if (shared) {
+    const int32_t kc = ((rows + kHeadWaves - 1) / kHeadWaves + 15) / 16 * 16;
+    kb = min(rows, wave * kc);
+    K = min(kc, rows - kb);
+  }
   const int64_t lda = D.lda, ldb = D.ldb;
-  const float *const A = D.A + (int64_t)off * lda, *const B = D.B + (int64_t)off * ldb;
+  const float *const A = D.A + (int64_t)(off + kb) * lda, *const B = D.B + (int64_t)(off + kb) * ldb;
   const uint32_t a0 = quad * (uint32_t)lda + min(m0 + j, M - 1), a1 = quad * (uint32_t)lda + min(m0 + 16 + j, M - 1);
   const int cj = n0 + 4 * ((j >> 2) + 4 * (j & 3));  // this lane's four columns
   const uint32_t bo = quad * (uint32_t)ldb + cj;
@@ -386,6 +410,48 @@ __device__ __forceinline__ void head_wgrad_tile(const HeadGemm& D, int32_t off, 
   }
   // lane: columns n0 + 16 e + 4 quad + y of rows m0 + 16 x + j (the loads' column
   // order makes a store instruction cover 64 contiguous bytes of 16 rows)
+  float bias[2];
+#pragma unroll
+  for (int x = 0; x < 2; ++x) bias[x] = sum_xor32(sum_xor16(cs[x]));
+  if (shared) {
+    // the waves' partials, added in wave order: 16 rows at a time, then the bias
+    constexpr int kLd = 68;  // LDS row stride
+    static_assert(kHeadWaves * 16 * kLd <= kHeadWaves * kHeadTile * kHeadRed, "partials fit");
+    const int t = threadIdx.x, c = 2 * (t & 31), r = t >> 5;
+#pragma unroll
+    for (int x = 0; x < 2; ++x) {
+      __syncthreads();
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        *reinterpret_cast<f32x4h*>(red + (wave * 16 + j) * kLd + 16 * e + 4 * quad) =
+            f32x4h{acc[0][x][e], acc[1][x][e], acc[2][x][e], acc[3][x][e]};
+      __syncthreads();
+      const int32_t m = m0 + 16 * x + r;
+      if (m < M) {
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          float v = red[r * kLd + c + i];
+#pragma unroll
+          for (int w = 1; w < kHeadWaves; ++w) v += red[(w * 16 + r) * kLd + c + i];
+          if (n0 + c + i < N) D.C[(int64_t)m * D.ldc + n0 + c + i] = v;
+        }
+      }
+    }
+    if (n0 == 0) {
+      __syncthreads();
+#pragma unroll
+      for (int x = 0; x < 2; ++x)
+        if (quad == 0) red[wave * 32 + 16 * x + j] = bias[x];
+      __syncthreads();
+      if (t < 32 && m0 + t < M) {
+        float v = red[t];
+#pragma unroll
+        for (int w = 1; w < kHeadWaves; ++w) v += red[w * 32 + t];
+        D.db[m0 + t] = v;
+      }
+    }
+    return;
+  }
 #pragma unroll
   for (int x = 0; x < 2; ++x) {
     const int32_t m = m0 + 16 * x + j;
@@ -402,13 +468,7 @@ __device__ __forceinline__ void head_wgrad_tile(const HeadGemm& D, int32_t off, 
         for (int y = 0; y < 4; ++y)
           if (n0 + 16 * e + 4 * quad + y < N) p[16 * e + y] = acc[y][x][e];
     }
-  }
-  if (n0 == 0) {
-#pragma unroll
-    for (int x = 0; x < 2; ++x) {
-      const float v = sum_xor32(sum_xor16(cs[x]));
-      if (quad == 0 && m0 + 16 * x + j < M) D.db[m0 + 16 * x + j] = v;
-    }
+    if (n0 == 0 && quad == 0) D.db[m] = bias[x];
   }
 }
 
@@ -423,18 +483,25 @@ __global__ __launch_bounds__(64 * kHeadWaves, FORWARD ? 2 : 4) void head_gemm_ke
                                                                                      const HeadTile* __restrict__ tiles,
                                                                                      const int32_t* __restrict__ tso,
                                                                                      int32_t nrow, int32_t tms,
-                                                                                     int32_t tm0) {
+                                                                                     int32_t tm0, int32_t nown, int32_t parts) {
   __shared__ __attribute__((aligned(16))) float red[kHeadWaves * kHeadTile * kHeadRed];
   __shared__ float scratch[kHeadWaves];
   const int32_t b = blockIdx.x;
   const bool own = !FORWARD && b >= nrow * tms;
   const int32_t row = own ? 0 : b / nrow;
-  const HeadTile tile = tiles[own ? nrow + (b - nrow * tms) : b - row * nrow];
+  // own tiles: `parts` workgroups of each, tile fastest (workgroups are dealt to the
+  // XCDs in turn: where only the first of a tile's eight has work, piece fastest
+  // would leave seven XCDs idle)
+  const int32_t at = b - nrow * tms, piece = own ? at / nown : 0;
+  const HeadTile tile = tiles[own ? nrow + at - piece * nown : b - row * nrow];
   const int32_t off = tso[tile.tenant], ng = tso[tile.tenant + 1] - off;
   const HeadGemm D = descs[tile.desc];
   if (!FORWARD && own) {
+    const bool shared = parts > 1 && ng > head_long_rows(D.M, D.N);
+    if (piece > 0 && (!shared || tile.tm == kHeadLossTile)) return;
     if (tile.tm != kHeadLossTile) {
-      head_wgrad_tile(D, off, tile.tm, tile.tn, ng);
+      head_wgrad_tile(D, red, off, tile.tm, tile.tn, ng, shared ? piece : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6),
+                      shared);
       return;
     }
     // the tenant's loss from its tiles' sums, in tile order per thread, then a fixed tree
@@ -469,14 +536,16 @@ hipError_t launch_head_gemm(hipStream_t s, const HeadGemm* descs, const HeadTile
   // a dispatch holds at most 2^32 - 1 threads: row tiles beyond it in further launches
   constexpr int64_t kMost = 0xffffffffll / (64 * kHeadWaves);
   if (n.nrow + (int64_t)n.nown > kMost) return hipErrorInvalidValue;
-  const int32_t step = n.nrow ? (int32_t)std::min<int64_t>(tms, (kMost - n.nown) / n.nrow) : 0;
-  for (int32_t tm0 = 0, own = n.nown;; own = 0) {
+  const bool longer = tms * (int64_t)kHeadTile > kHeadLongRows && n.nrow + (int64_t)n.nown * kHeadWaves <= kMost;
+  const int32_t parts = longer ? kHeadWaves : 1, all = n.nown * parts;
+  const int32_t step = n.nrow ? (int32_t)std::min<int64_t>(tms, (kMost - all) / n.nrow) : 0;
+  for (int32_t tm0 = 0, own = all;; own = 0) {
     const int32_t rows = std::min(step, tms - tm0);
     const dim3 grid((unsigned)(n.nrow * (int64_t)rows + own));
     if (forward)
-      head_gemm_kernel<true><<<grid, 64 * kHeadWaves, 0, s>>>(descs, tiles, tso, n.nrow, rows, tm0);
+      head_gemm_kernel<true><<<grid, 64 * kHeadWaves, 0, s>>>(descs, tiles, tso, n.nrow, rows, tm0, n.nown, parts);
     else
-      head_gemm_kernel<false><<<grid, 64 * kHeadWaves, 0, s>>>(descs, tiles, tso, n.nrow, rows, tm0);
+      head_gemm_kernel<false><<<grid, 64 * kHeadWaves, 0, s>>>(descs, tiles, tso, n.nrow, rows, tm0, n.nown, parts);
     const hipError_t e = hipGetLastError();
     tm0 += rows;
     if (e != hipSuccess || n.nrow == 0 || tm0 >= tms) return e;

@@ -15,6 +15,8 @@ extern "C" {
 
 long long jn_fake_launches = 0;
 long long jn_fake_graph_launches = 0;
+long long jn_fake_workgroups = 0;       // of all launches
+long long jn_fake_last_workgroups = 0;  // of the last one
 
 static dim3 g_grid, g_block;
 static size_t g_shm = 0;
@@ -62,6 +64,8 @@ hipError_t hipLaunchKernel(const void* fn, dim3 grid, dim3 block, void** args, s
   if (!fn || !args) std::abort();
   check_launch(grid, block, shm);
   ++jn_fake_launches;
+  jn_fake_last_workgroups = (long long)grid.x * grid.y * grid.z;
+  jn_fake_workgroups += jn_fake_last_workgroups;
   return hipSuccess;
 }
 

@@ -20,6 +20,8 @@
 
 extern "C" long long jn_fake_launches;
 extern "C" long long jn_fake_graph_launches;
+extern "C" long long jn_fake_workgroups;
+extern "C" long long jn_fake_last_workgroups;
 
 namespace {
 
@@ -490,6 +492,10 @@ void check_head_limits(jn_ctx* c) {
     if (need.tables <= (1u << 20) && need.total <= JN_HEADS_SCRATCH_BYTES) CHECK(st == JN_OK);
     accepted += st == JN_OK;
   };
+  // one tenant's long contraction is not left to the few tiles of its gradient
+  // (256 x 384 and, last, none but them)
+  run({4096}, {{384, 256, 350}});
+  CHECK(jn_fake_last_workgroups >= 64);
   // 32 tenants, the largest of 4,096 samples, widths below 512
   std::vector<int> samples(32, 1);
   samples[5] = 4096;
