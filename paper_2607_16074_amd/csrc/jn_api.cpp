@@ -550,7 +550,7 @@ jn_status jn_pack_group(jn_ctx* c, const jn_request* req, int32_t R, const jn_te
   tmp.tokens = tokens;
   JN_TRACED(c, JN_OP_PACK, p.T, o->d_model, 0,
             launch_pack(c->stream, (const ReqEntry*)tmp.req_table, tmp.sample_request, tmp.sample_local,
-                        tmp.seqlens, tmp.cu_seqlens, p.N, o->d_model, o->align, p.max_rows, tokens,
+                        tmp.seqlens, tmp.cu_seqlens, p.N, p.T, o->d_model, p.max_rows, tokens,
                         tmp.token_sample, tmp.token_pos),
             "pack kernel");
   *out = tmp;
@@ -990,7 +990,6 @@ jn_status jn_unpack(jn_ctx* c, const jn_packed* p, const jn_request* req, int32_
   if (((uintptr_t)rows) % 4 != 0) return fail(c, JN_EUNSUPPORTED, "rows not 4-byte aligned");
   std::vector<ReqEntry> rt(R);
   int64_t n = 0;
-  int32_t mreq = 0;
   bool vec16 = row_bytes % 16 == 0 && ((uintptr_t)rows) % 16 == 0;
   for (int32_t r = 0; r < R; ++r) {
     if (!req_out[r]) return fail(c, JN_EINVAL, "request %d output is null", r);
@@ -999,16 +998,18 @@ jn_status jn_unpack(jn_ctx* c, const jn_packed* p, const jn_request* req, int32_
     if (req[r].n_samples < 1 || req[r].max_len < 1) return fail(c, JN_ESHAPE, "request %d shape", r);
     rt[r] = ReqEntry{req[r].embeds, req_out[r], req[r].max_len, req[r].n_samples, (int32_t)n, 0};
     n += req[r].n_samples;
-    mreq = std::max(mreq, req[r].max_len);
   }
   if (n != p->N) return fail(c, JN_ESHAPE, "requests hold %lld samples, packed batch %d", (long long)n, p->N);
   if (request_signature(req, R) != p->req_sig)
     return fail(c, JN_ESHAPE, "requests differ from those the batch was packed from (sample counts or max_len)");
+  int32_t per = 0;
+  const int32_t blocks = unpack_blocks(rt.data(), R, p->N, (int64_t)row_bytes, vec16, &per);
   jn_status st = stage_copy(c, p->req_table, rt.data(), sizeof(ReqEntry) * R);
   if (st != JN_OK) return st;
-  JN_TRACED(c, JN_OP_UNPACK, p->T, (int64_t)row_bytes, 0, launch_unpack(c->stream, (const ReqEntry*)p->req_table, p->sample_request, p->sample_local,
-                          p->seqlens, p->cu_seqlens, p->N, mreq, rows, (int64_t)row_bytes, vec16),
-         "unpack kernel");
+  JN_TRACED(c, JN_OP_UNPACK, p->T, (int64_t)row_bytes, 0,
+            launch_unpack(c->stream, (const ReqEntry*)p->req_table, R, p->sample_request, p->sample_local, p->seqlens,
+                          p->cu_seqlens, p->N, blocks, per, rows, (int64_t)row_bytes, vec16),
+            "unpack kernel");
   return JN_OK;
 }
 
@@ -2090,7 +2091,7 @@ jn_status infer_enqueue(jn_ctx* c, const jn_infer_plan* pl) {
   hipStream_t s = c->stream;
   JN_TRACED(c, JN_OP_PACK, pk.T, pk.d, 0,
             launch_pack(s, (const ReqEntry*)pk.req_table, pk.sample_request, pk.sample_local, pk.seqlens,
-                        pk.cu_seqlens, pk.N, pk.d, pk.align, pl->max_rows, pk.tokens, pk.token_sample,
+                        pk.cu_seqlens, pk.N, pk.T, pk.d, pl->max_rows, pk.tokens, pk.token_sample,
                         pk.token_pos),
             "pack kernel");
   jn_status st = jn_backbone_forward(c, &pl->bb, &pk, pl->hidden, pl->bb_ws, pl->bb_bytes);

@@ -79,6 +79,16 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
+// Last k < n with at[k] <= x (at ascending, at[0] <= x).
+__device__ __forceinline__ int32_t last_at(const int32_t* at, int32_t n, int32_t x) {
+  int32_t lo = 0, hi = n - 1;
+  while (lo < hi) {
+    const int32_t mid = (lo + hi + 1) >> 1;
+    if (at[mid] <= x) lo = mid; else hi = mid - 1;
+  }
+  return lo;
+}
+
 // tanh-form GELU and its derivative, fp32.
 __device__ __forceinline__ float gelu_f(float u) {
   const float c = 0.7978845608028654f;  // sqrt(2/pi)

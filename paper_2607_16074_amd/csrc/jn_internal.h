@@ -18,7 +18,7 @@ struct ReqEntry {
   int32_t max_len;
   int32_t n;
   int32_t first;       // packed index of the request's first sample
-  int32_t reserved;
+  int32_t block;       // ragged unpack: the request's first workgroup
 };
 static_assert(sizeof(ReqEntry) == 32, "ReqEntry layout");
 
@@ -30,14 +30,32 @@ static_assert(sizeof(ReqEntry) == 32, "ReqEntry layout");
 constexpr size_t kUploadBytes = 64 << 10;
 hipError_t launch_upload(hipStream_t s, void* dst, const void* src, size_t bytes, void* tail_dst, size_t tail);
 
+// Copies of N samples' runs, `all` elements together, the longest `most`: blocks
+// for every sample, of `piece` elements at a time, or 0 for a walk over the samples'
+// common order.  A workgroup that finds nothing costs a ninth of one that moves 8
+// KB (0.3 ns, 2.7), so a sample gets the blocks of twice the mean at most and longer
+// ones go round again, up to four times; beyond that the walk, whose searches
+// cost about as much as the copy of short runs.
+constexpr int32_t kMostBlocks = 0xffffff;  // of 256 threads: a dispatch holds 2^32 - 1 threads
+inline int32_t most_per(int32_t N) { return kMostBlocks / N > 1 ? kMostBlocks / N : 1; }
+inline int32_t spread_blocks(int64_t most, int64_t all, int32_t N, int64_t piece) {
+  const int64_t pieces = (most + piece - 1) / piece, mean = all > 0 ? (all + N * piece - 1) / (N * piece) : 1;
+  if (pieces > 8 * mean) return 0;
+  const int64_t per = pieces < 4 * mean ? pieces : 2 * mean;
+  return (int32_t)(per < most_per(N) ? per : most_per(N));
+}
+
 hipError_t launch_pack(hipStream_t s, const ReqEntry* req_table, const int32_t* sample_request,
                        const int32_t* sample_local, const int32_t* seqlens, const int32_t* cu_seqlens,
-                       int32_t N, int32_t d, int32_t align, int32_t max_rows, void* tokens,
+                       int32_t N, int32_t T, int32_t d, int32_t max_rows, void* tokens,
                        int32_t* token_sample, int32_t* token_pos);
 
-hipError_t launch_unpack(hipStream_t s, const ReqEntry* req_table, const int32_t* sample_request,
-                         const int32_t* sample_local, const int32_t* seqlens, const int32_t* cu_seqlens,
-                         int32_t N, int32_t max_req_len, const void* rows, int64_t row_bytes, bool vec16);
+// Workgroups of an unpack and blocks per sample (0: those of each request's own
+// padded length, from the `block`s that this fills in).
+int32_t unpack_blocks(ReqEntry* table, int32_t R, int32_t N, int64_t row_bytes, bool vec16, int32_t* per);
+hipError_t launch_unpack(hipStream_t s, const ReqEntry* req_table, int32_t R, const int32_t* sample_request,
+                         const int32_t* sample_local, const int32_t* seqlens, const int32_t* cu_seqlens, int32_t N,
+                         int32_t blocks, int32_t per, const void* rows, int64_t row_bytes, bool vec16);
 
 // x_out (fp32, optional) = widened x_bf16; h = RMS(x) * g  (bf16)
 hipError_t launch_rmsnorm_bf16in(hipStream_t s, const void* x_bf16, float* x_out, const void* g,

@@ -275,12 +275,41 @@ __global__ __launch_bounds__(256) void prefix_gather_kernel(const uint16_t* __re
   }
 }
 
+// The same over consecutive chunks of the prefix buffer, whichever samples they
+// belong to (as the ragged walk of the pack kernel).
+__global__ __launch_bounds__(256) void prefix_ragged_kernel(const uint16_t* __restrict__ hidden,
+                                                           const int32_t* __restrict__ tenant_perm,
+                                                           const int32_t* __restrict__ cu_seqlens,
+                                                           const int32_t* __restrict__ zoff, int32_t N, int32_t d,
+                                                           int64_t cap, uint16_t* __restrict__ z) {
+  const int64_t chunks = d / 8, all = min((int64_t)zoff[N], cap) * chunks;
+  for (int64_t at = (int64_t)blockIdx.x * kPrefixRun; at < all; at += (int64_t)gridDim.x * kPrefixRun) {
+    const int64_t n = min((int64_t)kPrefixRun, all - at);
+    const int32_t ra = (int32_t)(at / chunks), rb = (int32_t)((at + n - 1) / chunks);
+    const int32_t ka = last_at(zoff, N, ra), kb = ka + last_at(zoff + ka, min(N - ka, rb - ra + 1), rb);
+    const uint32_t c0 = (uint32_t)(at - ra * chunks);
+    for (int64_t e = threadIdx.x; e < n; e += 256) {
+      const uint32_t r = (c0 + (uint32_t)e) / (uint32_t)chunks, c = c0 + (uint32_t)e - r * (uint32_t)chunks;
+      const int32_t row = ra + (int32_t)r, k = ka + last_at(zoff + ka, kb - ka + 1, row);
+      const int64_t src = cu_seqlens[tenant_perm[k]] + (row - zoff[k]);
+      reinterpret_cast<u32x4x*>(z)[at + e] =
+          __builtin_nontemporal_load(reinterpret_cast<const u32x4x*>(hidden) + src * chunks + c);
+    }
+  }
+}
+
 hipError_t launch_prefix(hipStream_t s, const void* hidden, const int32_t* tenant_perm, const int32_t* seqlens,
                          const int32_t* cu_seqlens, int32_t N, int32_t max_seqlen, int32_t d, int64_t cap,
                          int32_t* zoff, void* z) {
   prefix_offsets_kernel<<<1, 256, 0, s>>>(tenant_perm, seqlens, N, zoff);
-  const int32_t per = (int32_t)std::min<int64_t>(((int64_t)max_seqlen * (d / 8) + kPrefixRun - 1) / kPrefixRun,
-                                                 std::max(1, 0xffffff / N));
+  const int64_t chunks = d / 8;
+  const int32_t per = spread_blocks(max_seqlen * chunks, cap * chunks, N, kPrefixRun);
+  if (per == 0) {
+    const unsigned blocks = (unsigned)std::min<int64_t>((cap * chunks + kPrefixRun - 1) / kPrefixRun, kMostBlocks);
+    prefix_ragged_kernel<<<blocks, 256, 0, s>>>(reinterpret_cast<const uint16_t*>(hidden), tenant_perm, cu_seqlens, zoff,
+                                                N, d, cap, reinterpret_cast<uint16_t*>(z));
+    return hipGetLastError();
+  }
   prefix_gather_kernel<<<dim3((unsigned)N * per), 256, 0, s>>>(reinterpret_cast<const uint16_t*>(hidden), tenant_perm,
                                                                seqlens, cu_seqlens, zoff, d, cap,
                                                                reinterpret_cast<uint16_t*>(z), per);

@@ -1,6 +1,7 @@
 // Pack (canonicalize + pad into one physical batch) and unpack (split back by
 // the recorded slices).  Both are plain HBM copies.
 #include <algorithm>
+#include <type_traits>
 
 #include "jn_device.h"
 #include "jn_internal.h"
@@ -94,14 +95,78 @@ __global__ __launch_bounds__(256) void pack_kernel(const ReqEntry* __restrict__ 
   }
 }
 
-template <typename V>
-__global__ __launch_bounds__(256) void unpack_kernel(const ReqEntry* __restrict__ req_table,
+// The same over consecutive elements of the packed buffer, whichever samples they
+// belong to: for batches of a few long samples among many short ones (spread_blocks).
+constexpr int kRaggedRuns = 4;  // most kFlat runs of a workgroup, between two searches
+__global__ __launch_bounds__(256) void pack_ragged_kernel(const ReqEntry* __restrict__ req_table,
+                                                          const int32_t* __restrict__ sample_request,
+                                                          const int32_t* __restrict__ sample_local,
+                                                          const int32_t* __restrict__ seqlens,
+                                                          const int32_t* __restrict__ cu_seqlens, int32_t N, int32_t T,
+                                                          int32_t d, int32_t run, u32x4p* __restrict__ tokens,
+                                                          int32_t* __restrict__ token_sample,
+                                                          int32_t* __restrict__ token_pos) {
+  const uint32_t chunks = d / 8;
+  const int64_t all = (int64_t)T * chunks;
+  for (int64_t at = (int64_t)blockIdx.x * run; at < all; at += (int64_t)gridDim.x * run) {
+    // rows ra .. rb, of samples ia .. ib (a sample has a row or more)
+    const int64_t n = min((int64_t)run, all - at);
+    const int32_t ra = (int32_t)(at / chunks), rb = (int32_t)((at + n - 1) / chunks);
+    const int32_t ia = last_at(cu_seqlens, N, ra), ib = ia + last_at(cu_seqlens + ia, min(N - ia, rb - ra + 1), rb);
+    const uint32_t c0 = (uint32_t)(at - ra * (int64_t)chunks);
+    if (ia == ib) {
+      const ReqEntry q = req_table[sample_request[ia]];
+      const int64_t from = at - cu_seqlens[ia] * (int64_t)chunks;
+      const u32x4p* src = reinterpret_cast<const u32x4p*>(q.in) + (int64_t)sample_local[ia] * q.max_len * chunks + from;
+      for (int64_t e = 0; e < n; e += kFlat) move_run(src, tokens + at, e, seqlens[ia] * (int64_t)chunks - from, n);
+    } else {
+      for (int64_t e = threadIdx.x; e < n; e += 256) {
+        const uint32_t r = (c0 + (uint32_t)e) / chunks, c = c0 + (uint32_t)e - r * chunks;
+        const int32_t row = ra + (int32_t)r, i = ia + last_at(cu_seqlens + ia, ib - ia + 1, row), j = row - cu_seqlens[i];
+        u32x4p v{};
+        if (j < seqlens[i]) {
+          const ReqEntry q = req_table[sample_request[i]];
+          v = __builtin_nontemporal_load(reinterpret_cast<const u32x4p*>(q.in) +
+                                         ((int64_t)sample_local[i] * q.max_len + j) * chunks + c);
+        }
+        __builtin_nontemporal_store(v, tokens + at + e);
+      }
+    }
+    for (int32_t row = ra + (c0 != 0) + (int32_t)threadIdx.x; row <= rb; row += 256) {  // rows that start here
+      const int32_t i = ia + last_at(cu_seqlens + ia, ib - ia + 1, row), j = row - cu_seqlens[i];
+      const bool live = j < seqlens[i];
+      token_sample[row] = live ? i : -1;
+      token_pos[row] = live ? j : -1;
+    }
+  }
+}
+
+// RAGGED: the workgroups of a sample are those of its own request (as above, for
+// requests of unlike padded lengths), found in the request table.
+template <typename V, bool RAGGED>
+__global__ __launch_bounds__(256) void unpack_kernel(const ReqEntry* __restrict__ req_table, int32_t R,
                                                      const int32_t* __restrict__ sample_request,
                                                      const int32_t* __restrict__ sample_local,
                                                      const int32_t* __restrict__ seqlens,
                                                      const int32_t* __restrict__ cu_seqlens, const V* __restrict__ rows,
-                                                     int64_t row_vecs, int32_t per) {
-  const int32_t i = blockIdx.x / per, part = blockIdx.x % per;
+                                                     int64_t row_vecs, int32_t per, int32_t N) {
+  int32_t i, part;
+  if constexpr (RAGGED) {
+    const int32_t b = blockIdx.x;
+    int32_t lo = 0, hi = R - 1;
+    while (lo < hi) {
+      const int32_t mid = (lo + hi + 1) >> 1;
+      if (req_table[mid].block <= b) lo = mid; else hi = mid - 1;
+    }
+    const ReqEntry q = req_table[lo];
+    per = (int32_t)min((q.max_len * row_vecs + kFlat - 1) / kFlat, (int64_t)per);
+    i = q.first + (b - q.block) / per;
+    part = (b - q.block) % per;
+    if (i >= N) return;
+  } else {
+    i = blockIdx.x / per;
+    part = blockIdx.x % per;
+  }
   const ReqEntry e = req_table[sample_request[i]];
   const int32_t s = sample_local[i];
   // the host checks that the requests match the packed batch; a sample
@@ -113,39 +178,58 @@ __global__ __launch_bounds__(256) void unpack_kernel(const ReqEntry* __restrict_
     move_run(src, reinterpret_cast<V*>(e.out) + s * n, at, live, n);
 }
 
-// Blocks per sample of a run of `n` elements, of N samples; a dispatch holds at
-// most 2^32 - 1 threads, beyond which blocks move more than one piece.
-static int32_t flat_blocks(int64_t n, int32_t N) {
-  return (int32_t)std::min<int64_t>((n + kFlat - 1) / kFlat, std::max(1, 0xffffff / N));
-}
-
 hipError_t launch_pack(hipStream_t s, const ReqEntry* req_table, const int32_t* sample_request,
                        const int32_t* sample_local, const int32_t* seqlens, const int32_t* cu_seqlens, int32_t N,
-                       int32_t d, int32_t align, int32_t max_rows, void* tokens, int32_t* token_sample,
+                       int32_t T, int32_t d, int32_t max_rows, void* tokens, int32_t* token_sample,
                        int32_t* token_pos) {
-  (void)align;
-  const int32_t per = flat_blocks((int64_t)max_rows * (d / 8), N);
-  const dim3 grid((unsigned)N * per);
-  pack_kernel<<<grid, 256, 0, s>>>(req_table, sample_request, sample_local, seqlens, cu_seqlens, d,
-                                   reinterpret_cast<u32x4p*>(tokens), token_sample, token_pos, per);
+  const int64_t chunks = d / 8;
+  const int32_t per = spread_blocks(max_rows * chunks, T * chunks, N, kFlat);
+  if (per == 0) {
+    // (4096: two workgroups' worth of every place on the chip)
+    const int64_t pieces = (T * chunks + kFlat - 1) / kFlat;
+    const int32_t run = kFlat * (int32_t)std::min<int64_t>(kRaggedRuns, std::max<int64_t>(1, pieces / 4096));
+    const int64_t blocks = (T * chunks + run - 1) / run;
+    pack_ragged_kernel<<<(unsigned)std::min<int64_t>(blocks, kMostBlocks), 256, 0, s>>>(
+        req_table, sample_request, sample_local, seqlens, cu_seqlens, N, T, d, run,
+        reinterpret_cast<u32x4p*>(tokens), token_sample, token_pos);
+    return hipGetLastError();
+  }
+  pack_kernel<<<(unsigned)N * per, 256, 0, s>>>(req_table, sample_request, sample_local, seqlens, cu_seqlens, d,
+                                                reinterpret_cast<u32x4p*>(tokens), token_sample, token_pos, per);
   return hipGetLastError();
 }
 
-hipError_t launch_unpack(hipStream_t s, const ReqEntry* req_table, const int32_t* sample_request,
+int32_t unpack_blocks(ReqEntry* table, int32_t R, int32_t N, int64_t row_bytes, bool vec16, int32_t* per) {
+  const int64_t vecs = row_bytes / (vec16 ? 16 : 4);
+  int64_t most = 0, all = 0, blocks = 0;
+  for (int32_t r = 0; r < R; ++r) {
+    most = std::max(most, table[r].max_len * vecs);
+    all += table[r].n * (table[r].max_len * vecs);
+  }
+  *per = spread_blocks(most, all, N, kFlat);
+  if (*per > 0) return N * *per;
+  for (int32_t r = 0; r < R; ++r) {
+    table[r].block = (int32_t)blocks;
+    blocks += table[r].n * std::min<int64_t>((table[r].max_len * vecs + kFlat - 1) / kFlat, most_per(N));
+  }
+  return (int32_t)blocks;
+}
+
+hipError_t launch_unpack(hipStream_t s, const ReqEntry* req_table, int32_t R, const int32_t* sample_request,
                          const int32_t* sample_local, const int32_t* seqlens, const int32_t* cu_seqlens, int32_t N,
-                         int32_t max_req_len, const void* rows, int64_t row_bytes, bool vec16) {
+                         int32_t blocks, int32_t per, const void* rows, int64_t row_bytes, bool vec16) {
   // vec16: the caller checked that the source, every destination and the row
   // pitch are 16-byte aligned
   const int64_t vecs = row_bytes / (vec16 ? 16 : 4);
-  const int32_t per = flat_blocks(max_req_len * vecs, N);
-  const dim3 grid((unsigned)N * per);
-  if (vec16)
-    unpack_kernel<u32x4p><<<grid, 256, 0, s>>>(req_table, sample_request, sample_local, seqlens, cu_seqlens,
-                                               reinterpret_cast<const u32x4p*>(rows), vecs, per);
-  else
-    unpack_kernel<uint32_t><<<grid, 256, 0, s>>>(req_table, sample_request, sample_local, seqlens, cu_seqlens,
-                                                 reinterpret_cast<const uint32_t*>(rows), vecs, per);
-  return hipGetLastError();
+  auto go = [&](auto v, auto ragged) {
+    typedef decltype(v) V;
+    unpack_kernel<V, ragged()><<<(unsigned)blocks, 256, 0, s>>>(
+        req_table, R, sample_request, sample_local, seqlens, cu_seqlens, reinterpret_cast<const V*>(rows), vecs,
+        ragged() ? most_per(N) : per, N);
+    return hipGetLastError();
+  };
+  if (vec16) return per == 0 ? go(u32x4p(), std::true_type()) : go(u32x4p(), std::false_type());
+  return per == 0 ? go(uint32_t(), std::true_type()) : go(uint32_t(), std::false_type());
 }
 
 }  // namespace jnx

@@ -518,6 +518,40 @@ void check_head_limits(jn_ctx* c) {
   CHECK(accepted > 200);
 }
 
+// Workgroups of a copy follow what there is to copy, not the longest sample.
+void check_copy_blocks(jn_ctx* c) {
+  void* some = dev(64);
+  Rng r(11);
+  for (int it = 0; it < 60; ++it) {
+    const int d = it == 0 ? 2048 : 8 * r.range(1, 300), n = it == 0 ? 2048 : r.range(1, 3000), len = it == 0 ? 2048 : r.range(1, 5000);
+    Group g;
+    g.opts.d_model = d;
+    g.opts.align = 1;
+    g.ten.assign(1, jn_tenant{0x1234, d, 0});
+    g.lens = {std::vector<int32_t>(n, it == 0 ? 8 : r.range(1, 40)), {len}};
+    int64_t rows = 0;
+    for (auto& x : g.lens) {
+      jn_request q{};
+      q.n_samples = (int)x.size();
+      q.max_len = x[0];
+      q.embeds = some;
+      q.lengths = x.data();
+      g.req.push_back(q);
+      rows += (int64_t)x.size() * x[0];
+    }
+    jn_pack_sizes sz{};
+    CHECK(jn_pack_plan(g.req.data(), 2, g.ten.data(), 1, &g.opts, &sz) == JN_OK);
+    void* maps = dev(sz.map_bytes);
+    jn_packed p{};
+    const int64_t most = 3 * (rows * (d / 8) / 512 + n + 1);
+    CHECK(jn_pack_group(c, g.req.data(), 2, g.ten.data(), 1, &g.opts, maps, sz.map_bytes, some, sz.token_bytes, &p) == JN_OK);
+    CHECK(jn_fake_last_workgroups <= most);
+    void* outs[] = {some, some};
+    CHECK(jn_unpack(c, &p, g.req.data(), 2, some, d * 2, outs) == JN_OK);
+    CHECK(jn_fake_last_workgroups <= most);
+  }
+}
+
 // ------------------------------------------------------------ experts ---
 
 void check_experts(jn_ctx* c, bool flow, bool long_prefix = false) {
@@ -697,6 +731,7 @@ int main() {
   check_backbones(c);
   check_heads(c);
   check_head_limits(c);
+  check_copy_blocks(c);
   check_experts(c, false);
   check_experts(c, true);
   check_experts(c, false, true);
