@@ -989,7 +989,7 @@ jn_status jn_unpack(jn_ctx* c, const jn_packed* p, const jn_request* req, int32_
   if (row_bytes == 0 || row_bytes % 4 != 0) return fail(c, JN_EUNSUPPORTED, "row_bytes %zu not a positive multiple of 4", row_bytes);
   if (((uintptr_t)rows) % 4 != 0) return fail(c, JN_EUNSUPPORTED, "rows not 4-byte aligned");
   std::vector<ReqEntry> rt(R);
-  int64_t n = 0;
+  int64_t n = 0, out_rows = 0;
   bool vec16 = row_bytes % 16 == 0 && ((uintptr_t)rows) % 16 == 0;
   for (int32_t r = 0; r < R; ++r) {
     if (!req_out[r]) return fail(c, JN_EINVAL, "request %d output is null", r);
@@ -998,6 +998,7 @@ jn_status jn_unpack(jn_ctx* c, const jn_packed* p, const jn_request* req, int32_
     if (req[r].n_samples < 1 || req[r].max_len < 1) return fail(c, JN_ESHAPE, "request %d shape", r);
     rt[r] = ReqEntry{req[r].embeds, req_out[r], req[r].max_len, req[r].n_samples, (int32_t)n, 0};
     n += req[r].n_samples;
+    out_rows += (int64_t)req[r].n_samples * req[r].max_len;
   }
   if (n != p->N) return fail(c, JN_ESHAPE, "requests hold %lld samples, packed batch %d", (long long)n, p->N);
   if (request_signature(req, R) != p->req_sig)
@@ -1008,7 +1009,8 @@ jn_status jn_unpack(jn_ctx* c, const jn_packed* p, const jn_request* req, int32_
   if (st != JN_OK) return st;
   JN_TRACED(c, JN_OP_UNPACK, p->T, (int64_t)row_bytes, 0,
             launch_unpack(c->stream, (const ReqEntry*)p->req_table, R, p->sample_request, p->sample_local, p->seqlens,
-                          p->cu_seqlens, p->N, blocks, per, rows, (int64_t)row_bytes, vec16),
+                          p->cu_seqlens, p->N, blocks, per, rows, (int64_t)row_bytes, vec16,
+                          out_rows * (int64_t)row_bytes),
             "unpack kernel");
   return JN_OK;
 }

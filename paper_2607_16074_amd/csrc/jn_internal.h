@@ -55,7 +55,8 @@ hipError_t launch_pack(hipStream_t s, const ReqEntry* req_table, const int32_t* 
 int32_t unpack_blocks(ReqEntry* table, int32_t R, int32_t N, int64_t row_bytes, bool vec16, int32_t* per);
 hipError_t launch_unpack(hipStream_t s, const ReqEntry* req_table, int32_t R, const int32_t* sample_request,
                          const int32_t* sample_local, const int32_t* seqlens, const int32_t* cu_seqlens, int32_t N,
-                         int32_t blocks, int32_t per, const void* rows, int64_t row_bytes, bool vec16);
+                         int32_t blocks, int32_t per, const void* rows, int64_t row_bytes, bool vec16,
+                         int64_t out_bytes);
 
 // x_out (fp32, optional) = widened x_bf16; h = RMS(x) * g  (bf16)
 hipError_t launch_rmsnorm_bf16in(hipStream_t s, const void* x_bf16, float* x_out, const void* g,

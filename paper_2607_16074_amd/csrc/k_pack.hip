@@ -45,13 +45,22 @@ hipError_t launch_upload(hipStream_t s, void* dst, const void* src, size_t bytes
 // buffer, so a block moves kFlat consecutive elements of it (a row boundary
 // means nothing; live: elements that exist in the source, the rest are zeros),
 // all of a thread's loads issued before its first store.  Every byte is touched
-// once, so both sides are non-temporal.  Bound by HBM, and by which of its
+// once, so the loads are non-temporal, and ONCE, the stores too (kStreamBytes).
+// Bound by HBM, and by which of its
 // pieces are in flight together: with consecutive blocks on consecutive 8 KB of
 // a sample 256 samples of ~296 rows of 4 KB take 100 us (6.1 TB/s), with 16 KB
 // per block 109, 32 KB 112 (119 without the non-temporal hint), 32 KB with
 // consecutive blocks on different samples 125; 16 rows per block, samples
 // fastest, one load in flight: 130.
-template <typename V>
+template <bool ONCE, typename V>
+__device__ __forceinline__ void put(V v, V* p) {
+  if constexpr (ONCE)
+    __builtin_nontemporal_store(v, p);
+  else
+    *p = v;
+}
+
+template <bool ONCE, typename V>
 __device__ __forceinline__ void move_run(const V* __restrict__ src, V* __restrict__ dst, int64_t at, int64_t live,
                                          int64_t n) {
   const int64_t e0 = at + threadIdx.x;
@@ -60,7 +69,7 @@ __device__ __forceinline__ void move_run(const V* __restrict__ src, V* __restric
 #pragma unroll
     for (int u = 0; u < kFlat / 256; ++u) v[u] = __builtin_nontemporal_load(src + e0 + u * 256);
 #pragma unroll
-    for (int u = 0; u < kFlat / 256; ++u) __builtin_nontemporal_store(v[u], dst + e0 + u * 256);
+    for (int u = 0; u < kFlat / 256; ++u) put<ONCE>(v[u], dst + e0 + u * 256);
     return;
   }
 #pragma unroll
@@ -70,9 +79,10 @@ __device__ __forceinline__ void move_run(const V* __restrict__ src, V* __restric
   }
 #pragma unroll
   for (int u = 0; u < kFlat / 256; ++u)
-    if (e0 + u * 256 < n) __builtin_nontemporal_store(v[u], dst + e0 + u * 256);
+    if (e0 + u * 256 < n) put<ONCE>(v[u], dst + e0 + u * 256);
 }
 
+template <bool ONCE>
 __global__ __launch_bounds__(256) void pack_kernel(const ReqEntry* __restrict__ req_table,
                                                    const int32_t* __restrict__ sample_request,
                                                    const int32_t* __restrict__ sample_local,
@@ -88,7 +98,7 @@ __global__ __launch_bounds__(256) void pack_kernel(const ReqEntry* __restrict__ 
   const int64_t chunks = d / 8;  // 16-byte chunks per row
   const u32x4p* src = reinterpret_cast<const u32x4p*>(e.in) + (int64_t)sample_local[i] * e.max_len * chunks;
   for (int64_t at = (int64_t)part * kFlat; at < rows * chunks; at += (int64_t)per * kFlat)
-    move_run(src, tokens + base * chunks, at, L * chunks, rows * chunks);
+    move_run<ONCE>(src, tokens + base * chunks, at, L * chunks, rows * chunks);
   for (int64_t j = (int64_t)part * 256 + threadIdx.x; j < rows; j += (int64_t)per * 256) {
     token_sample[base + j] = j < L ? i : -1;
     token_pos[base + j] = j < L ? (int32_t)j : -1;
@@ -118,7 +128,7 @@ __global__ __launch_bounds__(256) void pack_ragged_kernel(const ReqEntry* __rest
       const ReqEntry q = req_table[sample_request[ia]];
       const int64_t from = at - cu_seqlens[ia] * (int64_t)chunks;
       const u32x4p* src = reinterpret_cast<const u32x4p*>(q.in) + (int64_t)sample_local[ia] * q.max_len * chunks + from;
-      for (int64_t e = 0; e < n; e += kFlat) move_run(src, tokens + at, e, seqlens[ia] * (int64_t)chunks - from, n);
+      for (int64_t e = 0; e < n; e += kFlat) move_run<false>(src, tokens + at, e, seqlens[ia] * (int64_t)chunks - from, n);
     } else {
       for (int64_t e = threadIdx.x; e < n; e += 256) {
         const uint32_t r = (c0 + (uint32_t)e) / chunks, c = c0 + (uint32_t)e - r * chunks;
@@ -129,7 +139,7 @@ __global__ __launch_bounds__(256) void pack_ragged_kernel(const ReqEntry* __rest
           v = __builtin_nontemporal_load(reinterpret_cast<const u32x4p*>(q.in) +
                                          ((int64_t)sample_local[i] * q.max_len + j) * chunks + c);
         }
-        __builtin_nontemporal_store(v, tokens + at + e);
+        tokens[at + e] = v;
       }
     }
     for (int32_t row = ra + (c0 != 0) + (int32_t)threadIdx.x; row <= rb; row += 256) {  // rows that start here
@@ -143,7 +153,7 @@ __global__ __launch_bounds__(256) void pack_ragged_kernel(const ReqEntry* __rest
 
 // RAGGED: the workgroups of a sample are those of its own request (as above, for
 // requests of unlike padded lengths), found in the request table.
-template <typename V, bool RAGGED>
+template <typename V, bool RAGGED, bool ONCE>
 __global__ __launch_bounds__(256) void unpack_kernel(const ReqEntry* __restrict__ req_table, int32_t R,
                                                      const int32_t* __restrict__ sample_request,
                                                      const int32_t* __restrict__ sample_local,
@@ -175,8 +185,13 @@ __global__ __launch_bounds__(256) void unpack_kernel(const ReqEntry* __restrict_
   const int64_t n = e.max_len * row_vecs, live = min((int64_t)seqlens[i] * row_vecs, n);
   const V* src = rows + cu_seqlens[i] * row_vecs;
   for (int64_t at = (int64_t)part * kFlat; at < n; at += (int64_t)per * kFlat)
-    move_run(src, reinterpret_cast<V*>(e.out) + s * n, at, live, n);
+    move_run<ONCE>(src, reinterpret_cast<V*>(e.out) + s * n, at, live, n);
 }
+
+// Results beyond the last-level cache are stored non-temporally: packed and unpacked
+// again, 300 rows of 4 KB, 225 MB take 158 us with plain and 167 with non-temporal
+// stores, 300 MB 228 and 217.
+constexpr int64_t kStreamBytes = 256 << 20;
 
 hipError_t launch_pack(hipStream_t s, const ReqEntry* req_table, const int32_t* sample_request,
                        const int32_t* sample_local, const int32_t* seqlens, const int32_t* cu_seqlens, int32_t N,
@@ -194,9 +209,13 @@ hipError_t launch_pack(hipStream_t s, const ReqEntry* req_table, const int32_t* 
         reinterpret_cast<u32x4p*>(tokens), token_sample, token_pos);
     return hipGetLastError();
   }
-  pack_kernel<<<(unsigned)N * per, 256, 0, s>>>(req_table, sample_request, sample_local, seqlens, cu_seqlens, d,
-                                                reinterpret_cast<u32x4p*>(tokens), token_sample, token_pos, per);
-  return hipGetLastError();
+  auto go = [&](auto once) {
+    pack_kernel<once()><<<(unsigned)N * per, 256, 0, s>>>(req_table, sample_request, sample_local, seqlens, cu_seqlens, d,
+                                                          reinterpret_cast<u32x4p*>(tokens), token_sample, token_pos,
+                                                          per);
+    return hipGetLastError();
+  };
+  return T * chunks * 16 > kStreamBytes ? go(std::true_type()) : go(std::false_type());
 }
 
 int32_t unpack_blocks(ReqEntry* table, int32_t R, int32_t N, int64_t row_bytes, bool vec16, int32_t* per) {
@@ -217,19 +236,24 @@ int32_t unpack_blocks(ReqEntry* table, int32_t R, int32_t N, int64_t row_bytes, 
 
 hipError_t launch_unpack(hipStream_t s, const ReqEntry* req_table, int32_t R, const int32_t* sample_request,
                          const int32_t* sample_local, const int32_t* seqlens, const int32_t* cu_seqlens, int32_t N,
-                         int32_t blocks, int32_t per, const void* rows, int64_t row_bytes, bool vec16) {
+                         int32_t blocks, int32_t per, const void* rows, int64_t row_bytes, bool vec16,
+                         int64_t out_bytes) {
   // vec16: the caller checked that the source, every destination and the row
   // pitch are 16-byte aligned
   const int64_t vecs = row_bytes / (vec16 ? 16 : 4);
-  auto go = [&](auto v, auto ragged) {
+  auto go = [&](auto v, auto ragged, auto once) {
     typedef decltype(v) V;
-    unpack_kernel<V, ragged()><<<(unsigned)blocks, 256, 0, s>>>(
+    unpack_kernel<V, ragged(), once()><<<(unsigned)blocks, 256, 0, s>>>(
         req_table, R, sample_request, sample_local, seqlens, cu_seqlens, reinterpret_cast<const V*>(rows), vecs,
         ragged() ? most_per(N) : per, N);
     return hipGetLastError();
   };
-  if (vec16) return per == 0 ? go(u32x4p(), std::true_type()) : go(u32x4p(), std::false_type());
-  return per == 0 ? go(uint32_t(), std::true_type()) : go(uint32_t(), std::false_type());
+  auto form = [&](auto v) {
+    if (per == 0) return go(v, std::true_type(), std::false_type());
+    return out_bytes > kStreamBytes ? go(v, std::false_type(), std::true_type())
+                                    : go(v, std::false_type(), std::false_type());
+  };
+  return vec16 ? form(u32x4p()) : form(uint32_t());
 }
 
 }  // namespace jnx

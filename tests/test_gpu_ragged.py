@@ -54,6 +54,26 @@ def test_copies(group, d, align):
             assert np.array_equal(o.cpu().numpy(), back[r]), (width, r)
 
 
+@pytest.mark.parametrize("samples", [64, 65])  # 256 MB are plain stores' last, 65 samples beyond
+def test_copies_around_the_last_level_cache(samples):
+    import paper_2607_16074_amd as jn
+    print(f"samples {samples}", flush=True)
+    ctx, d, rows = jn.Context(), 2048, 1024
+    x = torch.randint(-32768, 32767, (samples, rows, d), dtype=torch.int16, device="cuda")
+    lens = np.arange(rows, rows - samples, -1, dtype=np.int32)
+    for i, n in enumerate(lens):
+        x[i, n:] = 0
+    reqs, tenants = [jn.Request(0, x.view(torch.bfloat16), lens)], [jn.Tenant(7, d)]
+    sz = jn.jn_pack_plan(reqs, tenants, d, rows)  # aligned: every sample's rows and zeros
+    maps = torch.zeros(int(sz.map_bytes), dtype=torch.uint8, device="cuda")
+    tokens = torch.full((int(sz.T), d), -1, dtype=torch.int16, device="cuda")
+    packed = jn.jn_pack_group(ctx, reqs, tenants, d, rows, maps, tokens)
+    assert torch.equal(tokens.view_as(x), x)
+    out = torch.full_like(x, -1)
+    jn.jn_unpack(ctx, packed, reqs, tokens, d * 2, [out])
+    assert torch.equal(out, x)
+
+
 def test_expert_prefix_of_unlike_lengths():
     """Each tenant's own samples are alike, the group's are not: the same bits."""
     from paper_2607_16074_amd import step as jstep
