@@ -116,54 +116,70 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const void* __restrict__ x
 
 // Reduction of a split residual projection and the norm after it in one pass:
 // v = x + ((part[0] + part[1]) + ...), written back to x, then the norm of v in
-// rmsnorm_kernel's order.  One wavefront per workgroup and row: these batches
-// have few rows, and the S + 1 reads of a row are what it waits for.  At 300
-// rows of 2048, S = 8: 6.6 us against 5.1 + 4.7 us as two launches; 2,468
-// rows, S = 3: 19 us (32 + 7 us for the two launches with S = 8).
+// rmsnorm_kernel's order (which every wave forms for itself from the row in LDS).
+// One workgroup per row, its column blocks dealt to up to four wavefronts: these
+// batches have few rows, and the S + 1 reads of a row are what it waits for.  As two
+// launches, in one wavefront per row, and now: 1 row of 4096, S = 8, 10.3, 17.3 and
+// 5.8 us; 100 rows 9.7, 17.0 and 6.5; 300 rows of 2048, S = 8, 9.8, 6.6 and 6.4;
+// 2,468 rows 39 (S = 8), 19.9 and 19.8 (S = 3).
+constexpr int split_waves(int nc) { return nc < 4 ? nc : 4; }
 template <int VEC, int NC>
-__global__ __launch_bounds__(64) void rmsnorm_split_kernel(float* __restrict__ x, const float* __restrict__ part,
-                                                           int32_t S, int64_t stride, const uint16_t* __restrict__ g,
-                                                           uint16_t* __restrict__ h, int32_t d, float eps) {
-  const int lane = threadIdx.x;
+__global__ __launch_bounds__(64 * split_waves(NC)) void rmsnorm_split_kernel(float* __restrict__ x, const float* __restrict__ part,
+                                                               int32_t S, int64_t stride,
+                                                               const uint16_t* __restrict__ g, uint16_t* __restrict__ h,
+                                                               int32_t d, float eps) {
+  constexpr int W = split_waves(NC), CW = (NC + W - 1) / W;
+  __shared__ __attribute__((aligned(16))) float line[NC * 64 * VEC];
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int64_t row = blockIdx.x;
-  float v[NC][VEC], a[NC][VEC];
+  auto at = [&](int i) { return ((w + W * i) * 64 + lane) * VEC; };  // the wave's column block i
+  auto mine = [&](int i) { return NC % W == 0 || w + W * i < NC; };
+  float v[CW][VEC], a[CW][VEC];
 #pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    const int e = (c * 64 + lane) * VEC;
-    load_f32<VEC>(x + row * d, e, v[c]);
-    load_f32<VEC>(part + row * d, e, a[c]);
-  }
-#pragma unroll 2
+  for (int i = 0; i < CW; ++i)
+    if (mine(i)) {
+      load_f32<VEC>(x + row * d, at(i), v[i]);
+      load_f32<VEC>(part + row * d, at(i), a[i]);
+    }
+#pragma unroll 4
   for (int32_t s = 1; s < S; ++s) {
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      float q[VEC];
-      load_f32<VEC>(part + s * stride + row * d, (c * 64 + lane) * VEC, q);
+    for (int i = 0; i < CW; ++i)
+      if (mine(i)) {
+        float q[VEC];
+        load_f32<VEC>(part + s * stride + row * d, at(i), q);
 #pragma unroll
-      for (int k = 0; k < VEC; ++k) a[c][k] += q[k];
-    }
+        for (int k = 0; k < VEC; ++k) a[i][k] += q[k];
+      }
   }
+#pragma unroll
+  for (int i = 0; i < CW; ++i)
+    if (mine(i)) {
+#pragma unroll
+      for (int k = 0; k < VEC; ++k) v[i][k] += a[i][k];
+      store_f32<VEC>(x + row * d, at(i), v[i]);
+      store_f32<VEC>(line, at(i), v[i]);
+    }
+  __syncthreads();
   float ss = 0.f;
 #pragma unroll
   for (int c = 0; c < NC; ++c) {
+    float q[VEC];
+    load_f32<VEC>(line, (c * 64 + lane) * VEC, q);
 #pragma unroll
-    for (int k = 0; k < VEC; ++k) {
-      v[c][k] += a[c][k];
-      ss += v[c][k] * v[c][k];
-    }
+    for (int k = 0; k < VEC; ++k) ss += q[k] * q[k];
   }
   ss = wave_sum(ss);
   const float r = rsqrtf(ss / (float)d + eps);
 #pragma unroll
-  for (int c = 0; c < NC; ++c) {
-    const int e = (c * 64 + lane) * VEC;
-    store_f32<VEC>(x + row * d, e, v[c]);
-    float gv[VEC], o[VEC];
-    load_bf<VEC>(g, e, gv);
+  for (int i = 0; i < CW; ++i)
+    if (mine(i)) {
+      float gv[VEC], o[VEC];
+      load_bf<VEC>(g, at(i), gv);
 #pragma unroll
-    for (int k = 0; k < VEC; ++k) o[k] = v[c][k] * r * gv[k];
-    store_bf<VEC>(h + row * d, e, o);
-  }
+      for (int k = 0; k < VEC; ++k) o[k] = v[i][k] * r * gv[k];
+      store_bf<VEC>(h + row * d, at(i), o);
+    }
 }
 
 // Calls f<VEC, NC>() with the lane layout of row width d: a multiple of 128 up
@@ -205,9 +221,8 @@ static hipError_t launch_rms(hipStream_t s, const void* x, float* x_out, const v
 hipError_t launch_rmsnorm_split(hipStream_t s, float* x, const float* part, int32_t S, const void* g, void* h,
                                 int32_t rows, int32_t d, float eps) {
   return with_width(d, [&](auto vec, auto nc) {
-    rmsnorm_split_kernel<vec(), nc()><<<dim3(rows), 64, 0, s>>>(x, part, S, (int64_t)rows * d,
-                                                               reinterpret_cast<const uint16_t*>(g),
-                                                               reinterpret_cast<uint16_t*>(h), d, eps);
+    rmsnorm_split_kernel<vec(), nc()><<<dim3(rows), 64 * split_waves(nc()), 0, s>>>(
+        x, part, S, (int64_t)rows * d, reinterpret_cast<const uint16_t*>(g), reinterpret_cast<uint16_t*>(h), d, eps);
     return hipGetLastError();
   });
 }

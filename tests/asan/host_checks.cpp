@@ -22,6 +22,7 @@ extern "C" long long jn_fake_launches;
 extern "C" long long jn_fake_graph_launches;
 extern "C" long long jn_fake_workgroups;
 extern "C" long long jn_fake_last_workgroups;
+extern "C" long long jn_fake_last_threads;
 
 namespace {
 
@@ -518,6 +519,40 @@ void check_head_limits(jn_ctx* c) {
   CHECK(accepted > 200);
 }
 
+// The sum of a split projection's partials and the norm, last of a short batch's
+// launches, is not left to one wavefront.
+void check_split_norm(jn_ctx* c) {
+  void* some = dev(64);
+  const int d = 4096;
+  std::vector<int32_t> len{1};
+  jn_request q{};
+  q.n_samples = q.max_len = 1;
+  q.embeds = some;
+  q.lengths = len.data();
+  jn_tenant ten{0x1234, d, 0};
+  jn_pack_opts o{};
+  o.d_model = d;
+  o.align = 1;
+  jn_pack_sizes sz{};
+  CHECK(jn_pack_plan(&q, 1, &ten, 1, &o, &sz) == JN_OK);
+  jn_packed p{};
+  CHECK(jn_pack_group(c, &q, 1, &ten, 1, &o, dev(sz.map_bytes), sz.map_bytes, some, sz.token_bytes, &p) == JN_OK);
+  jn_layer ly{};
+  ly.wqkv = ly.wo = ly.w_up = ly.w_down = ly.g1 = ly.g2 = some;
+  jn_backbone bb{};
+  bb.n_layers = 1;
+  bb.d = d;
+  bb.n_heads = 32;
+  bb.ffn = 4 * d;
+  bb.eps = 1e-6f;
+  bb.layers = &ly;
+  bb.gf = some;
+  size_t ws = 0;
+  CHECK(jn_backbone_workspace_size(&bb, 1, &ws) == JN_OK);
+  CHECK(jn_backbone_forward(c, &bb, &p, some, dev(ws), ws) == JN_OK);
+  CHECK(jn_fake_last_workgroups == 1 && jn_fake_last_threads >= 256);
+}
+
 // Workgroups of a copy follow what there is to copy, not the longest sample.
 void check_copy_blocks(jn_ctx* c) {
   void* some = dev(64);
@@ -732,6 +767,7 @@ int main() {
   check_heads(c);
   check_head_limits(c);
   check_copy_blocks(c);
+  check_split_norm(c);
   check_experts(c, false);
   check_experts(c, true);
   check_experts(c, false, true);
