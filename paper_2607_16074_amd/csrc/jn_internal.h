@@ -139,6 +139,12 @@ hipError_t launch_gemm(hipStream_t s, int epi, const void* A, int64_t lda, const
                        const void* B2, int64_t ldb, void* C, int64_t ldc, int32_t M, int32_t N,
                        int32_t K, void* split_ws = nullptr, size_t split_bytes = 0, bool partials_only = false);
 int32_t gemm_split(int epi, int32_t M, int32_t N, int32_t K);
+struct GemmPlan {
+  int32_t m1 = 0;      // rows of the leading ring launch (0: none)
+  int32_t shape = 0;   // the other rows: 256x256, 256x160, 256x128, 128x160, 128x96, 64x96, 128x128
+  int32_t S = 1;
+};
+GemmPlan gemm_plan(int epi, int32_t M, int32_t N, int32_t K);
 size_t gemm_split_bytes(int epi, int32_t M, int32_t N, int32_t K);
 
 // Varlen attention over the packed batch (bidirectional or causal inside each

@@ -1225,16 +1225,6 @@ static double tiles_time(int epi, int64_t tiles, double slabs, int t) {
   return (rounds * slabs * T.slab + once) * (1.0 - 0.013 * std::min(rounds - 1.0, 10.0));
 }
 
-// One launch over `rows` rows and S K ranges; a split adds the launch of its
-// reduction and the second half of the fp32 partials' round trip.
-static double tile_time(int epi, int32_t rows, int32_t N, int32_t K, int t, int32_t S) {
-  const TileShape& T = kShapes[t];
-  const int64_t NL = epi == EPI_GEGLU_BF16 ? 2 * (int64_t)N : N;
-  const int64_t tiles = (rows + T.bm - 1) / T.bm * ((NL + T.bn - 1) / T.bn) * S;
-  const double us = tiles_time(S > 1 ? EPI_F32 : epi, tiles, (double)((K / kBK + S - 1) / S), t);
-  return S > 1 ? us + 4.0 + 4e-6 * S * (double)rows * N / 4.8 : us;
-}
-
 // K may be split (fp32 partials of S ranges added in range order by a second
 // launch, which applies the epilogue) where the launch has at most 128 tiles
 // of 256x256 and K >= 2048: with fewer, longer tiles most CUs would idle.  Two
@@ -1245,13 +1235,28 @@ static bool may_split(int epi, int32_t rows, int32_t N, int32_t K) {
   return K >= 2048 && N % 4 == 0 && (int64_t)((rows + 255) / 256) * ((N + 255) / 256) <= 128;
 }
 
+// One launch over `rows` rows and S K ranges; a split adds the launch of its
+// reduction and the second half of the fp32 partials' round trip.  Where a split is
+// a choice, no launch is faster than its weights come from memory (33 MB 8.6 us, 100
+// MB 20 to 23, 134 MB 28 to 31): without that more ranges looked faster than any
+// were (100 rows, 16,384 x 4,096 in two ranges 36 + 5 us, in one 36; one row, 4,096 x
+// 16,384 in eight ranges 37, in three 32).
+static double tile_time(int epi, int32_t rows, int32_t N, int32_t K, int t, int32_t S) {
+  const TileShape& T = kShapes[t];
+  const int64_t NL = epi == EPI_GEGLU_BF16 ? 2 * (int64_t)N : N;
+  const int64_t tiles = (rows + T.bm - 1) / T.bm * ((NL + T.bn - 1) / T.bn) * S;
+  const double stream = may_split(epi, rows, N, K) ? 3.0 + 2.0 * (double)N * K / 5.2e6 : 0.0;
+  const double us = std::max(stream, tiles_time(S > 1 ? EPI_F32 : epi, tiles, (double)((K / kBK + S - 1) / S), t));
+  return S > 1 ? us + 4.0 + 4e-6 * S * (double)rows * N / 4.8 : us;
+}
+
 // Shape and K split of one launch over `rows` rows; ranges of >= 8 slabs.
 static double plan_launch(int epi, int32_t rows, int32_t N, int32_t K, bool split, int* shape, int32_t* S) {
   const int32_t smax = split && may_split(epi, rows, N, K) ? std::min(16, K / (8 * kBK)) : 1;
   double best = 1e300;
-  for (int t = 0; t <= k128Shape; ++t) {
-    if (t == k128Shape && epi != EPI_RESID_F32) break;
-    for (int32_t k = 1; k <= (t == k128Shape ? 1 : smax); ++k) {
+  for (int32_t k = 1; k <= smax; ++k) {  // (of equal estimates the fewest ranges)
+    for (int t = 0; t <= k128Shape; ++t) {
+      if (t == k128Shape && (epi != EPI_RESID_F32 || k > 1)) break;
       const double us = tile_time(epi, rows, N, K, t, k);
       if (us < best * 0.999) {
         best = us;
@@ -1273,13 +1278,7 @@ static double plan_launch(int epi, int32_t rows, int32_t N, int32_t K, bool spli
 constexpr int32_t kTailSplitK = 8192;
 constexpr double kLaunchGap = 3.0;  // microseconds between two launches on one stream
 
-struct GemmPlan {
-  int32_t m1 = 0;      // rows of the leading ring launch (0: none)
-  int shape = 0;       // the other rows
-  int32_t S = 1;
-};
-
-static GemmPlan gemm_plan(int epi, int32_t M, int32_t N, int32_t K) {
+GemmPlan gemm_plan(int epi, int32_t M, int32_t N, int32_t K) {
   GemmPlan P;
   if (M <= 0 || N <= 0 || K <= 0) return P;
   double best = plan_launch(epi, M, N, K, true, &P.shape, &P.S);
