@@ -1,14 +1,19 @@
-"""Edges of the GEMM tile shapes and of the K split, through the backbone call:
-row counts around every tile height (96, 128, 160, 256), weight widths that end
-inside a tile, and a down projection (K = 2,176 = 34 slabs) that short batches
-split into ranges of unequal length, its reduction fused with the next norm.
-Hidden rows against the fp64 oracle at the 2e-2 max-relative bar of the other
-backbone tests (bf16 operands); a sample alone equals the same sample in a
-longer batch bitwise where no contraction is split (K < 2,048)."""
+"""Edges of the GEMM tile shapes and of the K split, through the backbone call.
+Every test asks the plan which shape its sizes get, so none passes on another one.
+
+Short batches run 64x96 tiles (weight rows x tokens): row counts around its and the
+other shapes' heights, and a down projection (K = 2,176 = 34 slabs) split into
+ranges of unequal length, its reduction fused with the next norm.  Every other
+shape, per epilogue: one row fewer than, exactly and one more than whole tiles, weight
+widths that end inside a 256-wide tile, unsplit and split.  Hidden rows against the
+fp64 oracle at the 2e-2 max-relative bar of the other backbone tests (bf16
+operands); a sample alone (64x96 for the most part) equals the same sample in batches
+of other shapes bitwise where no contraction is split (K < 2,048)."""
 import numpy as np
 import pytest
 
 import workloads as W
+from test_gemm_plan import BF16, GEGLU, GELU, RESID, gemm_plan
 
 torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
@@ -16,9 +21,16 @@ pytestmark = pytest.mark.gpu
 ROWS = (1, 17, 64, 95, 96, 97, 128, 129, 159, 161, 257, 320, 513)
 
 
-def spec(lens, d, ffn, glu):
+def spec(lens, d, ffn, glu, layers=2):
     ten = tuple(W.TenantSpec(1, n, 0, 0, n, (d, 64, 6), 3, 2) for n in lens)
-    return W.WorkloadSpec(97, W.BackboneSpec(2, d, 3, ffn, glu), ten, 0, "tile edges")
+    return W.WorkloadSpec(97, W.BackboneSpec(layers, d, d // 128, ffn, glu), ten, 0, "tile edges")
+
+
+def plans(rows, d, ffn, glu):
+    """(leading rows on 256x256 tiles, shape of the others, K ranges) of the four projections."""
+    import paper_2607_16074_amd as lib
+    return {"qkv": gemm_plan(lib, BF16, rows, 3 * d, d), "o": gemm_plan(lib, RESID, rows, d, d),
+            "up": gemm_plan(lib, GEGLU if glu else GELU, rows, ffn, d), "down": gemm_plan(lib, RESID, rows, d, ffn)}
 
 
 def hidden(wl, tenants):
@@ -30,41 +42,95 @@ def hidden(wl, tenants):
     return st
 
 
-@pytest.mark.parametrize("ffn,glu", [(2176, False), (640, True)])
-@pytest.mark.parametrize("rows", ROWS)
-def test_rows_at_tile_edges(rows, ffn, glu):
+def check_hidden(wl, lens):
     import oracle
-    print(f"rows {rows} ffn {ffn} glu {glu}", flush=True)
-    wl = W.make_workload(spec((rows,), 384, ffn, glu))
-    got = hidden(wl, [0]).hidden.float().cpu().numpy().astype(np.float64)
-    ref = oracle.step.isolated(wl, heads=False)["hidden"][(0, 0)]
+    got = hidden(wl, range(len(lens))).hidden.float().cpu().numpy().astype(np.float64)
+    by = oracle.step.isolated(wl, heads=False)["hidden"]
+    ref = np.concatenate([by[(r, 0)] for r in range(len(lens))])
     assert got.shape == ref.shape
     assert np.max(np.abs(got - ref)) / np.max(np.abs(ref)) < 2e-2
 
 
-def test_sample_alone_equals_sample_in_a_batch_bitwise():
-    lens = (97, 161, 33, 320, 256)
-    wl = W.make_workload(spec(lens, 384, 640, True))
+@pytest.mark.parametrize("ffn,glu", [(2176, False), (640, True)])
+@pytest.mark.parametrize("rows", ROWS)
+def test_rows_at_tile_edges(rows, ffn, glu):
+    print(f"rows {rows} ffn {ffn} glu {glu}", flush=True)
+    p = plans(rows, 384, ffn, glu)
+    assert all(x[:2] == (0, "64x96") for x in p.values()) and (p["down"][2] > 1) == (ffn > 2048), p
+    check_hidden(W.make_workload(spec((rows,), 384, ffn, glu)), (rows,))
+
+
+@pytest.mark.parametrize("gemm,shape,split,d,ffn,glu,tiles", [
+    ("qkv", "128x96", False, 256, 128, False, 22), ("qkv", "128x160", False, 256, 128, False, 26),
+    ("qkv", "256x128", False, 384, 128, False, 36), ("qkv", "256x160", False, 640, 128, False, 26),
+    ("qkv", "256x256", False, 640, 128, False, 21),
+    ("up", "128x96", False, 128, 4224, False, 4), ("up", "128x160", False, 128, 4224, False, 5),
+    ("up", "256x128", False, 128, 4224, False, 9), ("up", "256x160", False, 128, 2176, False, 23),
+    ("up", "256x256", False, 128, 2176, False, 18), ("up", "64x96", True, 2048, 128, False, 1),
+    ("up", "128x96", False, 128, 4224, True, 2), ("up", "128x160", False, 128, 4224, True, 2),
+    ("up", "256x128", False, 128, 4224, True, 4), ("up", "256x160", False, 128, 4224, True, 6),
+    ("up", "256x256", False, 128, 4224, True, 5),
+    ("o", "128x128", False, 128, 128, False, 1), ("o", "128x96", False, 1280, 128, False, 13),
+    ("o", "128x160", False, 768, 128, False, 34), ("o", "256x160", False, 1536, 128, False, 34),
+    ("down", "256x128", False, 1280, 2176, False, 32),
+    ("down", "128x96", True, 256, 4224, False, 33), ("down", "128x160", True, 384, 3072, False, 26),
+    ("down", "256x256", True, 1280, 4224, False, 16),
+])
+@pytest.mark.parametrize("more", [-1, 0, 1])
+def test_every_shape_at_its_edges(gemm, shape, split, d, ffn, glu, tiles, more):
+    rows = tiles * int(shape.split("x")[1]) + more
+    print(f"{gemm} {shape} split {split} d {d} ffn {ffn} glu {glu} rows {rows}", flush=True)
+    m1, got, ranges = plans(rows, d, ffn, glu)[gemm]
+    assert (m1, got, ranges > 1) == (0, shape, split)
+    lens = (97,) * (rows // 97) + ((rows % 97,) if rows % 97 else ())
+    check_hidden(W.make_workload(spec(lens, d, ffn, glu, layers=1)), lens)
+
+
+@pytest.mark.parametrize("d,ffn,glu,lens,shapes", [
+    (384, 1920, True, (97, 161, 33, 320, 256, 33) + (300,) * 12, ["256x128", "128x128", "256x160", "128x96"]),
+    (512, 1920, False, (97, 161, 33) + (330,) * 7, ["128x160", "64x96", "128x160", "64x96"]),
+    (1024, 1920, True, (97, 161, 33, 320, 289, 400), ["128x160", "64x96", "256x128", "64x96"]),
+    # leading rows on 256x256 tiles and a tail
+    (768, 1920, False, (300,) * 30, ["128x160", "128x128", "256x160", "128x128"]),
+])
+def test_sample_alone_equals_sample_in_a_batch_bitwise(d, ffn, glu, lens, shapes):
+    print(f"d {d} ffn {ffn} glu {glu} rows {sum(lens)}", flush=True)
+    p = plans(sum(lens), d, ffn, glu)
+    assert [x[1] for x in p.values()] == shapes and all(x[2] == 1 for x in p.values()), p
+    wl = W.make_workload(spec(lens, d, ffn, glu))
     full, at = hidden(wl, range(len(lens))).hidden, 0
     for g, n in enumerate(lens):
-        assert torch.equal(hidden(wl, [g]).hidden, full[at: at + n]), g
+        if g < 6 or g >= len(lens) - 6:
+            alone = plans(n, d, ffn, glu)
+            assert all(x[2] == 1 for x in alone.values()) and alone["up"][1] != p["up"][1], alone
+            assert torch.equal(hidden(wl, [g]).hidden, full[at: at + n]), g
         at += n
 
 
-@pytest.mark.parametrize("d", [128, 384])
-def test_workgroups_with_several_tiles_bitwise(d):
-    """Launches whose workgroups take several 256x256 tiles in turn (19,903
-    rows, 1,920 columns: 632 tiles), joined (384 columns are six K slabs) and
-    not (128 are two): samples at both ends and the middle equal themselves
-    alone, where no tile follows another."""
-    lens = (313,) * 31 + (300,) * 34
+@pytest.mark.parametrize("d,glu,lens,gemm,joined", [
+    (384, False, (313,) * 31 + (300,) * 34, "qkv", True),    # 78 x 5 tiles of six slabs
+    (128, True, (313,) * 31 + (300,) * 34, "up", False),     # 78 x 15 tiles of two
+    (128, False, (300,) * 100, "up", False),                 # 118 x 8
+])
+def test_workgroups_with_several_tiles_bitwise(d, glu, lens, gemm, joined):
+    """Launches of more than 256 tiles of 256x256, whose workgroups take several in
+    turn, joined (three K slabs or more: the next tile's first slabs are fetched
+    under the last ones) and not: samples at both ends and the middle equal
+    themselves alone, where no tile follows another."""
+    ffn, rows = 1920, sum(lens)
+    print(f"d {d} glu {glu} rows {rows}", flush=True)
+    m1, shape, ranges = plans(rows, d, ffn, glu)[gemm]
+    columns = 3 * d if gemm == "qkv" else ffn * (2 if glu else 1)
+    assert (m1, shape, ranges) == (0, "256x256", 1) and -(-rows // 256) * -(-columns // 256) > 256
+    assert (d // 64 >= 3) == joined
     wl = W.make_workload(W.WorkloadSpec(
-        96, W.BackboneSpec(1, d, d // 128, 1920, False),
+        96, W.BackboneSpec(1, d, d // 128, ffn, glu),
         tuple(W.TenantSpec(1, n, 0, 0, n, (d, 64, 6), 3, 2) for n in lens), 0, "many tiles"))
     full, at = hidden(wl, range(len(lens))).hidden, 0
-    assert full.shape[0] == sum(lens)
+    assert full.shape[0] == rows
+    last = len(lens) - 1
     for g, n in enumerate(lens):
-        if g in (0, 1, 30, 31, 47, 63, 64):
+        if g in (0, 1, 30, 31, 47, last - 1, last):
             print(f"sample {g}", flush=True)
             assert torch.equal(hidden(wl, [g]).hidden, full[at: at + n]), g
         at += n
