@@ -91,8 +91,8 @@ typedef struct jn_trace_entry {
 } jn_trace_entry;
 
 /* Enable (1) or disable (0) the launch trace: while enabled, every kernel the
- * context enqueues is bracketed by a pair of HIP timing events on its stream.
- * Enabling clears previously collected entries. */
+ * context enqueues is bracketed by a pair of HIP timing events on its stream
+ * (but for the uploads of its small tables).  Enabling clears previously collected entries. */
 jn_status jn_ctx_set_trace(jn_ctx* ctx, int32_t enable);
 /* Wait for the traced launches to finish and copy up to `cap` entries (in
  * launch order) to `out`; `*n` receives the number collected.  Clears the

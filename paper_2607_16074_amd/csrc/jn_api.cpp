@@ -647,8 +647,10 @@ jn_status jn_backbone_forward(jn_ctx* c, const jn_backbone* bb, const jn_packed*
   const int32_t T = p->T, d = bb->d, f = bb->ffn;
   {
     // launch-size limits, checked before anything is enqueued: a dispatch
-    // holds at most 2^32 - 1 work-items (GEMM: <= 512 threads per 128x128-or-
-    // larger tile), and the attention grid at most 2^30 workgroups
+    // holds at most 2^32 - 1 work-items, and the attention grid at most 2^30
+    // workgroups.  GEMM: batches near the bound below (rows x columns / 32 work-
+    // items) run on tiles of at least 64x128 per 256 threads, which stay under it;
+    // the smaller tiles are planned for short launches only
     const int64_t kv = bb->n_kv_heads ? bb->n_kv_heads : bb->n_heads;
     const int64_t nmax = std::max<int64_t>((bb->n_heads + 2 * kv) * (d / bb->n_heads),
                                            (bb->layers[0].w_gate ? 2 : 1) * (int64_t)f);

@@ -1,5 +1,6 @@
 """The tile shape and K split that a backbone GEMM's size gets, asked on the CPU."""
 import ctypes as C
+import random
 
 import pytest
 
@@ -30,3 +31,22 @@ def test_ranges_no_faster_than_the_weights_arrive(lib, rows):
 def test_no_split_where_one_range_is_bound_by_its_weights(lib, rows):
     """16,384 x 4,096 at 128 rows: 37 us in one launch, 36 and a reduction of 5 in two ranges."""
     assert gemm_plan(lib, GELU, rows, 16384, 4096)[2] == 1
+
+
+def test_launches_fit_a_dispatch(lib):
+    """The largest batches that the backbone accepts (rows x columns / 32 below 2^32):
+    no launch of the plan holds 2^32 work-items of its 256 threads a tile."""
+    rng = random.Random(3)
+    for _ in range(400):
+        d = 128 * rng.randint(1, 32)
+        f = 128 * int(2 ** rng.uniform(0, 15))
+        glu = rng.random() < 0.5
+        widest = max(3 * d, (1 + glu) * f)
+        rows = ((1 << 32) - 1) // 512 // -(-widest // 128) * 128
+        rows = min(int(rows * rng.choice((1.0, 1.0, rng.random()))), (1 << 31) - 2)
+        for epi, n, k in ((BF16, 3 * d, d), (RESID, d, d), (GEGLU if glu else GELU, f, d), (RESID, d, f)):
+            m1, shape, ranges = gemm_plan(lib, epi, rows, n, k)
+            columns = n * (2 if epi == GEGLU else 1)
+            for m, s, r in ((m1, "256x256", 1), (rows - m1, shape, ranges)):
+                bn, bm = map(int, s.split("x"))
+                assert -(-m // bm) * -(-columns // bn) * r * 256 < 1 << 32, (rows, n, k, s, r)
