@@ -20,11 +20,12 @@ def gemm_plan(lib, epi, m, n, k):
     return p.m1, SHAPES[p.shape], p.S
 
 
-@pytest.mark.parametrize("rows", [1, 33, 64])
-def test_ranges_no_faster_than_the_weights_arrive(lib, rows):
-    """134 MB of weights take 28 to 31 us however many ranges are fetched at once (one
-    row in three ranges 32 us, in eight, 256 workgroups, 37)."""
-    assert gemm_plan(lib, RESID, rows, 4096, 16384)[2] <= 6
+@pytest.mark.parametrize("n,rows", [(4096, 1), (4096, 33), (4096, 64), (4096, 128), (2048, 1), (2048, 64)])
+def test_ranges_do_not_start_on_the_same_channels(lib, n, rows):
+    """K = 16,384: ranges that start whole multiples of 4 KB apart take a fifth longer
+    (one row, 4,096 columns, four and eight ranges 34 and 37 us, three to six 30 to 32)."""
+    s = gemm_plan(lib, RESID, rows, n, 16384)[2]
+    assert s > 1 and 16384 % (2048 * s) != 0
 
 
 @pytest.mark.parametrize("rows", [107, 128])
