@@ -22,6 +22,10 @@ struct ReqEntry {
 };
 static_assert(sizeof(ReqEntry) == 32, "ReqEntry layout");
 
+// Size of the last-level cache: kernels that touch every byte once do so non-
+// temporally only where they touch more than this.
+constexpr int64_t kStreamBytes = 256 << 20;
+
 // ------------------------------------------------------------ launchers ---
 // All launchers enqueue on `s`; shapes were validated by the caller.
 

@@ -2,9 +2,11 @@
 // Block b updates elements [2048 (b - block_start), +2048) of the tensor whose
 // block range holds b; each thread handles 8 elements as two 16-byte accesses
 // per operand (the tail of a tensor element by element).  HBM-bound: 16 bytes
-// read and 12 written per element (+2 for a bf16 copy), all but p's read
-// non-temporal, since nothing of it is used again before it has left the caches
-// (28.5M parameters: 151 -> 135 us of the launch alone, 5.9 TB/s).
+// read and 12 written per element (+2 for a bf16 copy).  ONCE, more than the last-
+// level cache holds: all but p's read non-temporal, since nothing of it is used
+// again before it has left the caches (28.5M parameters: 151 -> 135 us of the launch
+// alone, 5.9 TB/s; the call over 336 MB 145 -> 113, but over 33 MB 14.5 -> 16.6 and over
+// 168 58 -> 60, so up to there plain).
 #include "jn_device.h"
 #include "jn_internal.h"
 
@@ -19,6 +21,22 @@ __device__ __forceinline__ void adamw_elem(const AdamwTenant& h, float& p, float
   p = p * h.decay - h.step_size * (m / den);
 }
 
+template <bool ONCE>
+__device__ __forceinline__ f32x4o get(const f32x4o* p) {
+  if constexpr (ONCE)
+    return __builtin_nontemporal_load(p);
+  else
+    return *p;
+}
+template <bool ONCE>
+__device__ __forceinline__ void put(f32x4o v, f32x4o* p) {
+  if constexpr (ONCE)
+    __builtin_nontemporal_store(v, p);
+  else
+    *p = v;
+}
+
+template <bool ONCE>
 __global__ __launch_bounds__(256) void adamw_kernel(const AdamwTensor* __restrict__ ts, int32_t n,
                                                     const AdamwTenant* __restrict__ tens) {
   // the last tensor whose block range starts at or before this block (binary search)
@@ -39,8 +57,8 @@ __global__ __launch_bounds__(256) void adamw_kernel(const AdamwTensor* __restric
     if (e + 4 <= T.numel) {
       f32x4o *const pp = reinterpret_cast<f32x4o*>(T.p + e), *const pm = reinterpret_cast<f32x4o*>(T.m + e),
              *const pv = reinterpret_cast<f32x4o*>(T.v + e);
-      f32x4o p = *pp, m = __builtin_nontemporal_load(pm), v = __builtin_nontemporal_load(pv);
-      const f32x4o g = __builtin_nontemporal_load(reinterpret_cast<const f32x4o*>(T.g + e));
+      f32x4o p = *pp, m = get<ONCE>(pm), v = get<ONCE>(pv);
+      const f32x4o g = get<ONCE>(reinterpret_cast<const f32x4o*>(T.g + e));
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         float pj = p[j], mj = m[j], vj = v[j];
@@ -49,9 +67,9 @@ __global__ __launch_bounds__(256) void adamw_kernel(const AdamwTensor* __restric
         m[j] = mj;
         v[j] = vj;
       }
-      __builtin_nontemporal_store(p, pp);
-      __builtin_nontemporal_store(m, pm);
-      __builtin_nontemporal_store(v, pv);
+      put<ONCE>(p, pp);
+      put<ONCE>(m, pm);
+      put<ONCE>(v, pv);
       if (T.b16) *reinterpret_cast<uint2*>(T.b16 + e) = make_uint2(pack_bf2(p[0], p[1]), pack_bf2(p[2], p[3]));
     } else {
       for (int64_t j = e; j < T.numel; ++j) {
@@ -77,7 +95,10 @@ int32_t adamw_prepare(AdamwTensor* t, int32_t n) {
 
 hipError_t launch_adamw(hipStream_t s, const AdamwTensor* t, int32_t n, const AdamwTenant* ten, int32_t blocks) {
   if (blocks <= 0) return hipSuccess;
-  adamw_kernel<<<blocks, 256, 0, s>>>(t, n, ten);
+  if (blocks * kAdamwBlockElems * 16 > kStreamBytes)
+    adamw_kernel<true><<<blocks, 256, 0, s>>>(t, n, ten);
+  else
+    adamw_kernel<false><<<blocks, 256, 0, s>>>(t, n, ten);
   return hipGetLastError();
 }
 

@@ -191,8 +191,6 @@ __global__ __launch_bounds__(256) void unpack_kernel(const ReqEntry* __restrict_
 // Results beyond the last-level cache are stored non-temporally: packed and unpacked
 // again, 300 rows of 4 KB, 225 MB take 158 us with plain and 167 with non-temporal
 // stores, 300 MB 228 and 217.
-constexpr int64_t kStreamBytes = 256 << 20;
-
 hipError_t launch_pack(hipStream_t s, const ReqEntry* req_table, const int32_t* sample_request,
                        const int32_t* sample_local, const int32_t* seqlens, const int32_t* cu_seqlens, int32_t N,
                        int32_t T, int32_t d, int32_t max_rows, void* tokens, int32_t* token_sample,

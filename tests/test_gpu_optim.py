@@ -116,3 +116,30 @@ def test_adamw_errors_enqueue_nothing(jn):
         jn.jn_tenant_adamw_step(ctx, [jn.AdamWTenant([p], [g], [m], [v], step=1, lr=1e-3)], ws[:16])
     torch.cuda.synchronize()
     assert torch.equal(p, torch.ones_like(p)) and torch.equal(m, torch.zeros_like(m))
+
+
+@pytest.mark.parametrize("extra", [0, 7])
+def test_adamw_around_the_last_level_cache(jn, extra):
+    """16 bytes of 2^24 elements are the most that is kept in the caches, 7 more (a
+    vector and a tail) stream: the same bits as two halves, each in the caches."""
+    n, ctx = (1 << 24) + extra, jn.Context()
+    _say(f"adamw {n} elements")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(extra)
+    state = [torch.randn(n, generator=g, device="cuda") for _ in range(4)]
+    state[3].square_()
+
+    def step(parts):
+        p, gr, m, v = ([x.clone() for x in s.split(parts)] for s in state)
+        b = [torch.zeros(x.numel(), dtype=torch.bfloat16, device="cuda") for x in p]
+        for k in range(len(p)):
+            t = [jn.AdamWTenant([p[k]], [gr[k]], [m[k]], [v[k]], step=3, lr=1e-3, weight_decay=0.01, bf16_out=[b[k]])]
+            ws = torch.empty(jn.jn_adamw_workspace_size(t), dtype=torch.uint8, device="cuda")
+            jn.jn_tenant_adamw_step(ctx, t, ws)
+            torch.cuda.synchronize()
+        return [torch.cat(x) for x in (p, m, v, b)]
+
+    whole, halves = step(n), step(1 << 23)
+    assert not torch.equal(whole[0], state[0])
+    for a, b in zip(whole, halves):
+        assert torch.equal(a, b)
