@@ -483,7 +483,8 @@ __global__ __launch_bounds__(64 * kHeadWaves, FORWARD ? 2 : 4) void head_gemm_ke
                                                                                      const HeadTile* __restrict__ tiles,
                                                                                      const int32_t* __restrict__ tso,
                                                                                      int32_t nrow, int32_t tms,
-                                                                                     int32_t tm0, int32_t nown, int32_t parts) {
+                                                                                     int32_t tm0, int32_t nown,
+                                                                                     int32_t parts) {
   __shared__ __attribute__((aligned(16))) float red[kHeadWaves * kHeadTile * kHeadRed];
   __shared__ float scratch[kHeadWaves];
   const int32_t b = blockIdx.x;
@@ -500,8 +501,8 @@ __global__ __launch_bounds__(64 * kHeadWaves, FORWARD ? 2 : 4) void head_gemm_ke
     const bool shared = parts > 1 && ng > head_long_rows(D.M, D.N);
     if (piece > 0 && (!shared || tile.tm == kHeadLossTile)) return;
     if (tile.tm != kHeadLossTile) {
-      head_wgrad_tile(D, red, off, tile.tm, tile.tn, ng, shared ? piece : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6),
-                      shared);
+      head_wgrad_tile(D, red, off, tile.tm, tile.tn, ng,
+                      shared ? piece : __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), shared);
       return;
     }
     // the tenant's loss from its tiles' sums, in tile order per thread, then a fixed tree

@@ -124,10 +124,9 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const void* __restrict__ x
 // 2,468 rows 39 (S = 8), 19.9 and 19.8 (S = 3).
 constexpr int split_waves(int nc) { return nc < 4 ? nc : 4; }
 template <int VEC, int NC>
-__global__ __launch_bounds__(64 * split_waves(NC)) void rmsnorm_split_kernel(float* __restrict__ x, const float* __restrict__ part,
-                                                               int32_t S, int64_t stride,
-                                                               const uint16_t* __restrict__ g, uint16_t* __restrict__ h,
-                                                               int32_t d, float eps) {
+__global__ __launch_bounds__(64 * split_waves(NC)) void rmsnorm_split_kernel(
+    float* __restrict__ x, const float* __restrict__ part, int32_t S, int64_t stride, const uint16_t* __restrict__ g,
+    uint16_t* __restrict__ h, int32_t d, float eps) {
   constexpr int W = split_waves(NC), CW = (NC + W - 1) / W;
   __shared__ __attribute__((aligned(16))) float line[NC * 64 * VEC];
   const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);

@@ -128,11 +128,13 @@ __global__ __launch_bounds__(256) void pack_ragged_kernel(const ReqEntry* __rest
       const ReqEntry q = req_table[sample_request[ia]];
       const int64_t from = at - cu_seqlens[ia] * (int64_t)chunks;
       const u32x4p* src = reinterpret_cast<const u32x4p*>(q.in) + (int64_t)sample_local[ia] * q.max_len * chunks + from;
-      for (int64_t e = 0; e < n; e += kFlat) move_run<false>(src, tokens + at, e, seqlens[ia] * (int64_t)chunks - from, n);
+      const int64_t live = seqlens[ia] * (int64_t)chunks - from;
+      for (int64_t e = 0; e < n; e += kFlat) move_run<false>(src, tokens + at, e, live, n);
     } else {
       for (int64_t e = threadIdx.x; e < n; e += 256) {
         const uint32_t r = (c0 + (uint32_t)e) / chunks, c = c0 + (uint32_t)e - r * chunks;
-        const int32_t row = ra + (int32_t)r, i = ia + last_at(cu_seqlens + ia, ib - ia + 1, row), j = row - cu_seqlens[i];
+        const int32_t row = ra + (int32_t)r, i = ia + last_at(cu_seqlens + ia, ib - ia + 1, row);
+        const int32_t j = row - cu_seqlens[i];
         u32x4p v{};
         if (j < seqlens[i]) {
           const ReqEntry q = req_table[sample_request[i]];
@@ -208,9 +210,9 @@ hipError_t launch_pack(hipStream_t s, const ReqEntry* req_table, const int32_t* 
     return hipGetLastError();
   }
   auto go = [&](auto once) {
-    pack_kernel<once()><<<(unsigned)N * per, 256, 0, s>>>(req_table, sample_request, sample_local, seqlens, cu_seqlens, d,
-                                                          reinterpret_cast<u32x4p*>(tokens), token_sample, token_pos,
-                                                          per);
+    pack_kernel<once()><<<(unsigned)N * per, 256, 0, s>>>(
+        req_table, sample_request, sample_local, seqlens, cu_seqlens, d, reinterpret_cast<u32x4p*>(tokens), token_sample,
+        token_pos, per);
     return hipGetLastError();
   };
   return T * chunks * 16 > kStreamBytes ? go(std::true_type()) : go(std::false_type());

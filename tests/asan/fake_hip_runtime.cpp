@@ -15,8 +15,7 @@ extern "C" {
 
 long long jn_fake_launches = 0;
 long long jn_fake_graph_launches = 0;
-long long jn_fake_workgroups = 0;       // of all launches
-long long jn_fake_last_workgroups = 0;  // of the last one
+long long jn_fake_last_workgroups = 0;  // of the last launch
 long long jn_fake_last_threads = 0;     // of its workgroups
 
 static dim3 g_grid, g_block;
@@ -66,7 +65,6 @@ hipError_t hipLaunchKernel(const void* fn, dim3 grid, dim3 block, void** args, s
   check_launch(grid, block, shm);
   ++jn_fake_launches;
   jn_fake_last_workgroups = (long long)grid.x * grid.y * grid.z;
-  jn_fake_workgroups += jn_fake_last_workgroups;
   jn_fake_last_threads = (long long)block.x * block.y * block.z;
   return hipSuccess;
 }

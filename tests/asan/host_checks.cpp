@@ -20,7 +20,6 @@
 
 extern "C" long long jn_fake_launches;
 extern "C" long long jn_fake_graph_launches;
-extern "C" long long jn_fake_workgroups;
 extern "C" long long jn_fake_last_workgroups;
 extern "C" long long jn_fake_last_threads;
 
