@@ -1236,30 +1236,37 @@ static bool may_split(int epi, int32_t rows, int32_t N, int32_t K) {
 }
 
 // One launch over `rows` rows and S K ranges; a split adds the launch of its
-// reduction and the second half of the fp32 partials' round trip.  Where a split is
-// a choice, no launch is faster than its weights come from memory (33 MB 8.6 us, 100
-// MB 20 to 23, 134 MB 28 to 31), and ranges that start whole multiples of 4 KB apart,
-// all workgroups then asking the same channels, take a fifth longer (one row, 4,096 x
-// 16,384 in 3, 5, 6 and 12 ranges 32, 30, 30 and 28 us, in 4 and 8 34 and 37; 2,048 x
-// 16,384 in 8 19, in 6 and 16 16 and 15).  Of two as fast, the one of fewer ranges.
-static double tile_time(int epi, int32_t rows, int32_t N, int32_t K, int t, int32_t S) {
+// reduction and the second half of the fp32 partials' round trip.  stream: the time
+// its weights take from memory at least.
+static double tile_time(int epi, int32_t rows, int32_t N, int32_t K, int t, int32_t S, double stream) {
   const TileShape& T = kShapes[t];
   const int64_t NL = epi == EPI_GEGLU_BF16 ? 2 * (int64_t)N : N;
   const int64_t tiles = (rows + T.bm - 1) / T.bm * ((NL + T.bn - 1) / T.bn) * S;
-  const double stream = may_split(epi, rows, N, K) ? 2.5 + 2.0 * (double)N * K / 5.4e6 : 0.0;
-  const double apart = S > 1 && K % (2048 * S) == 0 ? 1.2 : 1.0;
-  const double us = std::max(apart * stream + 0.05 * S, tiles_time(S > 1 ? EPI_F32 : epi, tiles, (double)((K / kBK + S - 1) / S), t));
+  const double us = std::max(stream, tiles_time(S > 1 ? EPI_F32 : epi, tiles, (double)((K / kBK + S - 1) / S), t));
   return S > 1 ? us + 4.0 + 4e-6 * S * (double)rows * N / 4.8 : us;
+}
+
+// Where a split is a choice, no launch is faster than its weights come from memory
+// (33 MB 8.6 us, 100 MB 20 to 23, 134 MB 28 to 31), and ranges that start whole
+// multiples of 4 KB apart, all workgroups then asking the same channels, take a fifth
+// longer (one row, 4,096 x 16,384 in 3, 5, 6 and 12 ranges 32, 30, 30 and 28 us, in 4
+// and 8 34 and 37; 2,048 x 16,384 in 8 19, in 6 and 16 16 and 15).  Of two as fast,
+// the one of fewer ranges.
+static double stream_time(int32_t N, int32_t K, int32_t S) {
+  const double us = 2.5 + 2.0 * (double)N * K / 5.4e6;
+  return (S > 1 && K % (2048 * S) == 0 ? 1.2 * us : us) + 0.05 * S;
 }
 
 // Shape and K split of one launch over `rows` rows; ranges of >= 8 slabs.
 static double plan_launch(int epi, int32_t rows, int32_t N, int32_t K, bool split, int* shape, int32_t* S) {
   const int32_t smax = split && may_split(epi, rows, N, K) ? std::min(16, K / (8 * kBK)) : 1;
+  double stream[17] = {};  // of k ranges
+  for (int32_t k = 1; smax > 1 && k <= smax; ++k) stream[k] = stream_time(N, K, k);
   double best = 1e300;
   for (int t = 0; t <= k128Shape; ++t) {
     if (t == k128Shape && epi != EPI_RESID_F32) break;
     for (int32_t k = 1; k <= (t == k128Shape ? 1 : smax); ++k) {
-      const double us = tile_time(epi, rows, N, K, t, k);
+      const double us = tile_time(epi, rows, N, K, t, k, stream[k]);
       if (us < best * 0.999) {
         best = us;
         *shape = t;
@@ -1294,7 +1301,7 @@ GemmPlan gemm_plan(int epi, int32_t M, int32_t N, int32_t K) {
     const int32_t m1 = (int32_t)(r * 256);
     int t = 0;
     int32_t S = 1;
-    double us = tile_time(epi, m1, N, K, 0, 1) + kLaunchGap;
+    double us = tile_time(epi, m1, N, K, 0, 1, 0.0) + kLaunchGap;
     us += plan_launch(epi, M - m1, N, K, K >= kTailSplitK, &t, &S);
     if (us < best * 0.99) {
       best = us;
